@@ -515,9 +515,8 @@ def time_kernels(w: Workload, hev: HipEvents, reps: int):
             k["key_stream_bytes"] = nb * HKV * key_rows * DH * 2
             k["key_stream_GBs"] = round(k["key_stream_bytes"] / (k["us_median"] * 1e-6) / 1e9, 1)
             entry[kernel] = k
-        for kernel in ("select", "write_index"):
-            ms = [traced(kernel, lambda v=v: level(v))[0] for _ in range(reps) for v in units]
-            entry[kernel] = dict(kernel=("score_hist_kernel + candidate_kernel" if kernel == "select" else kernel + "_kernel"), **stats_us(ms))
+        ms = [traced("select", lambda v=v: level(v))[0] for _ in range(reps) for v in units]
+        entry["select"] = dict(kernel="score_select_kernel", **stats_us(ms))          # scores, selection and index list
         ms = [traced("gather_rows", lambda v=v: level(v))[0] for _ in range(reps) for v in units]
         entry["gather_rows"] = hbm_entry(ms, nb * w.gather_bytes(lv), "gather_rows_kernel")
         out[f"stage2_level{lv + 1}"] = entry

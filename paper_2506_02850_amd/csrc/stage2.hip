@@ -6,17 +6,13 @@
 //   merge_stats_kernel   merges the per-workgroup (max, sum) pairs into one normaliser per row
 //   col_sums_kernel      MFMA pass 2 over the visual keys: recomputes the logits and adds up the
 //                        probabilities of every visual key over the rows of a workgroup
-//   score_hist_kernel    score_j = w_e(j) * mean probability; per 1024-token tile a histogram of the leading key
-//                        bits per retention class; the workgroup that arrives last finds each class's bucket
-//   candidate_kernel     per tile: tokens above the bucket counted, tokens inside it listed; the workgroup that
-//                        arrives last finishes the radix select on the list -> class threshold, number of equal
-//                        scores still kept, output offset of every tile
-//   prepare_kernel, select_kernel   the same two steps for more than four classes or more than 40 tiles: one
-//                        workgroup per class walks all keys
-//   write_index_kernel   one workgroup per 1024-token tile: keep rule (lowest index first among equal
-//                        scores), prefix sums -> ascending kept index list and carried metadata
+//   score_select_kernel  score_j = w_e(j) * mean probability per tile; the workgroup that arrives last selects per class
+//                        (radix select) and writes the ascending index list
+//   prepare_kernel, select_kernel, write_index_kernel   the same steps for more than 16 classes or more than 40960
+//                        tokens: scores; one workgroup per class walks all keys; one workgroup per 1024-token tile
+//                        applies the keep rule and writes the index list and the carried metadata
 //   gather_rows_kernel   compaction of the hidden states (hidden_index_kernel + the row mover of stage 3 when
-//                        the output is the input buffer)
+//                        the output is the input buffer) and, after score_select_kernel, of the carried metadata
 //
 // A batch of videos of one shape runs as one launch of every kernel: blockIdx.z is the video, every pointer
 // advances by that video's stride, and the per-video workspaces lie one after the other.
@@ -724,7 +720,6 @@ __global__ __launch_bounds__(kIdxThreads) void write_index_kernel(
     int n_vis, int n_seg, int n_tiles, int total_keep, const int32_t* __restrict__ token_event,
     const int32_t* __restrict__ orig_idx_in, int32_t* __restrict__ kept_idx, int32_t* __restrict__ token_seg_out,
     int32_t* __restrict__ token_event_out, int32_t* __restrict__ orig_idx_out,
-    const int32_t* __restrict__ given_tile_off, const int32_t* __restrict__ given_eq_before /*[class][kSelCache]*/,
     int64_t ws_video, int64_t keep_stride, int64_t orig_idx_in_stride, int64_t orig_idx_stride, const BatchKeep keeps) {
     __shared__ int scan_scratch[17];
     __shared__ uint32_t s_tau[METOK_MAX_SEGMENTS];
@@ -735,18 +730,10 @@ __global__ __launch_bounds__(kIdxThreads) void write_index_kernel(
     scores = of_video_elems(scores, n_vis); token_seg = of_video_elems(token_seg, n_vis);
     token_event = of_video_elems(token_event, n_vis); orig_idx_in = of_video_elems(orig_idx_in, orig_idx_in_stride);
     sel_info = of_video(sel_info, ws_video); gt_count = of_video(gt_count, ws_video); eq_count = of_video(eq_count, ws_video);
-    given_tile_off = of_video(given_tile_off, ws_video); given_eq_before = of_video(given_eq_before, ws_video);
     kept_idx = of_video_elems(kept_idx, keep_stride); token_seg_out = of_video_elems(token_seg_out, keep_stride);
     token_event_out = of_video_elems(token_event_out, keep_stride); orig_idx_out = of_video_elems(orig_idx_out, orig_idx_stride);
-    // kept tokens in earlier tiles: given by the fast path, else thread s walks the tiles of class s
+    // kept tokens in earlier tiles: thread s walks the tiles of class s
     int before = 0;
-    if (given_tile_off != nullptr) {
-        for (int sg = tid; sg < n_seg; sg += kIdxThreads) {
-            s_tau[sg] = sel_info[2 * sg]; s_rem[sg] = static_cast<int>(sel_info[2 * sg + 1]);
-            s_eq_before[sg] = given_eq_before[sg * kSelCache + tile];
-        }
-        if (tid == 0) before = given_tile_off[tile];
-    } else
     for (int sg = tid; sg < n_seg; sg += kIdxThreads) {
         const uint32_t tau = sel_info[2 * sg];
         const int rem = static_cast<int>(sel_info[2 * sg + 1]);
@@ -822,47 +809,38 @@ __global__ __launch_bounds__(kIdxThreads) void write_index_kernel(
 }
 
 // ---------------------------------------------------------------------------------------------
-// Fast selection path: at most kFastSeg retention classes and at most kFastTiles tiles of 1024 tokens.
-// The single-workgroup radix select above costs 20-25 us at 36864 tokens, most of it barriers of a 1024-thread
-// workgroup; here the token-parallel parts run on one workgroup per tile and only the short serial parts run
-// on the workgroup that arrives last at an atomic counter (it is the one that knows every other workgroup's
-// results are complete; nobody waits for anybody):
-//   score_hist_kernel   per tile: scores (what prepare_kernel does on the general path), histogram of the top 11 key bits per class
-//                       -> global histogram.  Last workgroup: per class the histogram bucket that holds the
-//                       quota-th largest key, how many keys of that bucket are still needed, or keep all / none.
-//   candidate_kernel    per tile: tokens above the bucket are kept for sure (counted per tile), tokens inside it are
-//                       appended to a candidate list.  Last workgroup: radix select of the remaining 21 bits on the
-//                       list -> class threshold and number of equal keys kept; per tile the candidates above / equal
-//                       to it; exclusive sums over the tiles -> output offset of every tile.
-//   write_index_kernel  per tile, as before, with the offsets given.
-// Results are the same integers as on the general path: the keep rule (key above the threshold, or equal and among
-// the first equal keys by index) does not depend on how the threshold was found.
+// Fast selection path: at most kFastSeg retention classes and at most kFastTiles tiles of 1024 tokens, one launch.
+//   every workgroup     scores of its tokens from the partial column sums (skipped when scores are given)
+//   the workgroup that arrives last at an atomic counter (it is the one that knows every other workgroup's scores are
+//   complete; nobody waits for anybody) selects for the video: all keys in registers, per class a histogram of the
+//   leading bits of (key - smallest key), the bucket of the quota-th largest key, the few keys of that bucket ranked
+//   against each other, then the ascending index list of the kept tokens.
+// The keep rule (key above the threshold, or equal and among the first equal keys by index) does not depend on how the
+// threshold was found, so the results are the integers of the general path.
+// What bounds it is latency, not work: a chain of about ten barriers and two memory round trips.  The digits start at
+// the smallest key because attention scores share their leading bits: a histogram of the top 11 bits of the key itself
+// left a third of the tokens in one bucket (and its atomics on one address), the shifted one leaves about twenty.
+// Measured against the launches it replaces (score + histogram, candidates, index list; with 5 to 16 classes the general
+// path's three): 2243 tokens 28.5 -> 9.9 us, 4507 tokens with 40 partial sums each 33 -> 12.4 us, 18432 tokens in 13
+// classes 31 -> 20 us, eight videos of 36864 tokens 46 -> 30 us.  One workgroup walking 36 tiles is what is left there
+// (0.6 us a tile: its loads, LDS atomics and ballots); more than 40 tiles or 16 classes take the general path, whose
+// workgroups (one per class) share the work of many classes.
 // ---------------------------------------------------------------------------------------------
-constexpr int kFastSeg = 4;
+constexpr int kFastSeg = 16;
 constexpr int kFastTiles = kSelCache;
-static_assert(kFastTiles <= 64, "the finishing workgroup scans the tiles with one wave, a lane per tile");
-constexpr uint32_t kKeepAll = 0x7fffffffu;
+constexpr int kSplitParts = 8;              // from so many partial sums per token on four threads share a token in the scoring part
+constexpr int kHistWords = 8192;            // histogram bins of all classes together: 2048 per class up to 4 classes, else 512
+constexpr int kListCap = 512;               // keys of the threshold buckets that are ranked against each other
 
 struct FastSel {
-    // cleared before the first kernel that uses them
-    uint32_t arrive_a, arrive_b, cand_total, pad;
-    int32_t hist[kFastSeg][2048];
-    // written before they are read
-    int32_t state[kFastSeg][4];             // bucket digit, keys of the bucket still needed, bucket population, mode
-    int32_t tile_sure[kFastSeg][kFastTiles];
-    int32_t tile_off[kFastTiles];
-    int32_t eq_before[kFastSeg][kFastTiles];
-    uint32_t sel_info[kFastSeg][2];         // threshold key, equal keys kept (kKeepAll = every one)
+    uint32_t arrive;                        // cleared before the kernel that counts on it
+    int32_t n_kept;                         // kept tokens written (the rest of the list is padding)
 };
-constexpr int kFastClearWords = 4 + kFastSeg * 2048;
-static size_t fast_state_bytes() { return round_up(sizeof(FastSel), 256); }
-enum { kModeSearch = 0, kModeNone = 1, kModeAll = 2 };
+constexpr int kFastClearWords = 1;
 
 struct FastArgs {
     FastSel* fs;
-    uint32_t* cand_key;                     // [n_vis]
-    uint32_t* cand_tok;                     // [n_vis]: class << 24 | token
-    const float* colpart;                   // NULL: scores are given
+    const float* colpart;                   // NULL: scores are given (one workgroup per video then)
     int n_parts;
     float rows_total;
     const int32_t* token_event;
@@ -871,34 +849,12 @@ struct FastArgs {
     float* scores;
     const int32_t* token_seg;
     int n_vis, n_seg;
+    int32_t* kept_idx;
+    int64_t keep_stride;
     int64_t ws_video;                       // bytes between the workspaces of consecutive videos
-    int32_t quota[METOK_MAX_BATCH][kFastSeg];
+    BatchKeep keeps;
+    uint16_t quota[METOK_MAX_BATCH][kFastSeg];      // at most n_vis <= 40960
 };
-// The arguments as video blockIdx.z sees them: its pointers and the scalars; the quota table stays in the kernel
-// arguments (a private copy of it would live in scratch memory).
-struct FastView {
-    FastSel* fs;
-    uint32_t* cand_key;
-    uint32_t* cand_tok;
-    const float* colpart;
-    int n_parts;
-    float rows_total;
-    const int32_t* token_event;
-    const float* event_weight;
-    int n_events;
-    float* scores;
-    const int32_t* token_seg;
-    int n_vis, n_seg;
-};
-__device__ __forceinline__ FastView to_video(const FastArgs& a) {
-    FastView v;
-    v.fs = of_video(a.fs, a.ws_video); v.cand_key = of_video(a.cand_key, a.ws_video); v.cand_tok = of_video(a.cand_tok, a.ws_video);
-    v.colpart = of_video(a.colpart, a.ws_video);
-    v.n_parts = a.n_parts; v.rows_total = a.rows_total; v.n_events = a.n_events; v.n_vis = a.n_vis; v.n_seg = a.n_seg;
-    v.token_event = of_video_elems(a.token_event, a.n_vis); v.event_weight = of_video_elems(a.event_weight, a.n_events);
-    v.scores = of_video_elems(a.scores, a.n_vis); v.token_seg = of_video_elems(a.token_seg, a.n_vis);
-    return v;
-}
 
 // Values handed from one workgroup to another inside a kernel travel through device-scope accesses (they pass the
 // caches that are not coherent between the chip's dies), so that no whole-cache write-back or invalidate is needed:
@@ -922,301 +878,353 @@ __device__ __forceinline__ bool arrive_and_check_last(uint32_t* counter, int* s_
     return *s_flag != 0;
 }
 
-__global__ __launch_bounds__(256) void clear_words_kernel(uint32_t* __restrict__ words, int n, int64_t ws_video) {
-    words = of_video(words, ws_video);
-    for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) words[i] = 0u;
-}
+// Histogram bins of a class lie one word further apart every 32 bins, so that the lanes of wave_find_bucket, which walk
+// 32 (or 8) neighbouring bins each, read different LDS banks.
+__device__ __forceinline__ int bin_slot(int bin) { return bin + (bin >> 5); }
+constexpr int kHistSlots = kHistWords + kHistWords / 32;
 
-// Orders the LDS traffic of one wave's lanes among themselves: LDS serves a wave's instructions in issue order, so
-// only the compiler has to be kept from moving accesses across this point.
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
-// One wave walks a histogram in LDS from the largest digit down and returns the digit at which the running count
-// reaches `need`, how many keys of that digit are still needed and how many keys the digit holds.  bins is 1024 or 2048.
-__device__ __forceinline__ void wave_find_bucket(const int* hist, int bins, int need, int* digit, int* rem, int* cnt) {
+// One wave walks the 64 * PER bins of a class from the largest digit down and returns the digit at which the running count
+// reaches `need`, how many keys of that digit are still needed, how many keys the digit holds, and the count of all bins.
+// A lane adds up PER neighbouring bins; then the lanes look at the bins of the one lane in which the count is reached.
+template <int PER>
+__device__ __forceinline__ void wave_find_bucket(const int* hist, int need, int* digit, int* rem, int* cnt, int* population) {
+    static_assert(32 % PER == 0, "the bins of a lane are neighbours in LDS");
     const int lane = threadIdx.x & 63;
-    const int per = bins / 64;
-    const int hi = bins - 1 - lane * per;                          // the largest digit of this lane
-    int mine_sum = 0;
-    for (int u = 0; u < per; ++u) mine_sum += hist[hi - u];
-    int incl = mine_sum;
+    const int* mine_hist = hist + bin_slot((63 - lane) * PER);      // lane 0 owns the largest digits
+    int sum = 0;
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int up = __shfl_up(incl, off, 64);
-        if (lane >= off) incl += up;
-    }
-    const int excl = incl - mine_sum;
-    const bool mine = excl < need && incl >= need;
-    int d = 0, r = 0, c = 0;
-    if (mine) {
-        int run = excl;
-        for (int u = 0; u < per; ++u) {
-            const int v = hist[hi - u];
-            if (run + v >= need) { d = hi - u; r = need - run; c = v; break; }
-            run += v;
-        }
-    }
-    const unsigned long long m = __ballot(mine);
-    const int src = m ? __ffsll(static_cast<long long>(m)) - 1 : 0;
-    *digit = __shfl(d, src, 64); *rem = __shfl(r, src, 64); *cnt = __shfl(c, src, 64);
-}
-// population of a histogram (one wave)
-__device__ __forceinline__ int wave_hist_total(const int* hist, int bins) {
-    const int lane = threadIdx.x & 63;
-    int s = 0;
-    for (int i = lane; i < bins; i += 64) s += hist[i];
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
-    return s;
-}
-
-__global__ __launch_bounds__(kSelThreads) void score_hist_kernel(const FastArgs args) {
-    __shared__ int hist[kFastSeg * 2048];
-    __shared__ int s_last;
-    const FastView a = to_video(args);
-    const int tid = threadIdx.x;
-    const int j = blockIdx.x * kSelThreads + tid;
-    for (int i = tid; i < a.n_seg * 2048; i += kSelThreads) hist[i] = 0;
-    float sc = 0.f;
-    int sg = -1;
-    if (j < a.n_vis) {
-        if (a.colpart) {
-            // the partial sums of the workgroup rows, added in order; four loads are requested together (a part past the
-            // last one reads the last one again and is not added)
-            float acc = 0.f;
-            for (int p0 = 0; p0 < a.n_parts; p0 += 4) {
-                float v[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int p = p0 + u < a.n_parts ? p0 + u : a.n_parts - 1;
-                    v[u] = a.colpart[static_cast<size_t>(p) * a.n_vis + j];
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) acc += p0 + u < a.n_parts ? v[u] : 0.f;
-            }
-            acc = acc / a.rows_total;
-            if (a.event_weight) {
-                int e = a.token_event[j];
-                e = e < 0 ? 0 : (e >= a.n_events ? a.n_events - 1 : e);
-                acc *= a.event_weight[e];
-            }
-            sc = acc;
-            a.scores[j] = sc;
-        } else {
-            sc = a.scores[j];
-        }
-        const int s = a.token_seg[j];
-        sg = (s >= 0 && s < a.n_seg) ? s : -1;
-    }
-    const uint32_t key = ordered_key(sc);
-    __syncthreads();
-    if (sg >= 0) atomicAdd(&hist[sg * 2048 + (key >> 21)], 1);
-    __syncthreads();
-    int32_t* ghist = &a.fs->hist[0][0];
-    for (int i = tid; i < a.n_seg * 2048; i += kSelThreads) {
-        const int v = hist[i];
-        if (v) atomicAdd(&ghist[i], v);
-    }
-    if (!arrive_and_check_last(&a.fs->arrive_a, &s_last)) return;
-    // last workgroup: the complete histograms come back into LDS, then one wave finds every class's bucket (no more barriers)
-    {
-        constexpr int kPer = kFastSeg * 2048 / kSelThreads;
-        int32_t h[kPer];
-#pragma unroll
-        for (int u = 0; u < kPer; ++u) h[u] = load_shared_between_workgroups(&ghist[tid + u * kSelThreads]);      // the block holds kFastSeg rows
-#pragma unroll
-        for (int u = 0; u < kPer; ++u) hist[tid + u * kSelThreads] = h[u];
-    }
-    __syncthreads();
-    if (tid >= 64) return;
-    for (int c = 0; c < a.n_seg; ++c) {
-        const int quota = args.quota[blockIdx.z][c];
-        const int pop = wave_hist_total(hist + c * 2048, 2048);
-        int digit = 0, rem = 0, cnt = 0;
-        const int mode = quota <= 0 ? kModeNone : (quota >= pop ? kModeAll : kModeSearch);
-        if (mode == kModeSearch) wave_find_bucket(hist + c * 2048, 2048, quota, &digit, &rem, &cnt);
-        if (tid == 0) { a.fs->state[c][0] = digit; a.fs->state[c][1] = rem; a.fs->state[c][2] = cnt; a.fs->state[c][3] = mode; }
-    }
-}
-
-constexpr int kCandRegs = 8;             // candidates a thread of the finishing workgroup keeps in registers
-
-__global__ __launch_bounds__(kSelThreads) void candidate_kernel(const FastArgs args) {
-    __shared__ int lhist[kFastSeg * 2048];
-    __shared__ int s_last, s_sure[kFastSeg], s_mode[kFastSeg], s_need[kFastSeg], s_cnt[kFastSeg];
-    __shared__ uint32_t s_tau[kFastSeg], s_keep_eq[kFastSeg], s_prefix[kFastSeg];
-    __shared__ int t_gt[kFastSeg][kFastTiles], t_eq[kFastSeg][kFastTiles];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int j = blockIdx.x * kSelThreads + tid;
-    const FastView a = to_video(args);
-    if (tid < kFastSeg) s_sure[tid] = 0;
-    int sg = -1;
-    uint32_t key = 0u;
-    if (j < a.n_vis) {
-        key = ordered_key(a.scores[j]);
-        const int s = a.token_seg[j];
-        sg = (s >= 0 && s < a.n_seg) ? s : -1;
-    }
-    bool sure = false, cand = false;
-    if (sg >= 0) {
-        const int mode = a.fs->state[sg][3], digit = a.fs->state[sg][0];
-        const int d = static_cast<int>(key >> 21);
-        sure = mode == kModeAll || (mode == kModeSearch && d > digit);
-        cand = mode == kModeSearch && d == digit;
-    }
-    __syncthreads();
-    for (int c = 0; c < a.n_seg; ++c) {
-        const unsigned long long m = __ballot(sure && sg == c);
-        if (lane == 0 && m) atomicAdd(&s_sure[c], __popcll(m));
-    }
-    {   // candidates of a wave take consecutive slots of the list
-        const unsigned long long m = __ballot(cand);
-        if (m) {
-            const int leader = __ffsll(static_cast<long long>(m)) - 1;
-            uint32_t base = 0u;
-            if (lane == leader) base = atomicAdd(&a.fs->cand_total, static_cast<uint32_t>(__popcll(m)));
-            base = __shfl(base, leader, 64);
-            if (cand) {
-                const uint32_t pos = base + __popcll(m & ((1ull << lane) - 1ull));
-                if (pos < static_cast<uint32_t>(a.n_vis)) {
-                    store_shared_between_workgroups(&a.cand_key[pos], key);
-                    store_shared_between_workgroups(&a.cand_tok[pos], (static_cast<uint32_t>(sg) << 24) | static_cast<uint32_t>(j));
-                }
-            }
-        }
-    }
-    __syncthreads();
-    if (tid < a.n_seg) store_shared_between_workgroups(&a.fs->tile_sure[tid][blockIdx.x], s_sure[tid]);
-    if (!arrive_and_check_last(&a.fs->arrive_b, &s_last)) return;
-
-    // ---- last workgroup: every thread keeps up to eight candidates in registers; the searches of all classes run
-    //      side by side, one wave per class walking that class's histogram ----
-    const int n_tiles = gridDim.x;
-    int m = static_cast<int>(load_shared_between_workgroups(&a.fs->cand_total));
-    m = m < a.n_vis ? m : a.n_vis;
-    const bool in_regs = m <= kCandRegs * kSelThreads;
-    uint32_t ck[kCandRegs];
-    int cm[kCandRegs];                                              // class << 6 | tile, -1: no candidate
-    {
-        // all loads are requested before the first is used: no branch between them (a slot past the list reads the
-        // list's last entry again and is dropped)
-        uint32_t tok[kCandRegs];
-        const int last = m > 0 ? m - 1 : 0;
-#pragma unroll
-        for (int u = 0; u < kCandRegs; ++u) {
-            const int i = tid + u * kSelThreads;
-            const int ic = i < last ? i : last;
-            tok[u] = load_shared_between_workgroups(&a.cand_tok[ic]);
-            ck[u] = load_shared_between_workgroups(&a.cand_key[ic]);
-        }
-#pragma unroll
-        for (int u = 0; u < kCandRegs; ++u) {
-            const int i = tid + u * kSelThreads;
-            const bool have = in_regs && i < m;
-            cm[u] = have ? static_cast<int>(((tok[u] >> 24) << 6) | (((tok[u] & 0xffffffu) >> 10) & 63u)) : -1;
-            ck[u] = have ? ck[u] : 0u;
-        }
-    }
-    // f(key, class, tile) for every candidate; a list too long for the registers is walked in memory
-    auto for_each_candidate = [&](auto&& f) {
-        if (in_regs) {
-#pragma unroll
-            for (int u = 0; u < kCandRegs; ++u)
-                if (cm[u] >= 0) f(ck[u], cm[u] >> 6, cm[u] & 63);
-        } else {
-            for (int i = tid; i < m; i += kSelThreads) {
-                const uint32_t tok = load_shared_between_workgroups(&a.cand_tok[i]);
-                f(load_shared_between_workgroups(&a.cand_key[i]), static_cast<int>(tok >> 24), static_cast<int>((tok & 0xffffffu) >> 10));
-            }
-        }
-    };
-    for (int i = tid; i < kFastSeg * kFastTiles; i += kSelThreads) {
-        const int c = i / kFastTiles, t = i % kFastTiles;
-        (&t_gt[0][0])[i] = (c < a.n_seg && t < n_tiles) ? load_shared_between_workgroups(&a.fs->tile_sure[c][t]) : 0;      // kept for sure
-        (&t_eq[0][0])[i] = 0;
-    }
-    if (tid < kFastSeg) {
-        const bool live = tid < a.n_seg;
-        s_mode[tid] = live ? a.fs->state[tid][3] : kModeNone;
-        s_prefix[tid] = live ? static_cast<uint32_t>(a.fs->state[tid][0]) << 21 : 0u;
-        s_need[tid] = live ? a.fs->state[tid][1] : 0;
-        s_cnt[tid] = live ? a.fs->state[tid][2] : 0;
-    }
-    __syncthreads();
-    // the remaining 21 key bits of every class's quota-th largest key, 11 then 10 bits
-    for (int top = 21; top > 0; top -= 11) {
-        const int bits = top < 11 ? top : 11, shift = top - bits, bins = 1 << bits;
-        const uint32_t hi_mask = 0xffffffffu << top, dmask = static_cast<uint32_t>(bins - 1);
-        for (int i = tid; i < kFastSeg * 2048; i += kSelThreads) lhist[i] = 0;
-        __syncthreads();
-        for_each_candidate([&](uint32_t k, int cls, int) {
-            if (s_mode[cls] == kModeSearch && (k & hi_mask) == s_prefix[cls]) atomicAdd(&lhist[cls * 2048 + ((k >> shift) & dmask)], 1);
-        });
-        __syncthreads();
-        const int w = tid >> 6;
-        if (w < a.n_seg && s_mode[w] == kModeSearch) {
-            int digit = 0, need = 0, cnt = 0;
-            wave_find_bucket(lhist + w * 2048, bins, s_need[w], &digit, &need, &cnt);
-            wave_sync();
-            if (lane == 0) { s_prefix[w] |= static_cast<uint32_t>(digit) << shift; s_need[w] = need; s_cnt[w] = cnt; }
-        }
-        __syncthreads();
-    }
-    if (tid < a.n_seg) {
-        const int mode = s_mode[tid];
-        uint32_t tau = 0u, keep_eq = kKeepAll;                      // kModeAll: every key is above or equal to 0
-        if (mode == kModeNone) { tau = 0xffffffffu; keep_eq = 0u; }
-        if (mode == kModeSearch) { tau = s_prefix[tid]; keep_eq = s_need[tid] >= s_cnt[tid] ? kKeepAll : static_cast<uint32_t>(s_need[tid]); }
-        s_tau[tid] = tau; s_keep_eq[tid] = keep_eq;
-        a.fs->sel_info[tid][0] = tau; a.fs->sel_info[tid][1] = keep_eq;
-    }
-    __syncthreads();
-    // per tile and class: candidates above / equal to the threshold (t_gt already holds the tokens kept for sure)
-    for_each_candidate([&](uint32_t k, int cls, int tile) {
-        if (cls < a.n_seg && tile < n_tiles) {
-            if (k > s_tau[cls]) atomicAdd(&t_gt[cls][tile], 1);
-            else if (k == s_tau[cls]) atomicAdd(&t_eq[cls][tile], 1);
-        }
-    });
-    __syncthreads();
-    if (tid >= 64) return;
-    // one wave, lane = tile (at most kFastTiles <= 64): per class the equal keys before every tile and the equal keys a
-    // tile still keeps (the first keep_eq by index), then the output offset of every tile
-    const bool live = lane < n_tiles;
-    int kept = 0;
-    for (int c = 0; c < a.n_seg; ++c) {
-        const int eq = live ? t_eq[c][lane] : 0;
-        int incl = eq;
+    for (int u = 0; u < PER; ++u) sum += mine_hist[u];
+    auto scan = [&](int v) {
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
-            const int up = __shfl_up(incl, off, 64);
-            if (lane >= off) incl += up;
+            const int up = __shfl_up(v, off, 64);
+            if (lane >= off) v += up;
         }
-        const int before = incl - eq;
-        const uint32_t keep_eq = s_keep_eq[c];
-        int room = keep_eq == kKeepAll ? eq : static_cast<int>(keep_eq) - before;
-        room = room < 0 ? 0 : room;
-        if (live) {
-            a.fs->eq_before[c][lane] = before;
-            kept += t_gt[c][lane] + (eq < room ? eq : room);
-        }
-    }
-    int incl = kept;
+        return v;
+    };
+    const int incl = scan(sum);
+    *population = __builtin_amdgcn_readlane(incl, 63);
+    const unsigned long long m = __ballot(incl - sum < need && incl >= need);
+    const int src = m ? __ffsll(static_cast<long long>(m)) - 1 : 0;
+    const int left = need - __builtin_amdgcn_readlane(incl - sum, src);      // keys needed from that lane's bins
+    const int hi = (64 - src) * PER - 1;                            // the largest digit among them
+    const int v = lane < PER ? hist[bin_slot(hi - lane)] : 0;
+    const int incl2 = scan(v);
+    const unsigned long long m2 = __ballot(incl2 - v < left && incl2 >= left);
+    const int at = m2 ? __ffsll(static_cast<long long>(m2)) - 1 : 0;
+    *digit = hi - at;
+    *rem = left - __builtin_amdgcn_readlane(incl2 - v, at);
+    *cnt = __builtin_amdgcn_readlane(v, at);
+}
+
+// What the selecting workgroup keeps in LDS.
+struct SelectShared {
+    int hist[kHistSlots];
+    int scan[17];
+    uint64_t kept[kFastTiles * 16];         // bit mask of the kept tokens of every 64-token group
+    uint64_t equal[kFastTiles * 16];        // of the tokens equal to a class's threshold (only with more ties than the list holds)
+    int before[kFastTiles * 16];            // kept (or equal) tokens of the groups before this one
+    uint32_t list_key[kListCap];
+    uint32_t list_tok[kListCap];
+    uint32_t lo, hi;                        // smallest and largest key
+    int need[kFastSeg], cnt[kFastSeg], base[kFastSeg + 1], fill[kFastSeg];
+    // a token is kept if key >> shift >= sure, and is a candidate if key >> shift == cand; the last entry is for tokens without a class
+    uint2 rule[kFastSeg + 1];
+};
+
+// Adds one to hist[slot] for every lane with slot >= 0.  A wave whose lanes all meet in one bin (a class of equal scores)
+// adds once instead of queueing at one address.
+__device__ __forceinline__ void hist_add(int* hist, int slot) {
+    const int first = __builtin_amdgcn_readfirstlane(slot);
+    const bool one_bin = __ballot(slot == first) == ~0ull;
+    if (slot >= 0 && (!one_bin || (threadIdx.x & 63) == 0)) atomicAdd(&hist[slot], one_bin ? 64 : 1);
+}
+
+// The selection of one video by one workgroup of 1024 threads: thread t owns tokens t, t + 1024, ... (at most K of them).
+template <int K>
+__device__ __forceinline__ void select_and_index(const FastArgs& a, const float* __restrict__ scores, const int32_t* __restrict__ token_seg,
+                                                 FastSel* fs, int32_t* __restrict__ kept_idx, SelectShared& sh) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n_vis = a.n_vis, n_seg = a.n_seg;
+    int n_tiles = (n_vis + kSelThreads - 1) / kSelThreads;
+    const int bits = n_seg <= 4 ? 11 : 9, class_slots = bin_slot(1 << bits);
+
+    // loads in rounds of up to twenty tokens, without a branch between them
+    uint32_t key[K], cls[(K + 3) / 4];      // class kFastSeg: a token without a valid class, never kept
+    uint32_t lo = 0xffffffffu, hi = 0u;
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int up = __shfl_up(incl, off, 64);
-        if (lane >= off) incl += up;
+    for (int i = 0; i < (K + 3) / 4; ++i) cls[i] = 0u;
+    constexpr int kRound = K < 20 ? K : 20;
+#pragma unroll
+    for (int i0 = 0; i0 < K; i0 += kRound) {
+        if (i0 < n_tiles) {
+            int sv[kRound];
+#pragma unroll
+            for (int u = 0; u < kRound; ++u) {
+                const uint32_t at = static_cast<uint32_t>(min(tid + (i0 + u) * kSelThreads, n_vis - 1)) * 4u;
+                key[i0 + u] = load_shared_between_workgroups(reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(scores) + at));
+                sv[u] = *reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(token_seg) + at);
+            }
+#pragma unroll
+            for (int u = 0; u < kRound; ++u) {
+                const int i = i0 + u;
+                key[i] = ordered_key(__uint_as_float(key[i]));
+                const bool ok = tid + i * kSelThreads < n_vis && sv[u] >= 0 && sv[u] < n_seg;
+                cls[i >> 2] |= static_cast<uint32_t>(ok ? sv[u] : kFastSeg) << (8 * (i & 3));
+                lo = ok && key[i] < lo ? key[i] : lo;
+                hi = ok && key[i] > hi ? key[i] : hi;
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < kRound; ++u) { key[i0 + u] = 0u; cls[(i0 + u) >> 2] |= static_cast<uint32_t>(kFastSeg) << (8 * ((i0 + u) & 3)); }
+        }
     }
-    if (live) a.fs->tile_off[lane] = incl - kept;
+    auto class_of = [&](int i) { return (cls[i >> 2] >> (8 * (i & 3))) & 0xffu; };
+    // Between the phases the keys and classes count as changed: otherwise the compiler keeps the K comparisons and class
+    // numbers of one phase for the next in registers it does not have.
+    auto fresh = [&]() {
+#pragma unroll
+        for (int i = 0; i < K; ++i) asm volatile("" : "+v"(key[i]));
+#pragma unroll
+        for (int i = 0; i < (K + 3) / 4; ++i) asm volatile("" : "+v"(cls[i]));
+        asm volatile("" : "+s"(n_tiles));
+    };
+    if (tid == 0) { sh.lo = 0xffffffffu; sh.hi = 0u; }
+    if (tid <= kFastSeg) sh.rule[tid] = make_uint2(0xffffffffu, 0xffffffffu);
+    if (tid < kFastSeg) { sh.fill[tid] = 0; sh.need[tid] = a.quota[blockIdx.z][tid]; sh.cnt[tid] = 0; }
+    for (int i = tid; i < n_seg * class_slots; i += kSelThreads) sh.hist[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        const uint32_t l2 = __shfl_xor(lo, off, 64), h2 = __shfl_xor(hi, off, 64);
+        lo = l2 < lo ? l2 : lo; hi = h2 > hi ? h2 : hi;
+    }
+    if (lane == 0) { atomicMin(&sh.lo, lo); atomicMax(&sh.hi, hi); }
+    __syncthreads();
+    lo = sh.lo;
+    const uint32_t range = sh.hi >= lo ? sh.hi - lo : 0u;
+#pragma unroll
+    for (int i = 0; i < K; ++i) key[i] -= lo;                       // (tokens without a class: any value, never looked at)
+
+    // digits of `bits` bits from the highest bit of the range down, until the threshold buckets of all classes together
+    // hold few enough keys, or to the last bit
+    int top = range ? 32 - __clz(range) : 0, shift = 0, listed = 0;
+    for (bool first = true;; first = false) {
+        shift = top > bits ? top - bits : 0;
+        fresh();
+        if (!first) {
+            for (int i = tid; i < n_seg * class_slots; i += kSelThreads) sh.hist[i] = 0;
+            __syncthreads();
+        }
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            if (i < n_tiles) {
+                const uint32_t c = class_of(i);
+                const bool in = c != kFastSeg && (first || (key[i] >> top) == sh.rule[c].y);
+                const int digit = static_cast<int>((key[i] >> shift) & ((1u << bits) - 1u));
+                hist_add(sh.hist, in ? static_cast<int>(c) * class_slots + bin_slot(digit) : -1);
+            }
+        }
+        __syncthreads();
+        if (wave < n_seg && (first || sh.cnt[wave] > 0)) {          // one wave per class
+            const int need = sh.need[wave];
+            int digit = 0, rem = 0, cnt = 0, population = 0;
+            if (bits == 11) wave_find_bucket<32>(sh.hist + wave * class_slots, need, &digit, &rem, &cnt, &population);
+            else            wave_find_bucket<8>(sh.hist + wave * class_slots, need, &digit, &rem, &cnt, &population);
+            if (lane == 0) {
+                if (first && need <= 0) { /* keeps nothing: the rule nobody meets stays */ }
+                else if (first && need >= population) sh.rule[wave] = make_uint2(0u, 0xffffffffu);        // keeps everything
+                else {
+                    const uint32_t prefix = (first ? 0u : sh.rule[wave].y << (top - shift)) | static_cast<uint32_t>(digit);
+                    sh.rule[wave] = make_uint2(prefix + 1u, prefix);
+                    sh.need[wave] = rem; sh.cnt[wave] = cnt;
+                }
+            }
+        }
+        __syncthreads();
+        listed = 0;
+        for (int c = 0; c < n_seg; ++c) listed += sh.cnt[c];
+        if (shift == 0 || listed <= kListCap) break;
+        top = shift;
+    }
+    // One pass decides every token but the candidates; those go to a list, class by class, and are ranked against each
+    // other under (key descending, index ascending).  More candidates than the list holds are equal keys of whole
+    // classes (shift is 0 then) and are taken in index order below.
+    const bool ranked = listed <= kListCap;
+    if (tid == 0) {
+        int run = 0;
+        for (int c = 0; c < n_seg; ++c) { sh.base[c] = run; run += sh.cnt[c]; }
+        sh.base[n_seg] = run;
+    }
+    __syncthreads();
+    fresh();
+    constexpr int kStep = 4;                                        // rules of four tokens are read from LDS together
+#pragma unroll
+    for (int i0 = 0; i0 < K; i0 += kStep) {
+        if (i0 < n_tiles) {
+            uint2 rule[kStep];
+            unsigned long long any = 0;
+#pragma unroll
+            for (int u = 0; u < kStep; ++u) rule[u] = sh.rule[class_of(i0 + u)];
+#pragma unroll
+            for (int u = 0; u < kStep; ++u) {
+                const uint32_t d = key[i0 + u] >> shift;
+                const bool has_class = class_of(i0 + u) != kFastSeg;
+                const unsigned long long m = __ballot(has_class && d >= rule[u].x);
+                any |= __ballot(has_class && d == rule[u].y);
+                if (lane == 0) sh.kept[(i0 + u) * 16 + wave] = m;
+            }
+            if (ranked && any) {
+#pragma unroll
+                for (int u = 0; u < kStep; ++u) {
+                    const uint32_t c = class_of(i0 + u);
+                    if (c != kFastSeg && (key[i0 + u] >> shift) == rule[u].y) {
+                        const int p = sh.base[c] + atomicAdd(&sh.fill[c], 1);
+                        if (p < kListCap) { sh.list_key[p] = key[i0 + u]; sh.list_tok[p] = static_cast<uint32_t>(tid + (i0 + u) * kSelThreads); }
+                    }
+                }
+            }
+        }
+    }
+    __syncthreads();
+    auto scan_groups = [&](const uint64_t* groups, int* total) {
+        const int ex = block_exclusive_scan(tid < n_tiles * 16 ? __popcll(groups[tid]) : 0, sh.scan, total);
+        if (tid < n_tiles * 16) sh.before[tid] = ex;
+        __syncthreads();
+    };
+    if (ranked) {
+        if (tid < sh.base[n_seg]) {
+            int c = 0;
+            while (c + 1 < n_seg && tid >= sh.base[c + 1]) ++c;
+            const uint32_t k = sh.list_key[tid], t = sh.list_tok[tid];
+            int above = 0;
+            for (int p = sh.base[c]; p < sh.base[c + 1]; ++p) {
+                const uint32_t o = sh.list_key[p];
+                above += (o > k || (o == k && sh.list_tok[p] < t)) ? 1 : 0;
+            }
+            if (above < sh.need[c]) atomicOr(reinterpret_cast<unsigned long long*>(&sh.kept[t >> 6]), 1ull << (t & 63));
+        }
+        __syncthreads();
+    } else {
+        for (int c = 0; c < n_seg; ++c) {
+            if (sh.cnt[c] == 0) continue;
+            const uint32_t tau = sh.rule[c].y;
+            fresh();
+#pragma unroll
+            for (int i = 0; i < K; ++i) {
+                if (i < n_tiles) {
+                    const unsigned long long m = __ballot(class_of(i) == static_cast<uint32_t>(c) && key[i] == tau);
+                    if (lane == 0) sh.equal[i * 16 + wave] = m;
+                }
+            }
+            __syncthreads();
+            int total = 0;
+            scan_groups(sh.equal, &total);
+            if (tid < n_tiles * 16) {
+                uint64_t left = sh.equal[tid], take = 0;
+                for (int room = sh.need[c] - sh.before[tid]; room > 0 && left; --room) { take |= left & (~left + 1); left &= left - 1; }
+                sh.kept[tid] |= take;
+            }
+            __syncthreads();
+        }
+    }
+    int total = 0;
+    scan_groups(sh.kept, &total);
+    asm volatile("" : "+s"(n_tiles));
+    const int total_keep = a.keeps.n[blockIdx.z];
+#pragma unroll 8
+    for (int i = 0; i < n_tiles; ++i) {
+        const uint64_t m = sh.kept[i * 16 + wave];
+        const int pos = sh.before[i * 16 + wave] + __popcll(m & ((1ull << lane) - 1ull));
+        if (((m >> lane) & 1ull) && pos < total_keep) kept_idx[pos] = tid + i * kSelThreads;
+    }
+    // fewer survivors than announced (a quota above its class population): the tail of the list is index 0, so that the
+    // gather stays in bounds
+    for (int p = total + tid; p < total_keep; p += kSelThreads) kept_idx[p] = 0;
+    if (tid == 0) fs->n_kept = total < total_keep ? total : total_keep;
+}
+
+template <int K>
+__global__ __launch_bounds__(kSelThreads) void score_select_kernel(const FastArgs a) {
+    __shared__ SelectShared sh;
+    __shared__ float part[3 * kSelThreads / 4];
+    __shared__ int s_last;
+    const int tid = threadIdx.x;
+    float* scores = of_video_elems(a.scores, a.n_vis);
+    const int32_t* token_seg = of_video_elems(a.token_seg, a.n_vis);
+    FastSel* fs = of_video(a.fs, a.ws_video);
+    if (a.colpart) {
+        // `split` threads share a token (a workgroup takes 1024 / split tokens): each adds its share of the workgroup rows'
+        // partial sums in order, four loads at a time (a part past the share's last one reads that one again and is not
+        // added).  With few partial sums a thread per token leaves one round of workgroups for eight videos instead of two
+        // and a half, with many the loads are the longer chain.
+        const float* colpart = of_video(a.colpart, a.ws_video);
+        const int split = a.n_parts >= kSplitParts ? 4 : 1, tokens = kSelThreads / split;
+        const int t = tid % tokens, quarter = tid / tokens;
+        const int j = blockIdx.x * tokens + t, jc = min(j, a.n_vis - 1);
+        const int per = (a.n_parts + split - 1) / split, p0 = quarter * per, p1 = min(a.n_parts, p0 + per);
+        float acc = 0.f;
+        for (int p = p0; p < p1; p += 4) {
+            float v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = colpart[static_cast<size_t>(min(p + u, p1 - 1)) * a.n_vis + jc];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) acc += p + u < p1 ? v[u] : 0.f;
+        }
+        float w = 1.f;
+        if (quarter == 0 && a.event_weight) {
+            const int32_t* token_event = of_video_elems(a.token_event, a.n_vis);
+            int e = token_event[jc];
+            e = e < 0 ? 0 : (e >= a.n_events ? a.n_events - 1 : e);
+            w = of_video_elems(a.event_weight, a.n_events)[e];
+        }
+        if (split > 1) {
+            if (quarter > 0) part[(quarter - 1) * tokens + t] = acc;
+            __syncthreads();
+        }
+        if (quarter == 0 && j < a.n_vis) {
+            if (split > 1) acc = ((acc + part[t]) + part[tokens + t]) + part[2 * tokens + t];
+            acc = acc / a.rows_total;
+            store_shared_between_workgroups(&scores[j], a.event_weight ? acc * w : acc);
+        }
+        if (!arrive_and_check_last(&fs->arrive, &s_last)) return;
+    }
+    select_and_index<K>(a, scores, token_seg, fs, of_video_elems(a.kept_idx, a.keep_stride), sh);
+}
+
+// Metadata that the kept tokens carry, written by the first n_blocks workgroups of the kernel that moves the rows, so that
+// the selecting workgroup leaves nothing but the index list (in the threads that move the rows themselves the extra
+// loads cost that kernel a tenth of its rate).
+struct CarryArgs {
+    const FastSel* fs;
+    const int32_t* token_seg;
+    const int32_t* token_event;
+    const int32_t* orig_idx_in;
+    int32_t* token_seg_out;
+    int32_t* token_event_out;
+    int32_t* orig_idx_out;
+    int64_t ws_video, keep_stride, orig_idx_in_stride, orig_idx_stride;
+    int n_blocks;                           // 0: nothing to carry (the general selection path writes the metadata itself)
+};
+// entry r of a video; kept_idx is the video's own list, entries past n_kept are padding
+__device__ __forceinline__ void carry_metadata(const CarryArgs& m, int video, int r, int n_keep, const int32_t* __restrict__ kept_idx, int n_vis) {
+    if (r >= n_keep) return;
+    const FastSel* fs = reinterpret_cast<const FastSel*>(reinterpret_cast<const char*>(m.fs) + video * m.ws_video);
+    int kidx = kept_idx[r];
+    kidx = kidx < 0 ? 0 : (kidx >= n_vis ? n_vis - 1 : kidx);
+    const bool real = r < fs->n_kept;
+    const int64_t in = static_cast<int64_t>(video) * n_vis + kidx, out = video * m.keep_stride + r;
+    if (m.token_seg_out) m.token_seg_out[out] = real ? m.token_seg[in] : 0;
+    if (m.token_event_out) m.token_event_out[out] = real ? m.token_event[in] : 0;
+    if (m.orig_idx_out)
+        m.orig_idx_out[video * m.orig_idx_stride + r] = real ? (m.orig_idx_in ? m.orig_idx_in[video * m.orig_idx_in_stride + kidx] : kidx) : 0;
 }
 
 // Source row of every output row of the compacted sequence [prefix; kept visual rows; text rows].
 __global__ __launch_bounds__(256) void hidden_index_kernel(int32_t* __restrict__ src_row, int out_rows, int vis_start, int n_vis, int n_keep,
-                                                           const int32_t* __restrict__ kept_idx) {
-    const int r = blockIdx.x * 256 + threadIdx.x;
+                                                           const int32_t* __restrict__ kept_idx, int video, const CarryArgs carry) {
+    if (static_cast<int>(blockIdx.x) < carry.n_blocks) { carry_metadata(carry, video, blockIdx.x * 256 + threadIdx.x, n_keep, kept_idx, n_vis); return; }
+    const int r = (blockIdx.x - carry.n_blocks) * 256 + threadIdx.x;
     if (r >= out_rows) return;
     int s;
     if (r < vis_start) s = r;
@@ -1234,15 +1242,24 @@ constexpr int kGatherThreads = 256;
 __global__ __launch_bounds__(kGatherThreads) void gather_rows_kernel(const u32x4_t* __restrict__ src, u32x4_t* __restrict__ dst,
                                                                      int64_t S, int64_t out_row_stride, int chunks_per_row, int vis_start,
                                                                      int n_vis, const int32_t* __restrict__ kept_idx, int64_t keep_stride,
-                                                                     const BatchKeep keeps) {
+                                                                     const BatchKeep keeps, const CarryArgs carry) {
     const int n_keep = keeps.n[blockIdx.z];
     const int64_t out_rows = S - n_vis + n_keep;
     src = of_video_elems(src, S * chunks_per_row); dst = of_video_elems(dst, out_row_stride * chunks_per_row);
     kept_idx = of_video_elems(kept_idx, keep_stride);
-    const int64_t gidx = static_cast<int64_t>(blockIdx.x) * kGatherThreads + threadIdx.x;
-    const int64_t r = gidx / chunks_per_row;
+    if (static_cast<int>(blockIdx.x) < carry.n_blocks) {
+        carry_metadata(carry, blockIdx.z, blockIdx.x * kGatherThreads + threadIdx.x, n_keep, kept_idx, n_vis);
+        return;
+    }
+    // row and chunk of the workgroup's first thread once (scalar), then a 32-bit division per thread
+    const int64_t first = static_cast<int64_t>(blockIdx.x - carry.n_blocks) * kGatherThreads;
+    const int64_t row0 = first < 0x7fffffff ? static_cast<int64_t>(static_cast<uint32_t>(first) / static_cast<uint32_t>(chunks_per_row))
+                                            : first / chunks_per_row;
+    const uint32_t x = static_cast<uint32_t>(first - row0 * chunks_per_row) + threadIdx.x;
+    const uint32_t dr = x / static_cast<uint32_t>(chunks_per_row);
+    const int64_t r = row0 + dr;
     if (r >= out_rows) return;
-    const int c = static_cast<int>(gidx - r * chunks_per_row);
+    const int c = static_cast<int>(x - dr * static_cast<uint32_t>(chunks_per_row));
     int64_t s;
     if (r < vis_start) s = r;
     else if (r < static_cast<int64_t>(vis_start) + n_keep) {
@@ -1263,11 +1280,13 @@ static size_t select_count_bytes(int n_vis) {
     return round_up(static_cast<size_t>(METOK_MAX_SEGMENTS) * select_tiles(n_vis) * sizeof(int32_t), 256);
 }
 static size_t select_general_bytes(int n_vis) { return 2 * select_count_bytes(n_vis) + METOK_MAX_SEGMENTS * 2 * sizeof(uint32_t); }
-// then the fast path: its state block and the candidate list (key and token of at most min(n_vis, 40960) candidates)
-static size_t fast_state_bytes();
+// then the fast path's state.  The reserve is larger than FastSel needs today: the size of a workspace is part of the
+// interface (it also decides which shapes metok_prefill_prune_static takes), so it stays what it has been.
+constexpr size_t kFastReserve = 34560;
+static_assert(sizeof(FastSel) <= kFastReserve, "the fast path's state outgrew its reserve");
 static size_t select_bytes(int n_vis) {
     const size_t cand = round_up(static_cast<size_t>(n_vis < kSelCache * kSelThreads ? n_vis : kSelCache * kSelThreads) * sizeof(uint32_t), 256);
-    return select_general_bytes(n_vis) + fast_state_bytes() + 2 * cand;
+    return select_general_bytes(n_vis) + kFastReserve + 2 * cand;
 }
 
 // In-place compaction (hidden_out == hidden): the source row of every output row as an index list, and the
@@ -1518,39 +1537,39 @@ static int prune_impl(int batch, const void* hidden, int64_t S, int D, int dtype
             return fail(METOK_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need, workspace_bytes);
         sel = ws;
         inplace_ws = ws + select_bytes(n_vis);
-        if (fast) {      // no packing kernel runs on this path: clear the fast path's counters and histograms here
-            hipLaunchKernelGGL(clear_words_kernel, dim3(8, 1, nb), dim3(256), 0, st, reinterpret_cast<uint32_t*>(sel + select_general_bytes(n_vis)),
-                               kFastClearWords, ws_video);
-            if ((rc = check_launch("clear"))) return rc;
-        }
     }
     int32_t* gt_count = reinterpret_cast<int32_t*>(sel);
     int32_t* eq_count = reinterpret_cast<int32_t*>(sel + select_count_bytes(n_vis));
     uint32_t* sel_info = reinterpret_cast<uint32_t*>(sel + 2 * select_count_bytes(n_vis));
-    const int32_t* tile_off = nullptr;
-    const int32_t* eq_before = nullptr;
+    CarryArgs carry = {};
     if (fast) {
         FastArgs fa;
         fa.fs = reinterpret_cast<FastSel*>(sel + select_general_bytes(n_vis));
-        const size_t cand = round_up(static_cast<size_t>(n_vis) * sizeof(uint32_t), 256);
-        fa.cand_key = reinterpret_cast<uint32_t*>(sel + select_general_bytes(n_vis) + fast_state_bytes());
-        fa.cand_tok = reinterpret_cast<uint32_t*>(sel + select_general_bytes(n_vis) + fast_state_bytes() + cand);
         fa.colpart = colpart; fa.n_parts = n_parts; fa.rows_total = static_cast<float>(static_cast<int64_t>(Hq) * Tq);
         fa.token_event = token_event; fa.event_weight = event_weight; fa.n_events = n_events;
         fa.scores = scores; fa.token_seg = token_seg; fa.n_vis = n_vis; fa.n_seg = n_seg; fa.ws_video = ws_video;
+        fa.kept_idx = kept_idx; fa.keep_stride = keep_stride; fa.keeps = keeps;
         for (int b = 0; b < METOK_MAX_BATCH; ++b)
-            for (int c = 0; c < kFastSeg; ++c) fa.quota[b][c] = (b < batch && c < n_seg) ? seg_quota[static_cast<size_t>(b) * n_seg + c] : 0;
+            for (int c = 0; c < kFastSeg; ++c)
+                fa.quota[b][c] = static_cast<uint16_t>((b < batch && c < n_seg) ? seg_quota[static_cast<size_t>(b) * n_seg + c] : 0);
         {
-            TraceScope trace_scope(METOK_TRACE_SELECT, st);          // both selection kernels
-            hipLaunchKernelGGL(score_hist_kernel, dim3(n_tiles, 1, nb), dim3(kSelThreads), 0, st, fa);
-            hipLaunchKernelGGL(candidate_kernel, dim3(n_tiles, 1, nb), dim3(kSelThreads), 0, st, fa);
+            // one launch is both "select" and "write index": the trace hook brackets it for either name
+            TraceScope trace_select(METOK_TRACE_SELECT, st);
+            TraceScope trace_index(METOK_TRACE_WRITE_INDEX, st);
+            const int score_tokens = kSelThreads / (n_parts >= kSplitParts ? 4 : 1);
+            const dim3 grid(colpart ? (n_vis + score_tokens - 1) / score_tokens : 1, 1, nb);
+            if (n_tiles <= 4) hipLaunchKernelGGL(score_select_kernel<4>, grid, dim3(kSelThreads), 0, st, fa);
+            else if (n_tiles <= 12) hipLaunchKernelGGL(score_select_kernel<12>, grid, dim3(kSelThreads), 0, st, fa);
+            else hipLaunchKernelGGL(score_select_kernel<kFastTiles>, grid, dim3(kSelThreads), 0, st, fa);
         }
         if ((rc = check_launch("select"))) return rc;
-        sel_info = &fa.fs->sel_info[0][0];
-        tile_off = fa.fs->tile_off;
-        eq_before = &fa.fs->eq_before[0][0];
+        carry.n_blocks = static_cast<int>((max_keep + 255) / 256);
+        carry.fs = fa.fs; carry.token_seg = token_seg; carry.token_event = token_event; carry.orig_idx_in = orig_idx_in;
+        carry.token_seg_out = token_seg_out; carry.token_event_out = token_event_out; carry.orig_idx_out = orig_idx_out;
+        carry.ws_video = ws_video; carry.keep_stride = keep_stride; carry.orig_idx_in_stride = orig_idx_in_stride; carry.orig_idx_stride = orig_idx_stride;
     } else {
         // the general selection takes its quotas by value: one launch per video
+        {
         TraceScope trace_scope(METOK_TRACE_SELECT, st);
         for (int b = 0; b < batch; ++b) {
             Quotas quotas;
@@ -1565,12 +1584,14 @@ static int prune_impl(int batch, const void* hidden, int64_t S, int D, int dtype
                 hipLaunchKernelGGL(select_kernel<false>, dim3(n_seg), dim3(kSelThreads), 0, st, sc_b, seg_b, n_vis, n_tiles, quotas,
                                    at(gt_count), at(eq_count), at(sel_info));
         }
+        }
         if ((rc = check_launch("select"))) return rc;
+        TraceScope trace_index(METOK_TRACE_WRITE_INDEX, st);
+        hipLaunchKernelGGL(write_index_kernel, dim3(n_tiles, 1, nb), dim3(kIdxThreads), 0, st, scores, sel_info, gt_count, eq_count, token_seg,
+                           n_vis, n_seg, n_tiles, 0, token_event, orig_idx_in, kept_idx, token_seg_out, token_event_out, orig_idx_out,
+                           ws_video, keep_stride, orig_idx_in_stride, orig_idx_stride, keeps);
+        if ((rc = check_launch("write index"))) return rc;
     }
-    { TraceScope trace_scope(METOK_TRACE_WRITE_INDEX, st); hipLaunchKernelGGL(write_index_kernel, dim3(n_tiles, 1, nb), dim3(kIdxThreads), 0, st, scores, sel_info, gt_count, eq_count, token_seg, n_vis, n_seg,
-                       n_tiles, 0, token_event, orig_idx_in, kept_idx, token_seg_out,
-                       token_event_out, orig_idx_out, tile_off, eq_before, ws_video, keep_stride, orig_idx_in_stride, orig_idx_stride, keeps); }
-    if ((rc = check_launch("write index"))) return rc;
     if (in_place) {
         // the row mover takes one sequence per call here: the videos of a batch go one after the other
         for (int b = 0; b < batch; ++b) {
@@ -1578,8 +1599,8 @@ static int prune_impl(int batch, const void* hidden, int64_t S, int D, int dtype
             if (out_rows == 0) continue;
             char* ws_b = inplace_ws + static_cast<size_t>(b) * ws_video;
             int32_t* src_row = reinterpret_cast<int32_t*>(ws_b);
-            hipLaunchKernelGGL(hidden_index_kernel, dim3(static_cast<unsigned>((out_rows + 255) / 256)), dim3(256), 0, st, src_row,
-                               static_cast<int>(out_rows), vis_start, n_vis, keeps.n[b], kept_idx + static_cast<size_t>(b) * keep_stride);
+            hipLaunchKernelGGL(hidden_index_kernel, dim3(static_cast<unsigned>((out_rows + 255) / 256) + carry.n_blocks), dim3(256), 0, st, src_row,
+                               static_cast<int>(out_rows), vis_start, n_vis, keeps.n[b], kept_idx + static_cast<size_t>(b) * keep_stride, b, carry);
             if ((rc = check_launch("hidden index"))) return rc;
             RowMoveLayer layer;
             layer.k = static_cast<char*>(hidden_out) + static_cast<size_t>(b) * S * row_bytes; layer.v = nullptr; layer.idx = src_row;
@@ -1593,11 +1614,11 @@ static int prune_impl(int batch, const void* hidden, int64_t S, int D, int dtype
     }
     const int chunks_per_row = static_cast<int>(row_bytes / 16);
     const int64_t blocks = (max_out_rows * chunks_per_row + kGatherThreads - 1) / kGatherThreads;
-    if (blocks > 0x7fffffff) return fail(METOK_ERR_INVALID_ARG, "hidden_out too large for one launch");
+    if (blocks + carry.n_blocks > 0x7fffffff) return fail(METOK_ERR_INVALID_ARG, "hidden_out too large for one launch");
     if (blocks == 0) return METOK_OK;
-    { TraceScope trace_scope(METOK_TRACE_GATHER_ROWS, st); hipLaunchKernelGGL(gather_rows_kernel, dim3(static_cast<unsigned>(blocks), 1, nb), dim3(kGatherThreads), 0, st,
+    { TraceScope trace_scope(METOK_TRACE_GATHER_ROWS, st); hipLaunchKernelGGL(gather_rows_kernel, dim3(static_cast<unsigned>(blocks) + carry.n_blocks, 1, nb), dim3(kGatherThreads), 0, st,
                        static_cast<const u32x4_t*>(hidden), static_cast<u32x4_t*>(hidden_out), S, out_row_stride, chunks_per_row,
-                       vis_start, n_vis, kept_idx, keep_stride, keeps); }
+                       vis_start, n_vis, kept_idx, keep_stride, keeps, carry); }
     return check_launch("gather");
 }
 
