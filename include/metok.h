@@ -205,8 +205,8 @@ METOK_API int metok_segment_compress(const void* feats, int dtype, int T, int gr
 /*
  * Stage 1 in one call for a batch of videos of one shape (Sec. 3.2.1, Algorithm 1): metok_segment_compress on each of
  * `batch` videos (1 <= batch <= METOK_MAX_BATCH) with the same settings.  Every kernel is launched once for the whole
- * batch (four launches in the one-pass case, four in the two-pass case: statistics, segmentation, plan, pooling; the
- * planning kernels, one workgroup per video, run side by side); only with METOK_SIM_POOLED the videos are processed
+ * batch (two launches in the one-pass case, three in the two-pass case: statistics, segmentation and plan, pooling; the
+ * videos' planning workgroups run side by side); only with METOK_SIM_POOLED the videos are processed
  * one after the other.  Per video the results are those of metok_segment_compress, bit for bit.
  *   Every array carries a leading batch dimension and is tightly packed: feats [batch, T, N, d], text_emb [batch, d],
  *   sim [batch, T-1], event_start [batch, k+1], frame_event / frame_is_key / frame_stride / frame_score [batch, T],
@@ -490,7 +490,7 @@ enum {
     METOK_TRACE_POOL = 2,               /* adaptive pooling pass */
     METOK_TRACE_FRAME_STATS_POOL2 = 3,  /* both in one pass (uniform stride 2) */
     METOK_TRACE_SEGMENT = 4,
-    METOK_TRACE_PLAN = 5,
+    METOK_TRACE_PLAN = 5,               /* the same launch as METOK_TRACE_SEGMENT in the calls that do both */
     METOK_TRACE_ROW_STATS = 6,          /* attention pass 1 (softmax statistics) */
     METOK_TRACE_COL_SUMS = 7,           /* attention pass 2 (probability mass per key) */
     METOK_TRACE_SELECT = 8,

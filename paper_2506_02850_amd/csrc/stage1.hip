@@ -4,8 +4,9 @@
 // Kernels
 //   frame_stats_kernel   one streaming pass over V: per frame |v_i|^2 and <v_i, v_{i+1}> (Eq. 4) and
 //                        the mean per-token cosine with the text embedding (Eq. 5)
-//   segment_kernel       one workgroup: T-1 cosines, the k-1 lowest become boundaries
-//   plan_kernel          one workgroup: event scores, key events, key frames, strides, row offsets
+//   segment_kernel       per-frame totals, then in the workgroup that arrives last: T-1 cosines, the k-1 lowest become
+//                        boundaries, and (calls that do all of stage 1) the plan
+//   plan_kernel          the plan on its own: event scores, key events, key frames, strides, row offsets
 //   pool_kernel          second streaming pass: s x s mean pooling of every frame, packed output
 //   frame_stats_pool2_kernel   statistics and 2 x 2 pooling from ONE pass, when every frame's stride is 2
 //   frame_mean_kernel, frame_score_kernel, fill_token_event_kernel   small helpers of the other readings / paths
@@ -48,7 +49,9 @@ __device__ __forceinline__ float swap16_add(float a, float b) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-template <typename T, int G, int KL>
+// KEEP: the loads stay without the streaming hint, so that the rows are still in the memory-side cache (256 MB) when the
+// pooling pass reads them again.
+template <typename T, int G, int KL, bool KEEP>
 __global__ __launch_bounds__(kStatsThreads) void frame_stats_kernel(
     const T* __restrict__ feats, const T* __restrict__ text, int T_frames, int N, int d,
     int frames_per_run, int do_pair, int sim_mode, float* __restrict__ part, int C, int64_t ws_video) {
@@ -75,8 +78,11 @@ __global__ __launch_bounds__(kStatsThreads) void frame_stats_kernel(
     const bool do_text = text != nullptr;
 #pragma unroll
     for (int k = 0; k < KL; ++k) {
+        // one unconditional 16-byte load and a mask: as a conditional load it became four dword loads behind a branch each
         const int c = sub + k * G;
-        txt[k] = (do_text && c < nchunks) ? reinterpret_cast<const uint4*>(text)[c] : zero;
+        const uint4 raw = reinterpret_cast<const uint4*>(do_text ? text : feats)[c < nchunks ? c : nchunks - 1];
+        const uint32_t in = do_text && c < nchunks ? 0xffffffffu : 0u;
+        txt[k] = make_uint4(raw.x & in, raw.y & in, raw.z & in, raw.w & in);
         tn2 = E::dot(txt[k], txt[k], tn2);
     }
     const float tnorm = sqrtf(group_sum<G>(tn2));
@@ -94,7 +100,10 @@ __global__ __launch_bounds__(kStatsThreads) void frame_stats_kernel(
     auto load_row = [&](int t, uint4 (&dst)[KL]) {
         const uint4* row = reinterpret_cast<const uint4*>(feats) + (static_cast<size_t>(t) * N + (tok_ok ? n : 0)) * row_chunks;
 #pragma unroll
-        for (int k = 0; k < KL; ++k) dst[k] = load_stream(row + chc[k]);
+        for (int k = 0; k < KL; ++k) {
+            if constexpr (KEEP) dst[k] = *(row + chc[k]);
+            else dst[k] = load_stream(row + chc[k]);
+        }
     };
 
     const int t_last = (do_pair && t1 < T_frames) ? t1 : t1 - 1;      // last frame that is loaded
@@ -189,77 +198,109 @@ __global__ __launch_bounds__(kStatsThreads) void frame_stats_kernel(
 }
 
 // ---------------------------------------------------------------------------------------------
-// segment_kernel: one workgroup of 1024 threads.
+// Segmentation and plan of a video.
+//
+// reduce_partials     every workgroup: per-frame totals of the partial sums, a wave per frame
+// segment_video       one workgroup: T-1 cosines, the k-1 lowest are boundaries
+// plan_video          one workgroup: event scores, key events, key frames, strides, row offsets
+//
+// segment_kernel spreads the totals over up to kMaxReduceWgs workgroups; the one that arrives last at an atomic counter
+// goes on with the segmentation and, in the calls that do the whole of stage 1, with the plan (and the event ids of
+// uniformly pooled rows), so that nothing but the totals is handed over and no launch is spent on one workgroup's work.
+// All of it is latency.  Against one workgroup per video for the totals and a launch of its own for the plan: 8 videos x
+// 256 frames 23 + 12 us (and 4.5 us for the event ids) -> 19.6 us, 128 frames 13 + 7 -> 13.4 us, 32 frames 13 + 7 -> 11 us.
 // ---------------------------------------------------------------------------------------------
 constexpr int kSegThreads = 1024;
+constexpr int kMaxReduceWgs = 64;
 constexpr int kRankLoopFrames = 2048;      // up to here every thread ranks its frames against all others
+constexpr int kFillRowsInPlan = 65536;     // up to so many uniformly pooled rows the planning workgroup writes their event ids
 
-__global__ __launch_bounds__(kSegThreads) void segment_kernel(
-    const float* __restrict__ part, int C, int T, int N, int k, int have_text, int sim_mode,
-    float* __restrict__ sim, int32_t* __restrict__ event_start, int32_t* __restrict__ frame_event,
-    float* __restrict__ frame_score, float* __restrict__ frame_norm2, float* __restrict__ pair_dot, int64_t ws_video) {
-    __shared__ __align__(16) uint32_t key[METOK_MAX_FRAMES + 8];      // ordered keys of S_i, padded with the largest key
-    __shared__ int scan_scratch[17];
-    const int tid = threadIdx.x;
-    part = of_video(part, ws_video); frame_norm2 = of_video(frame_norm2, ws_video); pair_dot = of_video(pair_dot, ws_video);
-    sim = of_video_elems(sim, T - 1); event_start = of_video_elems(event_start, k + 1);
-    frame_event = of_video_elems(frame_event, T); frame_score = of_video_elems(frame_score, T);
+struct SegmentArgs {
+    float* part;                           // [T][C][3]
+    int C, T, N, k, have_text, sim_mode;
+    float* sim;
+    int32_t* event_start;
+    int32_t* frame_event;
+    float* frame_score;                    // NULL: not wanted
+    float* frame_norm2;                    // workspace [T]
+    float* pair_dot;                       // workspace [T]
+    int64_t ws_video;
+};
+struct PlanArgs1 {
+    int n_key_events;
+    double beta;
+    int s_key_kf, s_key_nf, s_non_kf, s_non_nf;
+    int grid_h, grid_w, event_reduce, pool_edge;
+    float* event_score;
+    uint8_t* event_is_key;
+    uint8_t* frame_is_key;
+    int32_t* frame_stride;
+    int32_t* frame_offsets;
+    int32_t* frame_event_ws;               // workspace [T]
+    float* frame_score_out;                // NULL: not wanted
+    int fill_rows_per_frame;               // > 0: rows_per_frame consecutive rows carry their frame's event id
+    int32_t* token_event;
+    int64_t rows_video;
+    int64_t ws_video;
+};
 
-    // per-frame totals: the 3 C partial sums of a frame are contiguous (|v|^2, pair product, cosine sum, repeated C
-    // times).  A wave takes four frames at a time; a lane reads the floats lane, lane + 64, ... of each and adds every
-    // value to the total of its component; the lane totals are combined by a fixed butterfly, so the result does not
-    // depend on timing.  The 16 loads of a step are requested together, without a branch between them (a position past
-    // the end reads the last one again and is not added).
-    {
-        constexpr int kWaves = kSegThreads / 64, kBatch = 4, kRounds = 4;
-        const int lane = tid & 63, wave = tid >> 6;
-        const int n = 3 * C;
-        for (int tb = wave; tb < T; tb += kWaves * kBatch) {
-            float acc[kBatch][3];
+// Totals handed to the last workgroup pass the caches that are not coherent between the chip's dies.
+__device__ __forceinline__ void store_total(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ float load_total(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// The C partial triples of a frame are contiguous; a lane adds the triples lane, lane + 64, ..., four of them requested
+// together (a position past the end reads the last triple again and is not added), and the lane totals are combined by a
+// fixed butterfly: the result does not depend on timing or on the number of workgroups.
+__device__ __forceinline__ void reduce_partials(const SegmentArgs& a, const float* part, float* frame_score, float* frame_norm2, float* pair_dot) {
+    struct Triple { float x, y, z; };
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    constexpr int kWaves = kSegThreads / 64, kRounds = 4;
+    for (int t = blockIdx.x * kWaves + wave; t < a.T; t += gridDim.x * kWaves) {
+        const Triple* src = reinterpret_cast<const Triple*>(part) + static_cast<size_t>(t) * a.C;
+        float p = 0.f, q = 0.f, c = 0.f;
+        for (int c0 = 0; c0 < a.C; c0 += 64 * kRounds) {
+            Triple v[kRounds];
 #pragma unroll
-            for (int u = 0; u < kBatch; ++u) { acc[u][0] = 0.f; acc[u][1] = 0.f; acc[u][2] = 0.f; }
-            for (int e0 = 0; e0 < n; e0 += 64 * kRounds) {
-                float v[kBatch][kRounds];
+            for (int r = 0; r < kRounds; ++r) v[r] = src[min(c0 + 64 * r + lane, a.C - 1)];
 #pragma unroll
-                for (int u = 0; u < kBatch; ++u) {
-                    const int t = tb + u * kWaves < T ? tb + u * kWaves : T - 1;
-                    const float* src = part + static_cast<size_t>(t) * n;
-#pragma unroll
-                    for (int r = 0; r < kRounds; ++r) {
-                        const int e = e0 + 64 * r + lane;
-                        v[u][r] = src[e < n ? e : n - 1];
-                    }
-                }
-#pragma unroll
-                for (int r = 0; r < kRounds; ++r) {
-                    const int e = e0 + 64 * r + lane;
-                    const int comp = e < n ? e % 3 : 3;
-#pragma unroll
-                    for (int u = 0; u < kBatch; ++u) {
-                        acc[u][0] += comp == 0 ? v[u][r] : 0.f;
-                        acc[u][1] += comp == 1 ? v[u][r] : 0.f;
-                        acc[u][2] += comp == 2 ? v[u][r] : 0.f;
-                    }
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                const int t = tb + u * kWaves;
-                const float a = wave_sum(acc[u][0]), b = wave_sum(acc[u][1]), c3 = wave_sum(acc[u][2]);
-                if (lane == 0 && t < T) {
-                    frame_norm2[t] = a;
-                    pair_dot[t] = b;
-                    if (have_text && frame_score) frame_score[t] = c3 / static_cast<float>(N);
-                }
+            for (int r = 0; r < kRounds; ++r) {
+                const bool in = c0 + 64 * r + lane < a.C;
+                p += in ? v[r].x : 0.f; q += in ? v[r].y : 0.f; c += in ? v[r].z : 0.f;
             }
         }
+        p = wave_sum(p); q = wave_sum(q); c = wave_sum(c);
+        if (lane == 0) {
+            store_total(frame_norm2 + t, p);
+            store_total(pair_dot + t, q);
+            if (a.have_text && frame_score) store_total(frame_score + t, c / static_cast<float>(a.N));
+        }
     }
-    __syncthreads();
+}
+
+// LDS of the workgroup that segments and plans
+struct SegmentShared {
+    uint32_t key[METOK_MAX_FRAMES + 8];    // ordered keys of S_i (padded with the largest key), later of the frame scores
+    uint32_t ekey[METOK_MAX_FRAMES];       // ordered keys of the event scores
+    uint16_t start[METOK_MAX_FRAMES + 2];  // event_start
+    uint16_t event[METOK_MAX_FRAMES];      // frame -> event
+    uint8_t ev_key[METOK_MAX_FRAMES];
+    int scan[17];
+    int hist[256];
+    uint32_t prefix;
+    int need, last, n_long;
+    int long_list[8];
+};
+
+__device__ __forceinline__ void segment_video(const SegmentArgs& a, SegmentShared& sh, float* sim, int32_t* event_start, int32_t* frame_event,
+                                              const float* frame_norm2, const float* pair_dot) {
+    const int tid = threadIdx.x, T = a.T, k = a.k;
+    uint32_t* key = sh.key;
+    int* scan_scratch = sh.scan;
     // Eq. 4
     for (int t = tid; t < T - 1; t += kSegThreads) {
-        const float den = sqrtf(frame_norm2[t]) * sqrtf(frame_norm2[t + 1]);
-        const float s = sim_mode == METOK_SIM_TOKEN_MEAN ? pair_dot[t] / static_cast<float>(N)
-                                                         : ((den < kZeroNorm) ? 0.f : pair_dot[t] / den);
+        const float n0 = load_total(frame_norm2 + t), n1 = load_total(frame_norm2 + t + 1), dot = load_total(pair_dot + t);
+        const float den = sqrtf(n0) * sqrtf(n1);
+        const float s = a.sim_mode == METOK_SIM_TOKEN_MEAN ? dot / static_cast<float>(a.N) : ((den < kZeroNorm) ? 0.f : dot / den);
         sim[t] = s;
         key[t] = ordered_key(s);
     }
@@ -273,9 +314,9 @@ __global__ __launch_bounds__(kSegThreads) void segment_kernel(
         // Long videos: the (k-1)-th lowest key by a radix select over the keys in LDS (four 8-bit digits), then
         // "below it, or equal to it and among the first equal keys by index" -- the same set as the rank rule
         // below, in O(T) instead of O(T^2 / threads) compares.
-        __shared__ int hist[256];
-        __shared__ uint32_t s_prefix;
-        __shared__ int s_need;
+        int* hist = sh.hist;
+        uint32_t& s_prefix = sh.prefix;
+        int& s_need = sh.need;
         if (tid == 0) { s_prefix = 0u; s_need = k - 1; }
         for (int shift = 24; shift >= 0 && k > 1; shift -= 8) {
             if (tid < 256) hist[tid] = 0;
@@ -319,6 +360,29 @@ __global__ __launch_bounds__(kSegThreads) void segment_kernel(
                 ++eq_rank;
             }
         }
+    } else if (T <= kSegThreads / 2) {
+        // Short videos: `share` threads rank a frame together (with a thread per frame most of the workgroup would idle
+        // through the walk over all keys: 256 frames 14200 -> 4000 cycles).
+        int share = 2;
+        while (share < 64 && T * share * 2 <= kSegThreads) share *= 2;
+        const int f = tid / share, i = f - 1;
+        int rank = 0;
+        if (f >= 1 && f < T) {
+            const uint32_t ki = key[i];
+            const uint4* key4 = reinterpret_cast<const uint4*>(key);
+            for (int q = tid % share; q < n_quads; q += share) {
+                const uint4 km = key4[q];
+                const int m = 4 * q;
+                rank += (km.x < ki || (km.x == ki && m < i)) ? 1 : 0;
+                rank += (km.y < ki || (km.y == ki && m + 1 < i)) ? 1 : 0;
+                rank += (km.z < ki || (km.z == ki && m + 2 < i)) ? 1 : 0;
+                rank += (km.w < ki || (km.w == ki && m + 3 < i)) ? 1 : 0;
+            }
+        }
+        for (int off = share / 2; off >= 1; off >>= 1) rank += __shfl_xor(rank, off, 64);
+        if (tid % share == 0 && f < T) sh.ekey[f] = static_cast<uint32_t>(rank);
+        __syncthreads();
+        if (tid >= 1 && tid < T && static_cast<int>(sh.ekey[tid]) < k - 1) my_flags = 1u;      // per is 1
     } else
     for (int j = 0; j < per; ++j) {
         const int f = tid * per + j;                          // frame f opens an event if pair f-1 is a boundary
@@ -348,14 +412,15 @@ __global__ __launch_bounds__(kSegThreads) void segment_kernel(
         if (f < T) {
             if (my_flags & (1u << j)) {
                 ++ev;
-                if (ev <= k - 1) event_start[ev] = f;         // total == k-1 by construction; the guard is for NaN input
+                if (ev <= k - 1) { event_start[ev] = f; sh.start[ev] = static_cast<uint16_t>(f); }      // total == k-1 by construction; the guard is for NaN input
             }
             frame_event[f] = ev < k ? ev : k - 1;
+            sh.event[f] = static_cast<uint16_t>(ev < k ? ev : k - 1);
         }
     }
     if (tid == 0) {
-        event_start[0] = 0;
-        event_start[k] = T;
+        event_start[0] = 0; sh.start[0] = 0;
+        event_start[k] = T; sh.start[k] = static_cast<uint16_t>(T);
     }
 }
 
@@ -402,7 +467,7 @@ __global__ __launch_bounds__(kSegThreads) void frame_score_kernel(const float* _
 }
 
 // ---------------------------------------------------------------------------------------------
-// plan_kernel: one workgroup.  Event scores, key events, key frames, strides and output offsets.
+// plan_video: event scores, key events, key frames, strides and output offsets.
 // ---------------------------------------------------------------------------------------------
 __device__ __forceinline__ int pooled_side(int g, int s, int edge) {
     return edge == METOK_POOL_FLOOR ? max(1, g / s) : (g + s - 1) / s;
@@ -448,30 +513,39 @@ __device__ __forceinline__ uint32_t block_top_n_flags(const uint32_t* keys, int 
     return flags;
 }
 
-__global__ __launch_bounds__(kSegThreads) void plan_kernel(
-    const float* __restrict__ frame_score, const int32_t* __restrict__ event_start, int T, int k,
-    int n_key_events, double beta, int s_key_kf, int s_key_nf, int s_non_kf, int s_non_nf,
-    int grid_h, int grid_w, int event_reduce, int pool_edge,
-    float* __restrict__ event_score, uint8_t* __restrict__ event_is_key, uint8_t* __restrict__ frame_is_key,
-    int32_t* __restrict__ frame_stride, int32_t* __restrict__ frame_offsets, int32_t* __restrict__ frame_event_ws,
-    float* __restrict__ frame_score_out, int64_t ws_video) {
-    __shared__ __align__(16) uint32_t ekey[METOK_MAX_FRAMES];    // ordered keys of the event scores (k <= T), then of the frame scores
-    __shared__ uint8_t ev_key[METOK_MAX_FRAMES];
-    __shared__ int scan_scratch[17];
+// sh.start and sh.event hold the segmentation; frame_score is read past the caches (segment_kernel's totals).
+__device__ __forceinline__ void plan_video(const PlanArgs1& a, SegmentShared& sh, const float* frame_score, int T, int k) {
     const int tid = threadIdx.x;
-    frame_score = of_video_elems(frame_score, T); event_start = of_video_elems(event_start, k + 1);
-    event_score = of_video_elems(event_score, k); event_is_key = of_video_elems(event_is_key, k);
-    frame_is_key = of_video_elems(frame_is_key, T); frame_stride = of_video_elems(frame_stride, T);
-    frame_offsets = of_video_elems(frame_offsets, T + 1); frame_event_ws = of_video(frame_event_ws, ws_video);
-    frame_score_out = of_video_elems(frame_score_out, T);
-
+    const int n_key_events = a.n_key_events, event_reduce = a.event_reduce, pool_edge = a.pool_edge, grid_h = a.grid_h, grid_w = a.grid_w;
+    const double beta = a.beta;
+    float* event_score = of_video_elems(a.event_score, k);
+    uint8_t* event_is_key = of_video_elems(a.event_is_key, k);
+    uint8_t* frame_is_key = of_video_elems(a.frame_is_key, T);
+    int32_t* frame_stride = of_video_elems(a.frame_stride, T);
+    int32_t* frame_offsets = of_video_elems(a.frame_offsets, T + 1);
+    int32_t* frame_event_ws = of_video(a.frame_event_ws, a.ws_video);
+    float* frame_score_out = of_video_elems(a.frame_score_out, T);
+    int* scan_scratch = sh.scan;
+    uint32_t* fkey = sh.key;
+    uint32_t* ekey = sh.ekey;
+    uint8_t* ev_key = sh.ev_key;
+    // the frame scores as ordered keys: everything below compares or adds them from LDS
+    __syncthreads();
+    for (int f = tid; f < T; f += kSegThreads) {
+        const float x = load_total(frame_score + f);
+        fkey[f] = ordered_key(x);
+        if (frame_score_out) frame_score_out[f] = x;
+    }
+    if (tid == 0) sh.n_long = 0;
+    __syncthreads();
+    auto score_of = [&](int f) { const uint32_t u = fkey[f]; return __uint_as_float((u & 0x80000000u) ? u & 0x7fffffffu : ~u); };
     // event score: mean (Sec. 3.2.1) or max (Algorithm 1) of the frame scores, frames in index order
     for (int e = tid; e < k; e += kSegThreads) {
-        int a = event_start[e], b = event_start[e + 1];
-        a = max(0, min(a, T)); b = max(a, min(b, T));
+        const int lo = sh.start[e], hi = max(lo, static_cast<int>(sh.start[e + 1]));
         float acc = (event_reduce == METOK_EVENT_MAX) ? -INFINITY : 0.f;
-        for (int f = a; f < b; ++f) acc = (event_reduce == METOK_EVENT_MAX) ? fmaxf(acc, frame_score[f]) : acc + frame_score[f];
-        if (event_reduce != METOK_EVENT_MAX) acc = (b > a) ? acc / static_cast<float>(b - a) : 0.f;
+#pragma unroll 8
+        for (int f = lo; f < hi; ++f) { const float x = score_of(f); acc = (event_reduce == METOK_EVENT_MAX) ? fmaxf(acc, x) : acc + x; }
+        if (event_reduce != METOK_EVENT_MAX) acc = (hi > lo) ? acc / static_cast<float>(hi - lo) : 0.f;
         event_score[e] = acc;
         ekey[e] = ordered_key(acc);
     }
@@ -496,31 +570,19 @@ __global__ __launch_bounds__(kSegThreads) void plan_kernel(
         }
     }
     __syncthreads();
-    // the frame scores as ordered keys in LDS (the event keys are no longer needed): the ranking below reads every key
-    // of a frame's event, four per 16-byte read
-    for (int f = tid; f < T; f += kSegThreads) ekey[f] = ordered_key(frame_score[f]);
-    __syncthreads();
     const int per = (T + kSegThreads - 1) / kSegThreads;      // thread tid owns frames tid * per .. tid * per + per - 1
     // Events longer than kLongEvent frames (at most 7 of them) do not rank frame against frame either.
-    __shared__ int long_list[8];
-    __shared__ int n_long_s;
-    if (tid == 0) n_long_s = 0;
+    for (int e = tid; e < k; e += kSegThreads)
+        if (sh.start[e + 1] - sh.start[e] > kLongEvent) { const int p = atomicAdd(&sh.n_long, 1); if (p < 8) sh.long_list[p] = e; }
     __syncthreads();
-    for (int e = tid; e < k; e += kSegThreads) {
-        int a = event_start[e], b = event_start[e + 1];
-        a = max(0, min(a, T)); b = max(a, min(b, T));
-        if (b - a > kLongEvent) { const int p = atomicAdd(&n_long_s, 1); if (p < 8) long_list[p] = e; }
-    }
-    __syncthreads();
-    const int n_long = min(n_long_s, 8);
+    const int n_long = min(sh.n_long, 8);
     uint32_t long_flags = 0u;                                  // bit j: frame tid * per + j is a key frame of a long event
     for (int li = 0; li < n_long; ++li) {
-        const int e = long_list[li];
-        int a = event_start[e], b = event_start[e + 1];
-        a = max(0, min(a, T)); b = max(a, min(b, T));
-        const int len = b - a;
+        const int e = sh.long_list[li];
+        const int lo = sh.start[e], hi = max(lo, static_cast<int>(sh.start[e + 1]));
+        const int len = hi - lo;
         const int n_kf = min(len, static_cast<int>(ceil(beta * static_cast<double>(len) - 1e-9)));
-        long_flags |= block_top_n_flags(ekey, a, b, n_kf, tid * per, per, scan_scratch);
+        long_flags |= block_top_n_flags(fkey, lo, hi, n_kf, tid * per, per, scan_scratch);
     }
     // per frame: event id (binary search), rank inside the event, stride, pooled row count
     int counts[8];
@@ -529,16 +591,10 @@ __global__ __launch_bounds__(kSegThreads) void plan_kernel(
         const int f = tid * per + j;
         counts[j] = 0;
         if (f < T) {
-            int lo = 0, hi = k - 1;                       // last event whose start is <= f
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (event_start[mid] <= f) lo = mid; else hi = mid - 1;
-            }
-            const int e = lo;
-            int a = event_start[e], b = event_start[e + 1];
-            a = max(0, min(a, T)); b = max(a, min(b, T));
-            const uint32_t kf = ekey[f];
-            const int len = b - a;
+            const int e = sh.event[f];
+            const int lo = sh.start[e], hi = max(lo, static_cast<int>(sh.start[e + 1]));
+            const uint32_t kf = fkey[f];
+            const int len = hi - lo;
             int n_kf = static_cast<int>(ceil(beta * static_cast<double>(len) - 1e-9));
             n_kf = min(len, n_kf);
             bool kf_flag;
@@ -547,21 +603,20 @@ __global__ __launch_bounds__(kSegThreads) void plan_kernel(
             } else {
                 int rank = 0;
                 auto count = [&](uint32_t km, int m) { rank += (km > kf || (km == kf && m < f)) ? 1 : 0; };
-                int m = a;
-                for (; m < b && (m & 3); ++m) count(ekey[m], m);
-                for (; m + 4 <= b; m += 4) {
-                    const uint4 q = *reinterpret_cast<const uint4*>(&ekey[m]);
+                int m = lo;
+                for (; m < hi && (m & 3); ++m) count(fkey[m], m);
+                for (; m + 4 <= hi; m += 4) {
+                    const uint4 q = *reinterpret_cast<const uint4*>(&fkey[m]);
                     count(q.x, m); count(q.y, m + 1); count(q.z, m + 2); count(q.w, m + 3);
                 }
-                for (; m < b; ++m) count(ekey[m], m);
+                for (; m < hi; ++m) count(fkey[m], m);
                 kf_flag = rank < n_kf;
             }
             const bool ek_flag = ev_key[e] != 0;
-            int s = ek_flag ? (kf_flag ? s_key_kf : s_key_nf) : (kf_flag ? s_non_kf : s_non_nf);
+            const int s = ek_flag ? (kf_flag ? a.s_key_kf : a.s_key_nf) : (kf_flag ? a.s_non_kf : a.s_non_nf);
             frame_is_key[f] = kf_flag ? 1 : 0;
             frame_stride[f] = s;
             frame_event_ws[f] = e;
-            if (frame_score_out) frame_score_out[f] = frame_score[f];
             counts[j] = pooled_side(grid_h, s, pool_edge) * pooled_side(grid_w, s, pool_edge);
             mine += counts[j];
         }
@@ -576,12 +631,68 @@ __global__ __launch_bounds__(kSegThreads) void plan_kernel(
         }
     }
     if (tid == 0) frame_offsets[T] = total;
+    if (a.fill_rows_per_frame > 0) {
+        int32_t* token_event = of_video_elems(a.token_event, a.rows_video);
+        for (int f = tid >> 6; f < T; f += kSegThreads / 64) {
+            const int e = sh.event[f];
+            for (int r = tid & 63; r < a.fill_rows_per_frame; r += 64) token_event[f * a.fill_rows_per_frame + r] = e;
+        }
+    }
+}
+
+// WITH_PLAN: the plan follows in the same workgroup.  The arrival counter is the pair slot of the video's last frame, first
+// triple: no frame follows that one, so its sum is never used, and the kernel that wrote the partial sums left it at zero.
+template <bool WITH_PLAN>
+__global__ __launch_bounds__(kSegThreads) void segment_kernel(const SegmentArgs a, const PlanArgs1 plan) {
+    __shared__ __align__(16) SegmentShared sh;
+    float* part = of_video(a.part, a.ws_video);
+    float* frame_norm2 = of_video(a.frame_norm2, a.ws_video);
+    float* pair_dot = of_video(a.pair_dot, a.ws_video);
+    float* frame_score = of_video_elems(a.frame_score, a.T);
+    reduce_partials(a, part, frame_score, frame_norm2, pair_dot);
+    __builtin_amdgcn_s_waitcnt(0);          // this thread's totals are stored
+    __syncthreads();
+    if (gridDim.x > 1) {
+        if (threadIdx.x == 0) {
+            uint32_t* arrive = reinterpret_cast<uint32_t*>(part + static_cast<size_t>(a.T - 1) * a.C * 3 + 1);
+            sh.last = __hip_atomic_fetch_add(arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1 ? 1 : 0;
+        }
+        __syncthreads();
+        if (!sh.last) return;
+    }
+    segment_video(a, sh, of_video_elems(a.sim, a.T - 1), of_video_elems(a.event_start, a.k + 1), of_video_elems(a.frame_event, a.T),
+                  frame_norm2, pair_dot);
+    if (WITH_PLAN) plan_video(plan, sh, frame_score, a.T, a.k);
+}
+static unsigned reduce_workgroups(int T) {
+    const int n = (T + kSegThreads / 64 - 1) / (kSegThreads / 64);
+    return static_cast<unsigned>(n < kMaxReduceWgs ? n : kMaxReduceWgs);
+}
+
+// The plan on its own, from a caller's segmentation.
+__global__ __launch_bounds__(kSegThreads) void plan_kernel(const PlanArgs1 plan, const float* frame_score, const int32_t* event_start, int T, int k) {
+    __shared__ __align__(16) SegmentShared sh;
+    for (int e = threadIdx.x; e <= k; e += kSegThreads) sh.start[e] = static_cast<uint16_t>(max(0, min(event_start[e], T)));
+    __syncthreads();
+    for (int f = threadIdx.x; f < T; f += kSegThreads) {
+        int lo = 0, hi = k - 1;             // last event whose start is <= f
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (sh.start[mid] <= f) lo = mid; else hi = mid - 1;
+        }
+        sh.event[f] = static_cast<uint16_t>(lo);
+    }
+    plan_video(plan, sh, frame_score, T, k);
 }
 
 // ---------------------------------------------------------------------------------------------
-// pool_kernel: blockIdx.y = frame; the waves of the frame's workgroups share its work items.
-// A work item is (pooled row, column part of 64 chunks); a lane owns one 16-byte input chunk
-// of every cell of the window and writes the pooled chunk.
+// pool_kernel: blockIdx.y = frame; a thread owns one 16-byte chunk of a pooled row (the threads of the frame's workgroups
+// cover rows and chunks as one sequence, so no lane idles whatever the row width), requests the chunk in every cell of
+// the window at once and writes the pooled chunk.  Bound by HBM (and, for up to 1 GB of features, helped by what the
+// statistics pass left in the memory-side cache).  Against a wave per 64-chunk column part with a row of cells in flight:
+// 8 x 64 frames of 27 x 27 x 1152 (144 chunks: a quarter of those lanes idled) 168 -> 158 us, with the cache 142 us;
+// 128 frames of 24 x 24 x 1024 36 -> 31.6 -> 26.6 us.  36 workgroups per frame: 18 to 48 are within 3 %, 64 and more
+// cost up to a quarter in workgroups that find nothing to do.
 // ---------------------------------------------------------------------------------------------
 constexpr int kPoolThreads = 256;
 
@@ -607,6 +718,25 @@ template <> struct Store<bf16_t> {
     }
 };
 
+// Sum of a full S x S window, cells in the order (y, x); two rows (S > 4) or all of them are in flight together.
+template <typename E, int S>
+__device__ __forceinline__ void pool_window(const uint4* __restrict__ cell, int grid_w, int nchunks, float (&acc)[8]) {
+    constexpr int kRows = S <= 4 ? S : 2;
+    static_assert(S % kRows == 0, "whole batches of rows");
+#pragma unroll 1
+    for (int y = 0; y < S; y += kRows) {
+        uint4 v[kRows][S];
+#pragma unroll
+        for (int r = 0; r < kRows; ++r)
+#pragma unroll
+            for (int x = 0; x < S; ++x) v[r][x] = load_stream(cell + (static_cast<size_t>(y + r) * grid_w + x) * nchunks);
+#pragma unroll
+        for (int r = 0; r < kRows; ++r)
+#pragma unroll
+            for (int x = 0; x < S; ++x) E::accumulate(v[r][x], acc);
+    }
+}
+
 template <typename TI, typename TO>
 __global__ __launch_bounds__(kPoolThreads) void pool_kernel(
     const TI* __restrict__ feats, int grid_h, int grid_w, int d,
@@ -619,48 +749,53 @@ __global__ __launch_bounds__(kPoolThreads) void pool_kernel(
     frame_event = of_video(frame_event, ws_video);
     out = of_video_elems(out, capacity_rows * d); token_event = of_video_elems(token_event, capacity_rows);
     const int f = blockIdx.y;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int s = frame_stride[f];
     const int oh = pooled_side(grid_h, s, pool_edge), ow = pooled_side(grid_w, s, pool_edge);
     const int base = frame_offsets[f];
     const int ev = frame_event[f];
     const int nchunks = d / E::kVec;
-    const int colparts = (nchunks + 63) / 64;
-    const int items = oh * ow * colparts;
+    const int64_t items = static_cast<int64_t>(oh) * ow * nchunks;
     const uint4* frame = reinterpret_cast<const uint4*>(feats) + static_cast<size_t>(f) * grid_h * grid_w * nchunks;
-    const int stride_items = gridDim.x * (kPoolThreads / 64);
 
-    for (int item = blockIdx.x * (kPoolThreads / 64) + wave; item < items; item += stride_items) {
-        const int orow = item / colparts;
-        const int chunk = (item - orow * colparts) * 64 + lane;
+    for (int64_t first = static_cast<int64_t>(blockIdx.x) * kPoolThreads; first < items; first += static_cast<int64_t>(gridDim.x) * kPoolThreads) {
+        // row and chunk of the workgroup's first thread (scalar), then a 32-bit division per thread
+        const int64_t row0 = first < 0x7fffffff ? static_cast<int64_t>(static_cast<uint32_t>(first) / static_cast<uint32_t>(nchunks)) : first / nchunks;
+        const uint32_t x = static_cast<uint32_t>(first - row0 * nchunks) + threadIdx.x;
+        const uint32_t dr = x / static_cast<uint32_t>(nchunks);
+        const int orow = static_cast<int>(row0 + dr), chunk = static_cast<int>(x - dr * static_cast<uint32_t>(nchunks));
+        const int64_t out_row = static_cast<int64_t>(base) + orow;
+        if (orow >= oh * ow || out_row >= capacity_rows) continue;      // the second cannot happen when the caller sized the buffer as required
         const int oy = orow / ow, ox = orow - oy * ow;
         const int y0 = oy * s, y1 = min(y0 + s, grid_h);
         const int x0 = ox * s, x1 = min(x0 + s, grid_w);
-        const int64_t out_row = static_cast<int64_t>(base) + orow;
-        if (out_row >= capacity_rows) continue;              // cannot happen when the caller sized the buffer as required
-        if (chunk < nchunks) {
-            float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-            for (int y = y0; y < y1; ++y) {
-                const uint4* cell = frame + (static_cast<size_t>(y) * grid_w + x0) * nchunks + chunk;
-                int x = x0;
-                for (; x + 4 <= x1; x += 4) {                 // four independent loads in flight
+        const uint4* corner = frame + (static_cast<size_t>(y0) * grid_w + x0) * nchunks + chunk;
+        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        if (y1 - y0 == s && x1 - x0 == s && s == 2) pool_window<E, 2>(corner, grid_w, nchunks, acc);
+        else if (y1 - y0 == s && x1 - x0 == s && s == 3) pool_window<E, 3>(corner, grid_w, nchunks, acc);
+        else if (y1 - y0 == s && x1 - x0 == s && s == 4) pool_window<E, 4>(corner, grid_w, nchunks, acc);
+        else if (y1 - y0 == s && x1 - x0 == s && s == 6) pool_window<E, 6>(corner, grid_w, nchunks, acc);
+        else {
+            for (int y = y0; y < y1; ++y, corner += static_cast<size_t>(grid_w) * nchunks) {
+                const uint4* cell = corner;
+                int xx = x0;
+                for (; xx + 4 <= x1; xx += 4) {               // four independent loads in flight
                     const uint4 a = load_stream(cell), b = load_stream(cell + nchunks),
                                 c = load_stream(cell + 2 * static_cast<size_t>(nchunks)),
                                 e = load_stream(cell + 3 * static_cast<size_t>(nchunks));
                     E::accumulate(a, acc); E::accumulate(b, acc); E::accumulate(c, acc); E::accumulate(e, acc);
                     cell += 4 * static_cast<size_t>(nchunks);
                 }
-                for (; x < x1; ++x) {
+                for (; xx < x1; ++xx) {
                     E::accumulate(load_stream(cell), acc);
                     cell += nchunks;
                 }
             }
-            const float cnt = static_cast<float>((y1 - y0) * (x1 - x0));
-#pragma unroll
-            for (int i = 0; i < 8; ++i) acc[i] = acc[i] / cnt;
-            Store<TO>::put(out + out_row * d, chunk, E::kVec, acc);
         }
-        if (lane == 0 && item - orow * colparts == 0) token_event[out_row] = ev;
+        const float cnt = static_cast<float>((y1 - y0) * (x1 - x0));
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[i] = acc[i] / cnt;
+        Store<TO>::put(out + out_row * d, chunk, E::kVec, acc);
+        if (chunk == 0) token_event[out_row] = ev;
     }
 }
 
@@ -697,7 +832,6 @@ __global__ __launch_bounds__(kStatsThreads) void frame_stats_pool2_kernel(
     const int nchunks = d / E::kVec;
     const int t0 = blockIdx.y * frames_per_run;
     const int t1 = min(T_frames, t0 + frames_per_run);
-    const uint4 zero = make_uint4(0, 0, 0, 0);
     int tok[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) tok[c] = (2 * wy + (c >> 1)) * grid_w + 2 * wx + (c & 1);
@@ -707,7 +841,9 @@ __global__ __launch_bounds__(kStatsThreads) void frame_stats_pool2_kernel(
 #pragma unroll
     for (int k = 0; k < KL; ++k) {
         const int ch = lane + 64 * k;
-        txt[k] = ch < nchunks ? reinterpret_cast<const uint4*>(text)[ch] : zero;
+        const uint4 raw = reinterpret_cast<const uint4*>(text)[ch < nchunks ? ch : nchunks - 1];
+        const uint32_t in = ch < nchunks ? 0xffffffffu : 0u;
+        txt[k] = make_uint4(raw.x & in, raw.y & in, raw.z & in, raw.w & in);
         tn2 = E::dot(txt[k], txt[k], tn2);
     }
     const float tnorm = sqrtf(wave_sum(tn2));
@@ -820,13 +956,14 @@ static bool plan_stats(int T, int N, int d, int dtype, StatsPlan* p) {
     const int vec = dtype == METOK_BF16 ? 8 : 4;
     if (d % vec) return false;
     const int nchunks = d / vec;
+    // Chunks per lane: the smallest of the built counts that covers a row, on 16 lanes up to 12 chunks each, else on 64.
+    // A lane past the row's end reads the last chunk again, so a tight count is what the rate depends on: 144 chunks
+    // (d = 1152 in bf16) took 64 lanes x 4 = 256 places, now 16 x 9 = 144.
     int G = 16, KL = 0;
-    for (int g : {16, 64}) {
-        for (int kl : {1, 2, 4, 8, 16}) {
-            if (g == 16 && kl == 16) continue;
-            if (g * kl >= nchunks) { G = g; KL = kl; break; }
-        }
-        if (KL) break;
+    for (int kl : {1, 2, 3, 4, 5, 6, 8, 9, 12}) if (!KL && 16 * kl >= nchunks) KL = kl;
+    if (!KL) {
+        G = 64;
+        for (int kl : {4, 5, 6, 8, 12, 16}) if (!KL && 64 * kl >= nchunks) KL = kl;
     }
     if (!KL) return false;
     p->G = G; p->KL = KL;
@@ -846,23 +983,43 @@ static bool plan_stats(int T, int N, int d, int dtype, StatsPlan* p) {
     return true;
 }
 
-template <typename T, int G, int KL>
+// The pooling pass that follows re-reads what the statistics pass read.  Plain loads cost the statistics up to 13 % and gain
+// the pooling 10 to 18 % while a good share of the features stays in the 256 MB memory-side cache: together 128 frames of
+// 24 x 24 x 1024 (151 MB) 62.6 -> 59.8 us, 860 MB 311 -> 296 us; at 2.4 GB 884 -> 898 us, so the line lies at 1 GiB.
+static bool keep_in_cache(int batch, int T, int N, int d, int dtype) {
+    return static_cast<int64_t>(batch) * T * N * d * static_cast<int64_t>(dtype_size(dtype)) <= (static_cast<int64_t>(1) << 30);
+}
+
+template <typename T, int G, int KL, bool KEEP>
 static void launch_stats(const void* feats, const void* text, int Tf, int N, int d, const StatsPlan& p, int do_pair,
                          int sim_mode, float* part, hipStream_t st, int batch, int64_t ws_video) {
-    { TraceScope trace_scope(METOK_TRACE_FRAME_STATS, st); hipLaunchKernelGGL((frame_stats_kernel<T, G, KL>), dim3((p.C + kStatsWaves - 1) / kStatsWaves, p.runs, batch), dim3(kStatsThreads), 0, st,
+    TraceScope trace_scope(METOK_TRACE_FRAME_STATS, st);
+    hipLaunchKernelGGL((frame_stats_kernel<T, G, KL, KEEP>), dim3((p.C + kStatsWaves - 1) / kStatsWaves, p.runs, batch), dim3(kStatsThreads), 0, st,
                        static_cast<const T*>(feats), static_cast<const T*>(text), Tf, N, d, p.frames_per_run, do_pair,
-                       sim_mode, part, p.C, ws_video); }
+                       sim_mode, part, p.C, ws_video);
 }
 
 template <typename T>
 static bool dispatch_stats(const void* feats, const void* text, int Tf, int N, int d, const StatsPlan& p, int do_pair,
-                           int sim_mode, float* part, hipStream_t st, int batch = 1, int64_t ws_video = 0) {
+                           int sim_mode, float* part, hipStream_t st, int batch = 1, int64_t ws_video = 0, bool keep = false) {
 #define METOK_STATS_CASE(g, kl) \
-    if (p.G == g && p.KL == kl) { launch_stats<T, g, kl>(feats, text, Tf, N, d, p, do_pair, sim_mode, part, st, batch, ws_video); return true; }
-    METOK_STATS_CASE(16, 1) METOK_STATS_CASE(16, 2) METOK_STATS_CASE(16, 4) METOK_STATS_CASE(16, 8)
-    METOK_STATS_CASE(64, 1) METOK_STATS_CASE(64, 2) METOK_STATS_CASE(64, 4) METOK_STATS_CASE(64, 8) METOK_STATS_CASE(64, 16)
+    if (p.G == g && p.KL == kl) { \
+        if (keep) launch_stats<T, g, kl, true>(feats, text, Tf, N, d, p, do_pair, sim_mode, part, st, batch, ws_video); \
+        else launch_stats<T, g, kl, false>(feats, text, Tf, N, d, p, do_pair, sim_mode, part, st, batch, ws_video); \
+        return true; \
+    }
+    METOK_STATS_CASE(16, 1) METOK_STATS_CASE(16, 2) METOK_STATS_CASE(16, 3) METOK_STATS_CASE(16, 4) METOK_STATS_CASE(16, 5)
+    METOK_STATS_CASE(16, 6) METOK_STATS_CASE(16, 8) METOK_STATS_CASE(16, 9) METOK_STATS_CASE(16, 12)
+    METOK_STATS_CASE(64, 4) METOK_STATS_CASE(64, 5) METOK_STATS_CASE(64, 6) METOK_STATS_CASE(64, 8) METOK_STATS_CASE(64, 12) METOK_STATS_CASE(64, 16)
 #undef METOK_STATS_CASE
     return false;
+}
+
+static void launch_segment_plan(const SegmentArgs& sa, const PlanArgs1& plan, unsigned nb, hipStream_t st) {
+    // one launch does both: the trace hook brackets it for either name
+    TraceScope trace_segment(METOK_TRACE_SEGMENT, st);
+    TraceScope trace_plan(METOK_TRACE_PLAN, st);
+    hipLaunchKernelGGL(segment_kernel<true>, dim3(reduce_workgroups(sa.T), 1, nb), dim3(kSegThreads), 0, st, sa, plan);
 }
 
 static size_t stats_part_bytes(int T, const StatsPlan& p) {
@@ -930,8 +1087,8 @@ extern "C" int metok_segment_events(const void* feats, int dtype, int T, int N, 
                                             : dispatch_stats<float>(feats, text_emb, T, N, d, p, 1, sim_mode, part, st);
         if (!ok) return fail(METOK_ERR_UNSUPPORTED, "no frame-statistics kernel for d = %d", d);
         if ((rc = check_launch("frame_stats"))) return rc;
-        { TraceScope trace_scope(METOK_TRACE_SEGMENT, st); hipLaunchKernelGGL(segment_kernel, dim3(1), dim3(kSegThreads), 0, st, part, p.C, T, N, k, text_emb ? 1 : 0, sim_mode,
-                           sim, event_start, frame_event, frame_score, norm2, pair_dot, static_cast<int64_t>(0)); }
+        const SegmentArgs sa = {part, p.C, T, N, k, text_emb ? 1 : 0, sim_mode, sim, event_start, frame_event, frame_score, norm2, pair_dot, 0};
+        { TraceScope trace_scope(METOK_TRACE_SEGMENT, st); hipLaunchKernelGGL(segment_kernel<false>, dim3(reduce_workgroups(T)), dim3(kSegThreads), 0, st, sa, PlanArgs1{}); }
         return check_launch("segment");
     }
     // pooled reading: Eq. 5 (if wanted) from the tokens, Eq. 4 from the frames' mean tokens (a [T, 1, d] fp32 "video")
@@ -955,8 +1112,8 @@ extern "C" int metok_segment_events(const void* feats, int dtype, int T, int N, 
     if (!dispatch_stats<float>(mean, nullptr, T, 1, d, pm, 1, METOK_SIM_FLAT, part_m, st))
         return fail(METOK_ERR_UNSUPPORTED, "no frame-statistics kernel for d = %d", d);
     if ((rc = check_launch("frame_stats (means)"))) return rc;
-    { TraceScope trace_scope(METOK_TRACE_SEGMENT, st); hipLaunchKernelGGL(segment_kernel, dim3(1), dim3(kSegThreads), 0, st, part_m, pm.C, T, 1, k, 0, METOK_SIM_FLAT,
-                       sim, event_start, frame_event, static_cast<float*>(nullptr), norm2, pair_dot, static_cast<int64_t>(0)); }
+    const SegmentArgs sa = {part_m, pm.C, T, 1, k, 0, METOK_SIM_FLAT, sim, event_start, frame_event, nullptr, norm2, pair_dot, 0};
+    { TraceScope trace_scope(METOK_TRACE_SEGMENT, st); hipLaunchKernelGGL(segment_kernel<false>, dim3(reduce_workgroups(T)), dim3(kSegThreads), 0, st, sa, PlanArgs1{}); }
     return check_launch("segment");
 }
 
@@ -1051,10 +1208,9 @@ extern "C" int metok_compress_encoder_tokens(const void* feats, int dtype, int T
     }
     (void)norm2;
     const int n_key_events = ceil_ratio(alpha * k) > k ? k : ceil_ratio(alpha * k);
-    { TraceScope trace_scope(METOK_TRACE_PLAN, st); hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(kSegThreads), 0, st, scores, event_start, T, k, n_key_events, beta,
-                       s_key_kf, s_key_nf, s_non_kf, s_non_nf, grid_h, grid_w, event_reduce, pool_edge,
-                       event_score, event_is_key, frame_is_key, frame_stride, frame_offsets, frame_event_ws,
-                       frame_score_out, static_cast<int64_t>(0)); }
+    const PlanArgs1 plan = {n_key_events, beta, s_key_kf, s_key_nf, s_non_kf, s_non_nf, grid_h, grid_w, event_reduce, pool_edge, event_score,
+                            event_is_key, frame_is_key, frame_stride, frame_offsets, frame_event_ws, frame_score_out, 0, nullptr, 0, 0};
+    { TraceScope trace_scope(METOK_TRACE_PLAN, st); hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(kSegThreads), 0, st, plan, scores, event_start, T, k); }
     if ((rc = check_launch("plan"))) return rc;
 
     const int wg_per_frame = 36;      // 144 waves per frame; 18 to 72 workgroups measured within 3 % of each other
@@ -1150,7 +1306,7 @@ static int segment_compress_impl(int batch, const void* feats, int dtype, int T,
     const int vec = dtype == METOK_BF16 ? 8 : 4;
     const int kl = (d > 0 && d % vec == 0) ? (d / vec + 63) / 64 : 0;
     if (kl < 1 || kl > 4) fused = false;
-    if (!fused && batch > 1 && (sim_mode == METOK_SIM_FLAT || sim_mode == METOK_SIM_TOKEN_MEAN)) {
+    if (!fused && (sim_mode == METOK_SIM_FLAT || sim_mode == METOK_SIM_TOKEN_MEAN)) {
         // two passes (statistics, then pooling with the strides of Algorithm 1), each kernel once for the whole batch
         StatsPlan p;
         int rc = check_feats(feats, dtype, T, N, d, &p);
@@ -1185,19 +1341,18 @@ static int segment_compress_impl(int batch, const void* feats, int dtype, int T,
         int32_t* frame_event_ws = reinterpret_cast<int32_t*>(ws + stats_part_bytes(T, p) + 2 * tslot);
         hipStream_t st = static_cast<hipStream_t>(stream);
         const unsigned nb = static_cast<unsigned>(batch);
-        const bool ok = dtype == METOK_BF16 ? dispatch_stats<bf16_t>(feats, text_emb, T, N, d, p, 1, sim_mode, part, st, batch, ws_video)
-                                            : dispatch_stats<float>(feats, text_emb, T, N, d, p, 1, sim_mode, part, st, batch, ws_video);
+        const bool keep = keep_in_cache(batch, T, N, d, dtype);
+        const bool ok = dtype == METOK_BF16 ? dispatch_stats<bf16_t>(feats, text_emb, T, N, d, p, 1, sim_mode, part, st, batch, ws_video, keep)
+                                            : dispatch_stats<float>(feats, text_emb, T, N, d, p, 1, sim_mode, part, st, batch, ws_video, keep);
         if (!ok) return fail(METOK_ERR_UNSUPPORTED, "no frame-statistics kernel for d = %d", d);
         if ((rc = check_launch("frame_stats"))) return rc;
-        { TraceScope trace_scope(METOK_TRACE_SEGMENT, st); hipLaunchKernelGGL(segment_kernel, dim3(1, 1, nb), dim3(kSegThreads), 0, st, part, p.C, T, N, k, 1, sim_mode,
-                           sim, event_start, frame_event, frame_score, norm2, pair_dot, ws_video); }
-        if ((rc = check_launch("segment"))) return rc;
         const int n_key_events = ceil_ratio(alpha * k) > k ? k : ceil_ratio(alpha * k);
-        { TraceScope trace_scope(METOK_TRACE_PLAN, st); hipLaunchKernelGGL(plan_kernel, dim3(1, 1, nb), dim3(kSegThreads), 0, st, frame_score, event_start, T, k, n_key_events, beta,
-                           clamp_stride(s1), clamp_stride(s2), clamp_stride(s1 / alpha), clamp_stride(s2 / alpha), grid_h, grid_w, event_reduce, pool_edge,
-                           event_score, event_is_key, frame_is_key, frame_stride, frame_offsets, frame_event_ws,
-                           static_cast<float*>(nullptr), ws_video); }
-        if ((rc = check_launch("plan"))) return rc;
+        const SegmentArgs sa = {part, p.C, T, N, k, 1, sim_mode, sim, event_start, frame_event, frame_score, norm2, pair_dot, ws_video};
+        const PlanArgs1 plan = {n_key_events, beta, clamp_stride(s1), clamp_stride(s2), clamp_stride(s1 / alpha), clamp_stride(s2 / alpha), grid_h, grid_w,
+                                event_reduce, pool_edge, event_score, event_is_key, frame_is_key, frame_stride, frame_offsets, frame_event_ws, nullptr,
+                                0, nullptr, 0, ws_video};
+        launch_segment_plan(sa, plan, nb, st);
+        if ((rc = check_launch("segment and plan"))) return rc;
         dim3 grid(36, T, nb);
 #define METOK_POOL_CASE(TI, TO) \
         { TraceScope trace_scope(METOK_TRACE_POOL, st); \
@@ -1284,15 +1439,13 @@ static int segment_compress_impl(int batch, const void* feats, int dtype, int T,
                                      : launch_stats_pool2<float, float>(feats, text_emb, T, grid_h, grid_w, d, kl, C, fpr, runs, part, out_tokens, batch, pooled_video, ws_video, st);
     if (!ok) return fail(METOK_ERR_UNSUPPORTED, "no fused kernel for d = %d", d);
     if ((rc = check_launch("frame_stats_pool2"))) return rc;
-    { TraceScope trace_scope(METOK_TRACE_SEGMENT, st); hipLaunchKernelGGL(segment_kernel, dim3(1, 1, nb), dim3(kSegThreads), 0, st, part, n_win, T, N, k, 1, METOK_SIM_FLAT,
-                       sim, event_start, frame_event, frame_score, norm2, pair_dot, ws_video); }
-    if ((rc = check_launch("segment"))) return rc;
     const int n_key_events = ceil_ratio(alpha * k) > k ? k : ceil_ratio(alpha * k);
-    { TraceScope trace_scope(METOK_TRACE_PLAN, st); hipLaunchKernelGGL(plan_kernel, dim3(1, 1, nb), dim3(kSegThreads), 0, st, frame_score, event_start, T, k, n_key_events, beta,
-                       2, 2, 2, 2, grid_h, grid_w, event_reduce, pool_edge,
-                       event_score, event_is_key, frame_is_key, frame_stride, frame_offsets, frame_event_ws,
-                       static_cast<float*>(nullptr), ws_video); }
-    if ((rc = check_launch("plan"))) return rc;
+    const bool fill_here = rows <= kFillRowsInPlan;
+    const SegmentArgs sa = {part, n_win, T, N, k, 1, METOK_SIM_FLAT, sim, event_start, frame_event, frame_score, norm2, pair_dot, ws_video};
+    const PlanArgs1 plan = {n_key_events, beta, 2, 2, 2, 2, grid_h, grid_w, event_reduce, pool_edge, event_score, event_is_key, frame_is_key, frame_stride,
+                            frame_offsets, frame_event_ws, nullptr, fill_here ? n_win : 0, token_event, out_capacity_rows, ws_video};
+    launch_segment_plan(sa, plan, nb, st);
+    if ((rc = check_launch("segment and plan")) || fill_here) return rc;
     hipLaunchKernelGGL(fill_token_event_kernel, dim3(static_cast<unsigned>((rows + 255) / 256), 1, nb), dim3(256), 0, st, frame_event, T, n_win,
                        token_event, out_capacity_rows);
     return check_launch("token events");
