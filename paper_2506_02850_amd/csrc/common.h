@@ -170,6 +170,16 @@ __device__ __forceinline__ float wave_sum(float v) {
     v += __shfl_xor(v, 32, 64);
     return v;
 }
+// low half of the wave: a summed over the lane pairs (l, l + 32); high half: b likewise
+__device__ __forceinline__ float swap32_add(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// even 16-lane rows: a of the rows (r, r + 1) added; odd rows: b likewise
+__device__ __forceinline__ float swap16_add(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
 template <int G> __device__ __forceinline__ float group_sum(float v) {
     static_assert(G == 16 || G == 64, "token groups are one DPP row or one wave");
     return G == 16 ? row16_sum(v) : wave_sum(v);

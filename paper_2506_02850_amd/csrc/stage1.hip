@@ -38,17 +38,6 @@ constexpr float kZeroNorm = 1e-12f;
 // Cross-lane sums use v_permlane32_swap / v_permlane16_swap: they exchange halves of two registers, so one
 // swap and one add fold two values at once.
 // ---------------------------------------------------------------------------------------------
-// low half of the wave: a summed over the lane pairs (l, l + 32); high half: b likewise
-__device__ __forceinline__ float swap32_add(float a, float b) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-// even 16-lane rows: a of the rows (r, r + 1) added; odd rows: b likewise
-__device__ __forceinline__ float swap16_add(float a, float b) {
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
 // KEEP: the loads stay without the streaming hint, so that the rows are still in the memory-side cache (256 MB) when the
 // pooling pass reads them again.
 template <typename T, int G, int KL, bool KEEP>

@@ -6,6 +6,7 @@
 //   merge_stats_kernel   merges the per-workgroup (max, sum) pairs into one normaliser per row
 //   col_sums_kernel      MFMA pass 2 over the visual keys: recomputes the logits and adds up the
 //                        probabilities of every visual key over the rows of a workgroup
+//   narrow_row_stats_kernel, narrow_col_sums_kernel   the two passes for at most 64 query rows per kv head (no packing)
 //   score_select_kernel  score_j = w_e(j) * mean probability per tile; the workgroup that arrives last selects per class
 //                        (radix select) and writes the ascending index list
 //   prepare_kernel, select_kernel, write_index_kernel   the same steps for more than 16 classes or more than 40960
@@ -500,6 +501,222 @@ __global__ __launch_bounds__(kScoreThreads) void col_sums_kernel(const uint4* __
             }
         }
     }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Narrow scores: at most 64 query rows per kv head (one query head per kv head with up to 64 text queries, or the last
+// token's queries alone).  One or two 32-row blocks would leave six or seven of the eight waves above without work and
+// every stage waiting for memory behind a barrier; what bounds this shape is the stream of keys.  Here every wave keeps all
+// query rows (NB blocks of 16) in registers and walks its own 16-key subtiles of the workgroup's range, every eighth one,
+// straight from memory into registers in MFMA fragment order and several subtiles ahead; no wave waits for another.
+// 40 heads x 64 queries, 4571 keys of 128 bf16 (47 MB): row statistics 17.7 -> 15.6 us, column sums 15.9 -> 13.6 us, and no
+// packing launch (3.2 us); the launch and the first loads are 5 us of each.  16 heads, 30064 keys of 64: 27.4 + 28.8 ->
+// 15.1 + 14.8 us; the last token of 28 heads on 4, 18496 keys: 10.5 + 8.6 -> 8.0 + 6.1 us.  With more rows the loads cost
+// more than they save: a wave's 1 KB load in fragment order takes 64 bytes of 16 rows (four times the address work of a
+// contiguous one), and 28 blocks over four waves that each load their own fragments took 160 us where the shared stages
+// above take 154.
+// ---------------------------------------------------------------------------------------------
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
+template <typename T> struct NarrowMma;
+template <> struct NarrowMma<bf16_t> {             // one 16-byte chunk feeds one 16x16x32 MFMA
+    static __device__ __forceinline__ f32x4_t mma(const u32x4_t& a, const u32x4_t& b, f32x4_t c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+    }
+};
+template <> struct NarrowMma<float> {              // one chunk feeds four 16x16x4 MFMAs
+    static __device__ __forceinline__ f32x4_t mma(const u32x4_t& a, const u32x4_t& b, f32x4_t c) {
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.x), __uint_as_float(b.x), c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.y), __uint_as_float(b.y), c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), __uint_as_float(b.z), c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
+        return c;
+    }
+};
+constexpr int kSubKeys = 16;
+// Subtiles in registers: the one in work and those on their way.
+constexpr int subtile_depth(int nch, int nb) { return nch * nb >= 8 ? 4 : 6; }
+
+// Rows j0 + lane % 16 (at most `last`, which stands in for the rows behind it) of [*, dh]: pieces 4 c + lane / 16.
+template <typename T, int NCH>
+__device__ __forceinline__ void load_fragments(u32x4_t (&f)[NCH], const T* __restrict__ base, int64_t j0, int64_t last, int dh) {
+    constexpr int CE = Mma<T>::kChunkElems;
+    const int lane = threadIdx.x & 63;
+    int64_t j = j0 + (lane & 15);
+    j = j < last ? j : last;
+    // fewer than 2^31 rows: one 32 x 32 -> 64 bit multiply
+    const T* row = base + static_cast<size_t>(static_cast<uint32_t>(j)) * static_cast<uint32_t>(dh) + (lane >> 4) * CE;
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) f[c] = *reinterpret_cast<const u32x4_t*>(row + c * 4 * CE);
+}
+
+// The query rows of a kv head lie one after the other in q_text ([Hq, Tq, dh], group consecutive heads): no packing needed.
+template <typename T, int NCH, int NB>
+__device__ __forceinline__ void load_queries(u32x4_t (&q)[NB][NCH], const T* __restrict__ q_text, const ScoreGeom& g, int kvh) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b) load_fragments<T, NCH>(q[b], q_text + static_cast<size_t>(kvh) * g.R * g.dh, b * 16, g.R - 1, g.dh);
+}
+
+template <typename T, int NCH>
+__device__ __forceinline__ f32x4_t narrow_chain(const u32x4_t (&a)[NCH], const u32x4_t (&b)[NCH]) {
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) acc = NarrowMma<T>::mma(a[c], b[c], acc);
+    return acc;
+}
+
+// Subtiles t = 0 .. n-1 of a wave: k[0 .. DEPTH-2] await the first ones, load(dst, t) requests subtile t, work(fragments, t).
+template <int NCH, int DEPTH, typename LOAD, typename WORK>
+__device__ __forceinline__ void walk_subtiles(u32x4_t (&k)[DEPTH][NCH], int n, LOAD&& load, WORK&& work) {
+    for (int t0 = 0; t0 < n; t0 += DEPTH) {
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {
+            const int t = t0 + d;
+            if (t < n) {
+                load(k[(d + DEPTH - 1) % DEPTH], t + DEPTH - 1);      // past the end: the last key again
+                work(k[d], t);
+            }
+        }
+    }
+}
+
+// (m, l) stands for the sum l 2^m.
+__device__ __forceinline__ void merge_softmax(float& m, float& l, float m2, float l2) {
+    const float mm = fmaxf(m, m2);
+    l = l * fast_exp2(m - mm) + l2 * fast_exp2(m2 - mm);
+    m = mm;
+}
+
+// pass 1 (see row_stats_kernel): keys x queries, a lane's 4 accumulators are 4 keys (4 (lane / 16) + e) of query row lane % 16.
+template <typename T, int NCH, int NB>
+__global__ __launch_bounds__(kScoreThreads) void narrow_row_stats_kernel(const T* __restrict__ q_text, const T* __restrict__ k_all,
+                                                                         const ScoreGeom g, int sub_per_wg, float* __restrict__ pstat,
+                                                                         uint32_t* __restrict__ clear, int n_clear) {
+    constexpr int DEPTH = subtile_depth(NCH, NB);
+    __shared__ float2 red[kScoreWaves][NB * 16];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), h = lane >> 4;
+    const int kvh = blockIdx.y;
+    q_text = of_video_elems(q_text, g.q_video); pstat = of_video(pstat, g.ws_video); clear = of_video(clear, g.ws_video);
+    const T* k_head = of_video_elems(k_all, g.k_video) + static_cast<size_t>(kvh) * g.S * g.dh;
+    // as the first kernel of a call it clears the counters of the later ones
+    if (blockIdx.x == 0 && blockIdx.y == 0 && static_cast<int>(threadIdx.x) < n_clear) clear[threadIdx.x] = 0u;
+
+    const int64_t kb = g.key_begin + static_cast<int64_t>(blockIdx.x) * sub_per_wg * 32;
+    const int64_t ke = min(g.key_end, kb + static_cast<int64_t>(sub_per_wg) * 32);
+    const int64_t text_start = g.S - g.Tq;
+    const int64_t full_end = text_start < ke ? text_start : ke;      // keys below are visible to every query
+    const int subs = static_cast<int>((ke - kb + kSubKeys - 1) / kSubKeys);
+    const int n = subs > wave ? (subs - wave + kScoreWaves - 1) / kScoreWaves : 0;
+    auto first_key = [&](int t) { return kb + static_cast<int64_t>(wave + t * kScoreWaves) * kSubKeys; };
+    auto load = [&](u32x4_t (&dst)[NCH], int t) { load_fragments<T, NCH>(dst, k_head, first_key(t), ke - 1, g.dh); };
+    // the first subtiles and the queries are requested together: one memory round trip
+    u32x4_t k[DEPTH][NCH], q[NB][NCH];
+    load_queries<T, NCH, NB>(q, q_text, g, kvh);
+#pragma unroll
+    for (int d = 0; d < DEPTH - 1; ++d) load(k[d], d);
+
+    // m is the largest logit among the lane's keys of the first subtile and stays while whole subtiles are visible: terms
+    // relative to it keep their precision as long as none exceeds it by 2^127, and the running maximum with its masks is
+    // three quarters of the vector instructions.  A wave whose sums left the range of float starts over with the maximum.
+    float m[NB], l[NB];
+    for (bool online = false;; online = true) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) { m[b] = kNegBig; l[b] = 0.f; }
+        walk_subtiles<NCH, DEPTH>(k, n, load, [&](const u32x4_t (&kf)[NCH], int t) {
+            const int64_t j0 = first_key(t);
+            f32x4_t x[NB];
+#pragma unroll
+            for (int b = 0; b < NB; ++b) x[b] = narrow_chain<T, NCH>(kf, q[b]);
+            if (t > 0 && !online && j0 + kSubKeys <= full_end) {
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    float p[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) p[e] = fast_exp2(fmaf(x[b][e], g.scale_log2, -m[b]));
+                    l[b] += (p[0] + p[1]) + (p[2] + p[3]);
+                }
+            } else {
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    // causal: row r sees keys 0 .. text_start + r % Tq, and below ke
+                    int64_t last = text_start + (b * 16 + (lane & 15)) % g.Tq;
+                    last = (last < ke - 1 ? last : ke - 1) - j0;
+                    const int lim = last < 0 ? -1 : (last < kSubKeys - 1 ? static_cast<int>(last) : kSubKeys - 1);
+                    float mx = m[b];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) mx = 4 * h + e <= lim ? fmaxf(mx, x[b][e] * g.scale_log2) : mx;
+                    float sum = 0.f;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sum += 4 * h + e <= lim ? fast_exp2(fmaf(x[b][e], g.scale_log2, -mx)) : 0.f;
+                    l[b] = l[b] * fast_exp2(m[b] - mx) + sum;
+                    m[b] = mx;
+                }
+            }
+        });
+        bool bad = false;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) bad = bad || !(l[b] <= 3.0e38f);
+        if (online || !__any(bad ? 1 : 0)) break;
+#pragma unroll
+        for (int d = 0; d < DEPTH - 1; ++d) load(k[d], d);
+    }
+    // the four lanes of a row hold different keys, and so do the waves
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        // l = mantissa in [0.5, 1): a sum far from 1 must not lose the others when they are scaled to its m
+        if (l[b] > 0.f) { const int e = __builtin_amdgcn_frexp_expf(l[b]); l[b] = ldexpf(l[b], -e); m[b] += static_cast<float>(e); }
+        merge_softmax(m[b], l[b], __shfl_xor(m[b], 16, 64), __shfl_xor(l[b], 16, 64));
+        merge_softmax(m[b], l[b], __shfl_xor(m[b], 32, 64), __shfl_xor(l[b], 32, 64));
+        if (lane < 16) red[wave][b * 16 + lane] = make_float2(m[b], l[b]);
+    }
+    __syncthreads();
+    const int rows_per_y = g.rbw * 32;
+    if (static_cast<int>(threadIdx.x) < min(NB * 16, rows_per_y)) {
+        float2 a = red[0][threadIdx.x];
+#pragma unroll
+        for (int w = 1; w < kScoreWaves; ++w) { const float2 o = red[w][threadIdx.x]; merge_softmax(a.x, a.y, o.x, o.y); }
+        *reinterpret_cast<float2*>(pstat + ((static_cast<size_t>(blockIdx.y) * gridDim.x + blockIdx.x) * rows_per_y + threadIdx.x) * 2) = a;
+    }
+}
+
+// pass 2 (see col_sums_kernel): queries x keys, a lane's 4 accumulators are 4 rows (4 (lane / 16) + e) of key lane % 16.
+template <typename T, int NCH, int NB>
+__global__ __launch_bounds__(kScoreThreads) void narrow_col_sums_kernel(const T* __restrict__ q_text, const T* __restrict__ k_all,
+                                                                        const ScoreGeom g, int sub_per_wg, const float* __restrict__ norm,
+                                                                        float* __restrict__ colpart) {
+    constexpr int DEPTH = subtile_depth(NCH, NB);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), h = lane >> 4;
+    const int kvh = blockIdx.y;
+    q_text = of_video_elems(q_text, g.q_video); norm = of_video(norm, g.ws_video); colpart = of_video(colpart, g.ws_video);
+    const T* k_head = of_video_elems(k_all, g.k_video) + (static_cast<size_t>(kvh) * g.S + g.vis_start) * g.dh;
+    const int vb = blockIdx.x * sub_per_wg * 32;                       // visual keys [vb, ve) of this workgroup
+    const int ve = min(g.n_vis, vb + sub_per_wg * 32);
+    const int subs = (ve - vb + kSubKeys - 1) / kSubKeys;
+    const int n = subs > wave ? (subs - wave + kScoreWaves - 1) / kScoreWaves : 0;
+    auto load = [&](u32x4_t (&dst)[NCH], int t) { load_fragments<T, NCH>(dst, k_head, vb + (wave + t * kScoreWaves) * kSubKeys, ve - 1, g.dh); };
+    u32x4_t k[DEPTH][NCH], q[NB][NCH];
+    load_queries<T, NCH, NB>(q, q_text, g, kvh);
+    float cr[NB][4];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        const float4 c4 = *reinterpret_cast<const float4*>(norm + static_cast<size_t>(kvh) * g.rbw * 32 + b * 16 + 4 * h);       // +big for padding rows
+        cr[b][0] = c4.x; cr[b][1] = c4.y; cr[b][2] = c4.z; cr[b][3] = c4.w;
+    }
+#pragma unroll
+    for (int d = 0; d < DEPTH - 1; ++d) load(k[d], d);
+    walk_subtiles<NCH, DEPTH>(k, n, load, [&](const u32x4_t (&kf)[NCH], int t) {
+        float sum[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const f32x4_t x = narrow_chain<T, NCH>(q[b], kf);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum[e] += fast_exp2(fmaf(x[e], g.scale_log2, -cr[b][e]));
+        }
+        float total = (sum[0] + sum[1]) + (sum[2] + sum[3]);
+        total = swap32_add(total, total);
+        total = swap16_add(total, total);                              // every lane: all four lanes of its key
+        const int j = vb + (wave + t * kScoreWaves) * kSubKeys + lane;
+        if (lane < kSubKeys && j < ve) colpart[static_cast<size_t>(kvh) * g.n_vis + j] = total;
+    });
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1362,10 +1579,40 @@ static bool dh_supported(int dh, int dtype) {
     return dh == 32 || dh == 64 || dh == 128;
 }
 
+// Row blocks of 16 that the narrow kernels take for this shape, 0: the shape is not theirs.  Rows of at most four chunks per
+// lane: with eight (256 bf16, 128 fp32) the subtiles on their way no longer fit beside the queries (row statistics of
+// 9000 keys of 256: 8.5 us above, 11.1 us here).
+static int narrow_blocks(const ScoreGeom& g, int nch16) {
+    return g.R > 64 || nch16 > 4 ? 0 : (g.R <= 16 ? 1 : (g.R <= 32 ? 2 : 4));
+}
+
+template <typename T, int NCH16, int NB>
+static void launch_narrow_scores(const void* q, const void* k, const ScoreGeom& g, const ScorePlan& p, char* ws, int batch, hipStream_t st) {
+    float* pstat = reinterpret_cast<float*>(ws + p.off_pstat);
+    float* norm = reinterpret_cast<float*>(ws + p.off_norm);
+    float* colpart = reinterpret_cast<float*>(ws + p.off_colpart);
+    const unsigned nb = static_cast<unsigned>(batch);
+    { TraceScope trace_scope(METOK_TRACE_ROW_STATS, st); hipLaunchKernelGGL((narrow_row_stats_kernel<T, NCH16, NB>), dim3(p.nx1, g.Hkv, nb), dim3(kScoreThreads), 0, st,
+                       static_cast<const T*>(q), static_cast<const T*>(k), g, p.per1, pstat,
+                       reinterpret_cast<uint32_t*>(ws + p.off_sel + select_general_bytes(g.n_vis)), kFastClearWords); }
+    const int total_rows = g.Hkv * g.rbw * 32;
+    hipLaunchKernelGGL(merge_stats_kernel, dim3((total_rows + 15) / 16, 1, nb), dim3(256), 0, st, pstat, g, p.nx1, norm);
+    { TraceScope trace_scope(METOK_TRACE_COL_SUMS, st); hipLaunchKernelGGL((narrow_col_sums_kernel<T, NCH16, NB>), dim3(p.nx2, g.Hkv, nb), dim3(kScoreThreads), 0, st,
+                       static_cast<const T*>(q), static_cast<const T*>(k), g, p.per2, norm, colpart); }
+}
+
 template <typename T, int NCH>
 static void launch_scores(const void* q, const void* k, const ScoreGeom& g, const ScorePlan& p, char* ws, int batch, hipStream_t st) {
     constexpr int RBW = NCH <= 8 ? 2 : 1;
     constexpr int SUBS = NCH <= 8 ? 2 : 1;
+    constexpr int NCH16 = NCH / 2;                       // chunks per lane when four lanes share a row
+    if constexpr (NCH16 <= 4) {
+        switch (narrow_blocks(g, NCH16)) {
+            case 1: launch_narrow_scores<T, NCH16, 1>(q, k, g, p, ws, batch, st); return;
+            case 2: launch_narrow_scores<T, NCH16, 2>(q, k, g, p, ws, batch, st); return;
+            case 4: launch_narrow_scores<T, NCH16, 4>(q, k, g, p, ws, batch, st); return;
+        }
+    }
     using Stage = KeyStage<T, NCH, SUBS>;
     const size_t lds1 = kStageBuffers * static_cast<size_t>(Stage::kSlots) * sizeof(uint4);
     const size_t lds2 = 2 * static_cast<size_t>(Stage::kSlots) * sizeof(uint4) + 2 * static_cast<size_t>(kScoreWaves) * Stage::kKeys * sizeof(float);
