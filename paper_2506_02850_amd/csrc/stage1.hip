@@ -680,8 +680,8 @@ __global__ __launch_bounds__(kSegThreads) void plan_kernel(const PlanArgs1 plan,
 // the window at once and writes the pooled chunk.  Bound by HBM (and, for up to 1 GB of features, helped by what the
 // statistics pass left in the memory-side cache).  Against a wave per 64-chunk column part with a row of cells in flight:
 // 8 x 64 frames of 27 x 27 x 1152 (144 chunks: a quarter of those lanes idled) 168 -> 158 us, with the cache 142 us;
-// 128 frames of 24 x 24 x 1024 36 -> 31.6 -> 26.6 us.  36 workgroups per frame: 18 to 48 are within 3 %, 64 and more
-// cost up to a quarter in workgroups that find nothing to do.
+// 128 frames of 24 x 24 x 1024 36 -> 31.6 -> 26.6 us.  Four items of a thread in flight for strides 1 and 2, or eight cells
+// of a row in windows without code of their own, were 5 to 15 % slower.
 // ---------------------------------------------------------------------------------------------
 constexpr int kPoolThreads = 256;
 
@@ -941,7 +941,7 @@ struct StatsPlan {
     int G, KL, tok_per_wg, C, frames_per_run, runs;
 };
 
-static bool plan_stats(int T, int N, int d, int dtype, StatsPlan* p) {
+static bool plan_stats(int T, int N, int d, int dtype, StatsPlan* p, int batch = 1) {
     const int vec = dtype == METOK_BF16 ? 8 : 4;
     if (d % vec) return false;
     const int nchunks = d / vec;
@@ -961,6 +961,10 @@ static bool plan_stats(int T, int N, int d, int dtype, StatsPlan* p) {
     // about 2048 waves to fill 256 CUs twice over, but runs of at least 4 frames so that the extra frame read
     // per run stays a small fraction
     int runs = (2048 + p->C - 1) / p->C;
+    // waves of short rows have less in flight and fit a CU in larger numbers: up to four times as many, over the whole
+    // batch (two videos of 391 frames of 24 x 24 x 136: 41 -> 35 us)
+    const int more = (2048 * (KL >= 8 ? 1 : (KL >= 4 ? 2 : 4)) + p->C * batch - 1) / (p->C * batch);
+    if (more > runs) runs = more;
     int fpr = (T + runs - 1) / runs;
     if (fpr < 4) fpr = 4;
     // runs advance in step, their frames lie fpr frames apart: multiples of 8 frames put the runs' reads on the
@@ -1015,13 +1019,13 @@ static size_t stats_part_bytes(int T, const StatsPlan& p) {
     return round_up(static_cast<size_t>(T) * p.C * 3 * sizeof(float), 256);
 }
 
-static int check_feats(const void* feats, int dtype, int T, int N, int d, StatsPlan* p) {
+static int check_feats(const void* feats, int dtype, int T, int N, int d, StatsPlan* p, int batch = 1) {
     if (dtype != METOK_F32 && dtype != METOK_BF16) return fail(METOK_ERR_INVALID_ARG, "unknown dtype %d", dtype);
     if (T < 1 || T > METOK_MAX_FRAMES) return fail(METOK_ERR_INVALID_ARG, "T must be in [1, %d], got %d", METOK_MAX_FRAMES, T);
     if (N < 1 || d < 1) return fail(METOK_ERR_INVALID_ARG, "N and d must be positive");
     if (static_cast<int64_t>(T) * N > INT32_MAX) return fail(METOK_ERR_INVALID_ARG, "T * N must fit int32");
     if (!feats || !aligned16(feats)) return fail(METOK_ERR_INVALID_ARG, "feats is NULL or not 16-byte aligned");
-    if (!plan_stats(T, N, d, dtype, p))
+    if (!plan_stats(T, N, d, dtype, p, batch))
         return fail(METOK_ERR_UNSUPPORTED, "d = %d: need a multiple of %d and at most %d", d, dtype == METOK_BF16 ? 8 : 4,
                     dtype == METOK_BF16 ? 8192 : 4096);
     return METOK_OK;
@@ -1115,6 +1119,14 @@ static int64_t worst_case_rows(int T, int grid_h, int grid_w, int s1, int s2, in
     return static_cast<int64_t>(T) * side(grid_h) * side(grid_w);
 }
 
+// Workgroups of the pooling pass per frame: 36 (18 to 48 measured within 3 %, 64 and more up to a quarter slower), fewer if
+// a frame at its smallest stride does not hold a chunk for each of their threads (782 frames of 24 x 24 x 136: 55 -> 26 us, 2400 of 8 x 8 x 256: 110 -> 18 us).
+static unsigned pool_workgroups(int T, int grid_h, int grid_w, int d, int dtype, int s1, int s2, int pool_edge) {
+    const int64_t items = worst_case_rows(T, grid_h, grid_w, s1, s2, pool_edge) / T * (d / (dtype == METOK_BF16 ? 8 : 4));
+    const int64_t n = (items + kPoolThreads - 1) / kPoolThreads;
+    return static_cast<unsigned>(n < 1 ? 1 : (n < 36 ? n : 36));
+}
+
 extern "C" int64_t metok_compress_encoder_tokens_capacity_rows(int T, int grid_h, int grid_w, int s1, int s2, int pool_edge) {
     if (T < 1 || T > METOK_MAX_FRAMES || grid_h < 1 || grid_w < 1 || static_cast<int64_t>(grid_h) * grid_w > (1 << 24) || s1 < 1 || s2 < 1 ||
         (pool_edge != METOK_POOL_FLOOR && pool_edge != METOK_POOL_CEIL))
@@ -1202,8 +1214,7 @@ extern "C" int metok_compress_encoder_tokens(const void* feats, int dtype, int T
     { TraceScope trace_scope(METOK_TRACE_PLAN, st); hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(kSegThreads), 0, st, plan, scores, event_start, T, k); }
     if ((rc = check_launch("plan"))) return rc;
 
-    const int wg_per_frame = 36;      // 144 waves per frame; 18 to 72 workgroups measured within 3 % of each other
-    dim3 grid(wg_per_frame, T);
+    dim3 grid(pool_workgroups(T, grid_h, grid_w, d, dtype, s1, s2, pool_edge), T);
 #define METOK_POOL_CASE(TI, TO) \
     { TraceScope trace_scope(METOK_TRACE_POOL, st); \
       hipLaunchKernelGGL((pool_kernel<TI, TO>), grid, dim3(kPoolThreads), 0, st, static_cast<const TI*>(feats), grid_h, grid_w, d, \
@@ -1298,7 +1309,7 @@ static int segment_compress_impl(int batch, const void* feats, int dtype, int T,
     if (!fused && (sim_mode == METOK_SIM_FLAT || sim_mode == METOK_SIM_TOKEN_MEAN)) {
         // two passes (statistics, then pooling with the strides of Algorithm 1), each kernel once for the whole batch
         StatsPlan p;
-        int rc = check_feats(feats, dtype, T, N, d, &p);
+        int rc = check_feats(feats, dtype, T, N, d, &p, batch);
         if (rc) return rc;
         if (out_dtype != METOK_F32 && out_dtype != METOK_BF16) return fail(METOK_ERR_INVALID_ARG, "unknown out_dtype %d", out_dtype);
         if (k < 1 || k > T) return fail(METOK_ERR_INVALID_ARG, "k must be in [1, T] (k=%d, T=%d)", k, T);
@@ -1342,7 +1353,7 @@ static int segment_compress_impl(int batch, const void* feats, int dtype, int T,
                                 0, nullptr, 0, ws_video};
         launch_segment_plan(sa, plan, nb, st);
         if ((rc = check_launch("segment and plan"))) return rc;
-        dim3 grid(36, T, nb);
+        dim3 grid(pool_workgroups(T, grid_h, grid_w, d, dtype, s1, s2, pool_edge), T, nb);
 #define METOK_POOL_CASE(TI, TO) \
         { TraceScope trace_scope(METOK_TRACE_POOL, st); \
           hipLaunchKernelGGL((pool_kernel<TI, TO>), grid, dim3(kPoolThreads), 0, st, static_cast<const TI*>(feats), grid_h, grid_w, d, \

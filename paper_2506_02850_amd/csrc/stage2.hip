@@ -534,7 +534,7 @@ template <> struct NarrowMma<float> {              // one chunk feeds four 16x16
 };
 constexpr int kSubKeys = 16;
 // Subtiles in registers: the one in work and those on their way.
-constexpr int subtile_depth(int nch, int nb) { return nch * nb >= 8 ? 4 : 6; }
+constexpr int subtile_depth(int nch, int nb) { return nch * nb >= 32 ? 2 : (nch * nb >= 8 ? 4 : 6); }
 
 // Rows j0 + lane % 16 (at most `last`, which stands in for the rows behind it) of [*, dh]: pieces 4 c + lane / 16.
 template <typename T, int NCH>
@@ -1579,11 +1579,12 @@ static bool dh_supported(int dh, int dtype) {
     return dh == 32 || dh == 64 || dh == 128;
 }
 
-// Row blocks of 16 that the narrow kernels take for this shape, 0: the shape is not theirs.  Rows of at most four chunks per
-// lane: with eight (256 bf16, 128 fp32) the subtiles on their way no longer fit beside the queries (row statistics of
-// 9000 keys of 256: 8.5 us above, 11.1 us here).
-static int narrow_blocks(const ScoreGeom& g, int nch16) {
-    return g.R > 64 || nch16 > 4 ? 0 : (g.R <= 16 ? 1 : (g.R <= 32 ? 2 : 4));
+// Row blocks of 16 that the narrow kernels take for this shape, 0: the shape is not theirs.  bf16 rows of at most four
+// chunks per lane: with eight (256 elements) fewer subtiles are on their way beside the queries (row statistics of
+// 9000 keys of 256: 8.5 us above, 11.1 us here); fp32 products take sixteen times the matrix time, so there eight busy waves
+// win anyway (40 heads x 64 queries x 17219 keys of 128: 208 + 210 -> 143 + 127 us).
+static int narrow_blocks(const ScoreGeom& g, int nch16, bool f32) {
+    return g.R > 64 || (nch16 > 4 && !f32) ? 0 : (g.R <= 16 ? 1 : (g.R <= 32 ? 2 : 4));
 }
 
 template <typename T, int NCH16, int NB>
@@ -1606,8 +1607,8 @@ static void launch_scores(const void* q, const void* k, const ScoreGeom& g, cons
     constexpr int RBW = NCH <= 8 ? 2 : 1;
     constexpr int SUBS = NCH <= 8 ? 2 : 1;
     constexpr int NCH16 = NCH / 2;                       // chunks per lane when four lanes share a row
-    if constexpr (NCH16 <= 4) {
-        switch (narrow_blocks(g, NCH16)) {
+    if constexpr (NCH16 <= 4 || std::is_same<T, float>::value) {
+        switch (narrow_blocks(g, NCH16, std::is_same<T, float>::value)) {
             case 1: launch_narrow_scores<T, NCH16, 1>(q, k, g, p, ws, batch, st); return;
             case 2: launch_narrow_scores<T, NCH16, 2>(q, k, g, p, ws, batch, st); return;
             case 4: launch_narrow_scores<T, NCH16, 4>(q, k, g, p, ws, batch, st); return;
@@ -1625,12 +1626,24 @@ static void launch_scores(const void* q, const void* k, const ScoreGeom& g, cons
     const unsigned nb = static_cast<unsigned>(batch);
     hipLaunchKernelGGL((pack_q_kernel<T, NCH>), dim3((qslots + 255) / 256, 1, nb), dim3(256), 0, st, static_cast<const T*>(q), g, qfrag,
                        reinterpret_cast<uint32_t*>(ws + p.off_sel + select_general_bytes(g.n_vis)), kFastClearWords);
-    { TraceScope trace_scope(METOK_TRACE_ROW_STATS, st); hipLaunchKernelGGL((row_stats_kernel<T, NCH, RBW, SUBS>), dim3(p.nx1, ny, nb), dim3(kScoreThreads), lds1, st,
-                       qfrag, static_cast<const T*>(k), g, p.per1, pstat); }
+    {
+        // With at most one row block per wave the two-block pipeline would run its second chain on zeros (32 heads on 8,
+        // 4 x 36928 keys: 159 -> 124 us; 14 heads on 2, 32 queries, 5064 keys in fp32: 10.4 -> 9.6 us).
+        TraceScope trace_scope(METOK_TRACE_ROW_STATS, st);
+        if (g.rbw <= kScoreWaves)
+            hipLaunchKernelGGL((row_stats_kernel<T, NCH, 1, SUBS>), dim3(p.nx1, ny, nb), dim3(kScoreThreads), lds1, st, qfrag, static_cast<const T*>(k), g, p.per1, pstat);
+        else
+            hipLaunchKernelGGL((row_stats_kernel<T, NCH, RBW, SUBS>), dim3(p.nx1, ny, nb), dim3(kScoreThreads), lds1, st, qfrag, static_cast<const T*>(k), g, p.per1, pstat);
+    }
     const int total_rows = ny * g.rbw * 32;
     hipLaunchKernelGGL(merge_stats_kernel, dim3((total_rows + 15) / 16, 1, nb), dim3(256), 0, st, pstat, g, p.nx1, norm);
-    { TraceScope trace_scope(METOK_TRACE_COL_SUMS, st); hipLaunchKernelGGL((col_sums_kernel<T, NCH, RBW, SUBS>), dim3(p.nx2, ny, nb), dim3(kScoreThreads), lds2, st,
-                       qfrag, static_cast<const T*>(k), g, p.per2, norm, colpart); }
+    {
+        TraceScope trace_scope(METOK_TRACE_COL_SUMS, st);
+        if (g.rbw <= kScoreWaves)
+            hipLaunchKernelGGL((col_sums_kernel<T, NCH, 1, SUBS>), dim3(p.nx2, ny, nb), dim3(kScoreThreads), lds2, st, qfrag, static_cast<const T*>(k), g, p.per2, norm, colpart);
+        else
+            hipLaunchKernelGGL((col_sums_kernel<T, NCH, RBW, SUBS>), dim3(p.nx2, ny, nb), dim3(kScoreThreads), lds2, st, qfrag, static_cast<const T*>(k), g, p.per2, norm, colpart);
+    }
 }
 
 }  // namespace metok

@@ -16,7 +16,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("dtype,dh,Hq,Hkv,Tq", [
     ("bf16", 128, 4, 4, 1), ("bf16", 128, 28, 4, 1), ("bf16", 128, 4, 4, 16), ("bf16", 128, 4, 4, 17), ("bf16", 128, 2, 2, 33),
     ("bf16", 128, 2, 2, 64), ("bf16", 128, 2, 2, 65), ("bf16", 64, 6, 2, 21), ("bf16", 64, 4, 4, 5), ("bf16", 32, 3, 3, 64), ("bf16", 32, 2, 2, 32),
-    ("bf16", 256, 2, 2, 8), ("f32", 32, 4, 2, 16), ("f32", 64, 2, 2, 48), ("f32", 64, 3, 3, 2), ("f32", 128, 2, 2, 9)])
+    ("bf16", 256, 2, 2, 8), ("f32", 32, 4, 2, 16), ("f32", 64, 2, 2, 48), ("f32", 64, 3, 3, 2), ("f32", 128, 2, 2, 9), ("f32", 128, 2, 2, 30), ("f32", 128, 2, 2, 61),
+    ("bf16", 128, 8, 2, 64), ("bf16", 64, 14, 2, 32), ("f32", 64, 14, 2, 32), ("f32", 32, 6, 2, 40)])          # one row block per wave of the shared-stage kernels
 @pytest.mark.parametrize("frames,tokens,vis_start,mode", [(1, 5, 0, 0), (3, 43, 2, 0), (23, 37, 0, 1), (40, 113, 17, 0)])
 def test_narrow_scores(dtype, dh, Hq, Hkv, Tq, frames, tokens, vis_start, mode):
     layer = make_layer(4000 + dh + Tq, frames, tokens, min(3, frames), Tq + 3, 16, Hq, Hkv, dh, dtype, vis_start=vis_start)

@@ -64,3 +64,10 @@ def test_event_ids_of_uniformly_pooled_rows(T, grid):
     events, frames = got["token_event"].cpu().numpy().reshape(-1, T * rows), got["frame_event"].cpu().numpy().reshape(-1, T)
     for te, fe in zip(events, frames):
         np.testing.assert_array_equal(te, np.repeat(fe, rows))
+
+
+@pytest.mark.parametrize("T,grid,d,s1,s2", [(40, (4, 4), 8, 3, 4), (33, (12, 12), 64, 3, 4), (20, (24, 24), 40, 1, 2), (9, (27, 27), 136, 2, 3)])
+def test_few_or_many_pooling_workgroups_per_frame(T, grid, d, s1, s2):
+    # 1 chunk, 128, 2880 and 2873 chunks at the smallest stride: one workgroup per frame, one, twelve and twelve
+    v = synth.planted_video(9500 + T, T, grid, d, 3, 1, T, 0.2 / d ** 0.5, "bf16")
+    check(v, grid, 3, 0.5, 0.4, s1, s2, "bf16")
