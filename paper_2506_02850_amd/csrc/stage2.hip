@@ -1,12 +1,11 @@
 // Stage 2 (Sec. 3.2.2): one level of hierarchical pruning.
 //
-//   pack_q_kernel        text queries -> MFMA fragment order, once per call
 //   row_stats_kernel     MFMA pass 1 over all keys: per (head, text query) running max and sum of the
-//                        causal softmax, in the log2 domain, per workgroup
+//                        causal softmax, in the log2 domain, per workgroup; leaves the queries in MFMA fragment order
 //   merge_stats_kernel   merges the per-workgroup (max, sum) pairs into one normaliser per row
 //   col_sums_kernel      MFMA pass 2 over the visual keys: recomputes the logits and adds up the
 //                        probabilities of every visual key over the rows of a workgroup
-//   narrow_row_stats_kernel, narrow_col_sums_kernel   the two passes for at most 64 query rows per kv head (no packing)
+//   narrow_row_stats_kernel, narrow_col_sums_kernel   the two passes for at most 64 query rows per kv head 
 //   score_select_kernel  score_j = w_e(j) * mean probability per tile; the workgroup that arrives last selects per class
 //                        (radix select) and writes the ascending index list
 //   prepare_kernel, select_kernel, write_index_kernel   the same steps for more than 16 classes or more than 40960
@@ -22,6 +21,7 @@
 // registers and the workgroup streams its range of keys through LDS.  The contraction index may be
 // permuted freely as long as both operands agree; here lane half h = lane/32 owns the contiguous half h
 // of the head dimension, so every fragment is a contiguous 16-byte chunk of a row.
+#include <algorithm>
 #include <mutex>
 
 #include "common.h"
@@ -120,30 +120,73 @@ struct KeyStage {
     }
 };
 
-// Query fragments in MFMA operand order, written once per call and read by every workgroup of both passes:
+// Query fragments in MFMA operand order, written once per call (by the first workgroups of pass 1) for pass 2:
 //     qfrag[((kvh * rb_total + rb) * NCH + c) * 64 + lane],  row = 32 rb + lane % 32, half = lane / 32,
 // 16 bytes each (elements half * dh/2 + c * CE ... of the row); rows past the last query are zero.
 // A wave then fetches a fragment with one fully coalesced 1 KB load instead of 64 strided 16-byte pieces.
-// As the first kernel of a call it also clears the counters and histograms of the later kernels (`clear`, n_clear words).
-template <typename T, int NCH>
-__global__ __launch_bounds__(256) void pack_q_kernel(const T* __restrict__ q_text, const ScoreGeom g, uint4* __restrict__ qfrag,
-                                                     uint32_t* __restrict__ clear, int n_clear) {
-    constexpr int CE = Mma<T>::kChunkElems;
-    q_text = of_video_elems(q_text, g.q_video); qfrag = of_video(qfrag, g.ws_video); clear = of_video(clear, g.ws_video);
-    const int idx = blockIdx.x * 256 + threadIdx.x;
-    for (int i = idx; i < n_clear; i += gridDim.x * 256) clear[i] = 0u;
-    const int total = g.Hkv * g.rb_total * NCH * 64;
-    if (idx >= total) return;
-    const int lane = idx & 63, c = (idx >> 6) % NCH, rbg = idx / (64 * NCH);
-    const int kvh = rbg / g.rb_total, rb = rbg % g.rb_total;
-    const int r = rb * 32 + (lane & 31);
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (r < g.R) {
-        const int hq = kvh * g.group + r / g.Tq, qi = r % g.Tq;
-        v = *reinterpret_cast<const uint4*>(q_text + (static_cast<size_t>(hq) * g.Tq + qi) * g.dh + (lane >> 5) * (g.dh / 2) + c * CE);
+//
+// Pass 1 takes its fragments from the rows themselves.  The rows of a block lie one after the other (row r of kv head v is
+// row v * R + r of q_text), so a wave loads them in memory order, 1 KB a time, and turns them into fragments through a
+// part of LDS of its own: kRows rows a round, piece p of a row at p ^ (row mod pieces), which spreads both the writes
+// (pieces of a row) and the reads (one piece of 32 rows) over the banks.  A packing kernel in front
+// took 3.2 us a call; this costs pass 1 about 1 us (one level of 2243 tokens, 28 / 4 heads x 64 queries: 35.5 -> 33.4 us,
+// of 4500 in fp32: 39.2 -> 37.0 us, eight videos of 36864 tokens: within the noise).
+template <typename T, int NCH, int RBW>
+struct QueryRows {
+    static constexpr int kPieces = 2 * NCH;                                    // 16-byte pieces of a row, a power of two
+    static constexpr int kRows = kPieces > 16 ? 512 / kPieces : 32;            // rows per round: at most 8 KB per wave
+    static constexpr int kRounds = 32 / kRows;
+    static constexpr int kLoads = kRows * kPieces / 64;                        // per round
+    static constexpr size_t kLdsBytes = static_cast<size_t>(kScoreWaves) * kRows * kPieces * sizeof(uint4);
+    u32x4_t v[RBW][kRounds][kLoads];
+
+    __device__ __forceinline__ void load(const T* __restrict__ q_text, const ScoreGeom& g, int kvh, int rb0, int nrb, int wave, int lane) {
+        const u32x4_t* rows = reinterpret_cast<const u32x4_t*>(q_text) + static_cast<size_t>(kvh) * g.R * kPieces;
+#pragma unroll
+        for (int i = 0; i < RBW; ++i) {
+            const int rbl = wave + kScoreWaves * i;
+            const int r0 = (rb0 + (rbl < nrb ? rbl : 0)) * 32;
+#pragma unroll
+            for (int k = 0; k < kRounds; ++k)
+#pragma unroll
+                for (int u = 0; u < kLoads; ++u) {
+                    const int id = u * 64 + lane;
+                    const int r = min(r0 + k * kRows + id / kPieces, g.R - 1);     // rows past the last are cleared below
+                    v[i][k][u] = rows[r * kPieces + id % kPieces];
+                }
+        }
     }
-    qfrag[idx] = v;
-}
+    // Only the wave itself uses its part of LDS, and a wave's LDS accesses complete in order.
+    __device__ __forceinline__ void to_fragments(uint4 (&q)[RBW][NCH], uint4* lds, const ScoreGeom& g, int rb0, int nrb, int wave, int lane) {
+        u32x4_t* own = reinterpret_cast<u32x4_t*>(lds) + wave * kRows * kPieces;
+        const int row = lane & 31, half = lane >> 5;
+#pragma unroll
+        for (int i = 0; i < RBW; ++i) {
+            const int rbl = wave + kScoreWaves * i;
+            const bool ok = rbl < nrb && (rb0 + rbl) * 32 + row < g.R;
+#pragma unroll
+            for (int k = 0; k < kRounds; ++k) {
+#pragma unroll
+                for (int u = 0; u < kLoads; ++u) {
+                    const int id = u * 64 + lane, r = id / kPieces, p = id % kPieces;
+                    own[r * kPieces + (p ^ (r & (kPieces - 1)))] = v[i][k][u];
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                const int r = row % kRows;
+#pragma unroll
+                for (int c = 0; c < NCH; ++c) {
+                    const u32x4_t f = own[r * kPieces + ((half * NCH + c) ^ (r & (kPieces - 1)))];
+                    if (k == 0 || row / kRows == k) q[i][c] = make_uint4(f.x, f.y, f.z, f.w);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+            }
+#pragma unroll
+            for (int c = 0; c < NCH; ++c) if (!ok) q[i][c] = make_uint4(0, 0, 0, 0);
+        }
+    }
+};
 
 // q[i][c] belongs to the wave's local row block wave + 8 i.
 template <int NCH, int RBW>
@@ -232,17 +275,21 @@ constexpr int kStageBuffers = 3;       // LDS stages: one in use, one ready (its
 // Stages that need the mask, and workgroups with fewer row blocks than waves, take the plain path.
 // ---------------------------------------------------------------------------------------------
 template <typename T, int NCH, int RBW, int SUBS>
-__global__ __launch_bounds__(kScoreThreads) void row_stats_kernel(const uint4* __restrict__ qfrag, const T* __restrict__ k_all,
-                                                                  const ScoreGeom g, int sub_per_wg, float* __restrict__ pstat) {
+__global__ __launch_bounds__(kScoreThreads) void row_stats_kernel(const T* __restrict__ q_text, const T* __restrict__ k_all,
+                                                                  const ScoreGeom g, int sub_per_wg, float* __restrict__ pstat,
+                                                                  uint4* __restrict__ qfrag, uint32_t* __restrict__ clear, int n_clear) {
     using Stage = KeyStage<T, NCH, SUBS>;
-    extern __shared__ uint4 lds[];                      // kStageBuffers stages
+    extern __shared__ uint4 lds[];                      // the waves' query rows, then kStageBuffers stages
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5;
     const int kvh = blockIdx.y / g.rs, split = blockIdx.y % g.rs;
     const int rb0 = split * g.rbw;
     const int nrb = min(g.rbw, g.rb_total - rb0);
     const int nrb_w = nrb > wave ? (nrb - wave + kScoreWaves - 1) / kScoreWaves : 0;     // row blocks of this wave
-    qfrag = of_video(qfrag, g.ws_video); pstat = of_video(pstat, g.ws_video);
+    q_text = of_video_elems(q_text, g.q_video);
+    qfrag = of_video(qfrag, g.ws_video); pstat = of_video(pstat, g.ws_video); clear = of_video(clear, g.ws_video);
     const T* k_head = of_video_elems(k_all, g.k_video) + static_cast<size_t>(kvh) * g.S * g.dh;
+    // as the first kernel of a call it clears the counters of the later ones
+    if (blockIdx.x == 0 && blockIdx.y == 0 && static_cast<int>(threadIdx.x) < n_clear) clear[threadIdx.x] = 0u;
 
     const int64_t kb = g.key_begin + static_cast<int64_t>(blockIdx.x) * sub_per_wg * 32;
     const int64_t ke = min(g.key_end, kb + static_cast<int64_t>(sub_per_wg) * 32);
@@ -250,12 +297,17 @@ __global__ __launch_bounds__(kScoreThreads) void row_stats_kernel(const uint4* _
     const int64_t text_start = g.S - g.Tq;
     const int64_t full_end = text_start < ke ? text_start : ke;
 
-    // the first two key stages and the query fragments are requested together: one memory round trip
+    // the first two key stages and the queries are requested together: one memory round trip
     u32x4_t kv[Stage::kPerThread], kv1[Stage::kPerThread];
     Stage::load(kv, k_head, kb, g.S, g.dh);
     Stage::load(kv1, k_head, kb + (n_stage > 1 ? Stage::kKeys : 0), g.S, g.dh);
     uint4 q[RBW][NCH];
-    load_qfrag<NCH, RBW>(q, qfrag, g, kvh, rb0, nrb, wave, lane);
+    {
+        QueryRows<T, NCH, RBW> rows;
+        rows.load(q_text, g, kvh, rb0, nrb, wave, lane);
+        rows.to_fragments(q, lds, g, rb0, nrb, wave, lane);
+        __syncthreads();                                // the stages take over the waves' parts of LDS
+    }
     float m[RBW], l[RBW];
 #pragma unroll
     for (int i = 0; i < RBW; ++i) { m[i] = kNegBig; l[i] = 0.f; }
@@ -366,6 +418,19 @@ __global__ __launch_bounds__(kScoreThreads) void row_stats_kernel(const uint4* _
             }
         }
         publish(s);
+    }
+    // Pass 2 reads the fragments that the first workgroup of each kv head and split leaves (here, behind the key stages,
+    // whose loads would wait for the stores).
+    if (blockIdx.x == 0) {
+#pragma unroll
+        for (int i = 0; i < RBW; ++i) {
+            const int rbl = wave + kScoreWaves * i;
+            if (rbl < nrb) {
+                uint4* dst = qfrag + (static_cast<size_t>(kvh) * g.rb_total + rb0 + rbl) * NCH * 64 + lane;
+#pragma unroll
+                for (int c = 0; c < NCH; ++c) dst[c * 64] = q[i][c];
+            }
+        }
     }
     // the two lane halves hold different keys of the same row
     const int rows_per_y = g.rbw * 32;
@@ -1615,25 +1680,25 @@ static void launch_scores(const void* q, const void* k, const ScoreGeom& g, cons
         }
     }
     using Stage = KeyStage<T, NCH, SUBS>;
-    const size_t lds1 = kStageBuffers * static_cast<size_t>(Stage::kSlots) * sizeof(uint4);
+    const size_t lds1 = std::max(kStageBuffers * static_cast<size_t>(Stage::kSlots) * sizeof(uint4), QueryRows<T, NCH, 1>::kLdsBytes);
     const size_t lds2 = 2 * static_cast<size_t>(Stage::kSlots) * sizeof(uint4) + 2 * static_cast<size_t>(kScoreWaves) * Stage::kKeys * sizeof(float);
     const int ny = g.Hkv * g.rs;
+    uint32_t* clear = reinterpret_cast<uint32_t*>(ws + p.off_sel + select_general_bytes(g.n_vis));
     uint4* qfrag = reinterpret_cast<uint4*>(ws + p.off_qfrag);
     float* pstat = reinterpret_cast<float*>(ws + p.off_pstat);
     float* norm = reinterpret_cast<float*>(ws + p.off_norm);
     float* colpart = reinterpret_cast<float*>(ws + p.off_colpart);
-    const int qslots = g.Hkv * g.rb_total * NCH * 64;
     const unsigned nb = static_cast<unsigned>(batch);
-    hipLaunchKernelGGL((pack_q_kernel<T, NCH>), dim3((qslots + 255) / 256, 1, nb), dim3(256), 0, st, static_cast<const T*>(q), g, qfrag,
-                       reinterpret_cast<uint32_t*>(ws + p.off_sel + select_general_bytes(g.n_vis)), kFastClearWords);
     {
         // With at most one row block per wave the two-block pipeline would run its second chain on zeros (32 heads on 8,
         // 4 x 36928 keys: 159 -> 124 us; 14 heads on 2, 32 queries, 5064 keys in fp32: 10.4 -> 9.6 us).
         TraceScope trace_scope(METOK_TRACE_ROW_STATS, st);
         if (g.rbw <= kScoreWaves)
-            hipLaunchKernelGGL((row_stats_kernel<T, NCH, 1, SUBS>), dim3(p.nx1, ny, nb), dim3(kScoreThreads), lds1, st, qfrag, static_cast<const T*>(k), g, p.per1, pstat);
+            hipLaunchKernelGGL((row_stats_kernel<T, NCH, 1, SUBS>), dim3(p.nx1, ny, nb), dim3(kScoreThreads), lds1, st, static_cast<const T*>(q),
+                               static_cast<const T*>(k), g, p.per1, pstat, qfrag, clear, kFastClearWords);
         else
-            hipLaunchKernelGGL((row_stats_kernel<T, NCH, RBW, SUBS>), dim3(p.nx1, ny, nb), dim3(kScoreThreads), lds1, st, qfrag, static_cast<const T*>(k), g, p.per1, pstat);
+            hipLaunchKernelGGL((row_stats_kernel<T, NCH, RBW, SUBS>), dim3(p.nx1, ny, nb), dim3(kScoreThreads), lds1, st, static_cast<const T*>(q),
+                               static_cast<const T*>(k), g, p.per1, pstat, qfrag, clear, kFastClearWords);
     }
     const int total_rows = ny * g.rbw * 32;
     hipLaunchKernelGGL(merge_stats_kernel, dim3((total_rows + 15) / 16, 1, nb), dim3(256), 0, st, pstat, g, p.nx1, norm);

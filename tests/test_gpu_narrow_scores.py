@@ -27,6 +27,20 @@ def test_narrow_scores(dtype, dh, Hq, Hkv, Tq, frames, tokens, vis_start, mode):
     check_prune(layer, seg, quotas, got, q, score_mode=mode)
 
 
+# the shared-stage kernels: rows of every length, turned into fragments in one round (up to 16 pieces of 16 bytes) or two (32),
+# row counts that leave a block partly empty, fewer blocks than waves, two blocks per wave, several row splits
+@pytest.mark.parametrize("dtype,dh,Hq,Hkv,Tq", [
+    ("bf16", 32, 5, 1, 13), ("bf16", 64, 22, 2, 9), ("bf16", 128, 23, 1, 3), ("bf16", 128, 27, 1, 19), ("bf16", 256, 1, 1, 1),
+    ("bf16", 256, 7, 1, 7), ("bf16", 256, 26, 2, 20), ("f32", 32, 13, 1, 5), ("f32", 64, 21, 1, 20), ("f32", 128, 5, 1, 13), ("f32", 128, 43, 1, 6)])
+@pytest.mark.parametrize("frames,tokens,mode", [(3, 11, 0), (30, 97, 1)])
+def test_query_rows_of_the_shared_stage_kernels(dtype, dh, Hq, Hkv, Tq, frames, tokens, mode):
+    layer = make_layer(4300 + dh + Hq, frames, tokens, 3, Tq + 1, 16, Hq, Hkv, dh, dtype, vis_start=5)
+    seg = np.zeros(layer.n_vis, dtype=np.int32)
+    quotas = [layer.n_vis // 3]
+    got, q = run_prune(layer, seg, quotas, Tq=Tq, score_mode=mode)
+    check_prune(layer, seg, quotas, got, q, score_mode=mode)
+
+
 @pytest.mark.parametrize("Hq,Tq", [(2, 20), (2, 64), (14, 32)])          # narrow with two and four blocks; the shared-stage kernels
 def test_logits_far_above_the_first_keys(Hq, Tq):
     # later keys lift the logits by hundreds (log2): a sum relative to the first subtile would overflow
