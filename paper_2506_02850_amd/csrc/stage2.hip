@@ -1101,7 +1101,7 @@ __global__ __launch_bounds__(kIdxThreads) void write_index_kernel(
 // threshold was found, so the results are the integers of the general path.
 // What bounds it is latency, not work: a chain of about ten barriers and two memory round trips.  The digits start at
 // the smallest key because attention scores share their leading bits: a histogram of the top 11 bits of the key itself
-// left a third of the tokens in one bucket (and its atomics on one address), the shifted one leaves about twenty.
+// left a third of the tokens in one bucket (and its atomics on one address), the shifted one leaves 20 to 200.
 // Measured against the launches it replaces (score + histogram, candidates, index list; with 5 to 16 classes the general
 // path's three): 2243 tokens 28.5 -> 9.9 us, 4507 tokens with 40 partial sums each 33 -> 12.4 us, 18432 tokens in 13
 // classes 31 -> 20 us, eight videos of 36864 tokens 46 -> 30 us.  One workgroup walking 36 tiles is what is left there
@@ -1113,6 +1113,7 @@ constexpr int kFastTiles = kSelCache;
 constexpr int kSplitParts = 8;              // from so many partial sums per token on four threads share a token in the scoring part
 constexpr int kHistWords = 8192;            // histogram bins of all classes together: 2048 per class up to 4 classes, else 512
 constexpr int kListCap = 512;               // keys of the threshold buckets that are ranked against each other
+constexpr int kRankStep = 8;                // list entries read from LDS together
 
 struct FastSel {
     uint32_t arrive;                        // cleared before the kernel that counts on it
@@ -1206,8 +1207,7 @@ struct SelectShared {
     uint64_t kept[kFastTiles * 16];         // bit mask of the kept tokens of every 64-token group
     uint64_t equal[kFastTiles * 16];        // of the tokens equal to a class's threshold (only with more ties than the list holds)
     int before[kFastTiles * 16];            // kept (or equal) tokens of the groups before this one
-    uint32_t list_key[kListCap];
-    uint32_t list_tok[kListCap];
+    uint64_t list[kListCap + kRankStep];    // key and, below it, the complement of the token: larger is kept first
     uint32_t lo, hi;                        // smallest and largest key
     int need[kFastSeg], cnt[kFastSeg], base[kFastSeg + 1], fill[kFastSeg];
     // a token is kept if key >> shift >= sure, and is a candidate if key >> shift == cand; the last entry is for tokens without a class
@@ -1362,7 +1362,7 @@ __device__ __forceinline__ void select_and_index(const FastArgs& a, const float*
                     const uint32_t c = class_of(i0 + u);
                     if (c != kFastSeg && (key[i0 + u] >> shift) == rule[u].y) {
                         const int p = sh.base[c] + atomicAdd(&sh.fill[c], 1);
-                        if (p < kListCap) { sh.list_key[p] = key[i0 + u]; sh.list_tok[p] = static_cast<uint32_t>(tid + (i0 + u) * kSelThreads); }
+                        if (p < kListCap) sh.list[p] = static_cast<uint64_t>(key[i0 + u]) << 32 | static_cast<uint32_t>(~(tid + (i0 + u) * kSelThreads));
                     }
                 }
             }
@@ -1378,11 +1378,18 @@ __device__ __forceinline__ void select_and_index(const FastArgs& a, const float*
         if (tid < sh.base[n_seg]) {
             int c = 0;
             while (c + 1 < n_seg && tid >= sh.base[c + 1]) ++c;
-            const uint32_t k = sh.list_key[tid], t = sh.list_tok[tid];
+            // Eight entries a step: one at a time the walk is a chain of LDS round trips (about 200 candidates, eight
+            // videos of 36864 tokens in one class: 47 -> 34 us for the kernel; 9216 tokens: 16.8 -> 13.6 us).
+            const uint64_t own = sh.list[tid];
+            const uint32_t t = ~static_cast<uint32_t>(own);
+            const int end = sh.base[c + 1];
             int above = 0;
-            for (int p = sh.base[c]; p < sh.base[c + 1]; ++p) {
-                const uint32_t o = sh.list_key[p];
-                above += (o > k || (o == k && sh.list_tok[p] < t)) ? 1 : 0;
+            for (int p = sh.base[c]; p < end; p += kRankStep) {
+                uint64_t other[kRankStep];
+#pragma unroll
+                for (int u = 0; u < kRankStep; ++u) other[u] = sh.list[p + u];
+#pragma unroll
+                for (int u = 0; u < kRankStep; ++u) above += p + u < end && other[u] > own ? 1 : 0;
             }
             if (above < sh.need[c]) atomicOr(reinterpret_cast<unsigned long long*>(&sh.kept[t >> 6]), 1ull << (t & 63));
         }
