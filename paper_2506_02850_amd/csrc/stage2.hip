@@ -129,8 +129,9 @@ struct KeyStage {
 // row v * R + r of q_text), so a wave loads them in memory order, 1 KB a time, and turns them into fragments through a
 // part of LDS of its own: kRows rows a round, piece p of a row at p ^ (row mod pieces), which spreads both the writes
 // (pieces of a row) and the reads (one piece of 32 rows) over the banks.  A packing kernel in front
-// took 3.2 us a call; this costs pass 1 about 1 us (one level of 2243 tokens, 28 / 4 heads x 64 queries: 35.5 -> 33.4 us,
-// of 4500 in fp32: 39.2 -> 37.0 us, eight videos of 36864 tokens: within the noise).
+// took 3.2 us a call; this costs pass 1 about 1 us, with eight videos per launch 3 of the kernel's 5 us (one level of 2243
+// tokens, 28 / 4 heads x 64 queries: 35.5 -> 33.4 us, of 5000 in fp32: 39.2 -> 37.0 us, eight videos of 36864 tokens: within
+// the noise).
 template <typename T, int NCH, int RBW>
 struct QueryRows {
     static constexpr int kPieces = 2 * NCH;                                    // 16-byte pieces of a row, a power of two
@@ -574,8 +575,9 @@ __global__ __launch_bounds__(kScoreThreads) void col_sums_kernel(const uint4* __
 // every stage waiting for memory behind a barrier; what bounds this shape is the stream of keys.  Here every wave keeps all
 // query rows (NB blocks of 16) in registers and walks its own 16-key subtiles of the workgroup's range, every eighth one,
 // straight from memory into registers in MFMA fragment order and several subtiles ahead; no wave waits for another.
-// 40 heads x 64 queries, 4571 keys of 128 bf16 (47 MB): row statistics 17.7 -> 15.6 us, column sums 15.9 -> 13.6 us, and no
-// packing launch (3.2 us); the launch and the first loads are 5 us of each.  16 heads, 30064 keys of 64: 27.4 + 28.8 ->
+// 40 heads x 64 queries, 4571 keys of 128 bf16 (47 MB): row statistics 17.7 -> 15.6 us, column sums 15.9 -> 13.6 us (the
+// shared stages took packed queries then, a launch of 3.2 us more; turning them itself costs their pass 1 about 1 us); the
+// launch and the first loads are 5 us of each.  16 heads, 30064 keys of 64: 27.4 + 28.8 ->
 // 15.1 + 14.8 us; the last token of 28 heads on 4, 18496 keys: 10.5 + 8.6 -> 8.0 + 6.1 us.  With more rows the loads cost
 // more than they save: a wave's 1 KB load in fragment order takes 64 bytes of 16 rows (four times the address work of a
 // contiguous one), and 28 blocks over four waves that each load their own fragments took 160 us where the shared stages
