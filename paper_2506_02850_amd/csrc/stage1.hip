@@ -943,7 +943,7 @@ struct StatsPlan {
 
 static bool plan_stats(int T, int N, int d, int dtype, StatsPlan* p, int batch = 1) {
     const int vec = dtype == METOK_BF16 ? 8 : 4;
-    if (d % vec) return false;
+    if (N < 1 || d % vec) return false;                 // N < 1: a patch grid whose token count left 32 bits
     const int nchunks = d / vec;
     // Chunks per lane: the smallest of the built counts that covers a row, on 16 lanes up to 12 chunks each, else on 64.
     // A lane past the row's end reads the last chunk again, so a tight count is what the rate depends on: 144 chunks
@@ -957,13 +957,15 @@ static bool plan_stats(int T, int N, int d, int dtype, StatsPlan* p, int batch =
     if (!KL) return false;
     p->G = G; p->KL = KL;
     p->tok_per_wg = kStatsWaves * (64 / G);
-    p->C = (N + 64 / G - 1) / (64 / G);                 // wave chunks per frame: one partial triple each
+    p->C = (N - 1) / (64 / G) + 1;                      // wave chunks per frame: one partial triple each
     // about 2048 waves to fill 256 CUs twice over, but runs of at least 4 frames so that the extra frame read
     // per run stays a small fraction
-    int runs = (2048 + p->C - 1) / p->C;
+    // (64 bits: C reaches 2^31 - 1, and it is multiplied by the batch)
+    int runs = static_cast<int>((2048 + static_cast<int64_t>(p->C) - 1) / p->C);
     // waves of short rows have less in flight and fit a CU in larger numbers: up to four times as many, over the whole
     // batch (two videos of 391 frames of 24 x 24 x 136: 41 -> 35 us)
-    const int more = (2048 * (KL >= 8 ? 1 : (KL >= 4 ? 2 : 4)) + p->C * batch - 1) / (p->C * batch);
+    const int64_t waves = static_cast<int64_t>(p->C) * batch;
+    const int more = static_cast<int>((2048 * (KL >= 8 ? 1 : (KL >= 4 ? 2 : 4)) + waves - 1) / waves);
     if (more > runs) runs = more;
     int fpr = (T + runs - 1) / runs;
     if (fpr < 4) fpr = 4;
@@ -1308,6 +1310,7 @@ static int segment_compress_impl(int batch, const void* feats, int dtype, int T,
     if (kl < 1 || kl > 4) fused = false;
     if (!fused && (sim_mode == METOK_SIM_FLAT || sim_mode == METOK_SIM_TOKEN_MEAN)) {
         // two passes (statistics, then pooling with the strides of Algorithm 1), each kernel once for the whole batch
+        if (static_cast<int64_t>(grid_h) * grid_w > (1 << 24)) return fail(METOK_ERR_INVALID_ARG, "bad patch grid %d x %d", grid_h, grid_w);
         StatsPlan p;
         int rc = check_feats(feats, dtype, T, N, d, &p, batch);
         if (rc) return rc;
@@ -1326,7 +1329,6 @@ static int segment_compress_impl(int batch, const void* feats, int dtype, int T,
         if (!aligned16(text_emb) || !aligned16(out_tokens)) return fail(METOK_ERR_INVALID_ARG, "text_emb / out_tokens not 16-byte aligned");
         if ((static_cast<size_t>(d) * dtype_size(dtype)) % 16 || (static_cast<size_t>(d) * dtype_size(out_dtype)) % 16)
             return fail(METOK_ERR_INVALID_ARG, "d * sizeof(dtype) must be a multiple of 16 for the features and the pooled tokens");
-        if (static_cast<int64_t>(grid_h) * grid_w > (1 << 24)) return fail(METOK_ERR_INVALID_ARG, "bad patch grid %d x %d", grid_h, grid_w);
         const int gmax = grid_h > grid_w ? grid_h : grid_w;
         auto clamp_stride = [&](double v) { int c = ceil_ratio(v); return c < 1 ? 1 : (c > gmax ? gmax : c); };
         const int64_t worst = worst_case_rows(T, grid_h, grid_w, s1, s2, pool_edge);

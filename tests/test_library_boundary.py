@@ -270,3 +270,25 @@ def test_bench_refuses_more_than_one_gpu():
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True, timeout=120)
     assert r.returncode != 0
     assert "one GPU" in (r.stdout + r.stderr)
+
+
+def test_stage1_size_limits_are_reported_for_every_batch(lib):
+    """Sizes whose product with the batch leaves 32 bits (16384 x 16384 tokens of one frame are 2^26 groups of four tokens;
+    times 64 videos, 2^32) are refused by the patch-grid check, on the batched and on the one-video call."""
+    vp, i32, i64, sz, dbl = ctypes.c_void_p, ctypes.c_int, ctypes.c_int64, ctypes.c_size_t, ctypes.c_double
+    tail = [i32, i32, i32, i32, i32, vp, i32, i32, dbl, dbl, i32, i32, i32, i32, vp, vp, vp, vp, i64, i32] + [vp] * 8 + [sz, vp]
+    fake = 0x1000                                   # aligned, never dereferenced: validation fails first
+    for batch in (1, 2, 3, 63, 64):
+        for side in (4097, 16384, 65536):
+            for T in (1, 4):
+                one, many = lib.metok_segment_compress, lib.metok_segment_compress_batched
+                one.argtypes, many.argtypes = [vp] + tail, [i32, vp] + tail
+                args = [fake, 1, T, side, side, 64, fake, 1, 0, 0.5, 0.5, 2, 3, 0, 0, fake, fake, fake, fake, 1 << 40, 1] + [fake] * 8 + [1 << 62, None]
+                assert many(batch, *args) == -1 and b"bad patch grid" in lib.metok_last_error()
+                if batch == 1:
+                    assert one(*args) == -1 and b"bad patch grid" in lib.metok_last_error()
+    # the largest frame that the statistics call itself takes is planned in 64 bits too: refused for its workspace alone
+    seg = lib.metok_segment_events
+    seg.argtypes = [vp, i32, i32, i32, i32, vp, i32, i32, vp, vp, vp, vp, vp, sz, vp]
+    for d in (64, 8192):
+        assert seg(fake, 1, 1, 2 ** 31 - 1, d, None, 1, 0, fake, fake, fake, None, fake, 16, None) == -3
