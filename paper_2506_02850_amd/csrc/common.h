@@ -147,12 +147,13 @@ template <> struct Elem<float> {
     }
 };
 
-// Order-preserving map from float to uint32: a < b  <=>  key(a) < key(b) (-0 == +0, NaNs at the ends).
+// Order-preserving map from float to uint32: a < b  <=>  key(a) < key(b) (-0 == +0, NaNs at the ends).  Keys run from 1 to
+// 0xffffffff, so the difference of two keys is never 0xffffffff.
 __device__ __forceinline__ uint32_t ordered_key(float x) {
-    uint32_t u = __float_as_uint(x);
-    if (u == 0x80000000u) u = 0u;              // -0 and +0 are the same score
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+    const uint32_t u = __float_as_uint(x);
+    return (u & 0x80000000u) ? 0u - u : (u | 0x80000000u);      // -0 negates to the key of +0
 }
+__device__ __forceinline__ float score_of_key(uint32_t key) { return __uint_as_float((key & 0x80000000u) ? key & 0x7fffffffu : 0u - key); }
 
 // Sum over the 16 lanes of a DPP row; every lane of the row receives the total.
 __device__ __forceinline__ float row16_sum(float v) {

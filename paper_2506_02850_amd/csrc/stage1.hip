@@ -527,7 +527,7 @@ __device__ __forceinline__ void plan_video(const PlanArgs1& a, SegmentShared& sh
     }
     if (tid == 0) sh.n_long = 0;
     __syncthreads();
-    auto score_of = [&](int f) { const uint32_t u = fkey[f]; return __uint_as_float((u & 0x80000000u) ? u & 0x7fffffffu : ~u); };
+    auto score_of = [&](int f) { return score_of_key(fkey[f]); };
     // event score: mean (Sec. 3.2.1) or max (Algorithm 1) of the frame scores, frames in index order
     for (int e = tid; e < k; e += kSegThreads) {
         const int lo = sh.start[e], hi = max(lo, static_cast<int>(sh.start[e + 1]));

@@ -1212,7 +1212,8 @@ struct SelectShared {
     uint64_t list[kListCap + kRankStep];    // key and, below it, the complement of the token: larger is kept first
     uint32_t lo, hi;                        // smallest and largest key
     int need[kFastSeg], cnt[kFastSeg], base[kFastSeg + 1], fill[kFastSeg];
-    // a token is kept if key >> shift >= sure, and is a candidate if key >> shift == cand; the last entry is for tokens without a class
+    // a token is kept if key >> shift >= sure, and is a candidate if key >> shift == cand; 0xffffffff is met by no token (keys
+    // count from the smallest one here, and no two differ by that much); the last entry is for tokens without a class
     uint2 rule[kFastSeg + 1];
 };
 

@@ -96,3 +96,53 @@ def test_supplied_scores_of_a_batch_keep_each_video_apart():
         np.testing.assert_array_equal(out["kept_idx"][b, :len(kept)].cpu().numpy(), kept)
         np.testing.assert_array_equal(out["token_seg_out"][b, :len(kept)].cpu().numpy(), seg[b][kept])
         np.testing.assert_array_equal(out["hidden_out"][b, :len(kept)].cpu().numpy(), hidden[b][kept])
+
+
+def ordered_key(scores):
+    """The order of the selection on bit patterns: an unsigned integer that grows with the score (-0 like +0, NaN with the
+    sign bit below -inf, without it above +inf, the further the larger the payload)."""
+    u = scores.view(np.uint32).copy()
+    u[u == 0x80000000] = 0
+    return np.where(u & 0x80000000, ~u, u | 0x80000000).astype(np.int64)
+
+
+# bit patterns: the two NaN at the ends of the order, other NaN, the infinities, the largest and smallest finite values,
+# denormals and both zeros
+PATTERNS = np.array([0xffffffff, 0x7fffffff, 0xffc00000, 0x7fc00000, 0xff800000, 0x7f800000, 0xff7fffff, 0x7f7fffff,
+                     0x80000001, 0x00000001, 0x80000000, 0x00000000, 0xbf800000, 0x3f800000], dtype=np.uint32)
+
+
+@pytest.mark.parametrize("n_seg", [1, 3, 16, 17])                      # the one-launch selection with either digit width; the general path
+@pytest.mark.parametrize("n,top", [(700, 40), (3000, 1500), (13000, 6000)])      # candidates ranked in the list; more equal keys than it holds
+@pytest.mark.parametrize("batch", [1, 3])
+def test_nan_and_infinite_scores_keep_the_order_of_their_bits(n_seg, n, top, batch):
+    # Integers throughout: exactly quota tokens per class, by (key descending, index ascending).  `top` tokens hold the
+    # largest key there is, and the quota of class 0 lies inside them, so that the threshold is that key.
+    B = mk()
+    rng = np.random.default_rng(n + n_seg)
+    bits = PATTERNS[rng.integers(0, len(PATTERNS), size=(batch, n))]
+    seg = rng.integers(0, n_seg, size=(batch, n)).astype(np.int32)
+    for b in range(batch):
+        own = rng.permutation(n)[:top]
+        bits[b, own], seg[b, own] = 0x7fffffff, 0
+        rest = np.setdiff1d(np.arange(n), own)
+        bits[b, rest[bits[b, rest] == 0x7fffffff]] = 0xffffffff
+    scores = bits.view(np.float32)
+    quotas = [[top // 2] + [int(rng.integers(0, int((seg[b] == c).sum()) + 1)) for c in range(1, n_seg)] for b in range(batch)]
+    if n_seg > 2:
+        for q in quotas:
+            q[2] = 0                                                  # a class that keeps nothing beside one whose threshold is the largest key
+    hidden = torch.zeros((batch, n, 4), device="cuda")
+    if batch == 1:
+        out = B.metok_prefill_prune(hidden[0], 0, n, i32(seg[0]), quotas[0], scores=torch.from_numpy(scores[0]).cuda())
+        got = [out["kept_idx"].cpu().numpy()]
+    else:
+        out = B.metok_prefill_prune_batched(hidden, 0, n, i32(seg), quotas, scores=torch.from_numpy(scores).cuda())
+        got = [out["kept_idx"][b, :sum(quotas[b])].cpu().numpy() for b in range(batch)]
+    for b in range(batch):
+        key = ordered_key(scores[b])
+        want = []
+        for c in range(n_seg):
+            members = np.nonzero(seg[b] == c)[0]
+            want.append(members[np.lexsort((members, -key[members]))][:quotas[b][c]])
+        np.testing.assert_array_equal(got[b], np.sort(np.concatenate(want)), err_msg=f"video {b}")
