@@ -1207,8 +1207,8 @@ struct SelectShared {
     int hist[kHistSlots];
     int scan[17];
     uint64_t kept[kFastTiles * 16];         // bit mask of the kept tokens of every 64-token group
-    uint64_t equal[kFastTiles * 16];        // of the tokens equal to a class's threshold (only with more ties than the list holds)
-    int before[kFastTiles * 16];            // kept (or equal) tokens of the groups before this one
+    uint64_t equal[kFastTiles * 16];        // of the tokens equal to their class's threshold (only with more ties than the list holds)
+    int before[kFastTiles * 16];            // kept tokens of the groups before this one
     uint64_t list[kListCap + kRankStep];    // key and, below it, the complement of the token: larger is kept first
     uint32_t lo, hi;                        // smallest and largest key
     int need[kFastSeg], cnt[kFastSeg], base[kFastSeg + 1], fill[kFastSeg];
@@ -1334,8 +1334,12 @@ __device__ __forceinline__ void select_and_index(const FastArgs& a, const float*
     }
     // One pass decides every token but the candidates; those go to a list, class by class, and are ranked against each
     // other under (key descending, index ascending).  More candidates than the list holds are equal keys of whole
-    // classes (shift is 0 then) and are taken in index order below.
+    // classes (shift is 0 then) and are taken in index order below; for that the pass leaves them as a bit mask per group of
+    // 64 tokens, and the tokens' classes as up to four bit planes per group where the histogram was.
     const bool ranked = listed <= kListCap;
+    const int n_planes = 32 - __clz(n_seg - 1);                     // 0 for one class
+    uint64_t* planes = reinterpret_cast<uint64_t*>(sh.hist);
+    static_assert(sizeof(sh.hist) >= kFastTiles * 16 * 4 * sizeof(uint64_t) && kFastSeg <= 16, "four planes of every group fit the histogram");
     if (tid == 0) {
         int run = 0;
         for (int c = 0; c < n_seg; ++c) { sh.base[c] = run; run += sh.cnt[c]; }
@@ -1355,9 +1359,20 @@ __device__ __forceinline__ void select_and_index(const FastArgs& a, const float*
             for (int u = 0; u < kStep; ++u) {
                 const uint32_t d = key[i0 + u] >> shift;
                 const bool has_class = class_of(i0 + u) != kFastSeg;
-                const unsigned long long m = __ballot(has_class && d >= rule[u].x);
-                any |= __ballot(has_class && d == rule[u].y);
+                const unsigned long long m = __ballot(has_class && d >= rule[u].x), cand = __ballot(has_class && d == rule[u].y);
+                any |= cand;
                 if (lane == 0) sh.kept[(i0 + u) * 16 + wave] = m;
+                if (!ranked) {
+                    const int g = (i0 + u) * 16 + wave;
+                    if (lane == 0) sh.equal[g] = cand;
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) {
+                        if (b < n_planes) {
+                            const unsigned long long plane = __ballot((class_of(i0 + u) >> b) & 1u);
+                            if (lane == 0) planes[4 * g + b] = plane;
+                        }
+                    }
+                }
             }
             if (ranked && any) {
 #pragma unroll
@@ -1372,11 +1387,6 @@ __device__ __forceinline__ void select_and_index(const FastArgs& a, const float*
         }
     }
     __syncthreads();
-    auto scan_groups = [&](const uint64_t* groups, int* total) {
-        const int ex = block_exclusive_scan(tid < n_tiles * 16 ? __popcll(groups[tid]) : 0, sh.scan, total);
-        if (tid < n_tiles * 16) sh.before[tid] = ex;
-        __syncthreads();
-    };
     if (ranked) {
         if (tid < sh.base[n_seg]) {
             int c = 0;
@@ -1398,30 +1408,47 @@ __device__ __forceinline__ void select_and_index(const FastArgs& a, const float*
         }
         __syncthreads();
     } else {
-        for (int c = 0; c < n_seg; ++c) {
-            if (sh.cnt[c] == 0) continue;
-            const uint32_t tau = sh.rule[c].y;
-            fresh();
+        // One wave per class, a lane per run of neighbouring groups: the equal keys of the class before a lane's groups
+        // by a scan over the lanes, then the lane takes its own as long as there is room.  (A pass of the workgroup over all
+        // keys and a block scan per class took 4 us a class.)
+        if (wave < n_seg && sh.cnt[wave] > 0) {
+            constexpr int kPer = K / 4;                             // K * 16 groups on 64 lanes
+            const int n_groups = n_tiles * 16;
+            auto members = [&](int g) {
+                uint64_t m = sh.equal[g];
 #pragma unroll
-            for (int i = 0; i < K; ++i) {
-                if (i < n_tiles) {
-                    const unsigned long long m = __ballot(class_of(i) == static_cast<uint32_t>(c) && key[i] == tau);
-                    if (lane == 0) sh.equal[i * 16 + wave] = m;
-                }
+                for (int b = 0; b < 4; ++b)
+                    if (b < n_planes) m &= ((wave >> b) & 1) ? planes[4 * g + b] : ~planes[4 * g + b];
+                return m;
+            };
+            int mine = 0;
+            for (int u = 0; u < kPer; ++u) {
+                const int g = lane * kPer + u;
+                if (g < n_groups) mine += __popcll(members(g));
             }
-            __syncthreads();
-            int total = 0;
-            scan_groups(sh.equal, &total);
-            if (tid < n_tiles * 16) {
-                uint64_t left = sh.equal[tid], take = 0;
-                for (int room = sh.need[c] - sh.before[tid]; room > 0 && left; --room) { take |= left & (~left + 1); left &= left - 1; }
-                sh.kept[tid] |= take;
+            int incl = mine;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const int up = __shfl_up(incl, off, 64);
+                if (lane >= off) incl += up;
             }
-            __syncthreads();
+            int room = sh.need[wave] - (incl - mine);
+            for (int u = 0; u < kPer && room > 0; ++u) {
+                const int g = lane * kPer + u;
+                if (g >= n_groups) break;
+                uint64_t take = members(g);
+                const int n = __popcll(take);
+                for (int drop = n - room; drop > 0; --drop) take &= ~(1ull << (63 - __clzll(static_cast<long long>(take))));      // the last ones
+                room -= n;
+                if (take) atomicOr(reinterpret_cast<unsigned long long*>(&sh.kept[g]), static_cast<unsigned long long>(take));
+            }
         }
+        __syncthreads();
     }
     int total = 0;
-    scan_groups(sh.kept, &total);
+    const int before = block_exclusive_scan(tid < n_tiles * 16 ? __popcll(sh.kept[tid]) : 0, sh.scan, &total);
+    if (tid < n_tiles * 16) sh.before[tid] = before;
+    __syncthreads();
     asm volatile("" : "+s"(n_tiles));
     const int total_keep = a.keeps.n[blockIdx.z];
 #pragma unroll 8
