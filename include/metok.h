@@ -494,7 +494,7 @@ enum {
     METOK_TRACE_ROW_STATS = 6,          /* attention pass 1 (softmax statistics) */
     METOK_TRACE_COL_SUMS = 7,           /* attention pass 2 (probability mass per key) */
     METOK_TRACE_SELECT = 8,
-    METOK_TRACE_WRITE_INDEX = 9,        /* the same launch as METOK_TRACE_SELECT with up to 16 classes and 40960 tokens */
+    METOK_TRACE_WRITE_INDEX = 9,        /* the same launch as METOK_TRACE_SELECT with up to 16 classes and 40960 tokens (one video of 5 to 16 classes: 22528) */
     METOK_TRACE_GATHER_ROWS = 10,       /* hidden-state compaction */
     METOK_TRACE_MOVE_ROWS = 11          /* in-place row mover (KV compaction, in-place hidden compaction) */
 };

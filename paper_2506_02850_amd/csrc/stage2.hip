@@ -5,11 +5,11 @@
 //   merge_stats_kernel   merges the per-workgroup (max, sum) pairs into one normaliser per row
 //   col_sums_kernel      MFMA pass 2 over the visual keys: recomputes the logits and adds up the
 //                        probabilities of every visual key over the rows of a workgroup
-//   narrow_row_stats_kernel, narrow_col_sums_kernel   the two passes for at most 64 query rows per kv head 
+//   narrow_row_stats_kernel, narrow_col_sums_kernel   the two passes for at most 64 query rows per kv head
 //   score_select_kernel  score_j = w_e(j) * mean probability per tile; the workgroup that arrives last selects per class
 //                        (radix select) and writes the ascending index list
-//   prepare_kernel, select_kernel, write_index_kernel   the same steps for more than 16 classes or more than 40960
-//                        tokens: scores; one workgroup per class walks all keys; one workgroup per 1024-token tile
+//   prepare_kernel, select_kernel, write_index_kernel   the same steps where that one workgroup is no match for them (see
+//                        one_launch_selection): scores; one workgroup per class walks all keys; one workgroup per 1024-token tile
 //                        applies the keep rule and writes the index list and the carried metadata
 //   gather_rows_kernel   compaction of the hidden states (hidden_index_kernel + the row mover of stage 3 when
 //                        the output is the input buffer) and, after score_select_kernel, of the carried metadata
@@ -1093,7 +1093,8 @@ __global__ __launch_bounds__(kIdxThreads) void write_index_kernel(
 }
 
 // ---------------------------------------------------------------------------------------------
-// Fast selection path: at most kFastSeg retention classes and at most kFastTiles tiles of 1024 tokens, one launch.
+// Fast selection path: at most kFastSeg retention classes and at most kFastTiles tiles of 1024 tokens (fewer for one video
+// of many classes, see one_launch_selection), one launch.
 //   every workgroup     scores of its tokens from the partial column sums (skipped when scores are given)
 //   the workgroup that arrives last at an atomic counter (it is the one that knows every other workgroup's scores are
 //   complete; nobody waits for anybody) selects for the video: all keys in registers, per class a histogram of the
@@ -1107,8 +1108,7 @@ __global__ __launch_bounds__(kIdxThreads) void write_index_kernel(
 // Measured against the launches it replaces (score + histogram, candidates, index list; with 5 to 16 classes the general
 // path's three): 2243 tokens 28.5 -> 9.9 us, 4507 tokens with 40 partial sums each 33 -> 12.4 us, 18432 tokens in 13
 // classes 31 -> 20 us, eight videos of 36864 tokens 46 -> 30 us.  One workgroup walking 36 tiles is what is left there
-// (0.6 us a tile: its loads, LDS atomics and ballots); more than 40 tiles or 16 classes take the general path, whose
-// workgroups (one per class) share the work of many classes.
+// (0.6 us a tile: its loads, LDS atomics and ballots).
 // ---------------------------------------------------------------------------------------------
 constexpr int kFastSeg = 16;
 constexpr int kFastTiles = kSelCache;
@@ -1116,6 +1116,17 @@ constexpr int kSplitParts = 8;              // from so many partial sums per tok
 constexpr int kHistWords = 8192;            // histogram bins of all classes together: 2048 per class up to 4 classes, else 512
 constexpr int kListCap = 512;               // keys of the threshold buckets that are ranked against each other
 constexpr int kRankStep = 8;                // list entries read from LDS together
+
+// Which selection a call takes.  One workgroup per video walks all tiles where the general path has one per class, so with
+// more than four classes the line depends on the tiles: a level of one video with 28 / 4 heads x 64 queries in 13 classes
+// takes 50.5 us here and 58.8 on the general path at 12288 tokens, 63.8 and 67.3 at 20480, 71.6 and 71.9 at 24576, 83.2 and
+// 79.8 at 32768, 94.0 and 88.6 at 40960; scores within 1 % beside one large one, given, need more digits here: 31.0 and 30.0
+// at 20480, 36.4 and 31.1 at 24576.  The general path launches its selection per video: two or more videos are faster here
+// at every size (eight of 36864 tokens in 16 classes, scores given: 37 and 190 us).
+constexpr int kFastTilesManyClasses = 22;
+static bool one_launch_selection(int batch, int n_seg, int n_tiles) {
+    return n_seg <= kFastSeg && n_tiles <= (n_seg <= 4 || batch > 1 ? kFastTiles : kFastTilesManyClasses);
+}
 
 struct FastSel {
     uint32_t arrive;                        // cleared before the kernel that counts on it
@@ -1850,7 +1861,7 @@ static int prune_impl(int batch, const void* hidden, int64_t S, int D, int dtype
     const int64_t ws_video = static_cast<int64_t>(video_workspace_bytes(batch, S, q_text ? Hq : 0, q_text ? Hkv : 0, q_text ? dh : 0,
                                                                         q_text ? Tq : 0, n_vis, dtype));
     const int n_tiles = select_tiles(n_vis);
-    const bool fast = n_seg <= kFastSeg && n_tiles <= kFastTiles;       // else the general one-workgroup-per-class select
+    const bool fast = one_launch_selection(batch, n_seg, n_tiles);      // else the general one-workgroup-per-class select
     if (q_text) {
         if (!k_all || !aligned16(q_text) || !aligned16(k_all)) return fail(METOK_ERR_INVALID_ARG, "q_text / k_all NULL or misaligned");
         if (Hq < 1 || Hkv < 1 || Hq % Hkv) return fail(METOK_ERR_INVALID_ARG, "Hq = %d must be a positive multiple of Hkv = %d", Hq, Hkv);

@@ -146,3 +146,26 @@ def test_nan_and_infinite_scores_keep_the_order_of_their_bits(n_seg, n, top, bat
             members = np.nonzero(seg[b] == c)[0]
             want.append(members[np.lexsort((members, -key[members]))][:quotas[b][c]])
         np.testing.assert_array_equal(got[b], np.sort(np.concatenate(want)), err_msg=f"video {b}")
+
+
+@pytest.mark.parametrize("batch,n,n_seg", [(1, 22528, 16), (1, 22529, 16), (1, 22529, 4), (2, 40960, 16), (2, 40961, 5), (2, 3000, 17)])
+@pytest.mark.parametrize("kind", ["spread", "ties"])
+def test_both_sides_of_the_line_between_the_two_selections(batch, n, n_seg, kind):
+    B = mk()
+    rng = np.random.default_rng(n + n_seg)
+    scores = np.stack([scores_of(kind, n, rng) for _ in range(batch)])
+    seg = rng.integers(0, n_seg, size=(batch, n)).astype(np.int32)
+    quotas = [[int(rng.integers(0, int((seg[b] == c).sum()) + 1)) for c in range(n_seg)] for b in range(batch)]
+    hidden = rng.standard_normal((batch, n + 1, 4)).astype(np.float32)
+    dev = torch.from_numpy(hidden).cuda()
+    if batch == 1:
+        out = B.metok_prefill_prune(dev[0], 1, n, i32(seg[0]), quotas[0], scores=torch.from_numpy(scores[0]).cuda())
+        out = {name: t[None] for name, t in out.items()}
+    else:
+        out = B.metok_prefill_prune_batched(dev, 1, n, i32(seg), quotas, scores=torch.from_numpy(scores).cuda())
+    torch.cuda.synchronize()
+    for b in range(batch):
+        kept = O.segmented_topk(scores[b], seg[b], quotas[b])
+        np.testing.assert_array_equal(out["kept_idx"][b, :len(kept)].cpu().numpy(), kept)
+        np.testing.assert_array_equal(out["token_seg_out"][b, :len(kept)].cpu().numpy(), seg[b][kept])
+        np.testing.assert_array_equal(out["hidden_out"][b, :1 + len(kept)].cpu().numpy(), O.compact_hidden(hidden[b], 1, n, kept))
