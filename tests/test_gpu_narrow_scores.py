@@ -1,6 +1,7 @@
 """Attention scores with at most 64 query rows per kv head (the narrow kernels) and their neighbours, against the CPU oracle:
-row counts at the edges of the 16-row blocks, keys at the edges of the 16-key subtiles and of the eight waves, both softmax
-readings, a prefix, and logits so far apart that the sums relative to the first keys leave the range of float."""
+row counts at the edges of the 16-row blocks, keys at the edges of the 16-key subtiles and of the eight waves, several subtiles
+per wave, both softmax readings, a prefix, logits so far apart that a wave's sums relative to its first keys leave the range of
+float, and keys that are not finite."""
 import numpy as np
 import pytest
 import torch
@@ -43,7 +44,7 @@ def test_query_rows_of_the_shared_stage_kernels(dtype, dh, Hq, Hkv, Tq, frames, 
 
 @pytest.mark.parametrize("Hq,Tq", [(2, 20), (2, 64), (14, 32)])          # narrow with two and four blocks; the shared-stage kernels
 def test_logits_far_above_the_first_keys(Hq, Tq):
-    # later keys lift the logits by hundreds (log2): a sum relative to the first subtile would overflow
+    # later keys lift the logits by hundreds (log2): the partial sums that are merged are that far apart
     B = mk()
     rng = np.random.default_rng(Tq)
     n, dh, Hkv, text = 700, 64, 2, Tq
@@ -59,3 +60,81 @@ def test_logits_far_above_the_first_keys(Hq, Tq):
     want = O.text_to_visual_attention(q, k, 0, n, 0)
     assert_rel(out["scores"].cpu().numpy(), want, RTOL["bf16"], "scores", scale=want.max())
     assert want[600] > 0.9
+
+
+# 32 kv heads share the 256 workgroup slots: 8 workgroups of 256 keys each, so a wave of the narrow kernels walks two 16-key
+# subtiles (t = 0, 1) 128 keys apart in a 2048-key sequence, and three in a longer one
+MANY_KV_HEADS = 32
+
+
+@pytest.mark.parametrize("dtype,dh,Tq", [("bf16", 64, 5), ("bf16", 128, 20), ("bf16", 32, 64), ("f32", 64, 31), ("f32", 32, 7)])
+@pytest.mark.parametrize("tokens,vis_start,mode", [(2000, 0, 0), (2900, 40, 0), (2900, 40, 1)])
+def test_several_subtiles_per_wave(dtype, dh, Tq, tokens, vis_start, mode):
+    layer = make_layer(4500 + dh + Tq, 10, tokens // 10, 4, Tq + 3, 16, MANY_KV_HEADS, MANY_KV_HEADS, dh, dtype, vis_start=vis_start)
+    seg = np.zeros(layer.n_vis, dtype=np.int32)
+    quotas = [layer.n_vis // 2]
+    got, q = run_prune(layer, seg, quotas, Tq=Tq, score_mode=mode)
+    check_prune(layer, seg, quotas, got, q, score_mode=mode)
+
+
+@pytest.mark.parametrize("up", [True, False])
+@pytest.mark.parametrize("dtype,dh,Tq", [("bf16", 64, 9), ("bf16", 64, 20), ("bf16", 64, 64), ("bf16", 128, 40), ("f32", 32, 9), ("f32", 64, 33)])
+def test_sums_that_leave_the_range_of_float(dtype, dh, Tq, up):
+    """Keys alternate between low and high logits every 128 keys: relative to the largest logit of its first subtile, the
+    second subtile of every wave adds terms beyond 2^127 (`up`; the wave starts over with a running maximum) or far below the
+    smallest float (the other way round).  A wave that kept an infinite or lost sum would spoil every row's normaliser."""
+    B = mk()
+    rng = np.random.default_rng(dh + Tq)
+    H, S = MANY_KV_HEADS, 2048
+    n = S - Tq
+    q = np.abs(rng.standard_normal((H, Tq, dh))).astype(np.float32) + np.float32(0.1)
+    k = (0.3 * rng.standard_normal((H, S, dh))).astype(np.float32)
+    k[:, (np.arange(S) // 128) % 2 == (1 if up else 0)] += np.float32(1600 / dh)
+    if dtype == "bf16":
+        q, k = synth.bf16_round(q), synth.bf16_round(k)
+    # the premise, in log2 units: [head, query, workgroup, subtile t, wave, key of the subtile]
+    logits = np.matmul(q.astype(np.float64), k.astype(np.float64).transpose(0, 2, 1)) / np.sqrt(dh)
+    tops = (logits * 1.4426950408889634).reshape(H, Tq, S // 256, 2, 8, 16).max(axis=5)
+    jump = tops[:, :, :, 1] - tops[:, :, :, 0]
+    assert (jump > 130).all() if up else (jump < -130).all()
+    hidden = torch.zeros((S, 8), dtype=torch.bfloat16 if dtype == "bf16" else torch.float32, device="cuda")
+    out = B.metok_prefill_prune(hidden, 0, n, i32(np.zeros(n)), [n // 2], q_text=synth.to_torch(q, dtype, "cuda"),
+                                k_all=synth.to_torch(k, dtype, "cuda"))
+    torch.cuda.synchronize()
+    got, want = out["scores"].cpu().numpy().astype(np.float64), O.text_to_visual_attention(q, k, 0, n, 0)
+    # a logit is dh products added in fp32: at most dh 2^-24 of its size off, once in the term and once in the normaliser;
+    # the sums and the exponentials as elsewhere (RTOL); below 2^-126 a probability may be zero
+    tol = RTOL[dtype] + 2 * dh * 2.0 ** -24 * np.abs(logits).max()
+    assert np.isfinite(got).all()
+    assert (np.abs(got - want) <= tol * want + 2.0 ** -126).all(), float((np.abs(got - want) / (want + 1e-30)).max())
+
+
+@pytest.mark.parametrize("Hq,Tq", [(4, 20), (4, 64), (28, 10), (28, 64)])          # narrow; the shared-stage kernels with one and two blocks per wave
+def test_keys_that_are_not_finite(Hq, Tq):
+    """A key with a NaN has a NaN score, and the rows of its kv head, whose normaliser it spoils, add nothing to the other
+    keys; a key whose logits are -inf gets no probability and leaves the rest alone; the selection keeps its order."""
+    from tests.test_gpu_selection_paths import ordered_key
+    B = mk()
+    rng = np.random.default_rng(Hq + Tq)
+    Hkv, dh, n = 4, 64, 900
+    group, S = Hq // Hkv, n + Tq
+    q = synth.bf16_round(np.abs(rng.standard_normal((Hq, Tq, dh))).astype(np.float32) + np.float32(0.1))
+    k = synth.bf16_round((0.2 * rng.standard_normal((Hkv, S, dh))).astype(np.float32))
+    bad = k.copy()
+    bad[1, 50, 3] = np.nan
+    bad[2, 70, 5] = -np.inf
+    hidden = torch.zeros((S, 8), dtype=torch.bfloat16, device="cuda")
+    out = B.metok_prefill_prune(hidden, 0, n, i32(np.zeros(n)), [n // 2], q_text=synth.to_torch(q, "bf16", "cuda"),
+                                k_all=synth.to_torch(bad, "bf16", "cuda"))
+    torch.cuda.synchronize()
+    scores = out["scores"].cpu().numpy()
+    k[2, 70] = np.float32(-1e5)                                       # probability 0 in 64 bits too
+    want = np.zeros(n)
+    for h in range(Hkv):
+        if h != 1:
+            want += O.text_to_visual_attention(q[h * group:(h + 1) * group], k[h:h + 1], 0, n, 0) / Hkv
+    others = np.arange(n) != 50
+    assert np.isnan(scores[50])
+    assert_rel(scores[others], want[others], RTOL["bf16"], "scores")
+    order = np.lexsort((np.arange(n), -ordered_key(scores)))
+    np.testing.assert_array_equal(out["kept_idx"].cpu().numpy(), np.sort(order[:n // 2]))
