@@ -16,7 +16,7 @@ def test_selection_and_compaction_random_cases():
     rng = np.random.default_rng(123)
     for it in range(80):
         n = int(rng.integers(1, 7000))
-        n_seg = int(rng.integers(1, 6))
+        n_seg = int(rng.integers(1, 6)) if it % 5 else int(rng.integers(15, 25))       # both selection paths
         seg = rng.integers(0, n_seg, size=n).astype(np.int32)
         kind = it % 4
         if kind == 0:

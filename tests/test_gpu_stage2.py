@@ -300,3 +300,17 @@ def test_partial_overlap_and_too_wide_rows_are_refused_in_place():
     with pytest.raises(B.MetokError) as e:
         B.metok_prefill_prune(wide, 0, 8, seg[:8], [4], scores=scores[:8], hidden_out=wide[:8])
     assert e.value.code == -2
+
+
+@pytest.mark.parametrize("tokens,n_seg", [(1, 17), (70, 17), (300, 64), (2600, 5)])
+def test_general_selection_path_from_the_attention_on(tokens, n_seg):
+    # more than 16 classes (or, 16 x 2600, more tokens than the one-launch selection takes): the scores and event weights of
+    # the preparing kernel, single calls
+    rng = np.random.default_rng(tokens + n_seg)
+    layer = make_layer(5600 + tokens, 16, tokens, 6, 9, 16, 4, 2, 32, "bf16", vis_start=3)
+    seg = rng.integers(0, n_seg, size=layer.n_vis).astype(np.int32)
+    quotas = [int(rng.integers(0, int((seg == c).sum()) + 1)) for c in range(n_seg)]
+    orig = rng.permutation(layer.n_vis).astype(np.int32)
+    for use_weight in (True, False):
+        got, q = run_prune(layer, seg, quotas, use_weight=use_weight, orig_idx=orig)
+        check_prune(layer, seg, quotas, got, q, use_weight=use_weight, orig_idx=orig)

@@ -106,7 +106,7 @@ def test_batched_selection_on_supplied_scores_general_path_and_ties():
     rng = np.random.default_rng(8)
     B, n, D = 4, 5000, 8
     hidden = rng.standard_normal((B, n + 3, D)).astype(np.float32)
-    for n_seg in (3, 9):                                            # fast selection / one workgroup per class
+    for n_seg in (3, 9, 17):                                        # one-launch selection with either digit width / one workgroup per class
         seg = rng.integers(0, n_seg, size=(B, n)).astype(np.int32)
         scores = np.round(rng.standard_normal((B, n)), 1).astype(np.float32)          # heavy exact ties
         scores[2] = 0.25                                            # one video with all scores equal
@@ -121,6 +121,20 @@ def test_batched_selection_on_supplied_scores_general_path_and_ties():
             np.testing.assert_array_equal(out["kept_idx"][b, :k].cpu().numpy(), kept)
             np.testing.assert_array_equal(out["hidden_out"][b, :3 + k].cpu().numpy(), O.compact_hidden(hidden[b], 2, n, kept))
             np.testing.assert_array_equal(out["token_seg_out"][b, :k].cpu().numpy(), seg[b][kept])
+
+
+@pytest.mark.parametrize("in_place", [False, True])
+@pytest.mark.parametrize("tokens,n_seg", [(60, 17), (60, 64), (2600, 3)])
+def test_batched_general_path_from_the_attention_on(tokens, n_seg, in_place):
+    # more than 16 classes, or (16 x 2600) more than 40960 tokens: scores written by the preparing kernel with the event
+    # weights, one selecting launch per video, one index launch for the batch, every video at its own offset
+    rng = np.random.default_rng(tokens + n_seg)
+    layers = layers_of([5100, 5200, 5300], 16, tokens, 5, 9, 16, 4, 2, 32, "bf16", vis_start=3)
+    segs = [rng.integers(0, n_seg, size=l.n_vis).astype(np.int32) for l in layers]
+    quotas = [[int(rng.integers(0, int((s == c).sum()) + 1)) for c in range(n_seg)] for s in segs]
+    orig = [rng.permutation(l.n_vis).astype(np.int32) for l in layers]
+    for b, (got, q) in enumerate(run_batched(layers, segs, quotas, orig=orig, in_place=in_place)):
+        check_prune(layers[b], segs[b], quotas[b], got, q, orig_idx=orig[b])
 
 
 def test_batched_in_place():
