@@ -1,13 +1,14 @@
 """Stage 1 where its kernels change shape: rows at the edges of the chunk counts per lane, frame counts at the edges of the
-ranking and reduction splits, every pooling stride that has its own window code, and the event ids of uniformly pooled rows
-on both sides of the planning workgroup's limit.  Compared with the CPU oracle with the tolerances of tests/parity.py and,
-bit for bit, with the two-call path."""
+ranking and reduction splits, thousands of frames in one call, every pooling stride that has its own window code, the event
+ids of uniformly pooled rows on both sides of the planning workgroup's limit, and a frame that is not finite.  Compared with
+the CPU oracle with the tolerances of tests/parity.py and, bit for bit, with the two-call path."""
 import numpy as np
 import pytest
 import torch
 
 from oracle import metok_oracle as O
 from paper_2506_02850_amd import synth
+from tests.parity import RTOL, assert_rel, frame_score_scale
 from tests.test_gpu_stage1_one_call import check, mk
 
 pytestmark = pytest.mark.gpu
@@ -71,3 +72,87 @@ def test_few_or_many_pooling_workgroups_per_frame(T, grid, d, s1, s2):
     # 1 chunk, 128, 2880 and 2873 chunks at the smallest stride: one workgroup per frame, one, twelve and twelve
     v = synth.planted_video(9500 + T, T, grid, d, 3, 1, T, 0.2 / d ** 0.5, "bf16")
     check(v, grid, 3, 0.5, 0.4, s1, s2, "bf16")
+
+
+def tied_video(T, seed):
+    """Frames drawn from four vectors: most adjacent pairs tie exactly in their cosine, most frames in their text score."""
+    rng = np.random.default_rng(seed)
+    basis = rng.standard_normal((4, 4, 16)).astype(np.float32)
+    return basis[rng.integers(0, 4, size=T)], rng.standard_normal(16).astype(np.float32)
+
+
+@pytest.mark.parametrize("T,k", [(2048, 5), (2049, 5), (5000, 1), (3000, 2999), (4100, 1500), (8192, 61), (8192, 8192)])
+@pytest.mark.parametrize("uniform", [False, True])      # three strides after a pass of statistics; stride 2 in one pass
+def test_long_videos_in_one_call(T, k, uniform):
+    # boundaries by radix select, key frames of events and key events by bisection above 1024, then the plan in the same
+    # workgroup and the same LDS; the totals of 64 workgroups over several rounds of frames
+    B = mk()
+    feats_np, text_np = tied_video(T, T + k)
+    feats, text = torch.from_numpy(feats_np).cuda(), torch.from_numpy(text_np).cuda()
+    alpha, s1, s2 = (1.0, 2, 2) if uniform else (0.5, 1, 2)
+    one = B.metok_segment_compress(feats, 2, 2, k, text, alpha, 0.45, s1, s2)
+    torch.cuda.synchronize()
+    sim, score = one["sim"].cpu().numpy(), one["frame_score"].cpu().numpy()
+    assert_rel(sim, O.adjacent_frame_cosine(feats_np.astype(np.float64)), RTOL["f32"], "sim", scale=1.0)
+    assert_rel(score, O.frame_text_score(feats_np, text_np), RTOL["f32"], "frame_score", scale=frame_score_scale(feats_np, text_np))
+    # decisions on the GPU's own values, exactly
+    es, fe = O.event_boundaries(sim, k)
+    np.testing.assert_array_equal(one["event_start"].cpu().numpy(), es)
+    np.testing.assert_array_equal(one["frame_event"].cpu().numpy(), fe)
+    ref = O.compress_encoder_tokens(feats_np, (2, 2), None, es, alpha, 0.45, s1, s2, frame_score=score.astype(np.float64))
+    for name in ("event_is_key", "frame_is_key", "frame_stride", "frame_offsets"):
+        np.testing.assert_array_equal(one[name].cpu().numpy(), ref[name], err_msg=name)
+    M = int(ref["frame_offsets"][-1])
+    np.testing.assert_array_equal(one["token_event"][:M].cpu().numpy(), ref["token_event"])
+    np.testing.assert_allclose(one["out_tokens"][:M].cpu().numpy(), ref["tokens"], rtol=1e-5, atol=1e-6)
+    if uniform:
+        return
+    # the two calls, bit for bit
+    seg = B.metok_segment_events(feats, k, text)
+    two = B.metok_compress_encoder_tokens(feats, 2, 2, seg["event_start"], alpha, 0.45, s1, s2, frame_score=seg["frame_score"])
+    torch.cuda.synchronize()
+    for name in ("sim", "event_start", "frame_event", "frame_score"):
+        assert torch.equal(one[name], seg[name]), name
+    for name in ("event_is_key", "frame_is_key", "frame_stride", "frame_offsets", "event_score"):
+        assert torch.equal(one[name], two[name]), name
+    assert torch.equal(one["out_tokens"][:M], two["out_tokens"][:M]) and torch.equal(one["token_event"][:M], two["token_event"][:M])
+
+
+@pytest.mark.parametrize("T,k", [(2049, 3), (4100, 1500)])
+def test_long_videos_of_a_batch(T, k):
+    B = mk()
+    videos = [tied_video(T, 10 * T + b) for b in range(3)]
+    feats = [torch.from_numpy(f).cuda() for f, _ in videos]
+    texts = [torch.from_numpy(t).cuda() for _, t in videos]
+    got = B.metok_segment_compress_batched(torch.stack(feats), 2, 2, k, torch.stack(texts), 0.5, 0.45, 1, 2)
+    for b in range(3):
+        one = B.metok_segment_compress(feats[b], 2, 2, k, texts[b], 0.5, 0.45, 1, 2)
+        torch.cuda.synchronize()
+        M = int(one["frame_offsets"][-1])
+        for name, t in one.items():
+            rows = slice(0, M) if name in ("out_tokens", "token_event") else slice(None)
+            assert torch.equal(got[name][b][rows], t[rows]), (b, name)
+
+
+@pytest.mark.parametrize("T", [20, 600, 3000])          # boundaries ranked by several threads, by one, by radix select
+def test_a_frame_that_is_not_finite(T):
+    """Two pairs without a similarity (NaN): the boundaries are the k - 1 lowest keys of what the kernel wrote, in the order of
+    the bits, the events cover the video, and every frame gets its rows."""
+    from tests.test_gpu_selection_paths import ordered_key
+    B = mk()
+    feats_np, text_np = tied_video(T, T)
+    feats_np = feats_np.copy()
+    feats_np[7, 1, 3] = np.nan
+    k = 6
+    got = B.metok_segment_compress(torch.from_numpy(feats_np).cuda(), 2, 2, k, torch.from_numpy(text_np).cuda(), 0.5, 0.45, 1, 2)
+    torch.cuda.synchronize()
+    sim = got["sim"].cpu().numpy()
+    assert np.isnan(sim[6:8]).all() and np.isfinite(np.delete(sim, (6, 7))).all()
+    cuts = np.sort(np.lexsort((np.arange(T - 1), ordered_key(sim)))[:k - 1]) + 1
+    np.testing.assert_array_equal(got["event_start"].cpu().numpy(), np.concatenate([[0], cuts, [T]]))
+    stride, offsets = got["frame_stride"].cpu().numpy(), got["frame_offsets"].cpu().numpy()
+    assert set(np.unique(stride)) <= {1, 2}
+    np.testing.assert_array_equal(np.diff(offsets), np.where(stride == 1, 4, 1))
+    starts = got["event_start"].cpu().numpy()
+    for a, b in zip(starts[:-1], starts[1:]):
+        assert int(got["frame_is_key"][a:b].sum()) == int(np.ceil(0.45 * (b - a) - 1e-9))
