@@ -1233,7 +1233,8 @@ extern "C" int metok_compress_encoder_tokens(const void* feats, int dtype, int T
 // ---------------------------------------------------------------------------------------------
 // Stage 1 in one call.  When every frame is pooled with stride 2 whatever the segmentation decides
 // (all four strides of the adaptive rule are 2, even grid), the statistics and the pooled tokens come
-// out of ONE pass over V; otherwise the two calls above run back to back (two passes over V).
+// out of ONE pass over V; otherwise V is read twice, by the kernels of the two calls above: statistics, segmentation with
+// the plan in one launch, pooling (METOK_SIM_POOLED: the two calls themselves, one video after the other).
 // ---------------------------------------------------------------------------------------------
 // one-pass path: one partial triple per pooling window and frame, then the per-frame arrays of the small kernels
 static size_t fused_part_bytes(int T, int grid_h, int grid_w) {
@@ -1369,8 +1370,8 @@ static int segment_compress_impl(int batch, const void* feats, int dtype, int T,
         return check_launch("pool");
     }
     if (!fused) {
-        // a single video, or the reading of Eq. 4 that needs the extra pass over token means: the two stage-1 calls
-        // (statistics, then pooling with the strides of Algorithm 1), one video after the other
+        // the reading of Eq. 4 that needs the extra pass over token means: the two stage-1 calls (statistics, then pooling
+        // with the strides of Algorithm 1), one video after the other
         const size_t in_es = dtype_size(dtype), out_es = dtype_size(out_dtype);
         for (int b = 0; b < batch; ++b) {
             auto at = [&](auto* ptr, int64_t elems) { return ptr ? ptr + static_cast<int64_t>(b) * elems : ptr; };

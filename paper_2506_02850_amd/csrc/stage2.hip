@@ -333,7 +333,7 @@ __global__ __launch_bounds__(kScoreThreads) void row_stats_kernel(const T* __res
         // leading stages whose 64 keys are all visible to every query
         // The choice is the same for every wave of the workgroup (all waves must meet at the same barriers):
         // with at least one row block per wave, waves that own a single block run the second chain on the
-        // zero fragments load_qfrag gave them; its statistics belong to a padding row and are ignored.
+        // zero fragments QueryRows::to_fragments left them; its statistics belong to a padding row and are ignored.
         int n_fast = 0;
         if (nrb >= kScoreWaves) {
             const int64_t f = (full_end - kb) / Stage::kKeys;
@@ -1105,9 +1105,10 @@ __global__ __launch_bounds__(kIdxThreads) void write_index_kernel(
 // What bounds it is latency, not work: a chain of about ten barriers and two memory round trips.  The digits start at
 // the smallest key because attention scores share their leading bits: a histogram of the top 11 bits of the key itself
 // left a third of the tokens in one bucket (and its atomics on one address), the shifted one leaves 20 to 200.
-// Measured against the launches it replaces (score + histogram, candidates, index list; with 5 to 16 classes the general
-// path's three): 2243 tokens 28.5 -> 9.9 us, 4507 tokens with 40 partial sums each 33 -> 12.4 us, 18432 tokens in 13
-// classes 31 -> 20 us, eight videos of 36864 tokens 46 -> 30 us.  One workgroup walking 36 tiles is what is left there
+// Measured in kernel traces against the launches it replaces (score + histogram, candidates, index list; with 5 to 16
+// classes the general path's three): 2243 tokens 30.0 -> 10.1 us, 4507 tokens with 40 partial sums each 33.4 -> 12.0 us,
+// 18432 tokens in 13 classes 30.1 -> 19.2 us, eight videos of 36864 tokens 43.5 -> 31.1 us with about 20 candidates and
+// 39 -> 34.5 us with about 200 (more of them in one step to rank).  One workgroup walking 36 tiles is what is left there
 // (0.6 us a tile: its loads, LDS atomics and ballots).
 // ---------------------------------------------------------------------------------------------
 constexpr int kFastSeg = 16;
@@ -1610,13 +1611,14 @@ static size_t select_count_bytes(int n_vis) {
     return round_up(static_cast<size_t>(METOK_MAX_SEGMENTS) * select_tiles(n_vis) * sizeof(int32_t), 256);
 }
 static size_t select_general_bytes(int n_vis) { return 2 * select_count_bytes(n_vis) + METOK_MAX_SEGMENTS * 2 * sizeof(uint32_t); }
-// then the fast path's state.  The reserve is larger than FastSel needs today: the size of a workspace is part of the
+// then the fast path's state.  The reserve is larger than FastSel needs, and the two words per token behind it are used by
+// no kernel: they held the histograms and candidate lists of an earlier selection.  The size of a workspace is part of the
 // interface (it also decides which shapes metok_prefill_prune_static takes), so it stays what it has been.
 constexpr size_t kFastReserve = 34560;
 static_assert(sizeof(FastSel) <= kFastReserve, "the fast path's state outgrew its reserve");
 static size_t select_bytes(int n_vis) {
-    const size_t cand = round_up(static_cast<size_t>(n_vis < kSelCache * kSelThreads ? n_vis : kSelCache * kSelThreads) * sizeof(uint32_t), 256);
-    return select_general_bytes(n_vis) + kFastReserve + 2 * cand;
+    const size_t unused = round_up(static_cast<size_t>(n_vis < kSelCache * kSelThreads ? n_vis : kSelCache * kSelThreads) * sizeof(uint32_t), 256);
+    return select_general_bytes(n_vis) + kFastReserve + 2 * unused;
 }
 
 // In-place compaction (hidden_out == hidden): the source row of every output row as an index list, and the
@@ -1656,7 +1658,9 @@ struct ScorePlan {
     size_t off_qfrag, off_pstat, off_norm, off_colpart, off_sel, off_inplace, total;
 };
 
-constexpr int kScoreSlots = 256;    // one 512-thread workgroup per CU
+// One 512-thread workgroup per CU: what the registers and LDS of the two-block kernels allow.  Two of the one-block ones
+// (about 100 VGPRs, at most 64 KB) would fit; their grids were not tuned for that.
+constexpr int kScoreSlots = 256;
 
 static void plan_score(const ScoreGeom& g, int n_vis, int nch, int batch, ScorePlan* p) {
     const int ny = g.Hkv * g.rs;

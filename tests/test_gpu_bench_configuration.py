@@ -1,5 +1,5 @@
 """One step of bench.py's workload, launched the way bench.py times it -- 8 LongVA-7B-shaped 256-frame videos,
-stage 1 and the three pruning levels as batched calls (28 launches) replayed from one HIP graph, then one in-place
+stage 1 and the three pruning levels as batched calls (17 launches) replayed from one HIP graph, then one in-place
 KV compaction of the 28-layer cache -- checked against the CPU oracle: whole outputs where the oracle finishes in
 seconds (stage 1 of a video, the scores of a level), sampled rows for the bulk tensors.  The same for bench.py's
 --per-video launch (one call per video on 8 streams, one graph) and for the KV pass on its own stream."""

@@ -1,7 +1,7 @@
-"""The one-launch selection (at most 16 classes, at most 40960 tokens) and its neighbours, against the CPU oracle: sizes at
-the edges of its tiles and of its register variants, scores that need more than one digit, more ties than its candidate
-list holds, tokens without a class, quotas above a class's population, and the metadata the row mover carries.  All
-results are integers or copied rows: every comparison is exact."""
+"""The one-launch selection (at most 16 classes; at most 40960 tokens, one video of 5 to 16 classes 22528) and its neighbours,
+against the CPU oracle: sizes at the edges of its tiles and of its register variants, scores that need more than one digit,
+more ties than its candidate list holds, scores that are not finite, tokens without a class, quotas above a class's
+population, and the metadata the row mover carries.  All results are integers or copied rows: every comparison is exact."""
 import numpy as np
 import pytest
 import torch
