@@ -164,13 +164,6 @@ __device__ __forceinline__ float row16_sum(float v) {
     v += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), 0x121, 0xf, 0xf, false));
     return v;
 }
-// Sum over all 64 lanes of the wave; every lane receives the total.
-__device__ __forceinline__ float wave_sum(float v) {
-    v = row16_sum(v);
-    v += __shfl_xor(v, 16, 64);
-    v += __shfl_xor(v, 32, 64);
-    return v;
-}
 // low half of the wave: a summed over the lane pairs (l, l + 32); high half: b likewise
 __device__ __forceinline__ float swap32_add(float a, float b) {
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
@@ -180,6 +173,12 @@ __device__ __forceinline__ float swap32_add(float a, float b) {
 __device__ __forceinline__ float swap16_add(float a, float b) {
     const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// Sum over all 64 lanes of the wave; every lane receives the total.
+__device__ __forceinline__ float wave_sum(float v) {
+    v = row16_sum(v);
+    v = swap16_add(v, v);
+    return swap32_add(v, v);
 }
 template <int G> __device__ __forceinline__ float group_sum(float v) {
     static_assert(G == 16 || G == 64, "token groups are one DPP row or one wave");
@@ -196,27 +195,45 @@ template <typename P> __device__ __forceinline__ P* of_video_elems(P* p, int64_t
     return p ? p + static_cast<int64_t>(blockIdx.z) * elems : p;
 }
 
-// Exclusive prefix sum of one int per thread over a block of up to 1024 threads.
-// `scratch` is 17 ints of LDS; returns the exclusive prefix and stores the block total in *total.
-__device__ __forceinline__ int block_exclusive_scan(int v, int* scratch, int* total) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = (blockDim.x + 63) >> 6;
-    int incl = v;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        int up = __shfl_up(incl, off, 64);
-        if (lane >= off) incl += up;
-    }
-    __syncthreads();                       // scratch may still be read from a previous call
+// A barrier that orders LDS accesses alone.  __syncthreads() also waits until this thread's global stores have completed,
+// about 0.3 us each time in a workgroup that writes results between its steps.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Inclusive prefix sum over the 64 lanes of a wave with DPP adds: shifts by 1, 2, 4, 8 inside the 16-lane rows, then the last
+// lane of a row (of a pair of rows) is broadcast into the next one.  Every lane must be active.
+template <int CTRL, int ROW_MASK> __device__ __forceinline__ int dpp_add(int v) {
+    return v + __builtin_amdgcn_update_dpp(0, v, CTRL, ROW_MASK, 0xf, false);
+}
+__device__ __forceinline__ int row16_inclusive_scan(int v) {
+    v = dpp_add<0x111, 0xf>(v); v = dpp_add<0x112, 0xf>(v); v = dpp_add<0x114, 0xf>(v);
+    return dpp_add<0x118, 0xf>(v);
+}
+__device__ __forceinline__ int wave_inclusive_scan(int v) {
+    v = row16_inclusive_scan(v);
+    v = dpp_add<0x142, 0xa>(v);            // row_bcast:15 into rows 1 and 3
+    return dpp_add<0x143, 0xc>(v);         // row_bcast:31 into rows 2 and 3
+}
+
+// Exclusive prefix sum of one int per thread over a workgroup of up to 1024 threads (whole waves); *total receives the sum.
+// `scratch` is 16 ints of LDS that nobody reads any more; every wave scans the waves' totals for itself, so that one
+// barrier is enough (a serial walk by one thread behind two barriers took 0.8 us).
+__device__ __forceinline__ int block_exclusive_scan_lds(int v, int* scratch, int* total) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nwaves = (blockDim.x + 63) >> 6;
+    const int incl = wave_inclusive_scan(v);
     if (lane == 63) scratch[wave] = incl;
+    lds_barrier();
+    const int sums = row16_inclusive_scan((lane & 15) < nwaves ? scratch[lane & 15] : 0);
+    *total = __builtin_amdgcn_readlane(sums, 15);
+    return (wave > 0 ? __builtin_amdgcn_readlane(sums, wave - 1) : 0) + incl - v;
+}
+// The same with 17 ints of LDS that may still be read from the call before, and with barriers that publish global stores too.
+__device__ __forceinline__ int block_exclusive_scan(int v, int* scratch, int* total) {
     __syncthreads();
-    if (threadIdx.x == 0) {
-        int run = 0;
-        for (int w = 0; w < nwaves; ++w) { int t = scratch[w]; scratch[w] = run; run += t; }
-        scratch[16] = run;
-    }
-    __syncthreads();
-    *total = scratch[16];
-    return scratch[wave] + incl - v;
+    return block_exclusive_scan_lds(v, scratch, total);
 }
 
 }  // namespace metok

@@ -196,11 +196,13 @@ __global__ __launch_bounds__(kStatsThreads) void frame_stats_kernel(
 // segment_kernel spreads the totals over up to kMaxReduceWgs workgroups; the one that arrives last at an atomic counter
 // goes on with the segmentation and, in the calls that do the whole of stage 1, with the plan (and the event ids of
 // uniformly pooled rows), so that nothing but the totals is handed over and no launch is spent on one workgroup's work.
-// All of it is latency.  Against one workgroup per video for the totals and a launch of its own for the plan: 8 videos x
-// 256 frames 23 + 12 us (and 4.5 us for the event ids) -> 19.6 us, 128 frames 13 + 7 -> 13.4 us, 32 frames 13 + 7 -> 11 us.
+// All of it is latency: segment_short_kernel does the same for videos of at most kShortFrames frames with every comparison
+// of a ranking spread over the workgroup, see there.
 // ---------------------------------------------------------------------------------------------
 constexpr int kSegThreads = 1024;
 constexpr int kMaxReduceWgs = 64;
+constexpr int kShortFrames = 512;          // up to here segment_short_kernel: at least two threads per frame
+constexpr int kOneReduceFrames = 32;       // up to here one workgroup adds up the partials too: two frames per wave
 constexpr int kRankLoopFrames = 2048;      // up to here every thread ranks its frames against all others
 constexpr int kFillRowsInPlan = 65536;     // up to so many uniformly pooled rows the planning workgroup writes their event ids
 
@@ -215,11 +217,14 @@ struct SegmentArgs {
     float* pair_dot;                       // workspace [T]
     int64_t ws_video;
 };
+__host__ __device__ __forceinline__ int pooled_side(int g, int s, int edge) {
+    return edge == METOK_POOL_FLOOR ? (g / s > 1 ? g / s : 1) : (g + s - 1) / s;
+}
 struct PlanArgs1 {
     int n_key_events;
     double beta;
-    int s_key_kf, s_key_nf, s_non_kf, s_non_nf;
-    int grid_h, grid_w, event_reduce, pool_edge;
+    int stride[4], rows[4];                // of a frame: [key event, key frame], [key, other], [other, key], [other, other]
+    int event_reduce;
     float* event_score;
     uint8_t* event_is_key;
     uint8_t* frame_is_key;
@@ -231,39 +236,64 @@ struct PlanArgs1 {
     int32_t* token_event;
     int64_t rows_video;
     int64_t ws_video;
+
+    void set_strides(const int (&s)[4], int grid_h, int grid_w, int pool_edge) {
+        for (int i = 0; i < 4; ++i) { stride[i] = s[i]; rows[i] = pooled_side(grid_h, s[i], pool_edge) * pooled_side(grid_w, s[i], pool_edge); }
+    }
 };
 
 // Totals handed to the last workgroup pass the caches that are not coherent between the chip's dies.
 __device__ __forceinline__ void store_total(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ float load_total(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-// The C partial triples of a frame are contiguous; a lane adds the triples lane, lane + 64, ..., four of them requested
+// The C partial triples of a frame are contiguous; a lane adds the triples lane, lane + 64, ..., kRounds of them requested
 // together (a position past the end reads the last triple again and is not added), and the lane totals are combined by a
-// fixed butterfly: the result does not depend on timing or on the number of workgroups.
-__device__ __forceinline__ void reduce_partials(const SegmentArgs& a, const float* part, float* frame_score, float* frame_norm2, float* pair_dot) {
-    struct Triple { float x, y, z; };
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    constexpr int kWaves = kSegThreads / 64, kRounds = 4;
-    for (int t = blockIdx.x * kWaves + wave; t < a.T; t += gridDim.x * kWaves) {
-        const Triple* src = reinterpret_cast<const Triple*>(part) + static_cast<size_t>(t) * a.C;
-        float p = 0.f, q = 0.f, c = 0.f;
-        for (int c0 = 0; c0 < a.C; c0 += 64 * kRounds) {
-            Triple v[kRounds];
+// fixed butterfly: the result does not depend on timing or on the number of workgroups.  The wave takes F frames at a time
+// (one past the last reads that one again).
+struct Triple { float x, y, z; };
+template <int F>
+__device__ __forceinline__ void reduce_frames(const float* part, int C, int t, int dt, int T, Triple (&out)[F]) {
+    const int lane = threadIdx.x & 63;
+    constexpr int kRounds = 4;
+    const Triple* src[F];
 #pragma unroll
-            for (int r = 0; r < kRounds; ++r) v[r] = src[min(c0 + 64 * r + lane, a.C - 1)];
+    for (int f = 0; f < F; ++f) { src[f] = reinterpret_cast<const Triple*>(part) + static_cast<size_t>(min(t + f * dt, T - 1)) * C; out[f] = {0.f, 0.f, 0.f}; }
+    for (int c0 = 0; c0 < C; c0 += 64 * kRounds) {
+        Triple v[F][kRounds];
+#pragma unroll
+        for (int f = 0; f < F; ++f)
+#pragma unroll
+            for (int r = 0; r < kRounds; ++r) v[f][r] = src[f][min(c0 + 64 * r + lane, C - 1)];
+#pragma unroll
+        for (int f = 0; f < F; ++f)
 #pragma unroll
             for (int r = 0; r < kRounds; ++r) {
-                const bool in = c0 + 64 * r + lane < a.C;
-                p += in ? v[r].x : 0.f; q += in ? v[r].y : 0.f; c += in ? v[r].z : 0.f;
+                const bool in = c0 + 64 * r + lane < C;
+                out[f].x += in ? v[f][r].x : 0.f; out[f].y += in ? v[f][r].y : 0.f; out[f].z += in ? v[f][r].z : 0.f;
             }
-        }
-        p = wave_sum(p); q = wave_sum(q); c = wave_sum(c);
+    }
+#pragma unroll
+    for (int f = 0; f < F; ++f) { out[f].x = wave_sum(out[f].x); out[f].y = wave_sum(out[f].y); out[f].z = wave_sum(out[f].z); }
+}
+
+__device__ __forceinline__ void reduce_partials(const SegmentArgs& a, const float* part, float* frame_score, float* frame_norm2, float* pair_dot) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    constexpr int kWaves = kSegThreads / 64;
+    for (int t = blockIdx.x * kWaves + wave; t < a.T; t += gridDim.x * kWaves) {
+        Triple v[1];
+        reduce_frames<1>(part, a.C, t, 0, a.T, v);
         if (lane == 0) {
-            store_total(frame_norm2 + t, p);
-            store_total(pair_dot + t, q);
-            if (a.have_text && frame_score) store_total(frame_score + t, c / static_cast<float>(a.N));
+            store_total(frame_norm2 + t, v[0].x);
+            store_total(pair_dot + t, v[0].y);
+            if (a.have_text && frame_score) store_total(frame_score + t, v[0].z / static_cast<float>(a.N));
         }
     }
+}
+
+// Eq. 4 from the totals
+__device__ __forceinline__ float pair_similarity(const SegmentArgs& a, float n0, float n1, float dot) {
+    const float den = sqrtf(n0) * sqrtf(n1);
+    return a.sim_mode == METOK_SIM_TOKEN_MEAN ? dot / static_cast<float>(a.N) : ((den < kZeroNorm) ? 0.f : dot / den);
 }
 
 // LDS of the workgroup that segments and plans
@@ -287,9 +317,7 @@ __device__ __forceinline__ void segment_video(const SegmentArgs& a, SegmentShare
     int* scan_scratch = sh.scan;
     // Eq. 4
     for (int t = tid; t < T - 1; t += kSegThreads) {
-        const float n0 = load_total(frame_norm2 + t), n1 = load_total(frame_norm2 + t + 1), dot = load_total(pair_dot + t);
-        const float den = sqrtf(n0) * sqrtf(n1);
-        const float s = a.sim_mode == METOK_SIM_TOKEN_MEAN ? dot / static_cast<float>(a.N) : ((den < kZeroNorm) ? 0.f : dot / den);
+        const float s = pair_similarity(a, load_total(frame_norm2 + t), load_total(frame_norm2 + t + 1), load_total(pair_dot + t));
         sim[t] = s;
         key[t] = ordered_key(s);
     }
@@ -349,29 +377,6 @@ __device__ __forceinline__ void segment_video(const SegmentArgs& a, SegmentShare
                 ++eq_rank;
             }
         }
-    } else if (T <= kSegThreads / 2) {
-        // Short videos: `share` threads rank a frame together (with a thread per frame most of the workgroup would idle
-        // through the walk over all keys: 256 frames 14200 -> 4000 cycles).
-        int share = 2;
-        while (share < 64 && T * share * 2 <= kSegThreads) share *= 2;
-        const int f = tid / share, i = f - 1;
-        int rank = 0;
-        if (f >= 1 && f < T) {
-            const uint32_t ki = key[i];
-            const uint4* key4 = reinterpret_cast<const uint4*>(key);
-            for (int q = tid % share; q < n_quads; q += share) {
-                const uint4 km = key4[q];
-                const int m = 4 * q;
-                rank += (km.x < ki || (km.x == ki && m < i)) ? 1 : 0;
-                rank += (km.y < ki || (km.y == ki && m + 1 < i)) ? 1 : 0;
-                rank += (km.z < ki || (km.z == ki && m + 2 < i)) ? 1 : 0;
-                rank += (km.w < ki || (km.w == ki && m + 3 < i)) ? 1 : 0;
-            }
-        }
-        for (int off = share / 2; off >= 1; off >>= 1) rank += __shfl_xor(rank, off, 64);
-        if (tid % share == 0 && f < T) sh.ekey[f] = static_cast<uint32_t>(rank);
-        __syncthreads();
-        if (tid >= 1 && tid < T && static_cast<int>(sh.ekey[tid]) < k - 1) my_flags = 1u;      // per is 1
     } else
     for (int j = 0; j < per; ++j) {
         const int f = tid * per + j;                          // frame f opens an event if pair f-1 is a boundary
@@ -458,10 +463,6 @@ __global__ __launch_bounds__(kSegThreads) void frame_score_kernel(const float* _
 // ---------------------------------------------------------------------------------------------
 // plan_video: event scores, key events, key frames, strides and output offsets.
 // ---------------------------------------------------------------------------------------------
-__device__ __forceinline__ int pooled_side(int g, int s, int edge) {
-    return edge == METOK_POOL_FLOOR ? max(1, g / s) : (g + s - 1) / s;
-}
-
 // The n largest of keys[a, b) under (key descending, index ascending), found by the whole workgroup without comparing
 // item against item: the n-th largest key bit by bit (32 counting rounds), then the keys above it and, of the keys
 // equal to it, the first ones by index (an exclusive scan over the threads in index order).  The calling thread owns the
@@ -502,10 +503,31 @@ __device__ __forceinline__ uint32_t block_top_n_flags(const uint32_t* keys, int 
     return flags;
 }
 
+// Event ids of uniformly pooled rows, a wave per frame; event[] is complete.
+__device__ __forceinline__ void fill_token_events(const PlanArgs1& a, const uint16_t* event, int T) {
+    const int n = a.fill_rows_per_frame;
+    if (n <= 0) return;
+    int32_t* token_event = of_video_elems(a.token_event, a.rows_video);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (n % 4 == 0 && (reinterpret_cast<uintptr_t>(token_event) & 15u) == 0) {
+        // four rows per store: 36864 rows 2.5 -> 1.4 us
+        for (int f = wave; f < T; f += kSegThreads / 64) {
+            const int e = event[f];
+            int4* dst = reinterpret_cast<int4*>(token_event + static_cast<size_t>(f) * n);
+            for (int r = lane; r < n / 4; r += 64) dst[r] = make_int4(e, e, e, e);
+        }
+        return;
+    }
+    for (int f = wave; f < T; f += kSegThreads / 64) {
+        const int e = event[f];
+        for (int r = lane; r < n; r += 64) token_event[static_cast<size_t>(f) * n + r] = e;
+    }
+}
+
 // sh.start and sh.event hold the segmentation; frame_score is read past the caches (segment_kernel's totals).
 __device__ __forceinline__ void plan_video(const PlanArgs1& a, SegmentShared& sh, const float* frame_score, int T, int k) {
     const int tid = threadIdx.x;
-    const int n_key_events = a.n_key_events, event_reduce = a.event_reduce, pool_edge = a.pool_edge, grid_h = a.grid_h, grid_w = a.grid_w;
+    const int n_key_events = a.n_key_events, event_reduce = a.event_reduce;
     const double beta = a.beta;
     float* event_score = of_video_elems(a.event_score, k);
     uint8_t* event_is_key = of_video_elems(a.event_is_key, k);
@@ -601,12 +623,11 @@ __device__ __forceinline__ void plan_video(const PlanArgs1& a, SegmentShared& sh
                 for (; m < hi; ++m) count(fkey[m], m);
                 kf_flag = rank < n_kf;
             }
-            const bool ek_flag = ev_key[e] != 0;
-            const int s = ek_flag ? (kf_flag ? a.s_key_kf : a.s_key_nf) : (kf_flag ? a.s_non_kf : a.s_non_nf);
+            const int kind = (ev_key[e] ? 0 : 2) + (kf_flag ? 0 : 1);
             frame_is_key[f] = kf_flag ? 1 : 0;
-            frame_stride[f] = s;
+            frame_stride[f] = a.stride[kind];
             frame_event_ws[f] = e;
-            counts[j] = pooled_side(grid_h, s, pool_edge) * pooled_side(grid_w, s, pool_edge);
+            counts[j] = a.rows[kind];
             mine += counts[j];
         }
     }
@@ -620,13 +641,7 @@ __device__ __forceinline__ void plan_video(const PlanArgs1& a, SegmentShared& sh
         }
     }
     if (tid == 0) frame_offsets[T] = total;
-    if (a.fill_rows_per_frame > 0) {
-        int32_t* token_event = of_video_elems(a.token_event, a.rows_video);
-        for (int f = tid >> 6; f < T; f += kSegThreads / 64) {
-            const int e = sh.event[f];
-            for (int r = tid & 63; r < a.fill_rows_per_frame; r += 64) token_event[f * a.fill_rows_per_frame + r] = e;
-        }
-    }
+    fill_token_events(a, sh.event, T);
 }
 
 // WITH_PLAN: the plan follows in the same workgroup.  The arrival counter is the pair slot of the video's last frame, first
@@ -672,6 +687,242 @@ __global__ __launch_bounds__(kSegThreads) void plan_kernel(const PlanArgs1 plan,
         sh.event[f] = static_cast<uint16_t>(lo);
     }
     plan_video(plan, sh, frame_score, T, k);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Segmentation and plan of a video of at most kShortFrames frames, the whole of it in the workgroup that arrives last.
+// Nothing here is work; it is a chain of memory round trips, barriers and rankings.  Stamped inside the kernel, 8 videos of 256
+// frames (32 frames) took 16.5 us (10.0): totals and arrival 2.4 (2.2), one more round trip 0.7, the ranking of the
+// similarities 3.6 (1.2), two block scans 1.5, waits for the stores of results 1.0, event scores, key events and key frames
+// 4.8 (2.9), event ids 2.5.  So: a power of two of threads (`share`, 2 to 64) compares for a frame, and 16 lanes for an event;
+// keys start at 0, so that "smaller, or equal and earlier" is one comparison with a threshold of the compared frame; results
+// are stored without being waited for (lds_barrier); a frame's row count comes from a table of its four kinds; and
+// up to kOneReduceFrames frames the totals stay in LDS and no other workgroup is waited for.  Whole calls: 32 frames of 27 x 27 x
+// 1152 36.1 -> 31.8 us, 128 of 24 x 24 x 1024 68.3 -> 63.8 us, 8 x 64 of 27 x 27 x 1152 299 -> 294 us, 8 x 256 pooled uniformly
+// 550 -> 541 us.
+// ---------------------------------------------------------------------------------------------
+struct ShortShared {
+    uint32_t key[kShortFrames + 4];        // sort keys of S_i, padded with the largest value
+    uint32_t fkey[kShortFrames];           // of the frame scores
+    uint32_t ekey[kShortFrames];           // of the event scores
+    uint16_t start[kShortFrames + 2];
+    uint16_t event[kShortFrames];
+    uint16_t n_kf[kShortFrames];           // key frames of an event
+    uint8_t ev_key[kShortFrames];
+    float norm2[kOneReduceFrames + 1], pair[kOneReduceFrames], score[kOneReduceFrames];
+    int scan[2][16];
+    int last;
+};
+// 0 .. 0xfffffffe in the order of the values: a key plus one is a key's strict bound and does not wrap.
+__device__ __forceinline__ uint32_t sort_key(float x) { return ordered_key(x) - 1u; }
+
+// Sum over aligned groups of 2^log2 lanes (1 <= log2 <= 6); every lane of the group receives it.
+__device__ __forceinline__ int group_total(int v, int log2) {
+    v = dpp_add<0xb1, 0xf>(v);                                      // quad_perm 1 0 3 2
+    if (log2 > 1) v = dpp_add<0x4e, 0xf>(v);                        // quad_perm 2 3 0 1
+    if (log2 > 2) v = dpp_add<0x141, 0xf>(v);                       // row_half_mirror
+    if (log2 > 3) v = dpp_add<0x140, 0xf>(v);                       // row_mirror
+    if (log2 > 4) { const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false); v = static_cast<int>(r[0]) + static_cast<int>(r[1]); }
+    if (log2 > 5) { const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false); v = static_cast<int>(r[0]) + static_cast<int>(r[1]); }
+    return v;
+}
+// Threads per frame: the largest power of two up to 64 of which T fit the workgroup.
+__device__ __forceinline__ int share_log2(int T) {
+    const int l = 31 - __clz(kSegThreads / T);
+    return l < 6 ? l : 6;
+}
+
+// Every thread of the 2^sl that share frame f calls with the frame's event e; sh.start, sh.fkey and sh.event are written, and a
+// barrier is still to come.
+__device__ __forceinline__ void plan_short(const PlanArgs1& a, ShortShared& sh, int T, int k, int sl, int e) {
+    const int tid = threadIdx.x, f = tid >> sl, s = tid & ((1 << sl) - 1);
+    float* event_score = of_video_elems(a.event_score, k);
+    uint8_t* event_is_key = of_video_elems(a.event_is_key, k);
+    const bool use_max = a.event_reduce == METOK_EVENT_MAX;
+    lds_barrier();
+    // event score: mean (Sec. 3.2.1) or max (Algorithm 1) of the frame scores; 16 lanes per event
+    const int l16 = tid & 15;
+    for (int v = tid >> 4; v < k; v += kSegThreads / 16) {
+        const int lo = sh.start[v], hi = max(lo, static_cast<int>(sh.start[v + 1]));
+        float acc = use_max ? -INFINITY : 0.f;
+        for (int m = lo + l16; m < hi; m += 16) { const float x = score_of_key(sh.fkey[m] + 1u); acc = use_max ? fmaxf(acc, x) : acc + x; }
+        if (use_max) {
+#pragma unroll
+            for (int step = 0; step < 4; ++step) {
+                const int u = __float_as_int(acc);
+                const int o = step == 0 ? __builtin_amdgcn_update_dpp(0, u, 0x128, 0xf, 0xf, false) : step == 1 ? __builtin_amdgcn_update_dpp(0, u, 0x124, 0xf, 0xf, false)
+                            : step == 2 ? __builtin_amdgcn_update_dpp(0, u, 0x122, 0xf, 0xf, false) : __builtin_amdgcn_update_dpp(0, u, 0x121, 0xf, 0xf, false);
+                acc = fmaxf(acc, __int_as_float(o));
+            }
+        } else {
+            acc = row16_sum(acc);
+            acc = hi > lo ? acc / static_cast<float>(hi - lo) : 0.f;
+        }
+        if (l16 == 0) {
+            event_score[v] = acc;
+            sh.ekey[v] = sort_key(acc);
+            sh.n_kf[v] = static_cast<uint16_t>(min(hi - lo, static_cast<int>(ceil(a.beta * static_cast<double>(hi - lo) - 1e-9))));
+        }
+    }
+    // rank of the frame inside its event under (score descending, index ascending)
+    int above = 0;
+    if (f < T) {
+        const int lo = sh.start[e], hi = sh.start[e + 1];
+        const uint32_t kf = sh.fkey[f];
+        for (int m = lo + s; m < hi; m += 1 << sl) above += sh.fkey[m] >= kf + (m < f ? 0u : 1u) ? 1 : 0;
+    }
+    above = group_total(above, sl);
+    lds_barrier();
+    // key events, ranked likewise
+    for (int v = tid >> 4; v < k; v += kSegThreads / 16) {
+        const uint32_t ke = sh.ekey[v];
+        int n = 0;
+        for (int m = l16; m < k; m += 16) n += sh.ekey[m] >= ke + (m < v ? 0u : 1u) ? 1 : 0;
+        n = group_total(n, 4);
+        if (l16 == 0) {
+            const uint8_t is_key = n < a.n_key_events ? 1 : 0;
+            sh.ev_key[v] = is_key;
+            event_is_key[v] = is_key;
+        }
+    }
+    lds_barrier();
+    const bool own = f < T && s == 0;
+    bool kf_flag = false;
+    int kind = 0;
+    if (own) {
+        kf_flag = above < static_cast<int>(sh.n_kf[e]);
+        kind = (sh.ev_key[e] ? 0 : 2) + (kf_flag ? 0 : 1);
+    }
+    const int rows = own ? a.rows[kind] : 0;
+    int total = 0;
+    const int offset = block_exclusive_scan_lds(rows, sh.scan[1], &total);
+    if (own) {
+        of_video_elems(a.frame_is_key, T)[f] = kf_flag ? 1 : 0;
+        of_video_elems(a.frame_stride, T)[f] = a.stride[kind];
+        of_video_elems(a.frame_offsets, T + 1)[f] = offset;
+        of_video(a.frame_event_ws, a.ws_video)[f] = e;
+    }
+    if (tid == 0) of_video_elems(a.frame_offsets, T + 1)[T] = total;
+    fill_token_events(a, sh.event, T);
+}
+
+template <bool WITH_PLAN>
+__global__ __launch_bounds__(kSegThreads) void segment_short_kernel(const SegmentArgs a, const PlanArgs1 plan) {
+    __shared__ __align__(16) ShortShared sh;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, T = a.T, k = a.k;
+    constexpr int kWaves = kSegThreads / 64;
+    float* part = of_video(a.part, a.ws_video);
+    float* frame_score = of_video_elems(a.frame_score, T);
+    float* sim = of_video_elems(a.sim, T - 1);
+    int32_t* event_start = of_video_elems(a.event_start, k + 1);
+    int32_t* frame_event = of_video_elems(a.frame_event, T);
+    float n0 = 0.f, n1 = 0.f, dot = 0.f, score = 0.f;             // of frame tid, and |v|^2 of the next one
+    if (gridDim.x == 1) {
+        if (wave < T) {
+            Triple v[2];
+            reduce_frames<2>(part, a.C, wave, kWaves, T, v);
+#pragma unroll
+            for (int f = 0; f < 2; ++f) {
+                const int t = wave + f * kWaves;
+                if (t < T && lane == 0) { sh.norm2[t] = v[f].x; sh.pair[t] = v[f].y; sh.score[t] = v[f].z / static_cast<float>(a.N); }
+            }
+        }
+        lds_barrier();
+        if (tid < T) {
+            n0 = sh.norm2[tid]; n1 = sh.norm2[tid + 1]; dot = sh.pair[tid]; score = sh.score[tid];
+            if (a.have_text && frame_score) frame_score[tid] = score;
+        }
+    } else {
+        float* frame_norm2 = of_video(a.frame_norm2, a.ws_video);
+        float* pair_dot = of_video(a.pair_dot, a.ws_video);
+        reduce_partials(a, part, frame_score, frame_norm2, pair_dot);
+        __builtin_amdgcn_s_waitcnt(0);          // this thread's totals are stored
+        __syncthreads();
+        if (tid == 0) {
+            uint32_t* arrive = reinterpret_cast<uint32_t*>(part + static_cast<size_t>(T - 1) * a.C * 3 + 1);
+            sh.last = __hip_atomic_fetch_add(arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1 ? 1 : 0;
+        }
+        __syncthreads();
+        if (!sh.last) return;
+        if (tid < T) {
+            const int next = min(tid + 1, T - 1);
+            n0 = load_total(frame_norm2 + tid); n1 = load_total(frame_norm2 + next); dot = load_total(pair_dot + tid);
+            if (WITH_PLAN) score = load_total(frame_score + tid);
+        }
+    }
+    const int n_pairs = T - 1, n_quads = (n_pairs + 3) / 4;
+    if (tid < n_pairs) {
+        const float x = pair_similarity(a, n0, n1, dot);
+        sim[tid] = x;
+        sh.key[tid] = sort_key(x);
+    }
+    if (tid < 4 && n_pairs + tid < n_quads * 4) sh.key[n_pairs + tid] = 0xffffffffu;      // not below any key's bound
+    if (WITH_PLAN && tid < T) sh.fkey[tid] = sort_key(score);
+    lds_barrier();
+    // frame f opens an event if pair f - 1 is among the k - 1 lowest under (value, index)
+    const int sl = share_log2(T), f = tid >> sl, s = tid & ((1 << sl) - 1), i = f - 1;
+    int rank = 0;
+    if (f >= 1 && f < T) {
+        const uint32_t ki = sh.key[i];
+        const uint4* key4 = reinterpret_cast<const uint4*>(sh.key);
+        for (int q = s; q < n_quads; q += 1 << sl) {
+            const uint4 km = key4[q];
+            const uint32_t bound = ki + (q < (i >> 2) ? 1u : 0u);     // equal keys of earlier quads count
+            rank += (km.x < bound ? 1 : 0) + (km.y < bound ? 1 : 0) + (km.z < bound ? 1 : 0) + (km.w < bound ? 1 : 0);
+        }
+        if (s == 0) {                                                 // and those before i in its own quad
+            const uint4 km = key4[i >> 2];
+            const int in = i & 3;
+            rank += (in > 0 && km.x == ki ? 1 : 0) + (in > 1 && km.y == ki ? 1 : 0) + (in > 2 && km.z == ki ? 1 : 0);
+        }
+    }
+    rank = group_total(rank, sl);
+    const int opens = s == 0 && f >= 1 && f < T && rank < k - 1 ? 1 : 0;
+    int total = 0;
+    const int e = block_exclusive_scan_lds(opens, sh.scan[0], &total) + opens;      // openings at or before f; at most k - 1: the ranks are distinct
+    if (s == 0 && f < T) {
+        if (opens) { event_start[e] = f; sh.start[e] = static_cast<uint16_t>(f); }
+        frame_event[f] = e;
+        sh.event[f] = static_cast<uint16_t>(e);
+    }
+    if (tid == 0) {
+        event_start[0] = 0; sh.start[0] = 0;
+        event_start[k] = T; sh.start[k] = static_cast<uint16_t>(T);
+    }
+    if (WITH_PLAN) plan_short(plan, sh, T, k, sl, e);
+}
+
+// The plan on its own, from a caller's segmentation, T <= kShortFrames.
+__global__ __launch_bounds__(kSegThreads) void plan_short_kernel(const PlanArgs1 plan, const float* frame_score, const int32_t* event_start, int T, int k) {
+    __shared__ __align__(16) ShortShared sh;
+    const int tid = threadIdx.x;
+    if (tid <= k) sh.start[tid] = static_cast<uint16_t>(max(0, min(event_start[tid], T)));
+    if (tid < T) {
+        const float x = frame_score[tid];
+        sh.fkey[tid] = sort_key(x);
+        if (plan.frame_score_out) plan.frame_score_out[tid] = x;
+    }
+    lds_barrier();
+    const int sl = share_log2(T), f = tid >> sl;
+    int lo = 0, hi = k - 1;                 // last event whose start is <= f
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (sh.start[mid] <= f) lo = mid; else hi = mid - 1;
+    }
+    if (f < T && (tid & ((1 << sl) - 1)) == 0) sh.event[f] = static_cast<uint16_t>(lo);
+    plan_short(plan, sh, T, k, sl, lo);
+}
+
+template <bool WITH_PLAN>
+static void launch_segment(const SegmentArgs& sa, const PlanArgs1& plan, unsigned nb, hipStream_t st) {
+    if (sa.T <= kShortFrames)
+        hipLaunchKernelGGL(segment_short_kernel<WITH_PLAN>, dim3(sa.T <= kOneReduceFrames ? 1 : reduce_workgroups(sa.T), 1, nb), dim3(kSegThreads), 0, st, sa, plan);
+    else
+        hipLaunchKernelGGL(segment_kernel<WITH_PLAN>, dim3(reduce_workgroups(sa.T), 1, nb), dim3(kSegThreads), 0, st, sa, plan);
+}
+static void launch_plan(const PlanArgs1& plan, const float* frame_score, const int32_t* event_start, int T, int k, hipStream_t st) {
+    if (T <= kShortFrames) hipLaunchKernelGGL(plan_short_kernel, dim3(1), dim3(kSegThreads), 0, st, plan, frame_score, event_start, T, k);
+    else hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(kSegThreads), 0, st, plan, frame_score, event_start, T, k);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1014,7 +1265,7 @@ static void launch_segment_plan(const SegmentArgs& sa, const PlanArgs1& plan, un
     // one launch does both: the trace hook brackets it for either name
     TraceScope trace_segment(METOK_TRACE_SEGMENT, st);
     TraceScope trace_plan(METOK_TRACE_PLAN, st);
-    hipLaunchKernelGGL(segment_kernel<true>, dim3(reduce_workgroups(sa.T), 1, nb), dim3(kSegThreads), 0, st, sa, plan);
+    launch_segment<true>(sa, plan, nb, st);
 }
 
 static size_t stats_part_bytes(int T, const StatsPlan& p) {
@@ -1083,7 +1334,7 @@ extern "C" int metok_segment_events(const void* feats, int dtype, int T, int N, 
         if (!ok) return fail(METOK_ERR_UNSUPPORTED, "no frame-statistics kernel for d = %d", d);
         if ((rc = check_launch("frame_stats"))) return rc;
         const SegmentArgs sa = {part, p.C, T, N, k, text_emb ? 1 : 0, sim_mode, sim, event_start, frame_event, frame_score, norm2, pair_dot, 0};
-        { TraceScope trace_scope(METOK_TRACE_SEGMENT, st); hipLaunchKernelGGL(segment_kernel<false>, dim3(reduce_workgroups(T)), dim3(kSegThreads), 0, st, sa, PlanArgs1{}); }
+        { TraceScope trace_scope(METOK_TRACE_SEGMENT, st); launch_segment<false>(sa, PlanArgs1{}, 1, st); }
         return check_launch("segment");
     }
     // pooled reading: Eq. 5 (if wanted) from the tokens, Eq. 4 from the frames' mean tokens (a [T, 1, d] fp32 "video")
@@ -1108,7 +1359,7 @@ extern "C" int metok_segment_events(const void* feats, int dtype, int T, int N, 
         return fail(METOK_ERR_UNSUPPORTED, "no frame-statistics kernel for d = %d", d);
     if ((rc = check_launch("frame_stats (means)"))) return rc;
     const SegmentArgs sa = {part_m, pm.C, T, 1, k, 0, METOK_SIM_FLAT, sim, event_start, frame_event, nullptr, norm2, pair_dot, 0};
-    { TraceScope trace_scope(METOK_TRACE_SEGMENT, st); hipLaunchKernelGGL(segment_kernel<false>, dim3(reduce_workgroups(T)), dim3(kSegThreads), 0, st, sa, PlanArgs1{}); }
+    { TraceScope trace_scope(METOK_TRACE_SEGMENT, st); launch_segment<false>(sa, PlanArgs1{}, 1, st); }
     return check_launch("segment");
 }
 
@@ -1211,9 +1462,10 @@ extern "C" int metok_compress_encoder_tokens(const void* feats, int dtype, int T
     }
     (void)norm2;
     const int n_key_events = ceil_ratio(alpha * k) > k ? k : ceil_ratio(alpha * k);
-    const PlanArgs1 plan = {n_key_events, beta, s_key_kf, s_key_nf, s_non_kf, s_non_nf, grid_h, grid_w, event_reduce, pool_edge, event_score,
+    PlanArgs1 plan = {n_key_events, beta, {}, {}, event_reduce, event_score,
                             event_is_key, frame_is_key, frame_stride, frame_offsets, frame_event_ws, frame_score_out, 0, nullptr, 0, 0};
-    { TraceScope trace_scope(METOK_TRACE_PLAN, st); hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(kSegThreads), 0, st, plan, scores, event_start, T, k); }
+    plan.set_strides({s_key_kf, s_key_nf, s_non_kf, s_non_nf}, grid_h, grid_w, pool_edge);
+    { TraceScope trace_scope(METOK_TRACE_PLAN, st); launch_plan(plan, scores, event_start, T, k, st); }
     if ((rc = check_launch("plan"))) return rc;
 
     dim3 grid(pool_workgroups(T, grid_h, grid_w, d, dtype, s1, s2, pool_edge), T);
@@ -1351,9 +1603,9 @@ static int segment_compress_impl(int batch, const void* feats, int dtype, int T,
         if ((rc = check_launch("frame_stats"))) return rc;
         const int n_key_events = ceil_ratio(alpha * k) > k ? k : ceil_ratio(alpha * k);
         const SegmentArgs sa = {part, p.C, T, N, k, 1, sim_mode, sim, event_start, frame_event, frame_score, norm2, pair_dot, ws_video};
-        const PlanArgs1 plan = {n_key_events, beta, clamp_stride(s1), clamp_stride(s2), clamp_stride(s1 / alpha), clamp_stride(s2 / alpha), grid_h, grid_w,
-                                event_reduce, pool_edge, event_score, event_is_key, frame_is_key, frame_stride, frame_offsets, frame_event_ws, nullptr,
-                                0, nullptr, 0, ws_video};
+        PlanArgs1 plan = {n_key_events, beta, {}, {}, event_reduce, event_score, event_is_key, frame_is_key, frame_stride, frame_offsets, frame_event_ws, nullptr,
+                          0, nullptr, 0, ws_video};
+        plan.set_strides({clamp_stride(s1), clamp_stride(s2), clamp_stride(s1 / alpha), clamp_stride(s2 / alpha)}, grid_h, grid_w, pool_edge);
         launch_segment_plan(sa, plan, nb, st);
         if ((rc = check_launch("segment and plan"))) return rc;
         dim3 grid(pool_workgroups(T, grid_h, grid_w, d, dtype, s1, s2, pool_edge), T, nb);
@@ -1445,8 +1697,9 @@ static int segment_compress_impl(int batch, const void* feats, int dtype, int T,
     const int n_key_events = ceil_ratio(alpha * k) > k ? k : ceil_ratio(alpha * k);
     const bool fill_here = rows <= kFillRowsInPlan;
     const SegmentArgs sa = {part, n_win, T, N, k, 1, METOK_SIM_FLAT, sim, event_start, frame_event, frame_score, norm2, pair_dot, ws_video};
-    const PlanArgs1 plan = {n_key_events, beta, 2, 2, 2, 2, grid_h, grid_w, event_reduce, pool_edge, event_score, event_is_key, frame_is_key, frame_stride,
+    PlanArgs1 plan = {n_key_events, beta, {}, {}, event_reduce, event_score, event_is_key, frame_is_key, frame_stride,
                             frame_offsets, frame_event_ws, nullptr, fill_here ? n_win : 0, token_event, out_capacity_rows, ws_video};
+    plan.set_strides({2, 2, 2, 2}, grid_h, grid_w, pool_edge);
     launch_segment_plan(sa, plan, nb, st);
     if ((rc = check_launch("segment and plan")) || fill_here) return rc;
     hipLaunchKernelGGL(fill_token_event_kernel, dim3(static_cast<unsigned>((rows + 255) / 256), 1, nb), dim3(256), 0, st, frame_event, T, n_win,

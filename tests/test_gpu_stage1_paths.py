@@ -81,6 +81,47 @@ def tied_video(T, seed):
     return basis[rng.integers(0, 4, size=T)], rng.standard_normal(16).astype(np.float32)
 
 
+@pytest.mark.parametrize("T", [1, 3, 8, 9, 32, 33, 100, 511, 512, 513])     # 64 to 2 threads per frame, then one; totals by one workgroup up to 32
+@pytest.mark.parametrize("event_reduce", [O.EVENT_REDUCE_MEAN, O.EVENT_REDUCE_MAX])
+def test_short_videos_with_ties(T, event_reduce):
+    """Boundaries, key events and key frames of tied similarities and scores: the decisions on the GPU's own values, exactly, from
+    one call, from the two calls, and in a batch; k from one event to one per frame."""
+    B = mk()
+    feats_np, text_np = tied_video(T, 77 + T)
+    feats, text = torch.from_numpy(feats_np).cuda(), torch.from_numpy(text_np).cuda()
+    for k in sorted({1, max(1, T // 17), max(1, T // 3), T}):
+        one = B.metok_segment_compress(feats, 2, 2, k, text, 0.5, 0.45, 1, 2, event_reduce=event_reduce)
+        seg = B.metok_segment_events(feats, k, text)
+        two = B.metok_compress_encoder_tokens(feats, 2, 2, seg["event_start"], 0.5, 0.45, 1, 2, frame_score=seg["frame_score"], event_reduce=event_reduce)
+        many = B.metok_segment_compress_batched(torch.stack([feats] * 3), 2, 2, k, torch.stack([text] * 3), 0.5, 0.45, 1, 2, event_reduce=event_reduce)
+        torch.cuda.synchronize()
+        es, fe = O.event_boundaries(one["sim"].cpu().numpy(), k)
+        np.testing.assert_array_equal(one["event_start"].cpu().numpy(), es)
+        np.testing.assert_array_equal(one["frame_event"].cpu().numpy(), fe)
+        score = one["frame_score"].cpu().numpy().astype(np.float64)
+        ref = O.compress_encoder_tokens(feats_np, (2, 2), None, es, 0.5, 0.45, 1, 2, frame_score=score, event_reduce=event_reduce)
+        # float32 sums of up to T scores: relative to the largest score, T ulps at most
+        np.testing.assert_allclose(one["event_score"].cpu().numpy(), ref["event_score"], rtol=0, atol=T * 2.0 ** -24 * np.abs(score).max())
+        # key events: the rule on the GPU's own event scores (equal events tie), then key frames, strides and offsets follow
+        got_es = one["event_score"].cpu().numpy()
+        key = np.zeros(k, dtype=np.uint8)
+        key[np.lexsort((np.arange(k), -got_es))[:int(np.ceil(0.5 * k - 1e-9))]] = 1
+        np.testing.assert_array_equal(one["event_is_key"].cpu().numpy(), key)
+        np.testing.assert_array_equal(one["frame_is_key"].cpu().numpy(), ref["frame_is_key"])
+        stride = np.where(key[fe] == 1, np.where(ref["frame_is_key"] == 1, 1, 2), np.where(ref["frame_is_key"] == 1, 2, 2))
+        np.testing.assert_array_equal(one["frame_stride"].cpu().numpy(), stride)
+        np.testing.assert_array_equal(one["frame_offsets"].cpu().numpy(), np.concatenate([[0], np.cumsum(np.where(stride == 1, 4, 1))]))
+        M = int(one["frame_offsets"][-1])
+        for name in ("sim", "event_start", "frame_event", "frame_score"):
+            assert torch.equal(one[name], seg[name]), name
+        for name in ("event_is_key", "frame_is_key", "frame_stride", "frame_offsets", "event_score"):
+            assert torch.equal(one[name], two[name]), name
+        for b in range(3):
+            for name, t in one.items():
+                rows = slice(0, M) if name in ("out_tokens", "token_event") else slice(None)
+                assert torch.equal(many[name][b][rows], t[rows]), (b, name)
+
+
 @pytest.mark.parametrize("T,k", [(2048, 5), (2049, 5), (5000, 1), (3000, 2999), (4100, 1500), (8192, 61), (8192, 8192)])
 @pytest.mark.parametrize("uniform", [False, True])      # three strides after a pass of statistics; stride 2 in one pass
 def test_long_videos_in_one_call(T, k, uniform):
