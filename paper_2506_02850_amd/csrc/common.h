@@ -218,6 +218,19 @@ __device__ __forceinline__ int wave_inclusive_scan(int v) {
     return dpp_add<0x143, 0xc>(v);         // row_bcast:31 into rows 2 and 3
 }
 
+// Smallest / largest value of the 64 lanes of a wave; every lane receives it.  Every lane must be active.
+template <bool MAX> __device__ __forceinline__ uint32_t wave_extreme(uint32_t v) {
+    auto pick = [](uint32_t a, uint32_t b) { return MAX ? (a > b ? a : b) : (a < b ? a : b); };
+    v = pick(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x128, 0xf, 0xf, false)));      // row_ror 8, 4, 2, 1
+    v = pick(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x124, 0xf, 0xf, false)));
+    v = pick(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x122, 0xf, 0xf, false)));
+    v = pick(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x121, 0xf, 0xf, false)));
+    const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = pick(a[0], a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return pick(b[0], b[1]);
+}
+
 // Exclusive prefix sum of one int per thread over a workgroup of up to 1024 threads (whole waves); *total receives the sum.
 // `scratch` is 16 ints of LDS that nobody reads any more; every wave scans the waves' totals for itself, so that one
 // barrier is enough (a serial walk by one thread behind two barriers took 0.8 us).

@@ -1108,7 +1108,9 @@ __global__ __launch_bounds__(kIdxThreads) void write_index_kernel(
 // Measured in kernel traces against the launches it replaces (score + histogram, candidates, index list; with 5 to 16
 // classes the general path's three): 2243 tokens 30.0 -> 10.1 us, 4507 tokens with 40 partial sums each 33.4 -> 12.0 us,
 // 18432 tokens in 13 classes 30.1 -> 19.2 us, eight videos of 36864 tokens 43.5 -> 31.1 us with about 20 candidates and
-// 39 -> 34.5 us with about 200 (more of them in one step to rank).  One workgroup walking 36 tiles is what is left there
+// 39 -> 34.5 us with about 200 (more of them in one step to rank).  Scans and extremes by DPP instead of shuffles through LDS,
+// LDS made ready before the scores arrive and the events' weights requested ahead of the partial sums take another 1 to 1.3 us
+// off a call (2243 tokens 33.6 -> 32.3, 5000 in fp32 37.0 -> 35.5).  One workgroup walking 36 tiles is what is left there
 // (0.6 us a tile: its loads, LDS atomics and ballots).
 // ---------------------------------------------------------------------------------------------
 constexpr int kFastSeg = 16;
@@ -1191,22 +1193,14 @@ __device__ __forceinline__ void wave_find_bucket(const int* hist, int need, int*
     int sum = 0;
 #pragma unroll
     for (int u = 0; u < PER; ++u) sum += mine_hist[u];
-    auto scan = [&](int v) {
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int up = __shfl_up(v, off, 64);
-            if (lane >= off) v += up;
-        }
-        return v;
-    };
-    const int incl = scan(sum);
+    const int incl = wave_inclusive_scan(sum);
     *population = __builtin_amdgcn_readlane(incl, 63);
     const unsigned long long m = __ballot(incl - sum < need && incl >= need);
     const int src = m ? __ffsll(static_cast<long long>(m)) - 1 : 0;
     const int left = need - __builtin_amdgcn_readlane(incl - sum, src);      // keys needed from that lane's bins
     const int hi = (64 - src) * PER - 1;                            // the largest digit among them
     const int v = lane < PER ? hist[bin_slot(hi - lane)] : 0;
-    const int incl2 = scan(v);
+    const int incl2 = wave_inclusive_scan(v);
     const unsigned long long m2 = __ballot(incl2 - v < left && incl2 >= left);
     const int at = m2 ? __ffsll(static_cast<long long>(m2)) - 1 : 0;
     *digit = hi - at;
@@ -1246,6 +1240,11 @@ __device__ __forceinline__ void select_and_index(const FastArgs& a, const float*
     int n_tiles = (n_vis + kSelThreads - 1) / kSelThreads;
     const int bits = n_seg <= 4 ? 11 : 9, class_slots = bin_slot(1 << bits);
 
+    // LDS is made ready while nothing else can be done: the scores of the other workgroups are a memory round trip away
+    if (tid == 0) { sh.lo = 0xffffffffu; sh.hi = 0u; }
+    if (tid <= kFastSeg) sh.rule[tid] = make_uint2(0xffffffffu, 0xffffffffu);
+    if (tid < kFastSeg) { sh.fill[tid] = 0; sh.need[tid] = a.quota[blockIdx.z][tid]; sh.cnt[tid] = 0; }
+    for (int i = tid; i < n_seg * class_slots; i += kSelThreads) sh.hist[i] = 0;
     // loads in rounds of up to twenty tokens, without a branch between them
     uint32_t key[K], cls[(K + 3) / 4];      // class kFastSeg: a token without a valid class, never kept
     uint32_t lo = 0xffffffffu, hi = 0u;
@@ -1286,16 +1285,8 @@ __device__ __forceinline__ void select_and_index(const FastArgs& a, const float*
         for (int i = 0; i < (K + 3) / 4; ++i) asm volatile("" : "+v"(cls[i]));
         asm volatile("" : "+s"(n_tiles));
     };
-    if (tid == 0) { sh.lo = 0xffffffffu; sh.hi = 0u; }
-    if (tid <= kFastSeg) sh.rule[tid] = make_uint2(0xffffffffu, 0xffffffffu);
-    if (tid < kFastSeg) { sh.fill[tid] = 0; sh.need[tid] = a.quota[blockIdx.z][tid]; sh.cnt[tid] = 0; }
-    for (int i = tid; i < n_seg * class_slots; i += kSelThreads) sh.hist[i] = 0;
+    lo = wave_extreme<false>(lo); hi = wave_extreme<true>(hi);
     __syncthreads();
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const uint32_t l2 = __shfl_xor(lo, off, 64), h2 = __shfl_xor(hi, off, 64);
-        lo = l2 < lo ? l2 : lo; hi = h2 > hi ? h2 : hi;
-    }
     if (lane == 0) { atomicMin(&sh.lo, lo); atomicMax(&sh.hi, hi); }
     __syncthreads();
     lo = sh.lo;
@@ -1438,12 +1429,7 @@ __device__ __forceinline__ void select_and_index(const FastArgs& a, const float*
                 const int g = lane * kPer + u;
                 if (g < n_groups) mine += __popcll(members(g));
             }
-            int incl = mine;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const int up = __shfl_up(incl, off, 64);
-                if (lane >= off) incl += up;
-            }
+            const int incl = wave_inclusive_scan(mine);
             int room = sh.need[wave] - (incl - mine);
             for (int u = 0; u < kPer && room > 0; ++u) {
                 const int g = lane * kPer + u;
@@ -1458,7 +1444,7 @@ __device__ __forceinline__ void select_and_index(const FastArgs& a, const float*
         __syncthreads();
     }
     int total = 0;
-    const int before = block_exclusive_scan(tid < n_tiles * 16 ? __popcll(sh.kept[tid]) : 0, sh.scan, &total);
+    const int before = block_exclusive_scan_lds(tid < n_tiles * 16 ? __popcll(sh.kept[tid]) : 0, sh.scan, &total);
     if (tid < n_tiles * 16) sh.before[tid] = before;
     __syncthreads();
     asm volatile("" : "+s"(n_tiles));
@@ -1494,6 +1480,14 @@ __global__ __launch_bounds__(kSelThreads) void score_select_kernel(const FastArg
         const int t = tid % tokens, quarter = tid / tokens;
         const int j = blockIdx.x * tokens + t, jc = min(j, a.n_vis - 1);
         const int per = (a.n_parts + split - 1) / split, p0 = quarter * per, p1 = min(a.n_parts, p0 + per);
+        // the event and its weight are requested ahead of the sums: two dependent loads behind them are 0.7 us more
+        float w = 1.f;
+        if (quarter == 0 && a.event_weight) {
+            const int32_t* token_event = of_video_elems(a.token_event, a.n_vis);
+            int e = token_event[jc];
+            e = e < 0 ? 0 : (e >= a.n_events ? a.n_events - 1 : e);
+            w = of_video_elems(a.event_weight, a.n_events)[e];
+        }
         float acc = 0.f;
         for (int p = p0; p < p1; p += 4) {
             float v[4];
@@ -1501,13 +1495,6 @@ __global__ __launch_bounds__(kSelThreads) void score_select_kernel(const FastArg
             for (int u = 0; u < 4; ++u) v[u] = colpart[static_cast<size_t>(min(p + u, p1 - 1)) * a.n_vis + jc];
 #pragma unroll
             for (int u = 0; u < 4; ++u) acc += p + u < p1 ? v[u] : 0.f;
-        }
-        float w = 1.f;
-        if (quarter == 0 && a.event_weight) {
-            const int32_t* token_event = of_video_elems(a.token_event, a.n_vis);
-            int e = token_event[jc];
-            e = e < 0 ? 0 : (e >= a.n_events ? a.n_events - 1 : e);
-            w = of_video_elems(a.event_weight, a.n_events)[e];
         }
         if (split > 1) {
             if (quarter > 0) part[(quarter - 1) * tokens + t] = acc;
