@@ -2,7 +2,8 @@
 //
 //   row_stats_kernel     MFMA pass 1 over all keys: per (head, text query) running max and sum of the
 //                        causal softmax, in the log2 domain, per workgroup; leaves the queries in MFMA fragment order
-//   merge_stats_kernel   merges the per-workgroup (max, sum) pairs into one normaliser per row
+//   merge_stats_kernel   merges the per-workgroup partial sums into one normaliser per row (pass 2 does it for itself where
+//                        they are few)
 //   col_sums_kernel      MFMA pass 2 over the visual keys: recomputes the logits and adds up the
 //                        probabilities of every visual key over the rows of a workgroup
 //   narrow_row_stats_kernel, narrow_col_sums_kernel   the two passes for at most 64 query rows per kv head
@@ -259,6 +260,20 @@ __device__ __forceinline__ void softmax_step_masked(const f32x16_t& acc, float s
     m = m_new;
 }
 
+// (m, l) stands for the sum l 2^m.
+__device__ __forceinline__ void merge_softmax(float& m, float& l, float m2, float l2) {
+    const float mm = fmaxf(m, m2);
+    l = l * fast_exp2(m - mm) + l2 * fast_exp2(m2 - mm);
+    m = mm;
+}
+
+// What pass 1 leaves of a workgroup's rows: their m, then their l (the sum of 2^logit over the workgroup's keys is l 2^m; one
+// number, m + log2 l, would be half of it, but the sum of 40 rounded logarithms is measurably further from the row's).
+__device__ __forceinline__ void store_partial(float* pstat, int rows, int r, float m, float l) {
+    float* dst = pstat + (static_cast<size_t>(blockIdx.y) * gridDim.x + blockIdx.x) * rows * 2 + r;
+    dst[0] = m;
+    dst[rows] = l;
+}
 constexpr int kStageBuffers = 3;       // LDS stages: one in use, one ready (its first fragments are read early), one being filled
 
 // ---------------------------------------------------------------------------------------------
@@ -266,7 +281,7 @@ constexpr int kStageBuffers = 3;       // LDS stages: one in use, one ready (its
 // blockIdx.y = kvh * rs + split.  The product is taken as keys x queries, so a lane's 16 accumulators
 // are 16 keys of ONE query row (row = lane % 32) and the online softmax state is one (max, sum) pair
 // per lane and row block, in the log2 domain.
-// pstat[((y * gridDim.x + x) * rbw * 32 + local_row) * 2 + {0, 1}]
+// pstat[((y * gridDim.x + x) * 2 + {0, 1}) * rbw * 32 + local_row]: see store_partial
 //
 // Key stages are fetched two ahead (global -> registers at the top of a stage, registers -> LDS at its
 // end, one barrier per stage).  A wave that owns two row blocks runs the stages in which every key is
@@ -442,13 +457,69 @@ __global__ __launch_bounds__(kScoreThreads) void row_stats_kernel(const T* __res
             const float m2 = __shfl_xor(m[i], 32, 64), l2 = __shfl_xor(l[i], 32, 64);
             const float mm = fmaxf(m[i], m2);
             const float ll = l[i] * fast_exp2(m[i] - mm) + l2 * fast_exp2(m2 - mm);
-            if (h == 0) {
-                float* dst = pstat + ((static_cast<size_t>(blockIdx.y) * gridDim.x + blockIdx.x) * rows_per_y + rbl * 32 + lane) * 2;
-                dst[0] = mm;
-                dst[1] = ll;
-            }
+            if (h == 0) store_partial(pstat, rows_per_y, rbl * 32 + lane, mm, ll);
         }
     }
+}
+
+// (m, l) takes in N partials; those from `in` on are repetitions and do not count.
+template <int N>
+__device__ __forceinline__ void merge_partials(float& m, float& l, const float (&pm)[N], const float (&pl)[N], int in) {
+    float mx = m;
+#pragma unroll
+    for (int u = 0; u < N; ++u) mx = fmaxf(mx, pm[u]);
+    float sum = 0.f;
+#pragma unroll
+    for (int u = 0; u < N; ++u) sum += u < in ? pl[u] * fast_exp2(pm[u] - mx) : 0.f;
+    l = l * fast_exp2(m - mx) + sum;
+    m = mx;
+}
+__device__ __forceinline__ float row_norm(float m, float l, bool is_row) { return is_row && l > 0.f ? m + log2f(l) : kPosBig; }
+
+// Normalisers of the rows of one workgroup row from the partials that the nx workgroups of pass 1 left, by
+// every workgroup of pass 2 for itself: norm[r] = log2 of the row's whole sum, +big for padding rows.  Four neighbouring rows
+// per 16-byte load, the threads of a row spread over the workgroups, and a thread's loads (16 in a round) on their way together,
+// in the shadow of those for the keys and queries.  Called by the whole workgroup; ends with a barrier.
+struct MergeShared { float4 m[kScoreThreads], l[kScoreThreads]; };
+__device__ __forceinline__ void merge_rows(const float* __restrict__ part, int nx, int rows, int first_row, int R, MergeShared& sh, float* norm) {
+    constexpr int kBatch = 8;
+    const int lg = 32 - __clz(rows / 4 - 1);                        // rows / 4 <= 2^lg <= kScoreThreads / 4; rows is a multiple of 32
+    const int quad = threadIdx.x & ((1 << lg) - 1), g = threadIdx.x >> lg, groups = kScoreThreads >> lg;
+    const float4* src = reinterpret_cast<const float4*>(part) + min(quad, rows / 4 - 1);
+    float m[4], l[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { m[i] = kNegBig; l[i] = 0.f; }
+    for (int x0 = g; x0 < nx; x0 += groups * kBatch) {
+        float4 vm[kBatch], vl[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const float4* p = src + static_cast<size_t>(min(x0 + u * groups, nx - 1)) * (rows / 2);      // past the end: the last one again
+            vm[u] = p[0]; vl[u] = p[rows / 4];
+        }
+        const int in = (nx - x0 + groups - 1) / groups;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float pm[kBatch], pl[kBatch];
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                pm[u] = i == 0 ? vm[u].x : i == 1 ? vm[u].y : i == 2 ? vm[u].z : vm[u].w;
+                pl[u] = i == 0 ? vl[u].x : i == 1 ? vl[u].y : i == 2 ? vl[u].z : vl[u].w;
+            }
+            merge_partials(m[i], l[i], pm, pl, in);
+        }
+    }
+    sh.m[threadIdx.x] = make_float4(m[0], m[1], m[2], m[3]);
+    sh.l[threadIdx.x] = make_float4(l[0], l[1], l[2], l[3]);
+    lds_barrier();
+    const int r = threadIdx.x;
+    if (r < rows) {
+        const float* pm = reinterpret_cast<const float*>(sh.m) + r;
+        const float* pl = reinterpret_cast<const float*>(sh.l) + r;
+        float mm = pm[0], ll = pl[0];
+        for (int k = 1; k < groups; ++k) merge_softmax(mm, ll, pm[(k << lg) * 4], pl[(k << lg) * 4]);
+        norm[r] = row_norm(mm, ll, first_row + r < R);
+    }
+    lds_barrier();
 }
 
 // norm[y * rbw * 32 + local_row] = log2-domain normaliser max + log2(sum) of the row (+big for padding rows).
@@ -465,11 +536,8 @@ __global__ __launch_bounds__(256) void merge_stats_kernel(const float* __restric
     if (i < total) {
         y = i / rows_per_y; lr = i % rows_per_y;
         for (int x = p; x < nx; x += 16) {
-            const float* src = pstat + ((static_cast<size_t>(y) * nx + x) * rows_per_y + lr) * 2;
-            const float m2 = src[0], l2 = src[1];
-            const float mx = fmaxf(mm, m2);
-            ll = ll * fast_exp2(mm - mx) + l2 * fast_exp2(m2 - mx);
-            mm = mx;
+            const float* src = pstat + (static_cast<size_t>(y) * nx + x) * rows_per_y * 2 + lr;
+            merge_softmax(mm, ll, src[0], src[rows_per_y]);
         }
     }
 #pragma unroll
@@ -481,7 +549,7 @@ __global__ __launch_bounds__(256) void merge_stats_kernel(const float* __restric
     }
     if (i < total && p == 0) {
         const int r = (y % g.rs) * rows_per_y + lr;
-        norm[i] = (r < g.R && ll > 0.f) ? mm + log2f(ll) : kPosBig;
+        norm[i] = row_norm(mm, ll, r < g.R);
     }
 }
 
@@ -494,16 +562,18 @@ __global__ __launch_bounds__(256) void merge_stats_kernel(const float* __restric
 template <typename T, int NCH, int RBW, int SUBS>
 __global__ __launch_bounds__(kScoreThreads) void col_sums_kernel(const uint4* __restrict__ qfrag, const T* __restrict__ k_all,
                                                                  const ScoreGeom g, int sub_per_wg, const float* __restrict__ norm,
-                                                                 float* __restrict__ colpart) {
+                                                                 const float* __restrict__ pstat, int nx1, float* __restrict__ colpart) {
     using Stage = KeyStage<T, NCH, SUBS>;
     extern __shared__ uint4 lds[];                      // two stages, then the column partials [2][waves][stage keys]
     float* cs = reinterpret_cast<float*>(lds + 2 * Stage::kSlots);
+    __shared__ MergeShared red;
+    __shared__ __align__(16) float own_norm[kScoreThreads];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5;
     const int kvh = blockIdx.y / g.rs, split = blockIdx.y % g.rs;
     const int rb0 = split * g.rbw;
     const int nrb = min(g.rbw, g.rb_total - rb0);
     const int nrb_w = nrb > wave ? (nrb - wave + kScoreWaves - 1) / kScoreWaves : 0;
-    qfrag = of_video(qfrag, g.ws_video); norm = of_video(norm, g.ws_video); colpart = of_video(colpart, g.ws_video);
+    qfrag = of_video(qfrag, g.ws_video); norm = of_video(norm, g.ws_video); pstat = of_video(pstat, g.ws_video); colpart = of_video(colpart, g.ws_video);
     const T* k_head = of_video_elems(k_all, g.k_video) + static_cast<size_t>(kvh) * g.S * g.dh;
 
     const int vb = blockIdx.x * sub_per_wg * 32;                       // visual keys [vb, ve) of this workgroup
@@ -514,12 +584,17 @@ __global__ __launch_bounds__(kScoreThreads) void col_sums_kernel(const uint4* __
 
     uint4 q[RBW][NCH];
     load_qfrag<NCH, RBW>(q, qfrag, g, kvh, rb0, nrb, wave, lane);
+    const float* rows_norm = norm + static_cast<size_t>(blockIdx.y) * g.rbw * 32;
+    if (pstat) {                                                        // no kernel has merged the partials
+        merge_rows(pstat + static_cast<size_t>(blockIdx.y) * nx1 * g.rbw * 64, nx1, g.rbw * 32, rb0 * 32, g.R, red, own_norm);
+        rows_norm = own_norm;
+    }
     // accumulator e <-> query row 32 rbl + 8 (e / 4) + 4 h + e % 4
     float cr[RBW][16];
 #pragma unroll
     for (int i = 0; i < RBW; ++i) {
         const int rbl = wave + kScoreWaves * i;
-        const float* src = norm + static_cast<size_t>(blockIdx.y) * g.rbw * 32 + (rbl < g.rbw ? rbl : 0) * 32 + 4 * h;
+        const float* src = rows_norm + (rbl < g.rbw ? rbl : 0) * 32 + 4 * h;
 #pragma unroll
         for (int b4 = 0; b4 < 4; ++b4) {
             const float4 c4 = *reinterpret_cast<const float4*>(src + 8 * b4);
@@ -646,13 +721,6 @@ __device__ __forceinline__ void walk_subtiles(u32x4_t (&k)[DEPTH][NCH], int n, L
     }
 }
 
-// (m, l) stands for the sum l 2^m.
-__device__ __forceinline__ void merge_softmax(float& m, float& l, float m2, float l2) {
-    const float mm = fmaxf(m, m2);
-    l = l * fast_exp2(m - mm) + l2 * fast_exp2(m2 - mm);
-    m = mm;
-}
-
 // pass 1 (see row_stats_kernel): keys x queries, a lane's 4 accumulators are 4 keys (4 (lane / 16) + e) of query row lane % 16.
 template <typename T, int NCH, int NB>
 __global__ __launch_bounds__(kScoreThreads) void narrow_row_stats_kernel(const T* __restrict__ q_text, const T* __restrict__ k_all,
@@ -741,19 +809,21 @@ __global__ __launch_bounds__(kScoreThreads) void narrow_row_stats_kernel(const T
         float2 a = red[0][threadIdx.x];
 #pragma unroll
         for (int w = 1; w < kScoreWaves; ++w) { const float2 o = red[w][threadIdx.x]; merge_softmax(a.x, a.y, o.x, o.y); }
-        *reinterpret_cast<float2*>(pstat + ((static_cast<size_t>(blockIdx.y) * gridDim.x + blockIdx.x) * rows_per_y + threadIdx.x) * 2) = a;
+        store_partial(pstat, rows_per_y, threadIdx.x, a.x, a.y);
     }
 }
 
 // pass 2 (see col_sums_kernel): queries x keys, a lane's 4 accumulators are 4 rows (4 (lane / 16) + e) of key lane % 16.
 template <typename T, int NCH, int NB>
 __global__ __launch_bounds__(kScoreThreads) void narrow_col_sums_kernel(const T* __restrict__ q_text, const T* __restrict__ k_all,
-                                                                        const ScoreGeom g, int sub_per_wg, const float* __restrict__ norm,
-                                                                        float* __restrict__ colpart) {
+                                                                        const ScoreGeom g, int sub_per_wg, const float* __restrict__ pstat,
+                                                                        int nx1, float* __restrict__ colpart) {
+    __shared__ MergeShared red;
+    __shared__ __align__(16) float norm[64];
     constexpr int DEPTH = subtile_depth(NCH, NB);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), h = lane >> 4;
     const int kvh = blockIdx.y;
-    q_text = of_video_elems(q_text, g.q_video); norm = of_video(norm, g.ws_video); colpart = of_video(colpart, g.ws_video);
+    q_text = of_video_elems(q_text, g.q_video); pstat = of_video(pstat, g.ws_video); colpart = of_video(colpart, g.ws_video);
     const T* k_head = of_video_elems(k_all, g.k_video) + (static_cast<size_t>(kvh) * g.S + g.vis_start) * g.dh;
     const int vb = blockIdx.x * sub_per_wg * 32;                       // visual keys [vb, ve) of this workgroup
     const int ve = min(g.n_vis, vb + sub_per_wg * 32);
@@ -762,14 +832,16 @@ __global__ __launch_bounds__(kScoreThreads) void narrow_col_sums_kernel(const T*
     auto load = [&](u32x4_t (&dst)[NCH], int t) { load_fragments<T, NCH>(dst, k_head, vb + (wave + t * kScoreWaves) * kSubKeys, ve - 1, g.dh); };
     u32x4_t k[DEPTH][NCH], q[NB][NCH];
     load_queries<T, NCH, NB>(q, q_text, g, kvh);
+#pragma unroll
+    for (int d = 0; d < DEPTH - 1; ++d) load(k[d], d);
+    const int rows = g.rbw * 32;                                       // 32 or 64; NB * 16 of them are used
+    merge_rows(pstat + static_cast<size_t>(kvh) * nx1 * rows * 2, nx1, rows, 0, g.R, red, norm);
     float cr[NB][4];
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
-        const float4 c4 = *reinterpret_cast<const float4*>(norm + static_cast<size_t>(kvh) * g.rbw * 32 + b * 16 + 4 * h);       // +big for padding rows
+        const float4 c4 = *reinterpret_cast<const float4*>(norm + b * 16 + 4 * h);       // +big for padding rows
         cr[b][0] = c4.x; cr[b][1] = c4.y; cr[b][2] = c4.z; cr[b][3] = c4.w;
     }
-#pragma unroll
-    for (int d = 0; d < DEPTH - 1; ++d) load(k[d], d);
     walk_subtiles<NCH, DEPTH>(k, n, load, [&](const u32x4_t (&kf)[NCH], int t) {
         float sum[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -1683,6 +1755,13 @@ static bool dh_supported(int dh, int dtype) {
     return dh == 32 || dh == 64 || dh == 128;
 }
 
+// Up to here every workgroup of pass 2 merges the partial statistics of its rows for itself, above a kernel in between does it
+// once.  One level, us, merged in pass 2 / by the kernel: 300 tokens, 448 rows x 11 partials (40 KB) 28.6 / 30.2; 32 heads on 8, 256
+// x 32 (64 KB) 51.9 / 51.9; two videos of 4000 tokens, 448 x 32 (112 KB) 41.2 / 40.6; one of 3700, 448 x 59 (206 KB) 33.4 / 32.6; 14
+// heads on 2, 448 x 128 35.4 / 31.8; 7 heads on 1, 448 x 256 40.7 / 34.7: the exponentials of a large merge take longer than the
+// launch.  The narrow kernels have at most 64 rows and always merge for themselves.
+constexpr size_t kMergeInPass2Bytes = 64 * 1024;
+
 // Row blocks of 16 that the narrow kernels take for this shape, 0: the shape is not theirs.  bf16 rows of at most four
 // chunks per lane: with eight (256 elements) fewer subtiles are on their way beside the queries (row statistics of
 // 9000 keys of 256: 8.5 us above, 11.1 us here); fp32 products take sixteen times the matrix time, so there eight busy waves
@@ -1694,16 +1773,13 @@ static int narrow_blocks(const ScoreGeom& g, int nch16, bool f32) {
 template <typename T, int NCH16, int NB>
 static void launch_narrow_scores(const void* q, const void* k, const ScoreGeom& g, const ScorePlan& p, char* ws, int batch, hipStream_t st) {
     float* pstat = reinterpret_cast<float*>(ws + p.off_pstat);
-    float* norm = reinterpret_cast<float*>(ws + p.off_norm);
     float* colpart = reinterpret_cast<float*>(ws + p.off_colpart);
     const unsigned nb = static_cast<unsigned>(batch);
     { TraceScope trace_scope(METOK_TRACE_ROW_STATS, st); hipLaunchKernelGGL((narrow_row_stats_kernel<T, NCH16, NB>), dim3(p.nx1, g.Hkv, nb), dim3(kScoreThreads), 0, st,
                        static_cast<const T*>(q), static_cast<const T*>(k), g, p.per1, pstat,
                        reinterpret_cast<uint32_t*>(ws + p.off_sel + select_general_bytes(g.n_vis)), kFastClearWords); }
-    const int total_rows = g.Hkv * g.rbw * 32;
-    hipLaunchKernelGGL(merge_stats_kernel, dim3((total_rows + 15) / 16, 1, nb), dim3(256), 0, st, pstat, g, p.nx1, norm);
     { TraceScope trace_scope(METOK_TRACE_COL_SUMS, st); hipLaunchKernelGGL((narrow_col_sums_kernel<T, NCH16, NB>), dim3(p.nx2, g.Hkv, nb), dim3(kScoreThreads), 0, st,
-                       static_cast<const T*>(q), static_cast<const T*>(k), g, p.per2, norm, colpart); }
+                       static_cast<const T*>(q), static_cast<const T*>(k), g, p.per2, pstat, p.nx1, colpart); }
 }
 
 template <typename T, int NCH>
@@ -1739,14 +1815,18 @@ static void launch_scores(const void* q, const void* k, const ScoreGeom& g, cons
             hipLaunchKernelGGL((row_stats_kernel<T, NCH, RBW, SUBS>), dim3(p.nx1, ny, nb), dim3(kScoreThreads), lds1, st, static_cast<const T*>(q),
                                static_cast<const T*>(k), g, p.per1, pstat, qfrag, clear, kFastClearWords);
     }
-    const int total_rows = ny * g.rbw * 32;
-    hipLaunchKernelGGL(merge_stats_kernel, dim3((total_rows + 15) / 16, 1, nb), dim3(256), 0, st, pstat, g, p.nx1, norm);
+    const float* unmerged = pstat;
+    if (static_cast<size_t>(p.nx1) * g.rbw * 32 * 2 * sizeof(float) > kMergeInPass2Bytes) {
+        const int total_rows = ny * g.rbw * 32;
+        hipLaunchKernelGGL(merge_stats_kernel, dim3((total_rows + 15) / 16, 1, nb), dim3(256), 0, st, pstat, g, p.nx1, norm);
+        unmerged = nullptr;
+    }
     {
         TraceScope trace_scope(METOK_TRACE_COL_SUMS, st);
         if (g.rbw <= kScoreWaves)
-            hipLaunchKernelGGL((col_sums_kernel<T, NCH, 1, SUBS>), dim3(p.nx2, ny, nb), dim3(kScoreThreads), lds2, st, qfrag, static_cast<const T*>(k), g, p.per2, norm, colpart);
+            hipLaunchKernelGGL((col_sums_kernel<T, NCH, 1, SUBS>), dim3(p.nx2, ny, nb), dim3(kScoreThreads), lds2, st, qfrag, static_cast<const T*>(k), g, p.per2, norm, unmerged, p.nx1, colpart);
         else
-            hipLaunchKernelGGL((col_sums_kernel<T, NCH, RBW, SUBS>), dim3(p.nx2, ny, nb), dim3(kScoreThreads), lds2, st, qfrag, static_cast<const T*>(k), g, p.per2, norm, colpart);
+            hipLaunchKernelGGL((col_sums_kernel<T, NCH, RBW, SUBS>), dim3(p.nx2, ny, nb), dim3(kScoreThreads), lds2, st, qfrag, static_cast<const T*>(k), g, p.per2, norm, unmerged, p.nx1, colpart);
     }
 }
 
