@@ -1,4 +1,8 @@
-"""Thin ctypes binding of libmetok.so: same names as the C calls, argument marshalling only.
+"""Thin binding of libmetok.so: same names as the C calls, argument marshalling only.
+
+The calls a serving program repeats go through the native module _host (csrc/host.cpp) when they have the ordinary form --
+plain contiguous GPU tensors that fit, Python numbers -- and through the ctypes code below, with its checks and messages, when
+they do not.
 
 PyTorch is used for device memory and the current stream; every step of the method runs in
 the HIP kernels.  There is no CPU fallback: importing this module without the compiled library,
@@ -136,6 +140,14 @@ def _load() -> ctypes.CDLL:
 
 
 _lib = _load()
+from . import _host  # noqa: E402  (linked against the library loaded above)
+
+
+def _native(res):
+    """What a native call returned: its outputs, or the code of a call that the library refused."""
+    if type(res) is int:
+        _check(res)
+    return res
 
 
 def lib() -> ctypes.CDLL:
@@ -302,6 +314,11 @@ def metok_segment_compress(feats: torch.Tensor, grid_h: int, grid_w: int, k: int
                            out: Optional[Dict[str, torch.Tensor]] = None) -> Dict[str, torch.Tensor]:
     """Stage 1 in one call: the outputs of metok_segment_events and metok_compress_encoder_tokens together
     (one pass over feats when all frames are pooled with stride 2 on an even grid, else two)."""
+    if out_dtype is None:
+        res = _host.segment_compress(feats, grid_h, grid_w, k, text_emb, alpha, beta, s1, s2, sim_mode, event_reduce, pool_edge,
+                                     workspace, out, _stream)
+        if res is not None:
+            return _native(res)
     T, N, d = feats.shape
     if N != grid_h * grid_w:
         raise ValueError("feats.shape[1] must equal grid_h * grid_w")
@@ -340,6 +357,11 @@ def metok_segment_compress_batched(feats: torch.Tensor, grid_h: int, grid_w: int
                                    out: Optional[Dict[str, torch.Tensor]] = None) -> Dict[str, torch.Tensor]:
     """Stage 1 in one call for a batch of videos: feats [B, T, N, d], text_emb [B, d]; every output of
     metok_segment_compress with a leading batch dimension."""
+    if out_dtype is None:
+        res = _host.segment_compress_batched(feats, grid_h, grid_w, k, text_emb, alpha, beta, s1, s2, sim_mode, event_reduce, pool_edge,
+                                             workspace, out, _stream)
+        if res is not None:
+            return _native(res)
     B, T, N, d = feats.shape
     if N != grid_h * grid_w:
         raise ValueError("feats.shape[2] must equal grid_h * grid_w")
@@ -415,6 +437,10 @@ def metok_prefill_prune(hidden: torch.Tensor, vis_start: int, n_vis: int, token_
                         score_mode: int = 0, static_scratch: bool = False) -> Dict[str, torch.Tensor]:
     """One pruning level.  With q_text/k_all the attention scores are computed; otherwise `scores` is used as given.
     static_scratch=True calls metok_prefill_prune_static (no workspace argument)."""
+    res = _host.prefill_prune(hidden, vis_start, n_vis, token_seg, seg_quota, q_text, k_all, token_event, event_weight, orig_idx, scores,
+                              hidden_out, workspace, out, score_mode, static_scratch, _stream)
+    if res is not None:
+        return _native(res)
     S, D = hidden.shape
     dt = _dtype_code(hidden)
     dev = hidden.device
@@ -481,6 +507,10 @@ def metok_prefill_prune_batched(hidden: torch.Tensor, vis_start: int, n_vis: int
     """One pruning level of a batch of videos of one shape: every tensor of metok_prefill_prune with a leading batch
     dimension, seg_quota one list per video.  Returns the per-video kept counts as `n_keep` (a Python list) beside the
     padded outputs ([B, keep_stride] index lists, [B, out_row_stride, D] hidden states)."""
+    res = _host.prefill_prune_batched(hidden, vis_start, n_vis, token_seg, seg_quota, q_text, k_all, token_event, event_weight, orig_idx,
+                                      scores, hidden_out, workspace, out, score_mode, keep_stride, out_row_stride, _stream)
+    if res is not None:
+        return _native(res)
     B, S, D = hidden.shape
     dt = _dtype_code(hidden)
     dev = hidden.device
@@ -589,6 +619,9 @@ def metok_kv_compact(k_layers: Sequence[torch.Tensor], v_layers: Sequence[torch.
     """In-place compaction of per-layer K/V caches [B, Hkv, S_cap, dh] to idx[l] [B, n_keep_l] (None = untouched).
     `workspace` (uint8, metok_kv_compact_workspace_bytes) is allocated here when not given; after the call its
     first int32 word is 0 unless a bounded wait inside the kernel expired."""
+    res = _host.kv_compact(k_layers, v_layers, None, idx, new_len, workspace, _stream)
+    if res is not None:
+        return _native(res)
     B, Hkv, S_cap, dh = k_layers[0].shape
     L, karr, varr, iarr, nk = _layer_tables(k_layers, v_layers, idx, (B, Hkv, S_cap, dh), B)
     dev = k_layers[0].device
@@ -606,6 +639,10 @@ def metok_kv_compact_paged(k_pools: Sequence[torch.Tensor], v_pools: Sequence[to
                            workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
     """In-place compaction of paged per-layer K/V pools [n_pages, Hkv, page_size, dh] through page_table [B, pages_per_seq]
     to the logical rows idx[l] [B, n_keep_l] (None = untouched)."""
+    if page_table is not None:
+        res = _host.kv_compact(k_pools, v_pools, page_table, idx, new_len, workspace, _stream)
+        if res is not None:
+            return _native(res)
     n_pages, Hkv, page_size, dh = k_pools[0].shape
     if page_table.dtype != torch.int32 or page_table.dim() != 2:
         raise ValueError("page_table must be int32 [B, pages_per_seq]")
@@ -629,6 +666,9 @@ def metok_kv_relink_paged(k_pools: Sequence[torch.Tensor], v_pools: Sequence[tor
     """Compaction of paged per-layer K/V pools [n_pages, Hkv, page_size, dh] by relinking whole pages and copying the rest.
     page_table is [B, pages_per_seq] (shared by the layers) or [L, B, pages_per_seq]; returns page_table_out [L, B, pages],
     free_pages [L, B, pages], n_free [L, B], rows_copied [L, B], new_len [L] and the workspace."""
+    res = _host.kv_relink_paged(k_pools, v_pools, page_table, idx, len_in, workspace, _stream)
+    if res is not None:
+        return _native(res)
     n_pages, Hkv, page_size, dh = k_pools[0].shape
     if page_table.dtype != torch.int32 or page_table.dim() not in (2, 3):
         raise ValueError("page_table must be int32 [B, pages_per_seq] or [L, B, pages_per_seq]")
