@@ -34,8 +34,8 @@ constexpr int kScoreWaves = kScoreThreads / 64;
 constexpr float kNegBig = -1.0e30f;
 constexpr float kPosBig = 1.0e30f;
 
-// v_exp_f32 without the denormal-range fix-up of exp2f(): arguments here are <= 0 and a result below
-// 2^-126 may flush to zero (it is a softmax term that small).
+// v_exp_f32 without the denormal-range fix-up of exp2f(): a result below 2^-126 may flush to zero (it is a softmax term that
+// small).
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 template <typename T> struct Mma;
@@ -133,6 +133,30 @@ struct KeyStage {
 // took 3.2 us a call; this costs pass 1 about 1 us, with eight videos per launch 3 of the kernel's 5 us (one level of 2243
 // tokens, 28 / 4 heads x 64 queries: 35.5 -> 33.4 us, of 5000 in fp32: 39.2 -> 37.0 us, eight videos of 36864 tokens: within
 // the noise).
+//
+// Row blocks of the waves.  Block w belongs to wave w.  Of the x = nrb - 8 blocks beyond, block 8 + w is the second one of wave
+// w; waves w and w + 4 sit on one SIMD, so with x = 1, 2, 5 or 6 one or two SIMDs have a block more than the others and every
+// stage waits for them.  There the last x % 4 second blocks are shared with the waves two further on, which have one block
+// only: the first wave takes subtile 0 of a stage, the other one subtile 1.  28 heads on 4 x 64 queries are 14 blocks (4, 4, 3,
+// 3 a SIMD unshared, 3.5 shared): eight videos of 36864 tokens, pass 1 152 -> 144 us (1.05 PFLOP/s), pass 2 157 -> 151 us.  It
+// costs two waves a load more before the first stage, so short ranges go unshared: 18432 tokens (5 stages) 17.7 -> 17.1 us in
+// pass 1 but 13.8 -> 14.3 in pass 2, 2243 tokens (1 stage) 9.0 -> 9.4 and 6.2 -> 6.5.  Ranges below kMinPipelined stages do
+// not take pass 1's software pipeline either (2243 tokens 9.4 -> 9.2 us).
+constexpr int kMinPipelined = 4, kMinSharedRows = 4, kMinSharedCols = 8;         // stages of a workgroup
+enum class SecondBlock { kNone, kBoth, kSubtile0, kSubtile1 };
+template <int RBW>
+__device__ __forceinline__ SecondBlock second_block(int nrb, int wave, bool share) {
+    const int x = RBW == 2 ? nrb - kScoreWaves : 0, shared_from = share && ((x & 3) == 1 || (x & 3) == 2) ? x & ~3 : x;
+    if (wave < x) return wave < shared_from ? SecondBlock::kBoth : SecondBlock::kSubtile0;
+    return x > 0 && wave - 2 >= shared_from && wave - 2 < x ? SecondBlock::kSubtile1 : SecondBlock::kNone;
+}
+// Row block i of a wave among the workgroup's nrb, -1: it has none.
+template <int RBW>
+__device__ __forceinline__ int wave_block(int nrb, int wave, SecondBlock second, int i) {
+    if (i == 0) return wave < nrb ? wave : -1;
+    return second == SecondBlock::kNone ? -1 : kScoreWaves + wave - (second == SecondBlock::kSubtile1 ? 2 : 0);
+}
+
 template <typename T, int NCH, int RBW>
 struct QueryRows {
     static constexpr int kPieces = 2 * NCH;                                    // 16-byte pieces of a row, a power of two
@@ -142,12 +166,11 @@ struct QueryRows {
     static constexpr size_t kLdsBytes = static_cast<size_t>(kScoreWaves) * kRows * kPieces * sizeof(uint4);
     u32x4_t v[RBW][kRounds][kLoads];
 
-    __device__ __forceinline__ void load(const T* __restrict__ q_text, const ScoreGeom& g, int kvh, int rb0, int nrb, int wave, int lane) {
+    __device__ __forceinline__ void load(const T* __restrict__ q_text, const ScoreGeom& g, int kvh, int rb0, int nrb, int wave, SecondBlock second, int lane) {
         const u32x4_t* rows = reinterpret_cast<const u32x4_t*>(q_text) + static_cast<size_t>(kvh) * g.R * kPieces;
 #pragma unroll
         for (int i = 0; i < RBW; ++i) {
-            const int rbl = wave + kScoreWaves * i;
-            const int r0 = (rb0 + (rbl < nrb ? rbl : 0)) * 32;
+            const int r0 = (rb0 + max(wave_block<RBW>(nrb, wave, second, i), 0)) * 32;
 #pragma unroll
             for (int k = 0; k < kRounds; ++k)
 #pragma unroll
@@ -159,13 +182,13 @@ struct QueryRows {
         }
     }
     // Only the wave itself uses its part of LDS, and a wave's LDS accesses complete in order.
-    __device__ __forceinline__ void to_fragments(uint4 (&q)[RBW][NCH], uint4* lds, const ScoreGeom& g, int rb0, int nrb, int wave, int lane) {
+    __device__ __forceinline__ void to_fragments(uint4 (&q)[RBW][NCH], uint4* lds, const ScoreGeom& g, int rb0, int nrb, int wave, SecondBlock second, int lane) {
         u32x4_t* own = reinterpret_cast<u32x4_t*>(lds) + wave * kRows * kPieces;
         const int row = lane & 31, half = lane >> 5;
 #pragma unroll
         for (int i = 0; i < RBW; ++i) {
-            const int rbl = wave + kScoreWaves * i;
-            const bool ok = rbl < nrb && (rb0 + rbl) * 32 + row < g.R;
+            const int rbl = wave_block<RBW>(nrb, wave, second, i);
+            const bool ok = rbl >= 0 && (rb0 + rbl) * 32 + row < g.R;
 #pragma unroll
             for (int k = 0; k < kRounds; ++k) {
 #pragma unroll
@@ -190,14 +213,14 @@ struct QueryRows {
     }
 };
 
-// q[i][c] belongs to the wave's local row block wave + 8 i.
+// q[i][c] belongs to row block i of the wave.
 template <int NCH, int RBW>
 __device__ __forceinline__ void load_qfrag(uint4 (&q)[RBW][NCH], const uint4* __restrict__ qfrag, const ScoreGeom& g, int kvh,
-                                           int rb0, int nrb, int wave, int lane) {
+                                           int rb0, int nrb, int wave, SecondBlock second, int lane) {
 #pragma unroll
     for (int i = 0; i < RBW; ++i) {
-        const int rbl = wave + kScoreWaves * i;
-        const bool ok = rbl < nrb;
+        const int rbl = wave_block<RBW>(nrb, wave, second, i);
+        const bool ok = rbl >= 0;
         const uint4* src = qfrag + (static_cast<size_t>(kvh) * g.rb_total + rb0 + (ok ? rbl : 0)) * NCH * 64 + lane;
 #pragma unroll
         for (int c = 0; c < NCH; ++c) q[i][c] = ok ? src[c * 64] : make_uint4(0, 0, 0, 0);
@@ -214,17 +237,30 @@ __device__ __forceinline__ f32x16_t mma_chain(const uint4 (&a)[NCH], const uint4
 
 __device__ __forceinline__ float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
 
-// Online softmax step of one lane over its 16 accumulators when every key is visible (log2 domain).
-__device__ __forceinline__ void softmax_step_full(const f32x16_t& acc, float scale_log2, float& m, float& l) {
+__device__ __forceinline__ float max16(const f32x16_t& acc) {
     const float t0 = max3(acc[0], acc[1], acc[2]), t1 = max3(acc[3], acc[4], acc[5]), t2 = max3(acc[6], acc[7], acc[8]),
                 t3 = max3(acc[9], acc[10], acc[11]), t4 = max3(acc[12], acc[13], acc[14]);
-    const float tmax = max3(max3(t0, t1, t2), max3(t3, t4, acc[15]), acc[15]);
-    const float m_new = fmaxf(m, tmax * scale_log2);        // the scale is positive: max commutes with it
+    return max3(max3(t0, t1, t2), max3(t3, t4, acc[15]), acc[15]);
+}
+
+// Softmax steps of one lane over its 16 accumulators (log2 domain).  m, what the terms are relative to, is a whole number not
+// below the largest logit it was taken from, so that scaling a sum to another m is exact.
+__device__ __forceinline__ float reference_above(float logit_max) { return fmaxf(kNegBig, ceilf(logit_max)); }
+
+// Every key is visible and m stays.
+__device__ __forceinline__ void softmax_step_fixed(const f32x16_t& acc, float scale_log2, float m, float& l) {
     float sum = 0.f;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) sum += fast_exp2(fmaf(acc[e], scale_log2, -m_new));
-    l = l * fast_exp2(m - m_new) + sum;
+    for (int e = 0; e < 16; ++e) sum += fast_exp2(fmaf(acc[e], scale_log2, -m));
+    l += sum;
+}
+
+// Every key is visible and m follows the maximum.
+__device__ __forceinline__ void softmax_step_full(const f32x16_t& acc, float scale_log2, float& m, float& l) {
+    const float m_new = fmaxf(m, reference_above(max16(acc) * scale_log2));        // the scale is positive: max commutes with it
+    l *= fast_exp2(m - m_new);
     m = m_new;
+    softmax_step_fixed(acc, scale_log2, m, l);
 }
 
 // Keeps the MFMA chain that produces `acc` inside the scheduling region in which it was written: the value counts as
@@ -252,7 +288,7 @@ __device__ __forceinline__ void softmax_step_masked(const f32x16_t& acc, float s
         vis[e] = 8 * (e >> 2) + 4 * h + (e & 3) <= lim;
         if (vis[e]) tmax = fmaxf(tmax, acc[e] * scale_log2);
     }
-    const float m_new = fmaxf(m, tmax);
+    const float m_new = fmaxf(m, reference_above(tmax));
     float sum = 0.f;
 #pragma unroll
     for (int e = 0; e < 16; ++e) sum += vis[e] ? fast_exp2(fmaf(acc[e], scale_log2, -m_new)) : 0.f;
@@ -284,11 +320,16 @@ constexpr int kStageBuffers = 3;       // LDS stages: one in use, one ready (its
 // pstat[((y * gridDim.x + x) * 2 + {0, 1}) * rbw * 32 + local_row]: see store_partial
 //
 // Key stages are fetched two ahead (global -> registers at the top of a stage, registers -> LDS at its
-// end, one barrier per stage).  A wave that owns two row blocks runs the stages in which every key is
-// visible to every query as one software pipeline over the blocks (subtile, row block): the MFMA chain
+// end, one barrier per stage).  Where a workgroup has a row block for every wave, the stages in which every key is
+// visible to every query run as one software pipeline over a wave's blocks (subtile, row block): the MFMA chain
 // of block b + 1 is interleaved with the softmax arithmetic of block b, also across the barrier, and the
 // fragments of the next stage's first subtile are read from LDS as soon as their registers are free.
 // Stages that need the mask, and workgroups with fewer row blocks than waves, take the plain path.
+//
+// m is taken from a lane's keys of the first subtile and stays while whole subtiles are visible: terms relative to it keep
+// their precision as long as none exceeds it by 2^127, and following the maximum is 14 of the 64 vector instructions of a
+// block (eight videos of 36864 tokens: 160 -> 152 us).  A workgroup whose sums left the range of float starts over with the
+// maximum.
 // ---------------------------------------------------------------------------------------------
 template <typename T, int NCH, int RBW, int SUBS>
 __global__ __launch_bounds__(kScoreThreads) void row_stats_kernel(const T* __restrict__ q_text, const T* __restrict__ k_all,
@@ -296,11 +337,12 @@ __global__ __launch_bounds__(kScoreThreads) void row_stats_kernel(const T* __res
                                                                   uint4* __restrict__ qfrag, uint32_t* __restrict__ clear, int n_clear) {
     using Stage = KeyStage<T, NCH, SUBS>;
     extern __shared__ uint4 lds[];                      // the waves' query rows, then kStageBuffers stages
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), h = lane >> 5;
     const int kvh = blockIdx.y / g.rs, split = blockIdx.y % g.rs;
     const int rb0 = split * g.rbw;
     const int nrb = min(g.rbw, g.rb_total - rb0);
-    const int nrb_w = nrb > wave ? (nrb - wave + kScoreWaves - 1) / kScoreWaves : 0;     // row blocks of this wave
+    __shared__ int left_range[kScoreWaves];
+    __shared__ float2 shared_rows[2][64];
     q_text = of_video_elems(q_text, g.q_video);
     qfrag = of_video(qfrag, g.ws_video); pstat = of_video(pstat, g.ws_video); clear = of_video(clear, g.ws_video);
     const T* k_head = of_video_elems(k_all, g.k_video) + static_cast<size_t>(kvh) * g.S * g.dh;
@@ -312,6 +354,9 @@ __global__ __launch_bounds__(kScoreThreads) void row_stats_kernel(const T* __res
     const int n_stage = static_cast<int>((ke - kb + Stage::kKeys - 1) / Stage::kKeys);
     const int64_t text_start = g.S - g.Tq;
     const int64_t full_end = text_start < ke ? text_start : ke;
+    const SecondBlock second = second_block<RBW>(nrb, wave, n_stage >= kMinSharedRows);
+    // row blocks of this wave on the plain path, which shares none
+    const int nrb_w = wave < nrb ? (second == SecondBlock::kBoth || second == SecondBlock::kSubtile0 ? 2 : 1) : 0;
 
     // the first two key stages and the queries are requested together: one memory round trip
     u32x4_t kv[Stage::kPerThread], kv1[Stage::kPerThread];
@@ -320,13 +365,11 @@ __global__ __launch_bounds__(kScoreThreads) void row_stats_kernel(const T* __res
     uint4 q[RBW][NCH];
     {
         QueryRows<T, NCH, RBW> rows;
-        rows.load(q_text, g, kvh, rb0, nrb, wave, lane);
-        rows.to_fragments(q, lds, g, rb0, nrb, wave, lane);
+        rows.load(q_text, g, kvh, rb0, nrb, wave, second, lane);
+        rows.to_fragments(q, lds, g, rb0, nrb, wave, second, lane);
         __syncthreads();                                // the stages take over the waves' parts of LDS
     }
     float m[RBW], l[RBW];
-#pragma unroll
-    for (int i = 0; i < RBW; ++i) { m[i] = kNegBig; l[i] = 0.f; }
     Stage::store(kv, lds);
     if (n_stage > 1) Stage::store(kv1, lds + Stage::kSlots);
     // Every load issued so far has to land before the loop: with query loads still pending at its head the
@@ -343,105 +386,140 @@ __global__ __launch_bounds__(kScoreThreads) void row_stats_kernel(const T* __res
         __syncthreads();
     };
 
+    // stages s, s + 1, ... on the plain path; `online`: m follows the maximum
+    auto plain_stages = [&](int s, auto online_tag) {
+        constexpr bool online = decltype(online_tag)::value;
+        for (; s < n_stage; ++s) {
+            const uint4* kbuf = stage_buf(s);
+            const int64_t js = kb + static_cast<int64_t>(s) * Stage::kKeys;
+            prefetch(s);
+#pragma unroll
+            for (int sub = 0; sub < SUBS; ++sub) {
+                const int64_t j0 = js + sub * 32;
+                if (j0 < ke && nrb_w > 0) {
+                    uint4 kf[NCH];
+#pragma unroll
+                    for (int c = 0; c < NCH; ++c) kf[c] = kbuf[(sub * NCH + c) * 64 + lane];
+                    const bool full = j0 + 32 <= full_end;      // every key of the subtile is visible to every query
+#pragma unroll
+                    for (int i = 0; i < RBW; ++i) {
+                        if (i < nrb_w) {
+                            const f32x16_t acc = mma_chain<T, NCH>(kf, q[i]);
+                            if (full && !online && j0 > kb) {
+                                softmax_step_fixed(acc, g.scale_log2, m[i], l[i]);
+                            } else if (full) {
+                                softmax_step_full(acc, g.scale_log2, m[i], l[i]);
+                            } else {
+                                const int r = (rb0 + wave + kScoreWaves * i) * 32 + (lane & 31);
+                                int64_t last = text_start + (r % g.Tq);            // causal: keys 0..last, and below ke
+                                last = last < ke - 1 ? last : ke - 1;
+                                const int64_t d = last - j0;
+                                const int lim = d < 0 ? -1 : (d > 31 ? 31 : static_cast<int>(d));
+                                softmax_step_masked(acc, g.scale_log2, h, lim, m[i], l[i]);
+                            }
+                        }
+                    }
+                }
+            }
+            publish(s);
+        }
+    };
+
+#pragma unroll
+    for (int i = 0; i < RBW; ++i) { m[i] = kNegBig; l[i] = 0.f; }
     int s = 0;
     if constexpr (RBW == 2 && SUBS == 2) {
-        // leading stages whose 64 keys are all visible to every query
-        // The choice is the same for every wave of the workgroup (all waves must meet at the same barriers):
-        // with at least one row block per wave, waves that own a single block run the second chain on the
-        // zero fragments QueryRows::to_fragments left them; its statistics belong to a padding row and are ignored.
+        // Leading stages whose 64 keys are all visible to every query.  The choice is the same for every wave of the workgroup,
+        // and whatever its row blocks are a wave meets the others at one barrier per stage.
         int n_fast = 0;
         if (nrb >= kScoreWaves) {
             const int64_t f = (full_end - kb) / Stage::kKeys;
-            n_fast = f < 0 ? 0 : (f > n_stage ? n_stage : static_cast<int>(f));
+            n_fast = f < kMinPipelined ? 0 : (f > n_stage ? n_stage : static_cast<int>(f));
         }
         if (n_fast > 0) {
             constexpr int kMfmas = NCH * Mma<T>::kMfmaPerChunk;
-            constexpr int kValu = (64 + kMfmas - 1) / kMfmas;
+            constexpr int kValu = (49 + kMfmas - 1) / kMfmas;
+            const int first = second == SecondBlock::kSubtile1 ? NCH * 64 : 0, later = NCH * 64 - first;
             uint4 kf0[NCH], kf1[NCH];
 #pragma unroll
-            for (int c = 0; c < NCH; ++c) kf0[c] = lds[c * 64 + lane];
-            f32x16_t A = mma_chain<T, NCH>(kf0, q[0]), B;
-            // The body is branch-free so that the whole stage is one scheduling region: loads and stores
-            // that a conditional would skip are done anyway on clamped addresses (a stage is fetched twice,
-            // a free buffer is overwritten, the chain started for a stage that is not fast is dropped).
+            for (int c = 0; c < NCH; ++c) kf0[c] = lds[c * 64 + lane + first];
+            f32x16_t A, B = mma_chain<T, NCH>(kf0, q[1]);
+            m[1] = reference_above(max16(B) * g.scale_log2);
+            A = mma_chain<T, NCH>(kf0, q[0]);
+            m[0] = reference_above(max16(A) * g.scale_log2);
+            // the product of one block beside the softmax arithmetic of the block before
+            auto phase = [&](f32x16_t& next, const uint4 (&kf)[NCH], const uint4 (&qf)[NCH], const f32x16_t& acc, int i) {
+                next = mma_chain<T, NCH>(kf, qf);
+                softmax_step_fixed(acc, g.scale_log2, m[i], l[i]);
+                interleave_mfma_valu<kMfmas, kValu>();
+                pin_accumulators(next);
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            // Which subtile of a stage comes first is a wave's own choice: one that shares a block takes its subtile of it
+            // first, so that both waves of a pair do the same, block 0, block 1, block 0 of the other subtile.  The loads and
+            // stores are free of branches, on clamped addresses (a stage is fetched twice, a free buffer is overwritten,
+            // the product started for a stage that is not fast is dropped).
             for (; s < n_fast; ++s) {
                 const uint4* kbuf = stage_buf(s);
                 const int s2 = s + 2 < n_stage ? s + 2 : n_stage - 1;
                 Stage::load(kv, k_head, kb + static_cast<int64_t>(s2) * Stage::kKeys, g.S, g.dh);
 #pragma unroll
-                for (int c = 0; c < NCH; ++c) kf1[c] = kbuf[(NCH + c) * 64 + lane];
+                for (int c = 0; c < NCH; ++c) kf1[c] = kbuf[c * 64 + lane + later];
                 __builtin_amdgcn_sched_barrier(0);
-                B = mma_chain<T, NCH>(kf0, q[1]);
-                softmax_step_full(A, g.scale_log2, m[0], l[0]);
-                interleave_mfma_valu<kMfmas, kValu>();
-                pin_accumulators(B);
-                __builtin_amdgcn_sched_barrier(0);
-                {   // subtile 0 of the next stage: published before the previous barrier
+                phase(B, kf0, q[1], A, 0);
+                {   // first subtile of the next stage: published before the previous barrier
                     const uint4* knext = stage_buf(s + 1);
 #pragma unroll
-                    for (int c = 0; c < NCH; ++c) kf0[c] = knext[c * 64 + lane];
+                    for (int c = 0; c < NCH; ++c) kf0[c] = knext[c * 64 + lane + first];
                 }
                 __builtin_amdgcn_sched_barrier(0);
-                A = mma_chain<T, NCH>(kf1, q[0]);
-                softmax_step_full(B, g.scale_log2, m[1], l[1]);
-                interleave_mfma_valu<kMfmas, kValu>();
-                pin_accumulators(A);
-                __builtin_amdgcn_sched_barrier(0);
-                B = mma_chain<T, NCH>(kf1, q[1]);
-                softmax_step_full(A, g.scale_log2, m[0], l[0]);
-                interleave_mfma_valu<kMfmas, kValu>();
-                pin_accumulators(B);
-                __builtin_amdgcn_sched_barrier(0);
-                Stage::template store<true>(kv, stage_buf(s + 2));
-                __syncthreads();
-                __builtin_amdgcn_sched_barrier(0);
-                A = mma_chain<T, NCH>(kf0, q[0]);
-                softmax_step_full(B, g.scale_log2, m[1], l[1]);
-                interleave_mfma_valu<kMfmas, kValu>();
-                pin_accumulators(A);
-                __builtin_amdgcn_sched_barrier(0);
+                phase(A, kf1, q[0], B, 1);
+                if (second == SecondBlock::kBoth) {
+                    phase(B, kf1, q[1], A, 0);
+                    Stage::template store<true>(kv, stage_buf(s + 2));
+                    __syncthreads();
+                    __builtin_amdgcn_sched_barrier(0);
+                    phase(A, kf0, q[0], B, 1);
+                } else {
+                    Stage::template store<true>(kv, stage_buf(s + 2));
+                    __syncthreads();
+                    __builtin_amdgcn_sched_barrier(0);
+                    phase(B, kf0, q[0], A, 0);
+                    A = B;
+                }
             }
         }
     }
-    for (; s < n_stage; ++s) {
-        const uint4* kbuf = stage_buf(s);
-        const int64_t js = kb + static_cast<int64_t>(s) * Stage::kKeys;
-        prefetch(s);
+    plain_stages(s, std::integral_constant<bool, false>{});
+    bool bad = false;
 #pragma unroll
-        for (int sub = 0; sub < SUBS; ++sub) {
-            const int64_t j0 = js + sub * 32;
-            if (j0 < ke && nrb_w > 0) {
-                uint4 kf[NCH];
+    for (int i = 0; i < RBW; ++i) bad = bad || !(l[i] <= 3.0e38f);
+    // one barrier for both: the flags, and the sums of a shared block's second subtiles for the wave that owns it
+    if (lane == 0) left_range[wave] = 0;
+    if (bad) left_range[wave] = 1;
+    if constexpr (RBW == 2) if (second == SecondBlock::kSubtile1) shared_rows[wave & 1][lane] = make_float2(m[1], l[1]);
+    lds_barrier();
+    int any = 0;
 #pragma unroll
-                for (int c = 0; c < NCH; ++c) kf[c] = kbuf[(sub * NCH + c) * 64 + lane];
-                const bool full = j0 + 32 <= full_end;      // every key of the subtile is visible to every query
+    for (int w = 0; w < kScoreWaves; ++w) any |= left_range[w];
+    if (any) {                            // the stages once more; everybody has read them from LDS and meets again below
+        Stage::load(kv, k_head, kb, g.S, g.dh);
+        Stage::store(kv, lds);
+        Stage::load(kv, k_head, kb + (n_stage > 1 ? Stage::kKeys : 0), g.S, g.dh);
+        Stage::store(kv, lds + Stage::kSlots);
+        if constexpr (RBW == 2) shared_rows[wave & 1][lane] = make_float2(kNegBig, 0.f);
 #pragma unroll
-                for (int i = 0; i < RBW; ++i) {
-                    if (i < nrb_w) {
-                        const f32x16_t acc = mma_chain<T, NCH>(kf, q[i]);
-                        if (full) {
-                            softmax_step_full(acc, g.scale_log2, m[i], l[i]);
-                        } else {
-                            const int r = (rb0 + wave + kScoreWaves * i) * 32 + (lane & 31);
-                            int64_t last = text_start + (r % g.Tq);            // causal: keys 0..last, and below ke
-                            last = last < ke - 1 ? last : ke - 1;
-                            const int64_t d = last - j0;
-                            const int lim = d < 0 ? -1 : (d > 31 ? 31 : static_cast<int>(d));
-                            softmax_step_masked(acc, g.scale_log2, h, lim, m[i], l[i]);
-                        }
-                    }
-                }
-            }
-        }
-        publish(s);
+        for (int i = 0; i < RBW; ++i) { m[i] = kNegBig; l[i] = 0.f; }
+        __syncthreads();
+        plain_stages(0, std::integral_constant<bool, true>{});
     }
     // Pass 2 reads the fragments that the first workgroup of each kv head and split leaves (here, behind the key stages,
     // whose loads would wait for the stores).
     if (blockIdx.x == 0) {
 #pragma unroll
         for (int i = 0; i < RBW; ++i) {
-            const int rbl = wave + kScoreWaves * i;
-            if (rbl < nrb) {
+            const int rbl = wave_block<RBW>(nrb, wave, second, i);
+            if (rbl >= 0 && rbl % kScoreWaves == wave) {
                 uint4* dst = qfrag + (static_cast<size_t>(kvh) * g.rb_total + rb0 + rbl) * NCH * 64 + lane;
 #pragma unroll
                 for (int c = 0; c < NCH; ++c) dst[c * 64] = q[i][c];
@@ -454,6 +532,16 @@ __global__ __launch_bounds__(kScoreThreads) void row_stats_kernel(const T* __res
     for (int i = 0; i < RBW; ++i) {
         const int rbl = wave + kScoreWaves * i;
         if (rbl < g.rbw) {
+            // l = mantissa in [0.5, 1): a sum far from 1 must not lose the others when they are scaled to its m
+            auto normalise = [](float& mi, float& li) {
+                if (li > 0.f) { const int e = __builtin_amdgcn_frexp_expf(li); li = ldexpf(li, -e); mi += static_cast<float>(e); }
+            };
+            normalise(m[i], l[i]);
+            if (i == 1 && second == SecondBlock::kSubtile0) {
+                float2 o = shared_rows[wave & 1][lane];
+                normalise(o.x, o.y);
+                merge_softmax(m[i], l[i], o.x, o.y);
+            }
             const float m2 = __shfl_xor(m[i], 32, 64), l2 = __shfl_xor(l[i], 32, 64);
             const float mm = fmaxf(m[i], m2);
             const float ll = l[i] * fast_exp2(m[i] - mm) + l2 * fast_exp2(m2 - mm);
@@ -568,22 +656,28 @@ __global__ __launch_bounds__(kScoreThreads) void col_sums_kernel(const uint4* __
     float* cs = reinterpret_cast<float*>(lds + 2 * Stage::kSlots);
     __shared__ MergeShared red;
     __shared__ __align__(16) float own_norm[kScoreThreads];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), h = lane >> 5;
     const int kvh = blockIdx.y / g.rs, split = blockIdx.y % g.rs;
     const int rb0 = split * g.rbw;
     const int nrb = min(g.rbw, g.rb_total - rb0);
-    const int nrb_w = nrb > wave ? (nrb - wave + kScoreWaves - 1) / kScoreWaves : 0;
     qfrag = of_video(qfrag, g.ws_video); norm = of_video(norm, g.ws_video); pstat = of_video(pstat, g.ws_video); colpart = of_video(colpart, g.ws_video);
     const T* k_head = of_video_elems(k_all, g.k_video) + static_cast<size_t>(kvh) * g.S * g.dh;
 
     const int vb = blockIdx.x * sub_per_wg * 32;                       // visual keys [vb, ve) of this workgroup
     const int ve = min(g.n_vis, vb + sub_per_wg * 32);
     const int n_stage = (ve - vb + Stage::kKeys - 1) / Stage::kKeys;
+    // Subtiles of a stage that the wave takes of its second row block, bit by bit, and whether it has a first one: in vector
+    // registers, because behind scalar branches the compiler spreads a subtile's LDS reads between its products (eight videos
+    // of 36864 tokens: 166 us, now 151)
+    const SecondBlock second = second_block<RBW>(nrb, wave, n_stage >= kMinSharedCols);
+    int second_subtiles = second == SecondBlock::kBoth ? 3 : second == SecondBlock::kSubtile0 ? 1 : second == SecondBlock::kSubtile1 ? 2 : 0;
+    int has_rows = wave < nrb ? 1 : 0;
+    asm volatile("" : "+v"(second_subtiles), "+v"(has_rows));
     u32x4_t kv[Stage::kPerThread];
     Stage::load(kv, k_head, static_cast<int64_t>(g.vis_start) + vb, g.S, g.dh);
 
     uint4 q[RBW][NCH];
-    load_qfrag<NCH, RBW>(q, qfrag, g, kvh, rb0, nrb, wave, lane);
+    load_qfrag<NCH, RBW>(q, qfrag, g, kvh, rb0, nrb, wave, second, lane);
     const float* rows_norm = norm + static_cast<size_t>(blockIdx.y) * g.rbw * 32;
     if (pstat) {                                                        // no kernel has merged the partials
         merge_rows(pstat + static_cast<size_t>(blockIdx.y) * nx1 * g.rbw * 64, nx1, g.rbw * 32, rb0 * 32, g.R, red, own_norm);
@@ -593,8 +687,7 @@ __global__ __launch_bounds__(kScoreThreads) void col_sums_kernel(const uint4* __
     float cr[RBW][16];
 #pragma unroll
     for (int i = 0; i < RBW; ++i) {
-        const int rbl = wave + kScoreWaves * i;
-        const float* src = rows_norm + (rbl < g.rbw ? rbl : 0) * 32 + 4 * h;
+        const float* src = rows_norm + max(wave_block<RBW>(nrb, wave, second, i), 0) * 32 + 4 * h;
 #pragma unroll
         for (int b4 = 0; b4 < 4; ++b4) {
             const float4 c4 = *reinterpret_cast<const float4*>(src + 8 * b4);
@@ -613,13 +706,13 @@ __global__ __launch_bounds__(kScoreThreads) void col_sums_kernel(const uint4* __
         for (int sub = 0; sub < SUBS; ++sub) {
             if (vs + sub * 32 < ve) {
                 float colsum = 0.f;
-                if (nrb_w > 0) {
+                if (has_rows) {
                     uint4 kf[NCH];
 #pragma unroll
                     for (int c = 0; c < NCH; ++c) kf[c] = kbuf[(sub * NCH + c) * 64 + lane];
 #pragma unroll
                     for (int i = 0; i < RBW; ++i) {
-                        if (i < nrb_w) {
+                        if (i == 0 || (second_subtiles >> sub & 1)) {
                             const f32x16_t acc = mma_chain<T, NCH>(q[i], kf);
 #pragma unroll
                             for (int e = 0; e < 16; ++e) colsum += fast_exp2(fmaf(acc[e], g.scale_log2, -cr[i][e]));
