@@ -139,7 +139,7 @@ struct KeyStage {
 // stage waits for them.  There the last x % 4 second blocks are shared with the waves two further on, which have one block
 // only: the first wave takes subtile 0 of a stage, the other one subtile 1.  28 heads on 4 x 64 queries are 14 blocks (4, 4, 3,
 // 3 a SIMD unshared, 3.5 shared): eight videos of 36864 tokens, pass 1 152 -> 144 us (1.05 PFLOP/s), pass 2 157 -> 151 us.  It
-// costs two waves a load more before the first stage, so short ranges go unshared: 18432 tokens (5 stages) 17.7 -> 17.1 us in
+// costs two waves a load more before the first stage, so short ranges go unshared (where their rows are not split, see plan_score): 18432 tokens (5 stages) 17.7 -> 17.1 us in
 // pass 1 but 13.8 -> 14.3 in pass 2, 2243 tokens (1 stage) 9.0 -> 9.4 and 6.2 -> 6.5.  Ranges below kMinPipelined stages do
 // not take pass 1's software pipeline either (2243 tokens 9.4 -> 9.2 us).
 constexpr int kMinPipelined = 4, kMinSharedRows = 4, kMinSharedCols = 8;         // stages of a workgroup
@@ -1765,7 +1765,8 @@ static size_t select_count_bytes(int n_vis) {
 static size_t select_general_bytes(int n_vis) { return 2 * select_count_bytes(n_vis) + METOK_MAX_SEGMENTS * 2 * sizeof(uint32_t); }
 // then the fast path's state.  The reserve is larger than FastSel needs, and the two words per token behind it are used by
 // no kernel: they held the histograms and candidate lists of an earlier selection.  The size of a workspace is part of the
-// interface (it also decides which shapes metok_prefill_prune_static takes), so it stays what it has been.
+// interface (it also decides which shapes metok_prefill_prune_static takes), so it stays what it has been; row splits put their
+// additional column sums there, see plan_score.
 constexpr size_t kFastReserve = 34560;
 static_assert(sizeof(FastSel) <= kFastReserve, "the fast path's state outgrew its reserve");
 static size_t select_bytes(int n_vis) {
@@ -1814,7 +1815,7 @@ struct ScorePlan {
 // (about 100 VGPRs, at most 64 KB) would fit; their grids were not tuned for that.
 constexpr int kScoreSlots = 256;
 
-static void plan_score(const ScoreGeom& g, int n_vis, int nch, int batch, ScorePlan* p) {
+static void plan_grid(const ScoreGeom& g, int n_vis, int nch, int batch, size_t sel_bytes, ScorePlan* p) {
     const int ny = g.Hkv * g.rs;
     const int64_t rows_of_grid = static_cast<int64_t>(ny) * batch;          // the videos of a batch share the chip's slots
     const int nx0 = kScoreSlots / rows_of_grid < 1 ? 1 : static_cast<int>(kScoreSlots / rows_of_grid);
@@ -1838,22 +1839,47 @@ static void plan_score(const ScoreGeom& g, int n_vis, int nch, int batch, ScoreP
     p->off_pstat = off;   off += round_up(static_cast<size_t>(ny) * nx1_cap * g.rbw * 32 * 2 * sizeof(float), 256);
     p->off_norm = off;    off += round_up(static_cast<size_t>(ny) * g.rbw * 32 * sizeof(float), 256);
     p->off_colpart = off; off += round_up(static_cast<size_t>(ny) * n_vis * sizeof(float), 256);
-    p->off_sel = off;     off += select_bytes(n_vis);
+    p->off_sel = off;     off += sel_bytes;
     p->off_inplace = off; off += inplace_bytes(g.S);
     p->total = round_up(off, 256);
+}
+
+// Up to here every workgroup of pass 2 merges the partial statistics of its rows for itself, above a kernel in between does it
+// once.  One level, us, merged in pass 2 / by the kernel, rows whole: 300 tokens, 448 rows x 11 partials (40 KB) 28.6 / 30.2; 32 heads on 8, 256
+// x 32 (64 KB) 51.9 / 51.9; two videos of 4000 tokens, 448 x 32 (112 KB) 41.2 / 40.6; one of 3700, 448 x 59 (206 KB) 33.4 / 32.6; 14
+// heads on 2, 448 x 128 35.4 / 31.8; 7 heads on 1, 448 x 256 40.7 / 34.7: the exponentials of a large merge take longer than the
+// launch.  The narrow kernels have at most 64 rows and always merge for themselves.
+constexpr size_t kMergeInPass2Bytes = 64 * 1024;
+static size_t partial_bytes(const ScoreGeom& g, const ScorePlan& p) { return static_cast<size_t>(p.nx1) * g.rbw * 32 * 2 * sizeof(float); }
+
+// More than eight row blocks go two to a wave, which lets a key fragment feed two products and reads the keys once.  On short
+// ranges the fixed part of a workgroup (its queries, the merge of all its rows' partial statistics, the first stage) is what takes
+// the time, and half the rows in each of twice as many workgroups make it shorter: up to kSplitSubtiles subtiles a workgroup the
+// rows are split until every wave has one block, up to kSplitSubtilesMerged where the whole rows' partials would take the merging
+// kernel.  One level of 28 heads on 4 x 64 queries, us whole / split: 300 tokens 26.5 / 24.1, 2243 (2 subtiles) 32.7 / 28.9, 6000
+// 40.6 / 36.7, 9000 (5) 47.4 / 44.4, 15000 (8) 62.6 / 60.7, 18432 (10) 63.0 / 64.2; two videos of 4000 41.2 / 39.5, eight of 1000
+// (5) 45.5 / 42.6, four of 3000 (6, merged in pass 2) 49.5 / 50.1; 14 heads on 2 x 64, 8000 tokens 34.3 / 30.8.
+// A split needs more room for the column sums and none for the two words per token that select_bytes reserves for nobody; where
+// it does not fit the workspace of the whole rows, the rows stay whole.
+constexpr int kSplitSubtiles = 5, kSplitSubtilesMerged = 8;
+static void plan_score(ScoreGeom* g, int n_vis, int nch, int batch, ScorePlan* p) {
+    plan_grid(*g, n_vis, nch, batch, select_bytes(n_vis), p);
+    if (g->rbw <= kScoreWaves || p->per1 > (partial_bytes(*g, *p) > kMergeInPass2Bytes ? kSplitSubtilesMerged : kSplitSubtiles)) return;
+    ScoreGeom split = *g;
+    split.rs = (g->rb_total + kScoreWaves - 1) / kScoreWaves;
+    split.rbw = (g->rb_total + split.rs - 1) / split.rs;
+    if (static_cast<int64_t>(split.Hkv) * split.rs > 65535) return;
+    ScorePlan s;
+    plan_grid(split, n_vis, nch, batch, round_up(select_general_bytes(n_vis) + sizeof(FastSel), 256), &s);
+    if (s.total > p->total) return;
+    s.total = p->total;
+    *g = split; *p = s;
 }
 
 static bool dh_supported(int dh, int dtype) {
     if (dtype == METOK_BF16) return dh == 32 || dh == 64 || dh == 128 || dh == 256;
     return dh == 32 || dh == 64 || dh == 128;
 }
-
-// Up to here every workgroup of pass 2 merges the partial statistics of its rows for itself, above a kernel in between does it
-// once.  One level, us, merged in pass 2 / by the kernel: 300 tokens, 448 rows x 11 partials (40 KB) 28.6 / 30.2; 32 heads on 8, 256
-// x 32 (64 KB) 51.9 / 51.9; two videos of 4000 tokens, 448 x 32 (112 KB) 41.2 / 40.6; one of 3700, 448 x 59 (206 KB) 33.4 / 32.6; 14
-// heads on 2, 448 x 128 35.4 / 31.8; 7 heads on 1, 448 x 256 40.7 / 34.7: the exponentials of a large merge take longer than the
-// launch.  The narrow kernels have at most 64 rows and always merge for themselves.
-constexpr size_t kMergeInPass2Bytes = 64 * 1024;
 
 // Row blocks of 16 that the narrow kernels take for this shape, 0: the shape is not theirs.  bf16 rows of at most four
 // chunks per lane: with eight (256 elements) fewer subtiles are on their way beside the queries (row statistics of
@@ -1909,7 +1935,7 @@ static void launch_scores(const void* q, const void* k, const ScoreGeom& g, cons
                                static_cast<const T*>(k), g, p.per1, pstat, qfrag, clear, kFastClearWords);
     }
     const float* unmerged = pstat;
-    if (static_cast<size_t>(p.nx1) * g.rbw * 32 * 2 * sizeof(float) > kMergeInPass2Bytes) {
+    if (partial_bytes(g, p) > kMergeInPass2Bytes) {
         const int total_rows = ny * g.rbw * 32;
         hipLaunchKernelGGL(merge_stats_kernel, dim3((total_rows + 15) / 16, 1, nb), dim3(256), 0, st, pstat, g, p.nx1, norm);
         unmerged = nullptr;
@@ -1934,7 +1960,7 @@ static size_t video_workspace_bytes(int batch, int64_t S, int Hq, int Hkv, int d
     ScorePlan p;
     if (Hq >= 1 && Hkv >= 1 && Tq >= 1 && Hq % Hkv == 0 && dh_supported(dh, dtype) &&
         make_geom(S, Hq, Hkv, dh, Tq, 0, n_vis, dtype, METOK_SCORE_CAUSAL_ALL, &g)) {
-        plan_score(g, n_vis, chunk_count(dh, dtype), batch, &p);
+        plan_score(&g, n_vis, chunk_count(dh, dtype), batch, &p);
         return p.total;
     }
     return round_up(select_bytes(n_vis) + inplace_bytes(S), 256);      // no attention pass (scores supplied by the caller)
@@ -2038,7 +2064,7 @@ static int prune_impl(int batch, const void* hidden, int64_t S, int D, int dtype
         if (!make_geom(S, Hq, Hkv, dh, Tq, vis_start, n_vis, dtype, score_mode, &g)) return fail(METOK_ERR_UNSUPPORTED, "head dimension too large");
         if (static_cast<int64_t>(g.Hkv) * g.rs > 65535) return fail(METOK_ERR_UNSUPPORTED, "too many query rows");
         ScorePlan p;
-        plan_score(g, n_vis, chunk_count(dh, dtype), batch, &p);
+        plan_score(&g, n_vis, chunk_count(dh, dtype), batch, &p);
         g.q_video = static_cast<int64_t>(Hq) * Tq * dh; g.k_video = static_cast<int64_t>(Hkv) * S * dh; g.ws_video = ws_video;
         if (static_cast<int64_t>(p.total) != ws_video) return fail(METOK_ERR_DEVICE, "internal: workspace plan mismatch");
         if (!workspace || workspace_bytes < p.total * batch || !aligned16(workspace))
