@@ -361,7 +361,7 @@ class Workload:
             main.wait_stream(self.streams[i])
 
     def configure(self, mode="batched", kv_overlap=False, use_graph=True, split=1):
-        """mode: "batched" (one call per stage and level for the whole batch: 17 launches per step and the KV compaction) or "per-video" (one
+        """mode: "batched" (one call per stage and level for the whole batch: 14 launches per step and the KV compaction) or "per-video" (one
         call per video, 8 streams: about 230 launches).  kv_overlap: the KV compaction of a step runs on a stream of its
         own, beside the next step's stages 1-2 (which fill the other set of index lists).  use_graph: the stage-1/2 launches
         are replayed from a HIP graph.  The library calls only launch kernels on the stream they are given (no allocation,
