@@ -2,6 +2,8 @@
 // function, for the ordinary form of a call.  What is not of that form -- another tensor type or place, a shape or an output
 // that does not fit, numbers that are not Python numbers -- is declined (None) before anything has happened, and binding.py
 // goes through it step by step, with its own checks and messages.  A call that the library refuses returns its code.
+// Everything that can fail, the Python objects of the results included, is done before the library is called: a failure behind
+// the launch, taken for a declined call, would have binding.py launch it a second time.
 //
 // Why: of the 26 us of the smallest stage-1 call 18 were Python (nine outputs of 1.2 us each, fourteen pointers, thirty-five
 // ctypes arguments), of one pruning level's 28 us of host time 15; the kernels of both take less than that.
@@ -85,38 +87,51 @@ inline at::Tensor workspace_of(PyObject* o, const Outputs& out, size_t bytes) {
 }
 
 // ---- results -----------------------------------------------------------------------------------------------------------
-struct Result {
-    PyObject* dict = PyDict_New();
-    bool ok = dict != nullptr;
+struct Owned {                             // a reference of our own
+    PyObject* o;
+    explicit Owned(PyObject* p) : o(p) { need(o != nullptr); }
+    Owned(const Owned&) = delete;
+    ~Owned() { Py_XDECREF(o); }
+    PyObject* release() { PyObject* p = o; o = nullptr; return p; }
+};
+struct Result : Owned {
+    Result() : Owned(PyDict_New()) {}
     void put(const char* name, PyObject* v) {                // takes the reference
-        ok = ok && v && PyDict_SetItemString(dict, name, v) == 0;
-        Py_XDECREF(v);
+        const Owned own(v);
+        need(PyDict_SetItemString(o, name, v) == 0);
     }
     void put(const char* name, const at::Tensor& t) { put(name, THPVariable_Wrap(t)); }
-    PyObject* done() {
-        if (ok) return dict;
-        Py_XDECREF(dict);
-        return nullptr;
-    }
 };
 
-template <typename F> int without_gil(F&& call) {            // as ctypes does
-    struct Released {
-        PyThreadState* state = PyEval_SaveThread();
-        ~Released() { PyEval_RestoreThread(state); }
-    } released;
-    return call();
-}
+// A call with its arguments, pointers among them, read now.
+template <typename F, typename... A> auto bound(F f, A... a) { return [=] { return f(a...); }; }
+
+// The library call of one native call, without the interpreter's lock, as ctypes does.
+struct Launch {
+    bool made = false;
+    template <typename F> int operator()(F&& call) {
+        struct Released {
+            PyThreadState* state = PyEval_SaveThread();
+            ~Released() { PyEval_RestoreThread(state); }
+        } released;
+        made = true;
+        return call();
+    }
+};
+// The library's code, unless it is 0: then the results.
+inline PyObject* answer(int rc, Owned& results) { return rc ? PyLong_FromLong(rc) : results.release(); }
 
 template <typename F> PyObject* guarded(Py_ssize_t nargs, Py_ssize_t expected, F&& body) {
     if (nargs != expected) { PyErr_Format(PyExc_TypeError, "%zd arguments expected, %zd given", expected, nargs); return nullptr; }
+    Launch launch;
     try {
-        return body();
+        return body(launch);
     } catch (const Declined&) {
         PyErr_Clear();
         Py_RETURN_NONE;
-    } catch (const std::exception&) {      // an allocation that failed, for instance: the step-by-step path reports it
+    } catch (const std::exception& e) {    // an allocation that failed, for instance: the step-by-step path reports it
         PyErr_Clear();
+        if (launch.made) { PyErr_SetString(PyExc_RuntimeError, e.what()); return nullptr; }      // not again
         Py_RETURN_NONE;
     }
 }
@@ -134,7 +149,7 @@ inline void* stream_of(PyObject* f) {
 // feats, grid_h, grid_w, k, text_emb, alpha, beta, s1, s2, sim_mode, event_reduce, pool_edge, workspace, out, stream
 template <bool BATCHED>
 PyObject* segment_compress(PyObject*, PyObject* const* a, Py_ssize_t n) {
-    return guarded(n, 15, [&]() -> PyObject* {
+    return guarded(n, 15, [&](Launch& launch) -> PyObject* {
         const at::Tensor& feats = tensor(a[0]);
         const at::Tensor& text = tensor(a[4]);
         need(feats.dim() == (BATCHED ? 4 : 3));
@@ -169,24 +184,22 @@ PyObject* segment_compress(PyObject*, PyObject* const* a, Py_ssize_t n) {
                          frame_is_key = get("frame_is_key", T, at::kByte), event_is_key = get("event_is_key", k, at::kByte),
                          frame_score = get("frame_score", T, at::kFloat), sim = get("sim", std::max<int64_t>(T - 1, 0), at::kFloat),
                          event_score = get("event_score", k, at::kFloat);
-        void* stream = stream_of(a[14]);
-        const int rc = without_gil([&] {
-            auto tail = [&](auto&& f) {
-                return f(address(feats), dt, static_cast<int>(T), gh, gw, static_cast<int>(d), address(text), k, sim_mode, alpha, beta, s1, s2, reduce, edge,
-                         static_cast<float*>(address(sim)), static_cast<int32_t*>(address(event_start)), static_cast<int32_t*>(address(frame_event)), address(tokens), rows, odt,
-                         static_cast<int32_t*>(address(frame_offsets)), static_cast<int32_t*>(address(token_event)), static_cast<uint8_t*>(address(event_is_key)),
-                         static_cast<uint8_t*>(address(frame_is_key)), static_cast<int32_t*>(address(frame_stride)), static_cast<float*>(address(event_score)),
-                         static_cast<float*>(address(frame_score)), address(ws), static_cast<size_t>(ws.numel()), stream);
-            };
-            if (BATCHED) return tail([&](auto... x) { return metok_segment_compress_batched(static_cast<int>(B), x...); });
-            return tail([&](auto... x) { return metok_segment_compress(x...); });
-        });
-        if (rc) return PyLong_FromLong(rc);
         Result r;
         r.put("sim", sim); r.put("event_start", event_start); r.put("frame_event", frame_event); r.put("out_tokens", tokens);
         r.put("frame_offsets", frame_offsets); r.put("token_event", token_event); r.put("event_is_key", event_is_key); r.put("frame_is_key", frame_is_key);
         r.put("frame_stride", frame_stride); r.put("event_score", event_score); r.put("frame_score", frame_score);
-        return r.done();
+        void* stream = stream_of(a[14]);
+        auto call = [&](auto... first) {
+            return bound(first..., address(feats), dt, static_cast<int>(T), gh, gw, static_cast<int>(d), address(text), k, sim_mode, alpha, beta, s1, s2, reduce, edge,
+                         static_cast<float*>(address(sim)), static_cast<int32_t*>(address(event_start)), static_cast<int32_t*>(address(frame_event)), address(tokens), rows, odt,
+                         static_cast<int32_t*>(address(frame_offsets)), static_cast<int32_t*>(address(token_event)), static_cast<uint8_t*>(address(event_is_key)),
+                         static_cast<uint8_t*>(address(frame_is_key)), static_cast<int32_t*>(address(frame_stride)), static_cast<float*>(address(event_score)),
+                         static_cast<float*>(address(frame_score)), address(ws), static_cast<size_t>(ws.numel()), stream);
+        };
+        int rc;
+        if constexpr (BATCHED) rc = launch(call(&metok_segment_compress_batched, static_cast<int>(B)));
+        else rc = launch(call(&metok_segment_compress));
+        return answer(rc, r);
     });
 }
 
@@ -204,7 +217,7 @@ int64_t quotas_of(PyObject* o, std::vector<int32_t>& all) {
 // hidden, vis_start, n_vis, token_seg, seg_quota, q_text, k_all, token_event, event_weight, orig_idx, scores, hidden_out, workspace, out,
 // score_mode, static_scratch, stream
 PyObject* prefill_prune(PyObject*, PyObject* const* a, Py_ssize_t n) {
-    return guarded(n, 17, [&]() -> PyObject* {
+    return guarded(n, 17, [&](Launch& launch) -> PyObject* {
         const at::Tensor& hidden = tensor(a[0]);
         const at::Tensor& seg = tensor(a[3]);
         need(hidden.dim() == 2);
@@ -246,31 +259,27 @@ PyObject* prefill_prune(PyObject*, PyObject* const* a, Py_ssize_t n) {
         }
         auto at_ = [](const at::Tensor& t) -> void* { return t.defined() ? address(t) : nullptr; };
         const int n_events = weight.defined() ? static_cast<int>(weight.numel()) : 0;
-        void* stream = stream_of(a[16]);
-        const int rc = without_gil([&] {
-            auto call = [&](auto&& f) {
-                return f(address(hidden), S, static_cast<int>(D), dt, at_(q), at_(keys), Hq, Hkv, dh, Tq, mode, vis_start, n_vis, static_cast<const int32_t*>(address(seg)),
-                         static_cast<const int32_t*>(at_(event)), static_cast<const float*>(at_(weight)), n_events, static_cast<int>(quota.size()), quota.data(),
-                         static_cast<const int32_t*>(at_(orig)), static_cast<float*>(address(scores)), static_cast<int32_t*>(address(kept)), address(hidden_out),
-                         static_cast<int32_t*>(address(seg_out)), static_cast<int32_t*>(at_(event_out)), static_cast<int32_t*>(address(orig_out)));
-            };
-            if (fixed) return call([&](auto... x) { return metok_prefill_prune_static(x..., stream); });
-            return call([&](auto... x) { return metok_prefill_prune(x..., address(ws), static_cast<size_t>(ws.numel()), stream); });
-        });
-        if (rc) return PyLong_FromLong(rc);
         Result r;
         r.put("scores", scores); r.put("kept_idx", kept);
         if (ho) { Py_INCREF(ho); r.put("hidden_out", ho); } else r.put("hidden_out", hidden_out);
         r.put("token_seg_out", seg_out); r.put("orig_idx_out", orig_out);
         if (event_out.defined()) r.put("token_event_out", event_out);
-        return r.done();
+        void* stream = stream_of(a[16]);
+        auto call = [&](auto f, auto... last) {
+            return bound(f, address(hidden), S, static_cast<int>(D), dt, at_(q), at_(keys), Hq, Hkv, dh, Tq, mode, vis_start, n_vis, static_cast<const int32_t*>(address(seg)),
+                         static_cast<const int32_t*>(at_(event)), static_cast<const float*>(at_(weight)), n_events, static_cast<int>(quota.size()), quota.data(),
+                         static_cast<const int32_t*>(at_(orig)), static_cast<float*>(address(scores)), static_cast<int32_t*>(address(kept)), address(hidden_out),
+                         static_cast<int32_t*>(address(seg_out)), static_cast<int32_t*>(at_(event_out)), static_cast<int32_t*>(address(orig_out)), last...);
+        };
+        return answer(fixed ? launch(call(&metok_prefill_prune_static, stream))
+                            : launch(call(&metok_prefill_prune, address(ws), static_cast<size_t>(ws.numel()), stream)), r);
     });
 }
 
 // hidden, vis_start, n_vis, token_seg, seg_quota, q_text, k_all, token_event, event_weight, orig_idx, scores, hidden_out, workspace, out,
 // score_mode, keep_stride, out_row_stride, stream
 PyObject* prefill_prune_batched(PyObject*, PyObject* const* a, Py_ssize_t n) {
-    return guarded(n, 18, [&]() -> PyObject* {
+    return guarded(n, 18, [&](Launch& launch) -> PyObject* {
         const at::Tensor& hidden = tensor(a[0]);
         const at::Tensor& seg = tensor(a[3]);
         need(hidden.dim() == 3);
@@ -330,25 +339,21 @@ PyObject* prefill_prune_batched(PyObject*, PyObject* const* a, Py_ssize_t n) {
             orig_out = out.fresh({B, keep_stride}, at::kInt);
         }
         auto at_ = [](const at::Tensor& t) -> void* { return t.defined() ? address(t) : nullptr; };
-        void* stream = stream_of(a[17]);
-        const int rc = without_gil([&] {
-            return metok_prefill_prune_batched(static_cast<int>(B), address(hidden), S, static_cast<int>(D), dt, at_(q), at_(keys), Hq, Hkv, dh, Tq, mode, vis_start, n_vis,
-                                               static_cast<const int32_t*>(address(seg)), static_cast<const int32_t*>(at_(event)), static_cast<const float*>(at_(weight)),
-                                               weight.defined() ? static_cast<int>(weight.size(1)) : 0, n_seg, quota.data(), static_cast<const int32_t*>(at_(orig)),
-                                               orig.defined() ? orig.size(1) : 0, static_cast<float*>(address(scores)), static_cast<int32_t*>(address(kept)), keep_stride,
-                                               address(hidden_out), row_stride, static_cast<int32_t*>(address(seg_out)), static_cast<int32_t*>(at_(event_out)),
-                                               static_cast<int32_t*>(address(orig_out)), orig_out.size(1), address(ws), static_cast<size_t>(ws.numel()), stream);
-        });
-        if (rc) return PyLong_FromLong(rc);
         Result r;
         r.put("scores", scores); r.put("kept_idx", kept);
         if (ho) { Py_INCREF(ho); r.put("hidden_out", ho); } else r.put("hidden_out", hidden_out);
         r.put("token_seg_out", seg_out); r.put("orig_idx_out", orig_out);
-        PyObject* list = PyList_New(static_cast<Py_ssize_t>(B));
-        for (int64_t b = 0; list && b < B; ++b) PyList_SET_ITEM(list, b, PyLong_FromLongLong(keep[b]));
-        r.put("n_keep", list);
+        Owned list(PyList_New(static_cast<Py_ssize_t>(B)));
+        for (int64_t b = 0; b < B; ++b) PyList_SET_ITEM(list.o, b, Owned(PyLong_FromLongLong(keep[b])).release());
+        r.put("n_keep", list.release());
         if (event_out.defined()) r.put("token_event_out", event_out);
-        return r.done();
+        void* stream = stream_of(a[17]);
+        return answer(launch(bound(&metok_prefill_prune_batched, static_cast<int>(B), address(hidden), S, static_cast<int>(D), dt, at_(q), at_(keys), Hq, Hkv, dh, Tq, mode,
+                                   vis_start, n_vis, static_cast<const int32_t*>(address(seg)), static_cast<const int32_t*>(at_(event)), static_cast<const float*>(at_(weight)),
+                                   weight.defined() ? static_cast<int>(weight.size(1)) : 0, n_seg, quota.data(), static_cast<const int32_t*>(at_(orig)),
+                                   orig.defined() ? orig.size(1) : int64_t{0}, static_cast<float*>(address(scores)), static_cast<int32_t*>(address(kept)), keep_stride,
+                                   address(hidden_out), row_stride, static_cast<int32_t*>(address(seg_out)), static_cast<int32_t*>(at_(event_out)),
+                                   static_cast<int32_t*>(address(orig_out)), orig_out.size(1), address(ws), static_cast<size_t>(ws.numel()), stream)), r);
     });
 }
 
@@ -394,7 +399,7 @@ struct Layers {
 
 // k_layers, v_layers, page_table (None: dense), idx, new_len, workspace, stream
 PyObject* kv_compact(PyObject*, PyObject* const* a, Py_ssize_t n) {
-    return guarded(n, 7, [&]() -> PyObject* {
+    return guarded(n, 7, [&](Launch& launch) -> PyObject* {
         Layers x(a[0], a[1]);
         const bool paged = given(a[2]);
         at::Tensor table;
@@ -408,24 +413,22 @@ PyObject* kv_compact(PyObject*, PyObject* const* a, Py_ssize_t n) {
         at::Tensor len = given(a[4]) ? tensor(a[4]) : out.fresh({x.L}, at::kInt);
         const int64_t cap = paged ? table.size(1) * rows : rows;
         const at::Tensor ws = workspace_of(a[5], out, given(a[5]) ? 0 : metok_kv_compact_workspace_bytes(x.L, static_cast<int>(B), static_cast<int>(Hkv), cap, static_cast<int>(dh), x.dt));
+        if (given(a[4])) Py_INCREF(a[4]);
+        Owned result(given(a[4]) ? a[4] : THPVariable_Wrap(len));
         void* stream = stream_of(a[6]);
-        const int rc = without_gil([&] {
-            if (paged)
-                return metok_kv_compact_paged(x.k.data(), x.v.data(), x.L, static_cast<int>(B), static_cast<int>(Hkv), x.first.size(0), static_cast<int>(rows), static_cast<int>(dh), x.dt,
-                                              static_cast<const int32_t*>(address(table)), static_cast<int>(table.size(1)), x.idx.data(), x.n_keep.data(),
-                                              static_cast<int32_t*>(address(len)), address(ws), static_cast<size_t>(ws.numel()), stream);
-            return metok_kv_compact(x.k.data(), x.v.data(), x.L, static_cast<int>(B), static_cast<int>(Hkv), rows, static_cast<int>(dh), x.dt, x.idx.data(), x.n_keep.data(),
-                                    static_cast<int32_t*>(address(len)), address(ws), static_cast<size_t>(ws.numel()), stream);
-        });
-        if (rc) return PyLong_FromLong(rc);
-        if (given(a[4])) { Py_INCREF(a[4]); return a[4]; }
-        return THPVariable_Wrap(len);
+        auto call = [&](auto f, auto... middle) {
+            return bound(f, x.k.data(), x.v.data(), x.L, static_cast<int>(B), static_cast<int>(Hkv), middle..., x.idx.data(), x.n_keep.data(),
+                         static_cast<int32_t*>(address(len)), address(ws), static_cast<size_t>(ws.numel()), stream);
+        };
+        return answer(paged ? launch(call(&metok_kv_compact_paged, x.first.size(0), static_cast<int>(rows), static_cast<int>(dh), x.dt,
+                                          static_cast<const int32_t*>(address(table)), static_cast<int>(table.size(1))))
+                            : launch(call(&metok_kv_compact, rows, static_cast<int>(dh), x.dt)), result);
     });
 }
 
 // k_pools, v_pools, page_table, idx, len_in, workspace, stream
 PyObject* kv_relink_paged(PyObject*, PyObject* const* a, Py_ssize_t n) {
-    return guarded(n, 7, [&]() -> PyObject* {
+    return guarded(n, 7, [&](Launch& launch) -> PyObject* {
         Layers x(a[0], a[1]);
         const at::Tensor& table = tensor(a[2]);
         need(table.scalar_type() == at::kInt && (table.dim() == 2 || (table.dim() == 3 && table.size(0) == x.L)));
@@ -442,18 +445,15 @@ PyObject* kv_relink_paged(PyObject*, PyObject* const* a, Py_ssize_t n) {
                          copied = out.fresh({L, B}, at::kInt), len = out.fresh({L}, at::kInt);
         const int Hkv = static_cast<int>(x.first.size(1)), ps = static_cast<int>(x.first.size(2)), dh = static_cast<int>(x.first.size(3));
         const at::Tensor ws = workspace_of(a[5], out, given(a[5]) ? 0 : metok_kv_relink_paged_workspace_bytes(x.L, static_cast<int>(B), Hkv, ps, static_cast<int>(pages), dh, x.dt));
-        void* stream = stream_of(a[6]);
-        const int rc = without_gil([&] {
-            return metok_kv_relink_paged(x.k.data(), x.v.data(), x.L, static_cast<int>(B), Hkv, x.first.size(0), ps, dh, x.dt, static_cast<const int32_t*>(address(table)),
-                                         table.dim() == 2 ? 0 : B * pages, static_cast<int>(pages), given(a[4]) ? lens.data() : nullptr, x.idx.data(), x.n_keep.data(),
-                                         static_cast<int32_t*>(address(table_out)), static_cast<int32_t*>(address(free_pages)), static_cast<int32_t*>(address(n_free)),
-                                         static_cast<int32_t*>(address(copied)), static_cast<int32_t*>(address(len)), address(ws), static_cast<size_t>(ws.numel()), stream);
-        });
-        if (rc) return PyLong_FromLong(rc);
         Result r;
         r.put("page_table_out", table_out); r.put("free_pages", free_pages); r.put("n_free", n_free); r.put("rows_copied", copied); r.put("new_len", len);
         if (given(a[5])) { Py_INCREF(a[5]); r.put("workspace", a[5]); } else r.put("workspace", ws);
-        return r.done();
+        void* stream = stream_of(a[6]);
+        return answer(launch(bound(&metok_kv_relink_paged, x.k.data(), x.v.data(), x.L, static_cast<int>(B), Hkv, x.first.size(0), ps, dh, x.dt,
+                                   static_cast<const int32_t*>(address(table)), table.dim() == 2 ? int64_t{0} : B * pages, static_cast<int>(pages),
+                                   given(a[4]) ? lens.data() : nullptr, x.idx.data(), x.n_keep.data(), static_cast<int32_t*>(address(table_out)),
+                                   static_cast<int32_t*>(address(free_pages)), static_cast<int32_t*>(address(n_free)), static_cast<int32_t*>(address(copied)),
+                                   static_cast<int32_t*>(address(len)), address(ws), static_cast<size_t>(ws.numel()), stream)), r);
     });
 }
 

@@ -1,5 +1,7 @@
 """The native marshalling of binding.py against its step-by-step path: the same outputs bit for bit, under the same names and in
 the same order, over the forms a call can have; what is not of the ordinary form is declined before anything happens."""
+import gc
+
 import numpy as np
 import pytest
 import torch
@@ -208,3 +210,59 @@ def test_refusals_of_the_library_are_raised():
         B.metok_segment_compress(f.transpose(0, 1).contiguous().transpose(0, 1), 4, 5, 2, t, 0.5, 0.5, 1, 2)
     with pytest.raises(ValueError, match="out"):
         B.metok_segment_compress(f, 4, 5, 2, t, 0.5, 0.5, 1, 2, out=dict(sim=torch.zeros(3, device="cuda")))
+
+
+def native_calls():
+    """The six native functions on small inputs, each as a function of the stream function it is given."""
+    f, t = frames(0)
+    fb, tb = frames(2)
+    g = torch.Generator(device="cuda").manual_seed(11)
+    n, S, D = 70, 90, 64
+    hidden, seg, scores = (torch.randn(S, D, generator=g, device="cuda"), torch.zeros(n, dtype=torch.int32, device="cuda"),
+                           torch.rand(n, generator=g, device="cuda"))
+    two = lambda x: torch.stack([x, x])
+    kv = [torch.randn(2, 2, 96, 64, generator=g, device="cuda") for _ in range(2)]
+    pools, table = [x.view(12, 2, 16, 64) for x in kv], torch.arange(12, device="cuda").int().view(2, 6)
+    idx = [torch.arange(0, 96, 3, device="cuda").int().expand(2, -1).contiguous()]
+    shape = (4, 5, 3)
+    rest = (0.5, 0.45, 1, 2, 0, 0, 0, None, None)
+    nothing = [None] * 5
+    H = B._host
+    return {
+        "segment_compress": lambda s: H.segment_compress(f, *shape, t, *rest, s),
+        "segment_compress_batched": lambda s: H.segment_compress_batched(fb, *shape, tb, *rest, s),
+        "prefill_prune": lambda s, static=False: H.prefill_prune(hidden, 8, n, seg, [29], *nothing, scores, hidden[:S - n + 29], None, None, 0, static, s),
+        "prefill_prune_batched": lambda s: H.prefill_prune_batched(two(hidden), 8, n, two(seg), [[29], [15]], *nothing, two(scores), None, None, None, 0, None, None, s),
+        "kv_compact": lambda s: H.kv_compact(kv[:1], kv[1:], None, idx, None, None, s),
+        "kv_relink_paged": lambda s: H.kv_relink_paged(pools[:1], pools[1:], table, idx, None, None, s),
+    }
+
+
+NATIVE_CALLS = ["segment_compress", "segment_compress_batched", "prefill_prune", "prefill_prune_batched", "kv_compact", "kv_relink_paged"]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", NATIVE_CALLS)
+def test_nothing_that_can_fail_follows_the_launch(name):
+    """Had the wrapping of the results failed behind the launch, the step-by-step path would launch the call again, on data that an
+    in-place call has already moved.  The results are Python objects: with a collection due at every other one that is made, one
+    made after the stream was asked for, the last thing before the launch, would show."""
+    call, handles, late = native_calls()[name], [B._stream()], []
+
+    def watch(phase, info):
+        if not handles:
+            late.append(phase)
+
+    before = gc.get_threshold()
+    gc.collect()
+    gc.callbacks.append(watch)
+    gc.set_threshold(1)
+    try:
+        res = call(handles.pop)
+        gc.disable()
+    finally:
+        gc.callbacks.remove(watch)
+        gc.set_threshold(*before)
+        gc.enable()
+    torch.cuda.synchronize()
+    assert res is not None and not handles and not late
