@@ -12,6 +12,7 @@
 
 #include <ATen/core/Tensor.h>
 #include <ATen/ops/empty.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <algorithm>
@@ -21,7 +22,9 @@
 
 namespace {
 
-struct Declined {};                        // thrown and caught inside this file only
+// Thrown and caught inside this file only.  A Python error is never a reason to decline: it may be a signal's exception.
+struct Declined {};
+struct Raised {};                          // a Python error is set
 
 // ---- reading arguments -----------------------------------------------------------------------------------------------
 inline void need(bool ok) { if (!ok) throw Declined(); }
@@ -44,6 +47,14 @@ inline double real(PyObject* o) {
 }
 inline bool given(PyObject* o) { return o != Py_None; }
 
+struct Owned {                             // a reference of our own, to what a Python function returned
+    PyObject* o;
+    explicit Owned(PyObject* p) : o(p) { if (!o) throw Raised(); }
+    Owned(const Owned&) = delete;
+    ~Owned() { Py_XDECREF(o); }
+    PyObject* release() { PyObject* p = o; o = nullptr; return p; }
+};
+
 // A plain tensor on the GPU, contiguous.
 inline const at::Tensor& tensor(PyObject* o) {
     need(THPVariable_CheckExact(o));
@@ -65,7 +76,9 @@ struct Outputs {
     Outputs(PyObject* o, const at::Tensor& like) : dict(given(o) ? o : nullptr), device(like.device()) { need(!dict || PyDict_CheckExact(dict)); }
     PyObject* find(const char* name) const {
         if (!dict) return nullptr;
-        PyObject* v = PyDict_GetItemString(dict, name);      // borrowed
+        const Owned key(PyUnicode_FromString(name));
+        PyObject* v = PyDict_GetItemWithError(dict, key.o);  // borrowed
+        if (!v && PyErr_Occurred()) throw Raised();
         return v && given(v) ? v : nullptr;
     }
     at::Tensor fresh(at::IntArrayRef shape, at::ScalarType type) const {
@@ -87,18 +100,11 @@ inline at::Tensor workspace_of(PyObject* o, const Outputs& out, size_t bytes) {
 }
 
 // ---- results -----------------------------------------------------------------------------------------------------------
-struct Owned {                             // a reference of our own
-    PyObject* o;
-    explicit Owned(PyObject* p) : o(p) { need(o != nullptr); }
-    Owned(const Owned&) = delete;
-    ~Owned() { Py_XDECREF(o); }
-    PyObject* release() { PyObject* p = o; o = nullptr; return p; }
-};
 struct Result : Owned {
     Result() : Owned(PyDict_New()) {}
     void put(const char* name, PyObject* v) {                // takes the reference
         const Owned own(v);
-        need(PyDict_SetItemString(o, name, v) == 0);
+        if (PyDict_SetItemString(o, name, v)) throw Raised();
     }
     void put(const char* name, const at::Tensor& t) { put(name, THPVariable_Wrap(t)); }
 };
@@ -126,23 +132,22 @@ template <typename F> PyObject* guarded(Py_ssize_t nargs, Py_ssize_t expected, F
     Launch launch;
     try {
         return body(launch);
+    } catch (const Raised&) {
+        return nullptr;
+    } catch (python_error& e) {            // torch's form of the same
+        e.restore();
+        return nullptr;
     } catch (const Declined&) {
-        PyErr_Clear();
         Py_RETURN_NONE;
     } catch (const std::exception& e) {    // an allocation that failed, for instance: the step-by-step path reports it
-        PyErr_Clear();
         if (launch.made) { PyErr_SetString(PyExc_RuntimeError, e.what()); return nullptr; }      // not again
         Py_RETURN_NONE;
     }
 }
 // binding.py's function for the current stream's handle, asked once everything else fits.
 inline void* stream_of(PyObject* f) {
-    PyObject* o = PyObject_CallNoArgs(f);
-    need(o != nullptr);
-    const int64_t v = PyLong_CheckExact(o) ? PyLong_AsLongLong(o) : -1;
-    Py_DECREF(o);
-    need(v != -1);
-    return reinterpret_cast<void*>(v);
+    const Owned handle(PyObject_CallNoArgs(f));
+    return reinterpret_cast<void*>(integer(handle.o));
 }
 
 // ---- stage 1 -----------------------------------------------------------------------------------------------------------
@@ -224,7 +229,7 @@ PyObject* prefill_prune(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const int64_t S = hidden.size(0), D = hidden.size(1);
         need(D <= INT32_MAX);
         const int vis_start = int32(a[1]), n_vis = int32(a[2]), mode = int32(a[14]), dt = dtype_code(hidden);
-        const bool fixed = PyObject_IsTrue(a[15]) == 1;
+        const bool fixed = integer(a[15]) != 0;
         std::vector<int32_t> quota;
         const int64_t total = quotas_of(a[4], quota);
         const Outputs out(a[13], hidden);

@@ -266,3 +266,39 @@ def test_nothing_that_can_fail_follows_the_launch(name):
         gc.enable()
     torch.cuda.synchronize()
     assert res is not None and not handles and not late
+
+
+class Refuses:
+    def __bool__(self):
+        raise LookupError("asked for its truth")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", NATIVE_CALLS)
+def test_errors_of_the_stream_function_are_raised(name):
+    """A signal's exception is raised wherever Python code runs, here in the stream function: it must not be taken for a reason
+    to decline."""
+    def interrupted():
+        raise KeyboardInterrupt
+    with pytest.raises(KeyboardInterrupt):
+        native_calls()[name](interrupted)
+
+
+@pytest.mark.gpu
+def test_errors_of_the_arguments_are_raised():
+    asked = []
+
+    def stream():
+        asked.append(1)
+        return B._stream()
+    # a truth value that is no bool belongs to the step-by-step path; nothing goes on beside the error
+    assert native_calls()["prefill_prune"](stream, Refuses()) is None and not asked
+
+    class Key(str):
+        __hash__ = str.__hash__
+
+        def __eq__(self, other):
+            raise KeyboardInterrupt
+    f, t = frames(0)
+    with pytest.raises(KeyboardInterrupt):
+        B._host.segment_compress(f, 4, 5, 3, t, 0.5, 0.45, 1, 2, 0, 0, 0, None, {Key("sim"): None}, stream)
