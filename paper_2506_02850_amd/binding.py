@@ -140,7 +140,22 @@ def _load() -> ctypes.CDLL:
 
 
 _lib = _load()
-from . import _host  # noqa: E402  (linked against the library loaded above)
+
+
+class _StepByStep:
+    """Stands in for _host where it is not built, or not for this interpreter and torch: every call is declined."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+try:
+    from . import _host  # linked against the library loaded above
+except ImportError as e:
+    import warnings
+
+    warnings.warn(f"the native marshalling of the calls is not available ({e}): they go through ctypes, with more host time each")
+    _host = _StepByStep()
 
 
 def _native(res):

@@ -476,4 +476,17 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_host", nullptr, -1, methods, null
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__host() { return PyModule_Create(&module); }
+// The tensors' layout is that of the torch whose headers this was built with.
+PyMODINIT_FUNC PyInit__host() {
+    try {
+        const Owned torch(PyImport_ImportModule("torch")), version(PyObject_GetAttrString(torch.o, "__version__"));
+        const Owned text(PyObject_Str(version.o));
+        if (PyUnicode_CompareWithASCIIString(text.o, METOK_TORCH_VERSION) != 0) {
+            PyErr_Format(PyExc_ImportError, "built for torch %s, this is %U", METOK_TORCH_VERSION, text.o);
+            return nullptr;
+        }
+    } catch (const Raised&) {
+        return nullptr;
+    }
+    return PyModule_Create(&module);
+}

@@ -1,6 +1,9 @@
 """The native marshalling of binding.py against its step-by-step path: the same outputs bit for bit, under the same names and in
 the same order, over the forms a call can have; what is not of the ordinary form is declined before anything happens."""
 import gc
+import os
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -59,6 +62,45 @@ def test_arguments_of_other_types_are_declined(bad):
     a.update(bad)
     assert B._host.segment_compress(*a.values(), B._stream) is None
     assert B._host.segment_compress_batched(*a.values(), B._stream) is None
+
+
+def in_a_new_interpreter(before):
+    code = before + """
+import warnings
+with warnings.catch_warnings(record=True) as said:
+    warnings.simplefilter("always")
+    from paper_2506_02850_amd import binding as B
+import torch
+print([str(w.message) for w in said])
+print(B.metok_preset(B.MODEL_LONGVA_7B)["s1"], type(B._host).__name__)
+try:
+    B.metok_segment_compress(torch.zeros(4, 6, 16), 2, 3, 2, torch.zeros(16), 0.5, 0.5, 1, 2)
+except ValueError as e:
+    print(e)
+"""
+    p = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    assert p.returncode == 0, p.stderr
+    return p.stdout
+
+
+@pytest.mark.parametrize("before,said", [("import sys; sys.modules['paper_2506_02850_amd._host'] = None", "None in sys.modules"),
+                                         ("import torch; torch.__version__ = '1.0'", "this is 1.0")])
+def test_the_binding_works_without_its_native_part(before, said):
+    out = in_a_new_interpreter(before)
+    assert said in out and "ctypes" in out and "_StepByStep" in out and "must live on the GPU" in out
+
+
+def test_the_native_part_is_loaded_where_it_fits():
+    out = in_a_new_interpreter("")
+    assert "ctypes" not in out and "module" in out and "must live on the GPU" in out
+
+
+@pytest.mark.parametrize("commands", [[["false"]], [["no-such-compiler"]]])
+def test_a_native_part_that_cannot_be_built_is_reported(monkeypatch, tmp_path, commands):
+    from paper_2506_02850_amd import build
+    target = str(tmp_path / "_host.so")
+    monkeypatch.setattr(build, "host_commands", lambda obj, target: commands)
+    assert commands[0][0] in build.build_host(target) and not os.path.exists(target)
 
 
 # ---- on the GPU -----------------------------------------------------------------------------------------------------------
