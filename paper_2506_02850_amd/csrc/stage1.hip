@@ -202,7 +202,11 @@ __global__ __launch_bounds__(kStatsThreads) void frame_stats_kernel(
 constexpr int kSegThreads = 1024;
 constexpr int kMaxReduceWgs = 64;
 constexpr int kShortFrames = 512;          // up to here segment_short_kernel: at least two threads per frame
-constexpr int kOneReduceFrames = 32;       // up to here one workgroup adds up the partials too: two frames per wave
+// Up to here one workgroup adds up the partials too, two frames per wave, and nothing is handed over; but not where the frames
+// beyond one per wave bring more than kOneReducePartials partial sums, which a second workgroup would read in the meantime.  Whole
+// calls of T frames x C partials, us, one workgroup / several: 32 x 256 17.8 / 18.3 and 16.1 / 16.7, 32 x 576 22.4 / 21.6 and 29.3 / 28.3,
+// 32 x 4096 67.3 / 60.4; 24 x 1024 25.0 / 25.3, 24 x 1600 30.5 / 30.0; 17 x 4096 43.0 / 43.1.
+constexpr int kOneReduceFrames = 32, kOneReducePartials = 8192;
 constexpr int kRankLoopFrames = 2048;      // up to here every thread ranks its frames against all others
 constexpr int kFillRowsInPlan = 65536;     // up to so many uniformly pooled rows the planning workgroup writes their event ids
 
@@ -818,14 +822,18 @@ __global__ __launch_bounds__(kSegThreads) void segment_short_kernel(const Segmen
     int32_t* frame_event = of_video_elems(a.frame_event, T);
     float n0 = 0.f, n1 = 0.f, dot = 0.f, score = 0.f;             // of frame tid, and |v|^2 of the next one
     if (gridDim.x == 1) {
-        if (wave < T) {
+        auto keep = [&](int t, const Triple& v) {
+            if (lane == 0) { sh.norm2[t] = v.x; sh.pair[t] = v.y; sh.score[t] = v.z / static_cast<float>(a.N); }
+        };
+        if (wave + kWaves < T) {
             Triple v[2];
             reduce_frames<2>(part, a.C, wave, kWaves, T, v);
-#pragma unroll
-            for (int f = 0; f < 2; ++f) {
-                const int t = wave + f * kWaves;
-                if (t < T && lane == 0) { sh.norm2[t] = v[f].x; sh.pair[t] = v[f].y; sh.score[t] = v[f].z / static_cast<float>(a.N); }
-            }
+            keep(wave, v[0]);
+            keep(wave + kWaves, v[1]);
+        } else if (wave < T) {
+            Triple v[1];
+            reduce_frames<1>(part, a.C, wave, 0, T, v);
+            keep(wave, v[0]);
         }
         lds_barrier();
         if (tid < T) {
@@ -915,8 +923,9 @@ __global__ __launch_bounds__(kSegThreads) void plan_short_kernel(const PlanArgs1
 
 template <bool WITH_PLAN>
 static void launch_segment(const SegmentArgs& sa, const PlanArgs1& plan, unsigned nb, hipStream_t st) {
+    const bool one = sa.T <= kOneReduceFrames && static_cast<int64_t>(sa.T - kSegThreads / 64) * sa.C <= kOneReducePartials;
     if (sa.T <= kShortFrames)
-        hipLaunchKernelGGL(segment_short_kernel<WITH_PLAN>, dim3(sa.T <= kOneReduceFrames ? 1 : reduce_workgroups(sa.T), 1, nb), dim3(kSegThreads), 0, st, sa, plan);
+        hipLaunchKernelGGL(segment_short_kernel<WITH_PLAN>, dim3(one ? 1 : reduce_workgroups(sa.T), 1, nb), dim3(kSegThreads), 0, st, sa, plan);
     else
         hipLaunchKernelGGL(segment_kernel<WITH_PLAN>, dim3(reduce_workgroups(sa.T), 1, nb), dim3(kSegThreads), 0, st, sa, plan);
 }

@@ -74,6 +74,16 @@ def test_few_or_many_pooling_workgroups_per_frame(T, grid, d, s1, s2):
     check(v, grid, 3, 0.5, 0.4, s1, s2, "bf16")
 
 
+# partials per frame: 4 tokens each with strides of their own, a 2 x 2 window each with stride 2; one workgroup adds them up for one
+# frame per wave (T <= 16) and up to 8192 of those beyond (T - 16 times 512, 529; 8371 for the 17th frame)
+@pytest.mark.parametrize("T,grid,s1,s2", [(5, (96, 96), 6, 9), (16, (61, 64), 5, 7), (17, (182, 184), 12, 16), (17, (64, 64), 6, 9),
+                                          (32, (32, 64), 5, 7), (32, (46, 46), 5, 7), (32, (46, 46), 2, 2)])
+def test_few_frames_of_many_partials(T, grid, s1, s2):
+    v = synth.planted_video(9700 + T, T, grid, 16, 4, 1, T, 0.05, "f32")
+    alpha, beta = (1.0, 1.0) if s1 == s2 else (0.5, 0.4)
+    check(v, grid, 4, alpha, beta, s1, s2, "f32")
+
+
 def tied_video(T, seed):
     """Frames drawn from four vectors: most adjacent pairs tie exactly in their cosine, most frames in their text score."""
     rng = np.random.default_rng(seed)
