@@ -601,10 +601,21 @@ __device__ __forceinline__ void merge_rows(const float* __restrict__ part, int n
     lds_barrier();
     const int r = threadIdx.x;
     if (r < rows) {
-        const float* pm = reinterpret_cast<const float*>(sh.m) + r;
-        const float* pl = reinterpret_cast<const float*>(sh.l) + r;
-        float mm = pm[0], ll = pl[0];
-        for (int k = 1; k < groups; ++k) merge_softmax(mm, ll, pm[(k << lg) * 4], pl[(k << lg) * 4]);
+        // the groups that had a partial, eight at a time: a row's threads are up to 64, and one after the other through all of them
+        // was a chain of 1 us (300 tokens, 8 heads x 16 queries, kernels alone: 21.0 -> 18.8 us)
+        const float* gm = reinterpret_cast<const float*>(sh.m) + r;
+        const float* gl = reinterpret_cast<const float*>(sh.l) + r;
+        const int used = min(groups, nx);
+        float mm = kNegBig, ll = 0.f;
+        for (int k = 0; k < used; k += kBatch) {
+            float pm[kBatch], pl[kBatch];
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                const int at = (min(k + u, used - 1) << lg) * 4;
+                pm[u] = gm[at]; pl[u] = gl[at];
+            }
+            merge_partials(mm, ll, pm, pl, used - k);
+        }
         norm[r] = row_norm(mm, ll, first_row + r < R);
     }
     lds_barrier();
