@@ -247,20 +247,35 @@ __device__ __forceinline__ float max16(const f32x16_t& acc) {
 // below the largest logit it was taken from, so that scaling a sum to another m is exact.
 __device__ __forceinline__ float reference_above(float logit_max) { return fmaxf(kNegBig, ceilf(logit_max)); }
 
-// Every key is visible and m stays.
-__device__ __forceinline__ void softmax_step_fixed(const f32x16_t& acc, float scale_log2, float m, float& l) {
+// l = mantissa in [0.5, 1): a sum far from 1 must not lose others, or be lost, when they meet at another m
+__device__ __forceinline__ void normalise_softmax(float& m, float& l) {
+    if (l > 0.f) { const int e = __builtin_amdgcn_frexp_expf(l); l = ldexpf(l, -e); m += static_cast<float>(e); }
+}
+
+// Every key is visible and m stays: the new sum.
+__device__ __forceinline__ float softmax_sum(const f32x16_t& acc, float scale_log2, float m, float l) {
     float sum = 0.f;
 #pragma unroll
     for (int e = 0; e < 16; ++e) sum += fast_exp2(fmaf(acc[e], scale_log2, -m));
-    l += sum;
+    return l + sum;
 }
 
 // Every key is visible and m follows the maximum.
 __device__ __forceinline__ void softmax_step_full(const f32x16_t& acc, float scale_log2, float& m, float& l) {
     const float m_new = fmaxf(m, reference_above(max16(acc) * scale_log2));        // the scale is positive: max commutes with it
-    l *= fast_exp2(m - m_new);
+    l = softmax_sum(acc, scale_log2, m_new, l * fast_exp2(m - m_new));
     m = m_new;
-    softmax_step_fixed(acc, scale_log2, m, l);
+}
+
+// l becomes the sum that softmax_sum returned, unless it left the range of float in a lane: then the step is done once more with
+// a larger m.
+__device__ __forceinline__ void softmax_take(const f32x16_t& acc, float scale_log2, float& m, float& l, float sum) {
+    if (__builtin_expect(__any(sum == INFINITY), 0)) {
+        normalise_softmax(m, l);
+        softmax_step_full(acc, scale_log2, m, l);
+    } else {
+        l = sum;
+    }
 }
 
 // Keeps the MFMA chain that produces `acc` inside the scheduling region in which it was written: the value counts as
@@ -328,8 +343,10 @@ constexpr int kStageBuffers = 3;       // LDS stages: one in use, one ready (its
 //
 // m is taken from a lane's keys of the first subtile and stays while whole subtiles are visible: terms relative to it keep
 // their precision as long as none exceeds it by 2^127, and following the maximum is 14 of the 64 vector instructions of a
-// block (eight videos of 36864 tokens: 160 -> 152 us).  A workgroup whose sums left the range of float starts over with the
-// maximum.
+// block (eight videos of 36864 tokens: 160 -> 152 us).  A block whose sums left the range of float is added once more under a
+// larger m, while its products are still there.  The question costs the same level 0.7 % (312.5 -> 314.5 us without its row
+// gather); to let the whole workgroup start over instead made logits that jump by more than 2^127, or one key that is
+// not finite, pass 1 twice as long (354 and 343 us with the running maximum, 490 and 454 so, 352 and 325 now).
 // ---------------------------------------------------------------------------------------------
 template <typename T, int NCH, int RBW, int SUBS>
 __global__ __launch_bounds__(kScoreThreads) void row_stats_kernel(const T* __restrict__ q_text, const T* __restrict__ k_all,
@@ -341,7 +358,6 @@ __global__ __launch_bounds__(kScoreThreads) void row_stats_kernel(const T* __res
     const int kvh = blockIdx.y / g.rs, split = blockIdx.y % g.rs;
     const int rb0 = split * g.rbw;
     const int nrb = min(g.rbw, g.rb_total - rb0);
-    __shared__ int left_range[kScoreWaves];
     __shared__ float2 shared_rows[2][64];
     q_text = of_video_elems(q_text, g.q_video);
     qfrag = of_video(qfrag, g.ws_video); pstat = of_video(pstat, g.ws_video); clear = of_video(clear, g.ws_video);
@@ -387,8 +403,7 @@ __global__ __launch_bounds__(kScoreThreads) void row_stats_kernel(const T* __res
     };
 
     // stages s, s + 1, ... on the plain path; `online`: m follows the maximum
-    auto plain_stages = [&](int s, auto online_tag) {
-        constexpr bool online = decltype(online_tag)::value;
+    auto plain_stages = [&](int s) {
         for (; s < n_stage; ++s) {
             const uint4* kbuf = stage_buf(s);
             const int64_t js = kb + static_cast<int64_t>(s) * Stage::kKeys;
@@ -405,8 +420,8 @@ __global__ __launch_bounds__(kScoreThreads) void row_stats_kernel(const T* __res
                     for (int i = 0; i < RBW; ++i) {
                         if (i < nrb_w) {
                             const f32x16_t acc = mma_chain<T, NCH>(kf, q[i]);
-                            if (full && !online && j0 > kb) {
-                                softmax_step_fixed(acc, g.scale_log2, m[i], l[i]);
+                            if (full && j0 > kb) {
+                                softmax_take(acc, g.scale_log2, m[i], l[i], softmax_sum(acc, g.scale_log2, m[i], l[i]));
                             } else if (full) {
                                 softmax_step_full(acc, g.scale_log2, m[i], l[i]);
                             } else {
@@ -450,10 +465,11 @@ __global__ __launch_bounds__(kScoreThreads) void row_stats_kernel(const T* __res
             // the product of one block beside the softmax arithmetic of the block before
             auto phase = [&](f32x16_t& next, const uint4 (&kf)[NCH], const uint4 (&qf)[NCH], const f32x16_t& acc, int i) {
                 next = mma_chain<T, NCH>(kf, qf);
-                softmax_step_fixed(acc, g.scale_log2, m[i], l[i]);
+                const float sum = softmax_sum(acc, g.scale_log2, m[i], l[i]);
                 interleave_mfma_valu<kMfmas, kValu>();
                 pin_accumulators(next);
                 __builtin_amdgcn_sched_barrier(0);
+                softmax_take(acc, g.scale_log2, m[i], l[i], sum);
             };
             // Which subtile of a stage comes first is a wave's own choice: one that shares a block takes its subtile of it
             // first, so that both waves of a pair do the same, block 0, block 1, block 0 of the other subtile.  The loads and
@@ -490,29 +506,10 @@ __global__ __launch_bounds__(kScoreThreads) void row_stats_kernel(const T* __res
             }
         }
     }
-    plain_stages(s, std::integral_constant<bool, false>{});
-    bool bad = false;
-#pragma unroll
-    for (int i = 0; i < RBW; ++i) bad = bad || !(l[i] <= 3.0e38f);
-    // one barrier for both: the flags, and the sums of a shared block's second subtiles for the wave that owns it
-    if (lane == 0) left_range[wave] = 0;
-    if (bad) left_range[wave] = 1;
+    plain_stages(s);
+    // the sums of a shared block's second subtiles, for the wave that owns it
     if constexpr (RBW == 2) if (second == SecondBlock::kSubtile1) shared_rows[wave & 1][lane] = make_float2(m[1], l[1]);
     lds_barrier();
-    int any = 0;
-#pragma unroll
-    for (int w = 0; w < kScoreWaves; ++w) any |= left_range[w];
-    if (any) {                            // the stages once more; everybody has read them from LDS and meets again below
-        Stage::load(kv, k_head, kb, g.S, g.dh);
-        Stage::store(kv, lds);
-        Stage::load(kv, k_head, kb + (n_stage > 1 ? Stage::kKeys : 0), g.S, g.dh);
-        Stage::store(kv, lds + Stage::kSlots);
-        if constexpr (RBW == 2) shared_rows[wave & 1][lane] = make_float2(kNegBig, 0.f);
-#pragma unroll
-        for (int i = 0; i < RBW; ++i) { m[i] = kNegBig; l[i] = 0.f; }
-        __syncthreads();
-        plain_stages(0, std::integral_constant<bool, true>{});
-    }
     // Pass 2 reads the fragments that the first workgroup of each kv head and split leaves (here, behind the key stages,
     // whose loads would wait for the stores).
     if (blockIdx.x == 0) {
@@ -532,14 +529,10 @@ __global__ __launch_bounds__(kScoreThreads) void row_stats_kernel(const T* __res
     for (int i = 0; i < RBW; ++i) {
         const int rbl = wave + kScoreWaves * i;
         if (rbl < g.rbw) {
-            // l = mantissa in [0.5, 1): a sum far from 1 must not lose the others when they are scaled to its m
-            auto normalise = [](float& mi, float& li) {
-                if (li > 0.f) { const int e = __builtin_amdgcn_frexp_expf(li); li = ldexpf(li, -e); mi += static_cast<float>(e); }
-            };
-            normalise(m[i], l[i]);
+            normalise_softmax(m[i], l[i]);
             if (i == 1 && second == SecondBlock::kSubtile0) {
                 float2 o = shared_rows[wave & 1][lane];
-                normalise(o.x, o.y);
+                normalise_softmax(o.x, o.y);
                 merge_softmax(m[i], l[i], o.x, o.y);
             }
             const float m2 = __shfl_xor(m[i], 32, 64), l2 = __shfl_xor(l[i], 32, 64);
