@@ -928,9 +928,13 @@ __global__ __launch_bounds__(kScoreThreads) void narrow_col_sums_kernel(const T*
     const int n = subs > wave ? (subs - wave + kScoreWaves - 1) / kScoreWaves : 0;
     auto load = [&](u32x4_t (&dst)[NCH], int t) { load_fragments<T, NCH>(dst, k_head, vb + (wave + t * kScoreWaves) * kSubKeys, ve - 1, g.dh); };
     u32x4_t k[DEPTH][NCH], q[NB][NCH];
-    load_queries<T, NCH, NB>(q, q_text, g, kvh);
+    // a wave without keys only helps with the merge: loading its queries too made short levels in fp32 slower than the merging kernel
+    // did (300 tokens, 2 heads x 64 queries of 128 elements, kernels alone: 31.5 us so, 29.9 with the merging kernel, now 26.7)
+    if (n > 0) {
+        load_queries<T, NCH, NB>(q, q_text, g, kvh);
 #pragma unroll
-    for (int d = 0; d < DEPTH - 1; ++d) load(k[d], d);
+        for (int d = 0; d < DEPTH - 1; ++d) load(k[d], d);
+    }
     const int rows = g.rbw * 32;                                       // 32 or 64; NB * 16 of them are used
     // two partials a round: with eight the kernel takes up to twice the registers, and where there is more than one workgroup per CU the
     // second one waits (fp32, 40 heads x 64 queries of 64 elements, 8 x 5000 tokens: 421 -> 407 us)
