@@ -651,8 +651,11 @@ __global__ __launch_bounds__(256) void merge_stats_kernel(const float* __restric
 // visual keys.  The eight per-wave partial column sums of a stage are added in wave order through LDS.
 // colpart[y * n_vis + j] = sum over the rows of workgroup-row y of the probability of visual key j.
 // ---------------------------------------------------------------------------------------------
+// Grids of more workgroups than CUs run two (or three) to a CU where 128 (80) registers suffice, which the merge must not exceed:
+// with eight partials a round in every kernel, 20 x 3000 tokens of 40 heads x 100 queries took 438 us for 389 with the merging kernel,
+// in bf16 with 256 elements 934 for 810, and now 381 and 793.  A thread has at most four (kMergeInPass2Bytes).
 template <typename T, int NCH, int RBW, int SUBS>
-__global__ __launch_bounds__(kScoreThreads) void col_sums_kernel(const uint4* __restrict__ qfrag, const T* __restrict__ k_all,
+__global__ __launch_bounds__(kScoreThreads, RBW == 2 && NCH > 4 ? 2 : 4) void col_sums_kernel(const uint4* __restrict__ qfrag, const T* __restrict__ k_all,
                                                                  const ScoreGeom g, int sub_per_wg, const float* __restrict__ norm,
                                                                  const float* __restrict__ pstat, int nx1, float* __restrict__ colpart) {
     using Stage = KeyStage<T, NCH, SUBS>;
@@ -684,7 +687,7 @@ __global__ __launch_bounds__(kScoreThreads) void col_sums_kernel(const uint4* __
     load_qfrag<NCH, RBW>(q, qfrag, g, kvh, rb0, nrb, wave, second, lane);
     const float* rows_norm = norm + static_cast<size_t>(blockIdx.y) * g.rbw * 32;
     if (pstat) {                                                        // no kernel has merged the partials
-        merge_rows<8>(pstat + static_cast<size_t>(blockIdx.y) * nx1 * g.rbw * 64, nx1, g.rbw * 32, rb0 * 32, g.R, red, own_norm);
+        merge_rows<(RBW == 2 || NCH == 8 ? 4 : 2)>(pstat + static_cast<size_t>(blockIdx.y) * nx1 * g.rbw * 64, nx1, g.rbw * 32, rb0 * 32, g.R, red, own_norm);
         rows_norm = own_norm;
     }
     // accumulator e <-> query row 32 rbl + 8 (e / 4) + 4 h + e % 4
