@@ -1,0 +1,161 @@
+// How the score passes and the selection of stage 2 lie on the chip and in the workspace: host arithmetic in plain C++, without
+// HIP, so that it can be built and checked on its own.
+#pragma once
+
+#include <math.h>
+#include <stddef.h>
+#include <stdint.h>
+
+#include "metok.h"
+
+namespace metok {
+
+constexpr int kScoreThreads = 512;
+constexpr int kScoreWaves = kScoreThreads / 64;
+constexpr int kSelThreads = 1024;      // also the tile size of the selection: tile i = tokens [1024 i, 1024 i + 1024)
+constexpr int kSelCache = 40;          // keys per thread held in registers (n_vis <= 40960)
+
+inline size_t round_up_256(size_t x) { return (x + 255) / 256 * 256; }
+
+struct ScoreGeom {
+    int64_t S;
+    int Hq, Hkv, group, dh, Tq;
+    int R;              // rows per kv head = group * Tq
+    int rb_total;       // 32-row blocks per kv head
+    int rbw;            // row blocks per workgroup (<= kScoreWaves * RBW)
+    int rs;             // row splits per kv head
+    int vis_start, n_vis;
+    int64_t key_begin, key_end;   // keys the softmax of pass 1 normalises over (before the causal mask)
+    float scale_log2;   // log2(e) / sqrt(dh)
+    // a batch of videos runs as one launch, blockIdx.z = video: distances between consecutive videos
+    int64_t q_video, k_video;     // elements of q_text / k_all
+    int64_t ws_video;             // bytes of workspace
+};
+
+struct FastSel {
+    uint32_t arrive;                        // cleared before the kernel that counts on it
+    int32_t n_kept;                         // kept tokens written (the rest of the list is padding)
+};
+constexpr int kFastClearWords = 1;
+
+// selection scratch: per-class tile counts above / equal to the threshold [2][METOK_MAX_SEGMENTS][n_tiles], then
+// (threshold, equal keys kept) per class
+inline int select_tiles(int n_vis) { return (n_vis + kSelThreads - 1) / kSelThreads; }
+inline size_t select_count_bytes(int n_vis) {
+    return round_up_256(static_cast<size_t>(METOK_MAX_SEGMENTS) * select_tiles(n_vis) * sizeof(int32_t));
+}
+inline size_t select_general_bytes(int n_vis) { return 2 * select_count_bytes(n_vis) + METOK_MAX_SEGMENTS * 2 * sizeof(uint32_t); }
+// then the fast path's state.  The reserve is larger than FastSel needs, and the two words per token behind it are used by
+// no kernel: they held the histograms and candidate lists of an earlier selection.  The size of a workspace is part of the
+// interface (it also decides which shapes metok_prefill_prune_static takes), so it stays what it has been; row splits put their
+// additional column sums there, see plan_score.
+constexpr size_t kFastReserve = 34560;
+static_assert(sizeof(FastSel) <= kFastReserve, "the fast path's state outgrew its reserve");
+inline size_t select_bytes(int n_vis) {
+    const size_t unused = round_up_256(static_cast<size_t>(n_vis < kSelCache * kSelThreads ? n_vis : kSelCache * kSelThreads) * sizeof(uint32_t));
+    return select_general_bytes(n_vis) + kFastReserve + 2 * unused;
+}
+
+// In-place compaction (hidden_out == hidden): the source row of every output row as an index list, and the
+// progress flags of the row mover.  Rows of at most kInPlaceMaxRowBytes keep a row inside one workgroup
+// pass, so a tile has at least eight rows and the flag count is bounded by the sequence length alone.
+constexpr int64_t kInPlaceMaxRowBytes = 16384;
+inline size_t inplace_index_bytes(int64_t S) { return round_up_256(static_cast<size_t>(S) * sizeof(int32_t)); }
+inline size_t inplace_bytes(int64_t S) {
+    return inplace_index_bytes(S) + round_up_256((64 + static_cast<size_t>((S + 7) / 8)) * sizeof(uint32_t));
+}
+
+inline int chunk_count(int dh, int dtype) { return dtype == METOK_BF16 ? dh / 16 : dh / 8; }     // 16-byte chunks per lane
+
+// Row blocks a wave keeps in registers: two while the fragments of a block take at most 32 VGPRs, else one.
+inline int row_blocks_per_wave(int nch) { return nch <= 8 ? 2 : 1; }
+
+inline bool make_geom(int64_t S, int Hq, int Hkv, int dh, int Tq, int vis_start, int n_vis, int dtype, int score_mode,
+                      ScoreGeom* g) {
+    g->S = S; g->Hq = Hq; g->Hkv = Hkv; g->group = Hq / Hkv; g->dh = dh; g->Tq = Tq;
+    g->R = g->group * Tq;
+    g->rb_total = (g->R + 31) / 32;
+    const int nch = chunk_count(dh, dtype);
+    if (nch > 16) return false;
+    const int cap = kScoreWaves * row_blocks_per_wave(nch);
+    g->rs = (g->rb_total + cap - 1) / cap;
+    g->rbw = (g->rb_total + g->rs - 1) / g->rs;
+    g->vis_start = vis_start; g->n_vis = n_vis;
+    g->key_begin = score_mode == METOK_SCORE_VISUAL_ONLY ? vis_start : 0;
+    g->key_end = score_mode == METOK_SCORE_VISUAL_ONLY ? static_cast<int64_t>(vis_start) + n_vis : S;
+    g->scale_log2 = static_cast<float>(1.4426950408889634 / sqrt(static_cast<double>(dh)));
+    return true;
+}
+
+struct ScorePlan {
+    int nx1, nx2;                   // workgroups along the keys in pass 1 / pass 2
+    int per1, per2;                 // 32-key subtiles per workgroup
+    size_t off_qfrag, off_pstat, off_norm, off_colpart, off_sel, off_inplace, total;
+};
+
+// One 512-thread workgroup per CU: what the registers and LDS of the two-block kernels allow.  Two of the one-block ones
+// (about 100 VGPRs, at most 64 KB) would fit; their grids were not tuned for that.
+constexpr int kScoreSlots = 256;
+
+inline void plan_grid(const ScoreGeom& g, int n_vis, int nch, int batch, size_t sel_bytes, ScorePlan* p) {
+    const int ny = g.Hkv * g.rs;
+    const int64_t rows_of_grid = static_cast<int64_t>(ny) * batch;          // the videos of a batch share the chip's slots
+    const int nx0 = kScoreSlots / rows_of_grid < 1 ? 1 : static_cast<int>(kScoreSlots / rows_of_grid);
+    auto pick = [&](int64_t subtiles, int* per) {
+        int64_t nx = nx0 < subtiles ? nx0 : subtiles;
+        if (nx < 1) nx = 1;
+        *per = static_cast<int>((subtiles + nx - 1) / nx);
+        if (*per < 1) *per = 1;
+        nx = (subtiles + *per - 1) / *per;                  // smallest grid with the same critical path
+        return static_cast<int>(nx < 1 ? 1 : nx);
+    };
+    p->nx1 = pick((g.key_end - g.key_begin + 31) / 32, &p->per1);
+    p->nx2 = pick((static_cast<int64_t>(n_vis) + 31) / 32, &p->per2);
+    // the partial statistics are sized for the widest pass-1 grid of either score mode, so one
+    // workspace query serves both
+    int64_t nx1_cap = nx0;
+    const int64_t sub_all = (g.S + 31) / 32;
+    if (nx1_cap > sub_all) nx1_cap = sub_all;
+    size_t off = 0;
+    p->off_qfrag = off;   off += static_cast<size_t>(g.Hkv) * g.rb_total * nch * 1024;
+    p->off_pstat = off;   off += round_up_256(static_cast<size_t>(ny) * nx1_cap * g.rbw * 32 * 2 * sizeof(float));
+    p->off_norm = off;    off += round_up_256(static_cast<size_t>(ny) * g.rbw * 32 * sizeof(float));
+    p->off_colpart = off; off += round_up_256(static_cast<size_t>(ny) * n_vis * sizeof(float));
+    p->off_sel = off;     off += sel_bytes;
+    p->off_inplace = off; off += inplace_bytes(g.S);
+    p->total = round_up_256(off);
+}
+
+// Up to here every workgroup of pass 2 merges the partial statistics of its rows for itself, above a kernel in between does it
+// once.  One level, us, merged in pass 2 / by the kernel, rows whole: 300 tokens, 448 rows x 11 partials (40 KB) 28.6 / 30.2; 32 heads on 8, 256
+// x 32 (64 KB) 51.9 / 51.9; two videos of 4000 tokens, 448 x 32 (112 KB) 41.2 / 40.6; one of 3700, 448 x 59 (206 KB) 33.4 / 32.6; 14
+// heads on 2, 448 x 128 35.4 / 31.8; 7 heads on 1, 448 x 256 40.7 / 34.7: the exponentials of a large merge take longer than the
+// launch.  The narrow kernels have at most 64 rows and always merge for themselves.
+constexpr size_t kMergeInPass2Bytes = 64 * 1024;
+inline size_t partial_bytes(const ScoreGeom& g, const ScorePlan& p) { return static_cast<size_t>(p.nx1) * g.rbw * 32 * 2 * sizeof(float); }
+
+// More than eight row blocks go two to a wave, which lets a key fragment feed two products and reads the keys once.  On short
+// ranges the fixed part of a workgroup (its queries, the merge of all its rows' partial statistics, the first stage) is what takes
+// the time, and half the rows in each of twice as many workgroups make it shorter: up to kSplitSubtiles subtiles a workgroup the
+// rows are split until every wave has one block, up to kSplitSubtilesMerged where the whole rows' partials would take the merging
+// kernel.  One level of 28 heads on 4 x 64 queries, us whole / split: 300 tokens 26.5 / 24.1, 2243 (2 subtiles) 32.7 / 28.9, 6000
+// 40.6 / 36.7, 9000 (5) 47.4 / 44.4, 15000 (8) 62.6 / 60.7, 18432 (10) 63.0 / 64.2; two videos of 4000 41.2 / 39.5, eight of 1000
+// (5) 45.5 / 42.6, four of 3000 (6, merged in pass 2) 49.5 / 50.1; 14 heads on 2 x 64, 8000 tokens 34.3 / 30.8.
+// A split needs more room for the column sums and none for the two words per token that select_bytes reserves for nobody; where
+// it does not fit the workspace of the whole rows, the rows stay whole.
+constexpr int kSplitSubtiles = 5, kSplitSubtilesMerged = 8;
+inline void plan_score(ScoreGeom* g, int n_vis, int nch, int batch, ScorePlan* p) {
+    plan_grid(*g, n_vis, nch, batch, select_bytes(n_vis), p);
+    if (g->rbw <= kScoreWaves || p->per1 > (partial_bytes(*g, *p) > kMergeInPass2Bytes ? kSplitSubtilesMerged : kSplitSubtiles)) return;
+    ScoreGeom split = *g;
+    split.rs = (g->rb_total + kScoreWaves - 1) / kScoreWaves;
+    split.rbw = (g->rb_total + split.rs - 1) / split.rs;
+    if (static_cast<int64_t>(split.Hkv) * split.rs > 65535) return;
+    ScorePlan s;
+    plan_grid(split, n_vis, nch, batch, round_up_256(select_general_bytes(n_vis) + sizeof(FastSel)), &s);
+    if (s.total > p->total) return;
+    s.total = p->total;
+    *g = split; *p = s;
+}
+
+}  // namespace metok

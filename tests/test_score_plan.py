@@ -1,0 +1,48 @@
+"""The plan of the score passes over many shapes: every row block and key belongs to one workgroup, the regions of the workspace hold
+what the kernels put there without touching each other, and splitting the rows changes no workspace size."""
+import random
+
+import pytest
+
+from tests.score_plan import score_plans
+
+HEADS = [(28, 4), (40, 40), (32, 8), (14, 2), (9, 1), (64, 2), (16, 16), (52, 4), (300, 5)]
+
+
+def draw(rng):
+    Hq, Hkv = rng.choice(HEADS)
+    dtype = rng.choice(["bf16", "f32"])
+    dh = rng.choice([32, 64, 128, 256] if dtype == "bf16" else [32, 64, 128])
+    Tq = rng.choice([1, 16, 31, 64, rng.randint(1, 400)])
+    n_vis = int(2 ** rng.uniform(0, 16.3))
+    vis_start = rng.choice([0, 0, rng.randint(1, 60)])
+    S = vis_start + n_vis + Tq + rng.choice([0, rng.randint(0, 100)])
+    return dict(S=S, n_vis=n_vis, Hq=Hq, Hkv=Hkv, dh=dh, Tq=Tq, dtype=dtype, batch=rng.choice([1, 1, 1, 2, 3, 8, 17, 64]), vis_start=vis_start, mode=rng.choice([0, 0, 1]))
+
+
+@pytest.mark.parametrize("seed", range(8))
+def test_plans(seed):
+    rng = random.Random(seed)
+    split = 0
+    for _ in range(500):
+        a = draw(rng)
+        r = score_plans(**a)
+        p, n_vis, S, Hkv = r.plan, a["n_vis"], a["S"], a["Hkv"]
+        nch = a["dh"] // (16 if a["dtype"] == "bf16" else 8)
+        split += r.split
+        # rows: at most 16 (8) blocks a workgroup, no empty split
+        assert p.rbw <= (16 if nch <= 8 else 8) and (p.rs - 1) * p.rbw < r.rb_total <= p.rs * p.rbw, a
+        assert p.rbw <= 8 or not r.split, a
+        # keys: no workgroup without any
+        keys = n_vis if a["mode"] == 1 else S
+        for nx, per, n in ((p.nx1, p.per1, keys), (p.nx2, p.per2, n_vis)):
+            assert (nx - 1) * per * 32 < n <= nx * per * 32, a
+        # workspace: what the kernels address, region by region
+        ny = Hkv * p.rs
+        regions = [(p.qfrag, Hkv * r.rb_total * nch * 1024), (p.pstat, ny * p.nx1 * p.rbw * 32 * 8), (p.norm, ny * p.rbw * 32 * 4), (p.colpart, ny * n_vis * 4),
+                   (p.sel, r.general_bytes + r.fast_bytes), (p.inplace, r.inplace_bytes), (p.total, 0)]
+        for (at, size), (end, _) in zip(regions, regions[1:]):
+            assert at % 256 == 0 and at + size <= end, (a, at, size, end)
+        # the size does not depend on the split, the score mode or the first visual token
+        assert p.total == r.whole.total == score_plans(**{**a, "vis_start": 0, "mode": 0}).plan.total, a
+    assert split > 20                                                  # the draw reaches the splits
