@@ -1828,7 +1828,7 @@ static size_t video_workspace_bytes(int batch, int64_t S, int Hq, int Hkv, int d
     ScorePlan p;
     if (Hq >= 1 && Hkv >= 1 && Tq >= 1 && Hq % Hkv == 0 && dh_supported(dh, dtype) &&
         make_geom(S, Hq, Hkv, dh, Tq, 0, n_vis, dtype, METOK_SCORE_CAUSAL_ALL, &g)) {
-        plan_score(&g, n_vis, chunk_count(dh, dtype), batch, &p);
+        plan_score(&g, n_vis, dtype, batch, &p);
         return p.total;
     }
     return round_up(select_bytes(n_vis) + inplace_bytes(S), 256);      // no attention pass (scores supplied by the caller)
@@ -1932,7 +1932,7 @@ static int prune_impl(int batch, const void* hidden, int64_t S, int D, int dtype
         if (!make_geom(S, Hq, Hkv, dh, Tq, vis_start, n_vis, dtype, score_mode, &g)) return fail(METOK_ERR_UNSUPPORTED, "head dimension too large");
         if (static_cast<int64_t>(g.Hkv) * g.rs > 65535) return fail(METOK_ERR_UNSUPPORTED, "too many query rows");
         ScorePlan p;
-        plan_score(&g, n_vis, chunk_count(dh, dtype), batch, &p);
+        plan_score(&g, n_vis, dtype, batch, &p);
         g.q_video = static_cast<int64_t>(Hq) * Tq * dh; g.k_video = static_cast<int64_t>(Hkv) * S * dh; g.ws_video = ws_video;
         if (static_cast<int64_t>(p.total) != ws_video) return fail(METOK_ERR_DEVICE, "internal: workspace plan mismatch");
         if (!workspace || workspace_bytes < p.total * batch || !aligned16(workspace))

@@ -18,7 +18,7 @@ extern "C" int plans(int batch, int64_t S, int Hq, int Hkv, int dh, int Tq, int 
     if (!make_geom(S, Hq, Hkv, dh, Tq, vis_start, n_vis, dtype, mode, &whole)) return 1;
     g = whole;
     plan_grid(whole, n_vis, chunk_count(dh, dtype), batch, select_bytes(n_vis), &pw);
-    plan_score(&g, n_vis, chunk_count(dh, dtype), batch, &p);
+    plan_score(&g, n_vis, dtype, batch, &p);
     auto put = [&](const ScoreGeom& a, const ScorePlan& b) {
         for (int64_t v : {int64_t(a.rs), int64_t(a.rbw), int64_t(b.nx1), int64_t(b.per1), int64_t(b.nx2), int64_t(b.per2), int64_t(b.off_qfrag), int64_t(b.off_pstat),
                           int64_t(b.off_norm), int64_t(b.off_colpart), int64_t(b.off_sel), int64_t(b.off_inplace), int64_t(b.total), int64_t(partial_bytes(a, b))})

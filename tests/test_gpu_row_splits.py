@@ -88,9 +88,9 @@ def test_batch_around_the_row_split(keys):
 
 @pytest.mark.parametrize("keys", [8192, 8193])                        # 8 kv heads, 32 workgroups of eight subtiles along the keys
 def test_scores_around_the_row_split_with_many_partials(keys):
-    # 9 blocks x 32 partials are more than pass 2 merges for itself
+    # 14 blocks x 32 partials are more than pass 2 merges for itself
     Tq, Hkv = 32, 8
-    plans = score_plans(keys, keys - Tq, 9 * Hkv, Hkv, 64, Tq)
+    plans = score_plans(keys, keys - Tq, 14 * Hkv, Hkv, 64, Tq)
     assert plans.split == (keys == 8192) and plans.whole.partials > 65536
-    layer = make_layer(5900, 1, keys - Tq, 1, Tq, 16, 9 * Hkv, Hkv, 64, "bf16")
+    layer = make_layer(5900, 1, keys - Tq, 1, Tq, 16, 14 * Hkv, Hkv, 64, "bf16")
     check_level(layer, Tq)
