@@ -5,8 +5,8 @@
 // Everything that can fail, the Python objects of the results included, is done before the library is called: a failure behind
 // the launch, taken for a declined call, would have binding.py launch it a second time.
 //
-// Why: of the 26 us of the smallest stage-1 call 18 were Python (nine outputs of 1.2 us each, fourteen pointers, thirty-five
-// ctypes arguments), of one pruning level's 28 us of host time 15; the kernels of both take less than that.
+// Why: of the 26 us of the smallest stage-1 call 18 were Python (eleven outputs and a workspace of 1.2 us each, 31 ctypes
+// arguments), of one pruning level's 28 us of host time 15; the kernels of both take less than that.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 

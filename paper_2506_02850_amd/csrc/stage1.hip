@@ -201,7 +201,9 @@ __global__ __launch_bounds__(kStatsThreads) void frame_stats_kernel(
 // ---------------------------------------------------------------------------------------------
 constexpr int kSegThreads = 1024;
 constexpr int kMaxReduceWgs = 64;
-constexpr int kShortFrames = 512;          // up to here segment_short_kernel: at least two threads per frame
+// Up to here segment_short_kernel, with at least two threads per frame.  512 frames of 2 x 2 x 64, us, segment_kernel / segment_short_kernel:
+// 1 event 56.2 / 40.1, 5 46.7 / 32.4, 64 33.4 / 24.0, 256 37.1 / 29.0, 512 43.9 / 43.7; 384 frames, 1 event 44.7 / 31.1, 384 35.1 / 31.6.
+constexpr int kShortFrames = 512;
 // Up to here one workgroup adds up the partials too, two frames per wave, and nothing is handed over; but not where the frames
 // beyond one per wave bring more than kOneReducePartials partial sums, which a second workgroup would read in the meantime.  Whole
 // calls of T frames x C partials, us, one workgroup / several: 32 x 256 17.8 / 18.3 and 16.1 / 16.7, 32 x 576 22.4 / 21.6 and 29.3 / 28.3,
@@ -660,14 +662,12 @@ __global__ __launch_bounds__(kSegThreads) void segment_kernel(const SegmentArgs 
     reduce_partials(a, part, frame_score, frame_norm2, pair_dot);
     __builtin_amdgcn_s_waitcnt(0);          // this thread's totals are stored
     __syncthreads();
-    if (gridDim.x > 1) {
-        if (threadIdx.x == 0) {
-            uint32_t* arrive = reinterpret_cast<uint32_t*>(part + static_cast<size_t>(a.T - 1) * a.C * 3 + 1);
-            sh.last = __hip_atomic_fetch_add(arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1 ? 1 : 0;
-        }
-        __syncthreads();
-        if (!sh.last) return;
+    if (threadIdx.x == 0) {                 // more than kShortFrames frames: there are always several workgroups
+        uint32_t* arrive = reinterpret_cast<uint32_t*>(part + static_cast<size_t>(a.T - 1) * a.C * 3 + 1);
+        sh.last = __hip_atomic_fetch_add(arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1 ? 1 : 0;
     }
+    __syncthreads();
+    if (!sh.last) return;
     segment_video(a, sh, of_video_elems(a.sim, a.T - 1), of_video_elems(a.event_start, a.k + 1), of_video_elems(a.frame_event, a.T),
                   frame_norm2, pair_dot);
     if (WITH_PLAN) plan_video(plan, sh, frame_score, a.T, a.k);
@@ -702,8 +702,8 @@ __global__ __launch_bounds__(kSegThreads) void plan_kernel(const PlanArgs1 plan,
 // keys start at 0, so that "smaller, or equal and earlier" is one comparison with a threshold of the compared frame; results
 // are stored without being waited for (lds_barrier); a frame's row count comes from a table of its four kinds; and
 // up to kOneReduceFrames frames the totals stay in LDS and no other workgroup is waited for.  Whole calls: 32 frames of 27 x 27 x
-// 1152 36.1 -> 31.8 us, 128 of 24 x 24 x 1024 68.3 -> 63.8 us, 8 x 64 of 27 x 27 x 1152 299 -> 294 us, 8 x 256 pooled uniformly
-// 550 -> 541 us.
+// 1152 36.1 -> 31.8 us, 128 of 24 x 24 x 1024 68.3 -> 63.8 us, 8 x 64 of 27 x 27 x 1152 299 -> 294 us; the 8 us that it saves 8 x 256
+// frames pooled uniformly (19.6 -> 11.4) are within the noise of that call's 540 us.
 // ---------------------------------------------------------------------------------------------
 struct ShortShared {
     uint32_t key[kShortFrames + 4];        // sort keys of S_i, padded with the largest value

@@ -1,7 +1,7 @@
 // Stage 2 (Sec. 3.2.2): one level of hierarchical pruning.
 //
-//   row_stats_kernel     MFMA pass 1 over all keys: per (head, text query) running max and sum of the
-//                        causal softmax, in the log2 domain, per workgroup; leaves the queries in MFMA fragment order
+//   row_stats_kernel     MFMA pass 1 over all keys: per (head, text query) sum of the causal softmax, relative to a
+//                        number of its own, in the log2 domain, per workgroup; leaves the queries in MFMA fragment order
 //   merge_stats_kernel   merges the per-workgroup partial sums into one normaliser per row (pass 2 does it for itself where
 //                        they are few)
 //   col_sums_kernel      MFMA pass 2 over the visual keys: recomputes the logits and adds up the
@@ -518,10 +518,8 @@ __global__ __launch_bounds__(kScoreThreads) void row_stats_kernel(const T* __res
                 normalise_softmax(o.x, o.y);
                 merge_softmax(m[i], l[i], o.x, o.y);
             }
-            const float m2 = __shfl_xor(m[i], 32, 64), l2 = __shfl_xor(l[i], 32, 64);
-            const float mm = fmaxf(m[i], m2);
-            const float ll = l[i] * fast_exp2(m[i] - mm) + l2 * fast_exp2(m2 - mm);
-            if (h == 0) store_partial(pstat, rows_per_y, rbl * 32 + lane, mm, ll);
+            merge_softmax(m[i], l[i], __shfl_xor(m[i], 32, 64), __shfl_xor(l[i], 32, 64));
+            if (h == 0) store_partial(pstat, rows_per_y, rbl * 32 + lane, m[i], l[i]);
         }
     }
 }
@@ -617,10 +615,7 @@ __global__ __launch_bounds__(256) void merge_stats_kernel(const float* __restric
     }
 #pragma unroll
     for (int off = 8; off >= 1; off >>= 1) {
-        const float m2 = __shfl_xor(mm, off, 16), l2 = __shfl_xor(ll, off, 16);
-        const float mx = fmaxf(mm, m2);
-        ll = ll * fast_exp2(mm - mx) + l2 * fast_exp2(m2 - mx);
-        mm = mx;
+        merge_softmax(mm, ll, __shfl_xor(mm, off, 16), __shfl_xor(ll, off, 16));
     }
     if (i < total && p == 0) {
         const int r = (y % g.rs) * rows_per_y + lr;
