@@ -202,7 +202,7 @@ __global__ __launch_bounds__(kStatsThreads) void frame_stats_kernel(
 constexpr int kSegThreads = 1024;
 constexpr int kMaxReduceWgs = 64;
 // Up to here segment_short_kernel, with at least two threads per frame.  512 frames of 2 x 2 x 64, us, segment_kernel / segment_short_kernel:
-// 1 event 56.2 / 40.1, 5 46.7 / 32.4, 64 33.4 / 24.0, 256 37.1 / 29.0, 512 43.9 / 43.7; 384 frames, 1 event 44.7 / 31.1, 384 35.1 / 31.6.
+// 1 event 56.2 / 40.1, 5 46.7 / 31.9, 64 33.4 / 24.0, 256 37.1 / 25.1, 512 43.9 / 30.1; 384 frames, 1 event 44.7 / 31.1, 384 35.3 / 24.0.
 constexpr int kShortFrames = 512;
 // Up to here one workgroup adds up the partials too, two frames per wave, and nothing is handed over; but not where the frames
 // beyond one per wave bring more than kOneReducePartials partial sums, which a second workgroup would read in the meantime.  Whole
@@ -698,7 +698,7 @@ __global__ __launch_bounds__(kSegThreads) void plan_kernel(const PlanArgs1 plan,
 // Nothing here is work; it is a chain of memory round trips, barriers and rankings.  Stamped inside the kernel, 8 videos of 256
 // frames (32 frames) took 16.5 us (10.0): totals and arrival 2.4 (2.2), one more round trip 0.7, the ranking of the
 // similarities 3.6 (1.2), two block scans 1.5, waits for the stores of results 1.0, event scores, key events and key frames
-// 4.8 (2.9), event ids 2.5.  So: a power of two of threads (`share`, 2 to 64) compares for a frame, and 16 lanes for an event;
+// 4.8 (2.9), event ids 2.5.  So: a power of two of threads (`share`, 2 to 64) compares for a frame, and 2 to 16 lanes for an event;
 // keys start at 0, so that "smaller, or equal and earlier" is one comparison with a threshold of the compared frame; results
 // are stored without being waited for (lds_barrier); a frame's row count comes from a table of its four kinds; and
 // up to kOneReduceFrames frames the totals stay in LDS and no other workgroup is waited for.  Whole calls: 32 frames of 27 x 27 x
@@ -708,7 +708,7 @@ __global__ __launch_bounds__(kSegThreads) void plan_kernel(const PlanArgs1 plan,
 struct ShortShared {
     uint32_t key[kShortFrames + 4];        // sort keys of S_i, padded with the largest value
     uint32_t fkey[kShortFrames];           // of the frame scores
-    uint32_t ekey[kShortFrames];           // of the event scores
+    alignas(16) uint32_t ekey[kShortFrames];           // of the event scores, padded to four with the smallest key
     uint16_t start[kShortFrames + 2];
     uint16_t event[kShortFrames];
     uint16_t n_kf[kShortFrames];           // key frames of an event
@@ -730,9 +730,19 @@ __device__ __forceinline__ int group_total(int v, int log2) {
     if (log2 > 5) { const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false); v = static_cast<int>(r[0]) + static_cast<int>(r[1]); }
     return v;
 }
-// Threads per frame: the largest power of two up to 64 of which T fit the workgroup.
-__device__ __forceinline__ int share_log2(int T) {
-    const int l = 31 - __clz(kSegThreads / T);
+// The same for a maximum or a sum of floats, log2 <= 4.
+template <bool MAX> __device__ __forceinline__ float group_fold(float v, int log2) {
+    auto pick = [](float a, int b) { return MAX ? fmaxf(a, __int_as_float(b)) : a + __int_as_float(b); };
+    v = pick(v, __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xb1, 0xf, 0xf, false));
+    if (log2 > 1) v = pick(v, __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4e, 0xf, 0xf, false));
+    if (log2 > 2) v = pick(v, __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xf, 0xf, false));
+    if (log2 > 3) v = pick(v, __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xf, 0xf, false));
+    return v;
+}
+// Threads for each of n items: the largest power of two up to 64 of which n fit the workgroup (2^10 threads; without a division).
+__device__ __forceinline__ int share_log2(int n) {
+    static_assert(kSegThreads == 1 << 10, "22 is 32 - 10");
+    const int l = __clz(n - 1) - 22;
     return l < 6 ? l : 6;
 }
 
@@ -744,30 +754,24 @@ __device__ __forceinline__ void plan_short(const PlanArgs1& a, ShortShared& sh, 
     uint8_t* event_is_key = of_video_elems(a.event_is_key, k);
     const bool use_max = a.event_reduce == METOK_EVENT_MAX;
     lds_barrier();
-    // event score: mean (Sec. 3.2.1) or max (Algorithm 1) of the frame scores; 16 lanes per event
-    const int l16 = tid & 15;
-    for (int v = tid >> 4; v < k; v += kSegThreads / 16) {
+    // event score: mean (Sec. 3.2.1) or max (Algorithm 1) of the frame scores; 2 to 16 lanes per event, so that one pass takes all.
+    // (16 lanes whatever their number, several passes: plan and pooling of 512 frames in 512 events 30.1 us, with a thread per event 24.4, now 16.4.)
+    const int el = min(4, share_log2(k)), v = tid >> el, l = tid & ((1 << el) - 1);
+    if (v < k) {
         const int lo = sh.start[v], hi = max(lo, static_cast<int>(sh.start[v + 1]));
         float acc = use_max ? -INFINITY : 0.f;
-        for (int m = lo + l16; m < hi; m += 16) { const float x = score_of_key(sh.fkey[m] + 1u); acc = use_max ? fmaxf(acc, x) : acc + x; }
-        if (use_max) {
-#pragma unroll
-            for (int step = 0; step < 4; ++step) {
-                const int u = __float_as_int(acc);
-                const int o = step == 0 ? __builtin_amdgcn_update_dpp(0, u, 0x128, 0xf, 0xf, false) : step == 1 ? __builtin_amdgcn_update_dpp(0, u, 0x124, 0xf, 0xf, false)
-                            : step == 2 ? __builtin_amdgcn_update_dpp(0, u, 0x122, 0xf, 0xf, false) : __builtin_amdgcn_update_dpp(0, u, 0x121, 0xf, 0xf, false);
-                acc = fmaxf(acc, __int_as_float(o));
-            }
-        } else {
-            acc = row16_sum(acc);
+        for (int m = lo + l; m < hi; m += 1 << el) { const float x = score_of_key(sh.fkey[m] + 1u); acc = use_max ? fmaxf(acc, x) : acc + x; }
+        if (use_max) acc = group_fold<true>(acc, el);
+        else {
+            acc = el == 4 ? row16_sum(acc) : group_fold<false>(acc, el);
             acc = hi > lo ? acc / static_cast<float>(hi - lo) : 0.f;
         }
-        if (l16 == 0) {
+        if (l == 0) {
             event_score[v] = acc;
             sh.ekey[v] = sort_key(acc);
             sh.n_kf[v] = static_cast<uint16_t>(min(hi - lo, static_cast<int>(ceil(a.beta * static_cast<double>(hi - lo) - 1e-9))));
         }
-    }
+    } else if (v < ((k + 3) & ~3)) sh.ekey[v] = 0u;                  // above no event
     // rank of the frame inside its event under (score descending, index ascending)
     int above = 0;
     if (f < T) {
@@ -777,17 +781,27 @@ __device__ __forceinline__ void plan_short(const PlanArgs1& a, ShortShared& sh, 
     }
     above = group_total(above, sl);
     lds_barrier();
-    // key events, ranked likewise
-    for (int v = tid >> 4; v < k; v += kSegThreads / 16) {
+    // key events, ranked likewise, four keys at a time
+    int n = 0;
+    if (v < k) {
         const uint32_t ke = sh.ekey[v];
-        int n = 0;
-        for (int m = l16; m < k; m += 16) n += sh.ekey[m] >= ke + (m < v ? 0u : 1u) ? 1 : 0;
-        n = group_total(n, 4);
-        if (l16 == 0) {
-            const uint8_t is_key = n < a.n_key_events ? 1 : 0;
-            sh.ev_key[v] = is_key;
-            event_is_key[v] = is_key;
+        const uint4* ekey4 = reinterpret_cast<const uint4*>(sh.ekey);
+        for (int q = l; q < (k + 3) / 4; q += 1 << el) {
+            const uint4 km = ekey4[q];
+            const uint32_t bound = ke + (q < (v >> 2) ? 0u : 1u);      // equal keys of earlier quads count
+            n += (km.x >= bound ? 1 : 0) + (km.y >= bound ? 1 : 0) + (km.z >= bound ? 1 : 0) + (km.w >= bound ? 1 : 0);
         }
+        if (l == 0) {                                                  // and those before v in its own quad
+            const uint4 km = ekey4[v >> 2];
+            const int in = v & 3;
+            n += (in > 0 && km.x == ke ? 1 : 0) + (in > 1 && km.y == ke ? 1 : 0) + (in > 2 && km.z == ke ? 1 : 0);
+        }
+    }
+    n = group_total(n, el);
+    if (v < k && l == 0) {
+        const uint8_t is_key = n < a.n_key_events ? 1 : 0;
+        sh.ev_key[v] = is_key;
+        event_is_key[v] = is_key;
     }
     lds_barrier();
     const bool own = f < T && s == 0;
