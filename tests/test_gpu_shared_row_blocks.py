@@ -79,8 +79,9 @@ def check_scores_of_jumps(dtype, dh, group, Tq, S, high, run, up):
     assert (np.abs(got - want) <= tol * want + 2.0 ** -126).all(), float((np.abs(got - want) / (want + 1e-30)).max())
 
 
-# 14 blocks (four of them shared by two waves each), 16, 9 (one shared), 8, and a split of 27
-@pytest.mark.parametrize("dtype,dh,group,Tq", [("bf16", 64, 7, 64), ("bf16", 128, 8, 64), ("f32", 64, 9, 32), ("bf16", 64, 4, 64), ("bf16", 64, 27, 32)])
+# 14 blocks (two of them shared by two waves each), 16, 9 (one shared), 8, a split of 27, and the narrow kernels
+@pytest.mark.parametrize("dtype,dh,group,Tq", [("bf16", 64, 7, 64), ("bf16", 128, 8, 64), ("f32", 64, 9, 32), ("bf16", 64, 4, 64), ("bf16", 64, 27, 32),
+                                               ("bf16", 64, 1, 20), ("f32", 32, 2, 32)])
 @pytest.mark.parametrize("at", [5, 100, 1030, 1330])                  # the first keys of a workgroup, later ones, among them of a second subtile
 def test_keys_that_are_not_finite_on_long_ranges(dtype, dh, group, Tq, at):
     """A key with a NaN has a NaN score, one whose logits are +inf an infinite one; the rows of their kv heads, whose normalisers they
