@@ -127,10 +127,11 @@ inline void plan_grid(const ScoreGeom& g, int n_vis, int nch, int batch, size_t 
 }
 
 // Up to here every workgroup of pass 2 merges the partial statistics of its rows for itself, above a kernel in between does it
-// once.  One level, us, merged in pass 2 / by the kernel, rows whole: 300 tokens, 448 rows x 11 partials (40 KB) 28.6 / 30.2; 32 heads on 8, 256
-// x 32 (64 KB) 51.9 / 51.9; two videos of 4000 tokens, 448 x 32 (112 KB) 41.2 / 40.6; one of 3700, 448 x 59 (206 KB) 33.4 / 32.6; 14
-// heads on 2, 448 x 128 35.4 / 31.8; 7 heads on 1, 448 x 256 40.7 / 34.7: the exponentials of a large merge take longer than the
-// launch.  The narrow kernels have at most 64 rows and always merge for themselves.
+// once.  Levels, kernels alone, us, merged in pass 2 / by the kernel: 300 tokens of 28 heads on 4, 224 rows x 12 partials (21 KB) 20.0 / 21.1; 9000,
+// 32 heads on 8, 256 x 32 (64 KB) 37.7 / 38.7.  The line was drawn where larger merges lost: with eight partials a round, 448 rows x 59
+// (206 KB) took 33.4 / 32.6 and 448 x 128 35.4 / 31.8.  With four a round (see col_sums_kernel) they no longer do: 5000 tokens in fp32, 224 x 79 (138
+// KB) 31.4 / 32.7; 18432, 448 x 58 (203 KB) 52.3 / 53.0 and with 64 elements 46.5 / 46.1.  The line stays until the rule below, which
+// reads it too, has been measured with another.
 constexpr size_t kMergeInPass2Bytes = 64 * 1024;
 inline size_t partial_bytes(const ScoreGeom& g, const ScorePlan& p) { return static_cast<size_t>(p.nx1) * g.rbw * 32 * 2 * sizeof(float); }
 
