@@ -125,7 +125,7 @@ struct KeyStage {
 // costs two waves a load more before the first stage, so short ranges go unshared (where their rows are not split, see plan_score): 18432 tokens (5 stages) 17.7 -> 17.1 us in
 // pass 1 but 13.8 -> 14.3 in pass 2, 2243 tokens (1 stage) 9.0 -> 9.4 and 6.2 -> 6.5.  Ranges below kMinPipelined stages do
 // not take pass 1's software pipeline either (2243 tokens 9.4 -> 9.2 us).  Levels of 9 to 17 blocks, 300 to 24000 tokens, bf16 with 32
-// to 128 elements and fp32 with 32 and 64, are none slower than with neither line.
+// to 128 elements and fp32 with 32 and 64, are none slower than before these lines were drawn.
 constexpr int kMinPipelined = 4, kMinSharedRows = 4, kMinSharedCols = 8;         // stages of a workgroup
 enum class SecondBlock { kNone, kBoth, kSubtile0, kSubtile1 };
 template <int RBW>
