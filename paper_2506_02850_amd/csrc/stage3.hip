@@ -24,7 +24,12 @@
 //     few tiles.
 // Tiles are handed out by an atomic ticket in ascending order inside a slab, so a tile only ever waits
 // for tiles whose workgroups are already running, and a running workgroup publishes its flag before it
-// waits for anything: the waits always end.  They are bounded nevertheless: a wait that expires sets the
+// waits for anything: the waits always end.  The slabs of a (layer, video) are spread over up to four counters (tile t of slab s
+// comes from counter s mod 4, and workgroup w draws from counter w mod 4: as many workgroups as tiles), because a
+// counter hands out one ticket every 12 ns whatever else the chip does: the first 512 workgroups, two to a CU, queued for 6 us.  28
+// layers of 4500 tokens 36.9 -> 33.2 us, 24 layers of 20000 with 2 heads of 64 elements 32.2 -> 28.7, 28 of 3000 in pages 31.4 -> 29.6;
+// large caches are none the faster (four videos of 36992 tokens 713 -> 712), and with eight or sixteen counters up to 1.5 % slower.
+// The waits are bounded nevertheless: a wait that expires sets the
 // error word of the workspace and the tile is not stored.
 // Different slabs never alias, so they need no ordering; the column slices and the K / V halves of one
 // (layer, video) share the index list and are interleaved tile by tile.
@@ -37,12 +42,13 @@
 // With relinked page tables (metok_kv_relink_paged) the planning kernel decides which tiles copy anything at
 // all: it raises the flags of the others itself and writes the tiles with work, ascending inside a (layer,
 // video), to a list; only the first (length of the list) x (slabs per video) workgroups of the mover take a
-// ticket, and the ticket order is the order of the list, so the argument about the waits is unchanged.
+// ticket, and the ticket order of a slab is the order of the list, so the argument about the waits is unchanged.
 #include "common.h"
 
 namespace metok {
 
 constexpr int kMoveThreads = 1024;
+constexpr int kMaxTickets = 4, kTicketStride = 16;      // counters, and words between them: a cache line each
 constexpr int kMoveInFlight = 8;        // 16-byte pieces per thread: 1024 x 8 x 16 B = 128 KB per tile
 
 namespace {
@@ -62,7 +68,8 @@ struct MoveArgs {
     int64_t S_cap;
     int64_t row_bytes;
     uint32_t* flags;      // [n_layers][B * Hkv * n_which * parts][tiles_max]
-    uint32_t* ticket;     // this launch's tile counter
+    uint32_t* ticket;     // this launch's tile counters, kTicketStride words apart
+    int n_tickets;        // 1, 2 or 4, a divisor of the slabs per (layer, video)
     uint32_t* error;      // set to 1 if a bounded wait expired
     // paged variants only
     const int32_t* page_table;   // [B, pages_per_seq] (relink: the tables the rows are read through, + layer_id * table_in_layer_stride)
@@ -113,7 +120,10 @@ __global__ __launch_bounds__(kMoveThreads) void move_rows_kernel(const MoveArgs 
     // each, the others leave before they touch the counter.
     const int64_t n_items = MODE == kMoveRelink ? static_cast<int64_t>(*args.n_work) * n_sub : args.total_items;
     if (MODE == kMoveRelink && static_cast<int64_t>(blockIdx.x) >= n_items) return;
-    if (threadIdx.x == 0) s_item = static_cast<int>(atomicAdd(args.ticket, 1u));
+    if (threadIdx.x == 0) {
+        const int g = blockIdx.x & (args.n_tickets - 1);
+        s_item = static_cast<int>(atomicAdd(args.ticket + g * kTicketStride, 1u)) * args.n_tickets + g;
+    }
     __syncthreads();
     int item = s_item;
     if (item >= n_items) return;
@@ -446,9 +456,11 @@ RowMoveGeom row_move_geom(int64_t row_bytes) {
     return g;
 }
 
-// words: [0] error, [1 .. 1 + launches) tickets, [1 + launches .. 1 + 2 launches) work-list lengths (relinked tables),
-// then padding to 64 words, then the flags
+// words: [0] error, [1 .. 1 + launches) first tickets, [1 + launches .. 1 + 2 launches) work-list lengths (relinked tables), the other
+// tickets of a launch kTicketStride words behind its first one, then padding to 64 words, then the flags
 static int move_launches(int L) { return (L + kMaxLayersPerLaunch - 1) / kMaxLayersPerLaunch; }
+static_assert(1 + 2 * ((METOK_MAX_LAYERS + kMaxLayersPerLaunch - 1) / kMaxLayersPerLaunch) <= kTicketStride && kMaxTickets * kTicketStride <= 64,
+              "the tickets fit the header");
 static size_t move_header_words(int L) { return round_up(1 + 2 * static_cast<size_t>(move_launches(L)), 64); }
 
 size_t row_move_workspace_bytes(int L, int B, int Hkv, int n_which, int64_t S_cap, int64_t row_bytes) {
@@ -530,6 +542,7 @@ int launch_row_moves(RowMoveLayer* layers, int n_active, int B, int Hkv, int n_w
         args.spin_limit = g_spin_limit;
         args.S_cap = S_cap; args.row_bytes = row_bytes;
         args.flags = words + header; args.ticket = words + 1 + launch; args.error = words;
+        args.n_tickets = n_sub % 4 == 0 ? kMaxTickets : (n_sub % 2 == 0 ? 2 : 1);
         args.page_table = page_table; args.page_size = page_size; args.pages_per_seq = pages_per_seq; args.n_pages_pool = n_pages_pool;
         args.table_in_layer_stride = relink ? relink->table_in_layer_stride : 0;
         args.table_out = relink ? relink->table_out : nullptr;
