@@ -9,6 +9,7 @@
 //   plan_kernel          the plan on its own: event scores, key events, key frames, strides, row offsets
 //   pool_kernel          second streaming pass: s x s mean pooling of every frame, packed output
 //   frame_stats_pool2_kernel   statistics and 2 x 2 pooling from ONE pass, when every frame's stride is 2
+//   small_video_kernel   all of it in one launch, a workgroup per video, for videos of at most 128 KB
 //   frame_mean_kernel, frame_score_kernel, fill_token_event_kernel   small helpers of the other readings / paths
 //
 // In the one-pass call a batch of videos of one shape runs as one launch of every kernel: blockIdx.z is the
@@ -714,6 +715,7 @@ struct ShortShared {
     uint16_t n_kf[kShortFrames];           // key frames of an event
     uint8_t ev_key[kShortFrames];
     float norm2[kOneReduceFrames + 1], pair[kOneReduceFrames], score[kOneReduceFrames];
+    int stride[kOneReduceFrames], offset[kOneReduceFrames + 1];       // of the frames, for small_video_kernel
     int scan[2][16];
     int last;
 };
@@ -747,7 +749,8 @@ __device__ __forceinline__ int share_log2(int n) {
 }
 
 // Every thread of the 2^sl that share frame f calls with the frame's event e; sh.start, sh.fkey and sh.event are written, and a
-// barrier is still to come.
+// barrier is still to come.  POOL: the caller goes on with the pooling and finds the frames' strides and offsets in LDS.
+template <bool POOL>
 __device__ __forceinline__ void plan_short(const PlanArgs1& a, ShortShared& sh, int T, int k, int sl, int e) {
     const int tid = threadIdx.x, f = tid >> sl, s = tid & ((1 << sl) - 1);
     float* event_score = of_video_elems(a.event_score, k);
@@ -818,60 +821,23 @@ __device__ __forceinline__ void plan_short(const PlanArgs1& a, ShortShared& sh, 
         of_video_elems(a.frame_is_key, T)[f] = kf_flag ? 1 : 0;
         of_video_elems(a.frame_stride, T)[f] = a.stride[kind];
         of_video_elems(a.frame_offsets, T + 1)[f] = offset;
-        of_video(a.frame_event_ws, a.ws_video)[f] = e;
+        if (POOL) { sh.stride[f] = a.stride[kind]; sh.offset[f] = offset; }
+        else of_video(a.frame_event_ws, a.ws_video)[f] = e;
     }
-    if (tid == 0) of_video_elems(a.frame_offsets, T + 1)[T] = total;
-    fill_token_events(a, sh.event, T);
+    if (tid == 0) {
+        of_video_elems(a.frame_offsets, T + 1)[T] = total;
+        if (POOL) sh.offset[T] = total;
+    }
+    if (!POOL) fill_token_events(a, sh.event, T);
 }
 
-template <bool WITH_PLAN>
-__global__ __launch_bounds__(kSegThreads) void segment_short_kernel(const SegmentArgs a, const PlanArgs1 plan) {
-    __shared__ __align__(16) ShortShared sh;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, T = a.T, k = a.k;
-    constexpr int kWaves = kSegThreads / 64;
-    float* part = of_video(a.part, a.ws_video);
-    float* frame_score = of_video_elems(a.frame_score, T);
+// Segmentation (and plan) from the totals: thread t < T has |v|^2 of the frames t and t + 1, their product and the score of frame t.
+template <bool WITH_PLAN, bool POOL>
+__device__ __forceinline__ void segment_short(const SegmentArgs& a, const PlanArgs1& plan, ShortShared& sh, float n0, float n1, float dot, float score) {
+    const int tid = threadIdx.x, T = a.T, k = a.k;
     float* sim = of_video_elems(a.sim, T - 1);
     int32_t* event_start = of_video_elems(a.event_start, k + 1);
     int32_t* frame_event = of_video_elems(a.frame_event, T);
-    float n0 = 0.f, n1 = 0.f, dot = 0.f, score = 0.f;             // of frame tid, and |v|^2 of the next one
-    if (gridDim.x == 1) {
-        auto keep = [&](int t, const Triple& v) {
-            if (lane == 0) { sh.norm2[t] = v.x; sh.pair[t] = v.y; sh.score[t] = v.z / static_cast<float>(a.N); }
-        };
-        if (wave + kWaves < T) {
-            Triple v[2];
-            reduce_frames<2>(part, a.C, wave, kWaves, T, v);
-            keep(wave, v[0]);
-            keep(wave + kWaves, v[1]);
-        } else if (wave < T) {
-            Triple v[1];
-            reduce_frames<1>(part, a.C, wave, 0, T, v);
-            keep(wave, v[0]);
-        }
-        lds_barrier();
-        if (tid < T) {
-            n0 = sh.norm2[tid]; n1 = sh.norm2[tid + 1]; dot = sh.pair[tid]; score = sh.score[tid];
-            if (a.have_text && frame_score) frame_score[tid] = score;
-        }
-    } else {
-        float* frame_norm2 = of_video(a.frame_norm2, a.ws_video);
-        float* pair_dot = of_video(a.pair_dot, a.ws_video);
-        reduce_partials(a, part, frame_score, frame_norm2, pair_dot);
-        __builtin_amdgcn_s_waitcnt(0);          // this thread's totals are stored
-        __syncthreads();
-        if (tid == 0) {
-            uint32_t* arrive = reinterpret_cast<uint32_t*>(part + static_cast<size_t>(T - 1) * a.C * 3 + 1);
-            sh.last = __hip_atomic_fetch_add(arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1 ? 1 : 0;
-        }
-        __syncthreads();
-        if (!sh.last) return;
-        if (tid < T) {
-            const int next = min(tid + 1, T - 1);
-            n0 = load_total(frame_norm2 + tid); n1 = load_total(frame_norm2 + next); dot = load_total(pair_dot + tid);
-            if (WITH_PLAN) score = load_total(frame_score + tid);
-        }
-    }
     const int n_pairs = T - 1, n_quads = (n_pairs + 3) / 4;
     if (tid < n_pairs) {
         const float x = pair_similarity(a, n0, n1, dot);
@@ -911,7 +877,55 @@ __global__ __launch_bounds__(kSegThreads) void segment_short_kernel(const Segmen
         event_start[0] = 0; sh.start[0] = 0;
         event_start[k] = T; sh.start[k] = static_cast<uint16_t>(T);
     }
-    if (WITH_PLAN) plan_short(plan, sh, T, k, sl, e);
+    if (WITH_PLAN) plan_short<POOL>(plan, sh, T, k, sl, e);
+}
+
+template <bool WITH_PLAN>
+__global__ __launch_bounds__(kSegThreads) void segment_short_kernel(const SegmentArgs a, const PlanArgs1 plan) {
+    __shared__ __align__(16) ShortShared sh;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, T = a.T;
+    constexpr int kWaves = kSegThreads / 64;
+    float* part = of_video(a.part, a.ws_video);
+    float* frame_score = of_video_elems(a.frame_score, T);
+    float n0 = 0.f, n1 = 0.f, dot = 0.f, score = 0.f;             // of frame tid, and |v|^2 of the next one
+    if (gridDim.x == 1) {
+        auto keep = [&](int t, const Triple& v) {
+            if (lane == 0) { sh.norm2[t] = v.x; sh.pair[t] = v.y; sh.score[t] = v.z / static_cast<float>(a.N); }
+        };
+        if (wave + kWaves < T) {
+            Triple v[2];
+            reduce_frames<2>(part, a.C, wave, kWaves, T, v);
+            keep(wave, v[0]);
+            keep(wave + kWaves, v[1]);
+        } else if (wave < T) {
+            Triple v[1];
+            reduce_frames<1>(part, a.C, wave, 0, T, v);
+            keep(wave, v[0]);
+        }
+        lds_barrier();
+        if (tid < T) {
+            n0 = sh.norm2[tid]; n1 = sh.norm2[tid + 1]; dot = sh.pair[tid]; score = sh.score[tid];
+            if (a.have_text && frame_score) frame_score[tid] = score;
+        }
+    } else {
+        float* frame_norm2 = of_video(a.frame_norm2, a.ws_video);
+        float* pair_dot = of_video(a.pair_dot, a.ws_video);
+        reduce_partials(a, part, frame_score, frame_norm2, pair_dot);
+        __builtin_amdgcn_s_waitcnt(0);          // this thread's totals are stored
+        __syncthreads();
+        if (tid == 0) {
+            uint32_t* arrive = reinterpret_cast<uint32_t*>(part + static_cast<size_t>(T - 1) * a.C * 3 + 1);
+            sh.last = __hip_atomic_fetch_add(arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1 ? 1 : 0;
+        }
+        __syncthreads();
+        if (!sh.last) return;
+        if (tid < T) {
+            const int next = min(tid + 1, T - 1);
+            n0 = load_total(frame_norm2 + tid); n1 = load_total(frame_norm2 + next); dot = load_total(pair_dot + tid);
+            if (WITH_PLAN) score = load_total(frame_score + tid);
+        }
+    }
+    segment_short<WITH_PLAN, false>(a, plan, sh, n0, n1, dot, score);
 }
 
 // The plan on its own, from a caller's segmentation, T <= kShortFrames.
@@ -932,7 +946,7 @@ __global__ __launch_bounds__(kSegThreads) void plan_short_kernel(const PlanArgs1
         if (sh.start[mid] <= f) lo = mid; else hi = mid - 1;
     }
     if (f < T && (tid & ((1 << sl) - 1)) == 0) sh.event[f] = static_cast<uint16_t>(lo);
-    plan_short(plan, sh, T, k, sl, lo);
+    plan_short<false>(plan, sh, T, k, sl, lo);
 }
 
 template <bool WITH_PLAN>
@@ -1000,6 +1014,44 @@ __device__ __forceinline__ void pool_window(const uint4* __restrict__ cell, int 
     }
 }
 
+// Chunk `chunk` of pooled row `orow` of a frame (ow rows of the pooled grid to a line), stored as row out_row.
+template <typename TI, typename TO>
+__device__ __forceinline__ void pool_item(const uint4* __restrict__ frame, int grid_h, int grid_w, int d, int nchunks, int s, int ow, int orow, int chunk,
+                                          int64_t out_row, int ev, TO* __restrict__ out, int32_t* __restrict__ token_event) {
+    using E = Elem<TI>;
+            const int oy = orow / ow, ox = orow - oy * ow;
+            const int y0 = oy * s, y1 = min(y0 + s, grid_h);
+            const int x0 = ox * s, x1 = min(x0 + s, grid_w);
+            const uint4* corner = frame + (static_cast<size_t>(y0) * grid_w + x0) * nchunks + chunk;
+            float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            if (y1 - y0 == s && x1 - x0 == s && s == 2) pool_window<E, 2>(corner, grid_w, nchunks, acc);
+            else if (y1 - y0 == s && x1 - x0 == s && s == 3) pool_window<E, 3>(corner, grid_w, nchunks, acc);
+            else if (y1 - y0 == s && x1 - x0 == s && s == 4) pool_window<E, 4>(corner, grid_w, nchunks, acc);
+            else if (y1 - y0 == s && x1 - x0 == s && s == 6) pool_window<E, 6>(corner, grid_w, nchunks, acc);
+            else {
+                for (int y = y0; y < y1; ++y, corner += static_cast<size_t>(grid_w) * nchunks) {
+                    const uint4* cell = corner;
+                    int xx = x0;
+                    for (; xx + 4 <= x1; xx += 4) {               // four independent loads in flight
+                        const uint4 a = load_stream(cell), b = load_stream(cell + nchunks),
+                                    c = load_stream(cell + 2 * static_cast<size_t>(nchunks)),
+                                    e = load_stream(cell + 3 * static_cast<size_t>(nchunks));
+                        E::accumulate(a, acc); E::accumulate(b, acc); E::accumulate(c, acc); E::accumulate(e, acc);
+                        cell += 4 * static_cast<size_t>(nchunks);
+                    }
+                    for (; xx < x1; ++xx) {
+                        E::accumulate(load_stream(cell), acc);
+                        cell += nchunks;
+                    }
+                }
+            }
+            const float cnt = static_cast<float>((y1 - y0) * (x1 - x0));
+    #pragma unroll
+            for (int i = 0; i < 8; ++i) acc[i] = acc[i] / cnt;
+            Store<TO>::put(out + out_row * d, chunk, E::kVec, acc);
+            if (chunk == 0) token_event[out_row] = ev;
+}
+
 template <typename TI, typename TO>
 __global__ __launch_bounds__(kPoolThreads) void pool_kernel(
     const TI* __restrict__ feats, int grid_h, int grid_w, int d,
@@ -1028,37 +1080,96 @@ __global__ __launch_bounds__(kPoolThreads) void pool_kernel(
         const int orow = static_cast<int>(row0 + dr), chunk = static_cast<int>(x - dr * static_cast<uint32_t>(nchunks));
         const int64_t out_row = static_cast<int64_t>(base) + orow;
         if (orow >= oh * ow || out_row >= capacity_rows) continue;      // the second cannot happen when the caller sized the buffer as required
-        const int oy = orow / ow, ox = orow - oy * ow;
-        const int y0 = oy * s, y1 = min(y0 + s, grid_h);
-        const int x0 = ox * s, x1 = min(x0 + s, grid_w);
-        const uint4* corner = frame + (static_cast<size_t>(y0) * grid_w + x0) * nchunks + chunk;
-        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        if (y1 - y0 == s && x1 - x0 == s && s == 2) pool_window<E, 2>(corner, grid_w, nchunks, acc);
-        else if (y1 - y0 == s && x1 - x0 == s && s == 3) pool_window<E, 3>(corner, grid_w, nchunks, acc);
-        else if (y1 - y0 == s && x1 - x0 == s && s == 4) pool_window<E, 4>(corner, grid_w, nchunks, acc);
-        else if (y1 - y0 == s && x1 - x0 == s && s == 6) pool_window<E, 6>(corner, grid_w, nchunks, acc);
-        else {
-            for (int y = y0; y < y1; ++y, corner += static_cast<size_t>(grid_w) * nchunks) {
-                const uint4* cell = corner;
-                int xx = x0;
-                for (; xx + 4 <= x1; xx += 4) {               // four independent loads in flight
-                    const uint4 a = load_stream(cell), b = load_stream(cell + nchunks),
-                                c = load_stream(cell + 2 * static_cast<size_t>(nchunks)),
-                                e = load_stream(cell + 3 * static_cast<size_t>(nchunks));
-                    E::accumulate(a, acc); E::accumulate(b, acc); E::accumulate(c, acc); E::accumulate(e, acc);
-                    cell += 4 * static_cast<size_t>(nchunks);
-                }
-                for (; xx < x1; ++xx) {
-                    E::accumulate(load_stream(cell), acc);
-                    cell += nchunks;
-                }
-            }
-        }
-        const float cnt = static_cast<float>((y1 - y0) * (x1 - x0));
+        pool_item<TI, TO>(frame, grid_h, grid_w, d, nchunks, s, ow, orow, chunk, out_row, ev, out, token_event);
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// small_video_kernel: the whole of stage 1 of a video that one workgroup reads in a few round trips (see small_video).  Three
+// launches are 5.5 us on the device and 7.5 through a stream: 8 frames of 4 x 4 x 64 in a stream of calls 18.6 -> 13.3 us.  Sixteen lanes take a token of a frame together with the same token of the next frame; the
+// per-token sums meet in LDS and are added per frame; segmentation and plan are segment_short_kernel's; the pooling reads the
+// features a second time, from the caches.
+// ---------------------------------------------------------------------------------------------
+constexpr int kSmallRun = 4;                        // frames of a token that sixteen lanes take together
+constexpr int kSmallTokens = 512;                   // of all frames of the video
+constexpr int64_t kSmallBytes = 128 * 1024;
+
+template <typename TI, typename TO>
+__global__ __launch_bounds__(kSegThreads) void small_video_kernel(
+    const SegmentArgs a, const PlanArgs1 plan, const TI* __restrict__ feats, const TI* __restrict__ text, int grid_h, int grid_w, int d, int pool_edge,
+    int64_t capacity_rows, TO* __restrict__ out, int32_t* __restrict__ token_event) {
+    using E = Elem<TI>;
+    __shared__ __align__(16) ShortShared sh;
+    __shared__ Triple part[kSmallTokens];
+    __shared__ float text_norm2;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, sub = tid & 15, T = a.T, N = a.N;
+    const int nchunks = d / E::kVec;
+    const uint4* rows = reinterpret_cast<const uint4*>(of_video_elems(feats, static_cast<int64_t>(T) * N * d));
+    const uint4* txt = reinterpret_cast<const uint4*>(of_video_elems(text, d));
+    out = of_video_elems(out, capacity_rows * d); token_event = of_video_elems(token_event, capacity_rows);
+    // units of kRun frames of one token; a frame past the last one is read as the last one and not stored
+    constexpr int kRun = kSmallRun;
+    const int units = (T + kRun - 1) / kRun * N;
+    for (int unit = tid >> 4; unit < units; unit += kSegThreads / 16) {
+        const int t0 = unit / N * kRun, n = unit - unit / N * N;
+        const uint4* row[kRun + 1];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] = acc[i] / cnt;
-        Store<TO>::put(out + out_row * d, chunk, E::kVec, acc);
-        if (chunk == 0) token_event[out_row] = ev;
+        for (int r = 0; r <= kRun; ++r) row[r] = rows + (static_cast<size_t>(min(t0 + r, T - 1)) * N + n) * nchunks;
+        float p[kRun] = {}, q[kRun] = {}, cd[kRun] = {}, tn = 0.f;
+#pragma unroll 2
+        for (int c = sub; c < nchunks; c += 16) {
+            const uint4 w = txt[c];
+            uint4 x[kRun + 1];
+#pragma unroll
+            for (int r = 0; r <= kRun; ++r) x[r] = row[r][c];
+            tn = E::dot(w, w, tn);
+#pragma unroll
+            for (int r = 0; r < kRun; ++r) { p[r] = E::dot(x[r], x[r], p[r]); q[r] = E::dot(x[r], w, q[r]); cd[r] = E::dot(x[r], x[r + 1], cd[r]); }
+        }
+        if (unit == 0) { tn = row16_sum(tn); if (sub == 0) text_norm2 = tn; }
+#pragma unroll
+        for (int r = 0; r < kRun; ++r) {
+            const int t = t0 + r;
+            const float sp = row16_sum(p[r]), sd = row16_sum(cd[r]), sq = row16_sum(q[r]);
+            if (sub == 0 && t < T) part[t * N + n] = {sp, sd, sq};
+        }
+    }
+    lds_barrier();
+    // the cosines by a thread per token: sixteen lanes with the same roots and quotients took most of the time
+    const float tnorm = sqrtf(text_norm2);
+    for (int t = wave; t < T; t += kSegThreads / 64) {
+        Triple v = {0.f, 0.f, 0.f};
+        for (int n = lane; n < N; n += 64) {
+            const Triple o = part[t * N + n];
+            const float norm = sqrtf(o.x), den = norm * tnorm;
+            float dot = o.y;                                        // (of the last frame: never read)
+            if (a.sim_mode == METOK_SIM_TOKEN_MEAN) {
+                const float dn = norm * sqrtf(part[min(t + 1, T - 1) * N + n].x);
+                dot = !(dn < kZeroNorm) ? dot / dn : 0.f;
+            }
+            v.x += o.x; v.y += dot; v.z += !(den < kZeroNorm) ? o.z / den : 0.f;
+        }
+        v.x = wave_sum(v.x); v.y = wave_sum(v.y); v.z = wave_sum(v.z);
+        if (lane == 0) { sh.norm2[t] = v.x; sh.pair[t] = v.y; sh.score[t] = v.z / static_cast<float>(N); }
+    }
+    lds_barrier();
+    float n0 = 0.f, n1 = 0.f, dot = 0.f, score = 0.f;
+    if (tid < T) {
+        n0 = sh.norm2[tid]; n1 = sh.norm2[min(tid + 1, T - 1)]; dot = sh.pair[tid]; score = sh.score[tid];
+        of_video_elems(a.frame_score, T)[tid] = score;
+    }
+    segment_short<true, true>(a, plan, sh, n0, n1, dot, score);
+    lds_barrier();
+    const int items = sh.offset[T] * nchunks;
+    for (int i = tid; i < items; i += kSegThreads) {
+        const int row = i / nchunks, chunk = i - row * nchunks;
+        int f = 0;                                                  // the last frame whose first row is at or before this one
+#pragma unroll
+        for (int step = kOneReduceFrames / 2; step >= 1; step >>= 1) f = f + step < T && sh.offset[f + step] <= row ? f + step : f;
+        const int s = sh.stride[f];
+        if (row < capacity_rows)
+            pool_item<TI, TO>(rows + static_cast<size_t>(f) * N * nchunks, grid_h, grid_w, d, nchunks, s, pooled_side(grid_w, s, pool_edge), row - sh.offset[f],
+                              chunk, row, sh.event[f], out, token_event);
     }
 }
 
@@ -1553,6 +1664,34 @@ static bool launch_stats_pool2(const void* feats, const void* text, int Tf, int 
     return false;
 }
 
+// Whether small_video_kernel takes the call: the rounds of loads that its statistics and its pooling take one after the other, and
+// what it reads at one compute unit's rate.  Whole calls by graph replay, us, three launches / this one: 8 frames of 4 x 4 x 64 fp32
+// (32 KB) 12.7 / 8.3, 4 of 5 x 5 x 64 12.9 / 8.4, 4 of 4 x 4 x 1024 (128 KB) 13.8 / 10.8, 8 of 8 x 8 x 128 (128 KB) 14.3 / 12.7, 32 of 4 x 4 x 128
+// (128 KB) 15.0 / 13.5; beyond the lines, 2 of 16 x 16 x 64 (4 rounds of the statistics with half the frames missing) 11.7 / 14.3, 4 of
+// 2 x 2 x 4096 (16 rounds) 13.6 / 15.6, 32 of 4 x 4 x 128 at stride 1 (8 rounds of the pooling) 14.7 / 19.8.  Where the one-pass kernel
+// makes it two launches: 8 of 4 x 4 x 64 fp32 10.1 / 7.9, 32 of 4 x 4 x 128 12.1 / 14.4.
+static bool small_video(int T, int N, int d, int dtype, int64_t worst_rows, bool one_pass) {
+    const int64_t chunks = d / (dtype == METOK_BF16 ? 8 : 4), units = static_cast<int64_t>((T + kSmallRun - 1) / kSmallRun) * N;
+    if (T > kOneReduceFrames || units * kSmallRun > kSmallTokens || T * N * chunks * 16 > kSmallBytes) return false;
+    const int64_t stats = (units + kSegThreads / 16 - 1) / (kSegThreads / 16) * ((chunks + 31) / 32), pool = (worst_rows * chunks + kSegThreads - 1) / kSegThreads;
+    return one_pass ? stats <= 1 && pool <= 1 : stats <= 4 && pool <= 2;
+}
+static int launch_small_video(const SegmentArgs& sa, const PlanArgs1& plan, const void* feats, int dtype, const void* text, int grid_h, int grid_w, int d,
+                              int pool_edge, int64_t capacity_rows, void* out, int out_dtype, int32_t* token_event, unsigned nb, hipStream_t st) {
+    // one launch does everything: the trace hook brackets it for any name
+    TraceScope trace_stats(METOK_TRACE_FRAME_STATS, st), trace_segment(METOK_TRACE_SEGMENT, st), trace_plan(METOK_TRACE_PLAN, st), trace_pool(METOK_TRACE_POOL, st),
+               trace_pool2(METOK_TRACE_FRAME_STATS_POOL2, st);
+#define METOK_SMALL_CASE(TI, TO) \
+    hipLaunchKernelGGL((small_video_kernel<TI, TO>), dim3(1, 1, nb), dim3(kSegThreads), 0, st, sa, plan, static_cast<const TI*>(feats), \
+                       static_cast<const TI*>(text), grid_h, grid_w, d, pool_edge, capacity_rows, static_cast<TO*>(out), token_event);
+    if (dtype == METOK_BF16 && out_dtype == METOK_BF16) METOK_SMALL_CASE(bf16_t, bf16_t)
+    else if (dtype == METOK_BF16 && out_dtype == METOK_F32) METOK_SMALL_CASE(bf16_t, float)
+    else if (dtype == METOK_F32 && out_dtype == METOK_BF16) METOK_SMALL_CASE(float, bf16_t)
+    else METOK_SMALL_CASE(float, float)
+#undef METOK_SMALL_CASE
+    return check_launch("stage 1 of a small video");
+}
+
 // Shared body of metok_segment_compress (batch = 1) and metok_segment_compress_batched: every array carries a leading
 // dimension of `batch` videos, the workspace one slice per video; every kernel takes the video from blockIdx.z.
 static int segment_compress_impl(int batch, const void* feats, int dtype, int T, int grid_h, int grid_w, int d,
@@ -1619,16 +1758,18 @@ static int segment_compress_impl(int batch, const void* feats, int dtype, int T,
         int32_t* frame_event_ws = reinterpret_cast<int32_t*>(ws + stats_part_bytes(T, p) + 2 * tslot);
         hipStream_t st = static_cast<hipStream_t>(stream);
         const unsigned nb = static_cast<unsigned>(batch);
-        const bool keep = keep_in_cache(batch, T, N, d, dtype);
-        const bool ok = dtype == METOK_BF16 ? dispatch_stats<bf16_t>(feats, text_emb, T, N, d, p, 1, sim_mode, part, st, batch, ws_video, keep)
-                                            : dispatch_stats<float>(feats, text_emb, T, N, d, p, 1, sim_mode, part, st, batch, ws_video, keep);
-        if (!ok) return fail(METOK_ERR_UNSUPPORTED, "no frame-statistics kernel for d = %d", d);
-        if ((rc = check_launch("frame_stats"))) return rc;
         const int n_key_events = ceil_ratio(alpha * k) > k ? k : ceil_ratio(alpha * k);
         const SegmentArgs sa = {part, p.C, T, N, k, 1, sim_mode, sim, event_start, frame_event, frame_score, norm2, pair_dot, ws_video};
         PlanArgs1 plan = {n_key_events, beta, {}, {}, event_reduce, event_score, event_is_key, frame_is_key, frame_stride, frame_offsets, frame_event_ws, nullptr,
                           0, nullptr, 0, ws_video};
         plan.set_strides({clamp_stride(s1), clamp_stride(s2), clamp_stride(s1 / alpha), clamp_stride(s2 / alpha)}, grid_h, grid_w, pool_edge);
+        if (small_video(T, N, d, dtype, worst, false))
+            return launch_small_video(sa, plan, feats, dtype, text_emb, grid_h, grid_w, d, pool_edge, out_capacity_rows, out_tokens, out_dtype, token_event, nb, st);
+        const bool keep = keep_in_cache(batch, T, N, d, dtype);
+        const bool ok = dtype == METOK_BF16 ? dispatch_stats<bf16_t>(feats, text_emb, T, N, d, p, 1, sim_mode, part, st, batch, ws_video, keep)
+                                            : dispatch_stats<float>(feats, text_emb, T, N, d, p, 1, sim_mode, part, st, batch, ws_video, keep);
+        if (!ok) return fail(METOK_ERR_UNSUPPORTED, "no frame-statistics kernel for d = %d", d);
+        if ((rc = check_launch("frame_stats"))) return rc;
         launch_segment_plan(sa, plan, nb, st);
         if ((rc = check_launch("segment and plan"))) return rc;
         dim3 grid(pool_workgroups(T, grid_h, grid_w, d, dtype, s1, s2, pool_edge), T, nb);
@@ -1689,6 +1830,23 @@ static int segment_compress_impl(int batch, const void* feats, int dtype, int T,
         return fail(METOK_ERR_CAPACITY, "out_capacity_rows = %lld, worst case needs %lld", (long long)out_capacity_rows, (long long)rows);
     if (rows > INT32_MAX) return fail(METOK_ERR_INVALID_ARG, "pooled row count must fit int32");
 
+    char* ws = static_cast<char*>(workspace);
+    const size_t part_bytes = fused_part_bytes(T, grid_h, grid_w);
+    const size_t tslot = round_up(static_cast<size_t>(T) * sizeof(float), 256);
+    float* part = reinterpret_cast<float*>(ws);
+    float* norm2 = reinterpret_cast<float*>(ws + part_bytes);
+    float* pair_dot = reinterpret_cast<float*>(ws + part_bytes + tslot);
+    int32_t* frame_event_ws = reinterpret_cast<int32_t*>(ws + part_bytes + 2 * tslot);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    const unsigned nb = static_cast<unsigned>(batch);
+    const int n_key_events = ceil_ratio(alpha * k) > k ? k : ceil_ratio(alpha * k);
+    const bool fill_here = rows <= kFillRowsInPlan;
+    const SegmentArgs sa = {part, n_win, T, N, k, 1, METOK_SIM_FLAT, sim, event_start, frame_event, frame_score, norm2, pair_dot, ws_video};
+    PlanArgs1 plan = {n_key_events, beta, {}, {}, event_reduce, event_score, event_is_key, frame_is_key, frame_stride,
+                            frame_offsets, frame_event_ws, nullptr, fill_here ? n_win : 0, token_event, out_capacity_rows, ws_video};
+    plan.set_strides({2, 2, 2, 2}, grid_h, grid_w, pool_edge);
+    if (small_video(T, N, d, dtype, rows, true))
+        return launch_small_video(sa, plan, feats, dtype, text_emb, grid_h, grid_w, d, pool_edge, out_capacity_rows, out_tokens, out_dtype, token_event, nb, st);
     const int C = (n_win + kStatsWaves - 1) / kStatsWaves;          // workgroups per run of frames
     int runs = (2048 + C * kStatsWaves - 1) / (C * kStatsWaves);
     int fpr = (T + runs - 1) / runs;
@@ -1698,16 +1856,7 @@ static int segment_compress_impl(int batch, const void* feats, int dtype, int T,
     if (fpr % 8 == 0) ++fpr;
     if (fpr > T) fpr = T;
     runs = (T + fpr - 1) / fpr;
-    char* ws = static_cast<char*>(workspace);
-    const size_t part_bytes = fused_part_bytes(T, grid_h, grid_w);
-    const size_t tslot = round_up(static_cast<size_t>(T) * sizeof(float), 256);
-    float* part = reinterpret_cast<float*>(ws);
-    float* norm2 = reinterpret_cast<float*>(ws + part_bytes);
-    float* pair_dot = reinterpret_cast<float*>(ws + part_bytes + tslot);
-    int32_t* frame_event_ws = reinterpret_cast<int32_t*>(ws + part_bytes + 2 * tslot);
-    hipStream_t st = static_cast<hipStream_t>(stream);
     const int64_t pooled_video = out_capacity_rows * d;
-    const unsigned nb = static_cast<unsigned>(batch);
     bool ok;
     if (dtype == METOK_BF16)
         ok = out_dtype == METOK_BF16 ? launch_stats_pool2<bf16_t, bf16_t>(feats, text_emb, T, grid_h, grid_w, d, kl, C, fpr, runs, part, out_tokens, batch, pooled_video, ws_video, st)
@@ -1717,12 +1866,6 @@ static int segment_compress_impl(int batch, const void* feats, int dtype, int T,
                                      : launch_stats_pool2<float, float>(feats, text_emb, T, grid_h, grid_w, d, kl, C, fpr, runs, part, out_tokens, batch, pooled_video, ws_video, st);
     if (!ok) return fail(METOK_ERR_UNSUPPORTED, "no fused kernel for d = %d", d);
     if ((rc = check_launch("frame_stats_pool2"))) return rc;
-    const int n_key_events = ceil_ratio(alpha * k) > k ? k : ceil_ratio(alpha * k);
-    const bool fill_here = rows <= kFillRowsInPlan;
-    const SegmentArgs sa = {part, n_win, T, N, k, 1, METOK_SIM_FLAT, sim, event_start, frame_event, frame_score, norm2, pair_dot, ws_video};
-    PlanArgs1 plan = {n_key_events, beta, {}, {}, event_reduce, event_score, event_is_key, frame_is_key, frame_stride,
-                            frame_offsets, frame_event_ws, nullptr, fill_here ? n_win : 0, token_event, out_capacity_rows, ws_video};
-    plan.set_strides({2, 2, 2, 2}, grid_h, grid_w, pool_edge);
     launch_segment_plan(sa, plan, nb, st);
     if ((rc = check_launch("segment and plan")) || fill_here) return rc;
     hipLaunchKernelGGL(fill_token_event_kernel, dim3(static_cast<unsigned>((rows + 255) / 256), 1, nb), dim3(256), 0, st, frame_event, T, n_win,
