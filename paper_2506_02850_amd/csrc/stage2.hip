@@ -57,6 +57,89 @@ template <> struct Mma<float> {
     }
 };
 
+// fp32 rows multiplied as bf16.  A finite x is the sum of three bf16 numbers, its leading, middle and last eight bits, without a
+// rounding; of the nine products of two such numbers the six that reach 2^-24 of the whole are taken, each with 16 times the rate of
+// an fp32 MFMA: 192 cycles of the matrix pipe per 32 x 32 x 16 products instead of 512.  28 heads on 4 x 64 queries of 128 elements, 8 x 4000 tokens: 291 ->
+// 184 us a level, 24000 tokens 233 -> 153; see split_products for where it is taken.  Against 64 bits the scores are as close as with fp32
+// products on normal data (1.64 to 1.73e-7 either way) and closer with logits three times as large (1.5e-6 -> 0.95e-6).
+struct split_t { float value; };
+template <> struct Mma<split_t> : Mma<float> {};
+
+// 16-byte operand registers of a lane for a row block or a subtile: its NCH pieces of memory, or three numbers for each of their elements
+template <typename T, int NCH> constexpr int kOperands = std::is_same<T, split_t>::value ? NCH / 2 * 3 : NCH;
+
+__device__ __forceinline__ bool is_finite_bits(uint32_t x) { return (x & 0x7f800000u) != 0x7f800000u; }
+// x without its leading part; nothing is left of what is not finite
+__device__ __forceinline__ uint32_t below_leading(uint32_t x) { return __float_as_uint(__uint_as_float(x) - __uint_as_float(x & 0xffff0000u)); }
+// Upper halves of two words as a pair
+__device__ __forceinline__ uint32_t upper_halves(uint32_t lo, uint32_t hi) { return __builtin_amdgcn_perm(hi, lo, 0x07060302u); }
+
+// Four elements -> their leading, middle and last parts.  Where an element is not finite its parts mean nothing (a NaN with only low
+// bits would even become an infinity): the caller asks all_finite and takes exact_parts instead.
+__device__ __forceinline__ void split_piece(const uint4& x, uint2 (&part)[3]) {
+    uint32_t e[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        part[p] = make_uint2(upper_halves(e[0], e[1]), upper_halves(e[2], e[3]));
+        if (p < 2) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) e[i] = below_leading(e[i]);
+        }
+    }
+}
+__device__ __forceinline__ bool all_finite(const uint4& x) { return is_finite_bits(x.x) && is_finite_bits(x.y) && is_finite_bits(x.z) && is_finite_bits(x.w); }
+// The same for elements of which some may not be finite: those are their leading part alone, a NaN stays one.
+__device__ __forceinline__ uint32_t quiet(uint32_t x) { return (x & 0x7fffffffu) > 0x7f800000u ? x | 0x00400000u : x; }
+__device__ __forceinline__ void exact_parts(const uint4& x, uint2 (&part)[3]) {
+    const uint32_t e[4] = {quiet(x.x), quiet(x.y), quiet(x.z), quiet(x.w)};
+    uint32_t lead[4], mid[4], last[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const bool f = is_finite_bits(e[i]);
+        lead[i] = e[i];
+        mid[i] = f ? below_leading(e[i]) : 0u;
+        last[i] = f ? below_leading(mid[i]) : 0u;
+    }
+    part[0] = make_uint2(upper_halves(lead[0], lead[1]), upper_halves(lead[2], lead[3]));
+    part[1] = make_uint2(upper_halves(mid[0], mid[1]), upper_halves(mid[2], mid[3]));
+    part[2] = make_uint2(upper_halves(last[0], last[1]), upper_halves(last[2], last[3]));
+}
+// Piece c of the 2 n pieces that the operands f[3 n] were made of
+__device__ __forceinline__ uint4 joined_piece(const uint4* f, int c) {
+    const uint4* a = f + c / 2 * 3;
+    uint32_t w[3][2];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        w[p][0] = c & 1 ? a[p].z : a[p].x; w[p][1] = c & 1 ? a[p].w : a[p].y;
+        asm volatile("" : "+v"(w[p][0]), "+v"(w[p][1]));            // made where it is used, not kept from one subtile to the next
+    }
+    auto element = [&](int i) {
+        auto part = [&](int p) { return i & 1 ? bf16_hi(w[p][i >> 1]) : bf16_lo(w[p][i >> 1]); };
+        return __float_as_uint(part(0) + part(1) + part(2));
+    };
+    return make_uint4(element(0), element(1), element(2), element(3));
+}
+// Operands of a row block from its pieces; true: every element of the lane is finite.
+template <typename T, int NCH>
+__device__ __forceinline__ bool make_operands(const uint4 (&raw)[NCH], uint4 (&op)[kOperands<T, NCH>]) {
+    bool finite = true;
+    if constexpr (std::is_same<T, split_t>::value) {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) finite = finite && all_finite(raw[c]);
+#pragma unroll
+        for (int c = 0; c < NCH; c += 2) {
+            uint2 a[3], b[3];
+            if (finite) { split_piece(raw[c], a); split_piece(raw[c + 1], b); } else { exact_parts(raw[c], a); exact_parts(raw[c + 1], b); }
+#pragma unroll
+            for (int p = 0; p < 3; ++p) op[c / 2 * 3 + p] = make_uint4(a[p].x, a[p].y, b[p].x, b[p].y);
+        }
+    } else {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) op[c] = raw[c];
+    }
+    return finite;
+}
+
 // Kept visual tokens of every video of a batch (the quotas of a video added up), passed by value.
 struct BatchKeep { int32_t n[METOK_MAX_BATCH]; };
 
@@ -72,8 +155,9 @@ struct BatchKeep { int32_t n[METOK_MAX_BATCH]; };
 template <typename T, int NCH, int SUBS>
 struct KeyStage {
     static constexpr int kKeys = SUBS * 32;
-    static constexpr int kSlots = SUBS * NCH * 64;                 // 16-byte pieces per stage
-    static constexpr int kPerThread = (kSlots + kScoreThreads - 1) / kScoreThreads;
+    static constexpr int kPieces = SUBS * NCH * 64;                // 16-byte pieces of memory per stage
+    static constexpr int kSlots = SUBS * kOperands<T, NCH> * 64;   // of LDS
+    static constexpr int kPerThread = (kPieces + kScoreThreads - 1) / kScoreThreads;
 
     // piece id -> (key in stage, half, chunk); the key runs fastest so that the LDS writes of a wave are contiguous
     static __device__ __forceinline__ void load(u32x4_t (&v)[kPerThread], const T* __restrict__ k_head, int64_t j0, int64_t S, int dh) {
@@ -81,7 +165,7 @@ struct KeyStage {
 #pragma unroll
         for (int u = 0; u < kPerThread; ++u) {
             int id = threadIdx.x + u * kScoreThreads;
-            id = id < kSlots ? id : 0;                              // surplus threads repeat piece 0 and do not store it
+            id = id < kPieces ? id : 0;                             // surplus threads repeat piece 0 and do not store it
             const int jl = id % kKeys, p = id / kKeys;
             int64_t j = j0 + jl;
             j = j < S ? j : S - 1;                                  // stages may overhang the sequence; masked later
@@ -98,9 +182,28 @@ struct KeyStage {
         for (int u = 0; u < kPerThread; ++u) {
             const int id = threadIdx.x + u * kScoreThreads;
             const int jl = id % kKeys, p = id / kKeys;
-            if ((UNCHECKED_ROUNDS && (u + 1) * kScoreThreads <= kSlots) || id < kSlots)
+            if ((UNCHECKED_ROUNDS && (u + 1) * kScoreThreads <= kPieces) || id < kPieces)
                 reinterpret_cast<u32x4_t*>(kbuf)[((jl >> 5) * NCH + (p % NCH)) * 64 + (jl & 31) + 32 * (p / NCH)] = v[u];
         }
+    }
+    // Three parts of every element; false: an element of this thread is not finite.
+    static __device__ __forceinline__ bool store_split(const u32x4_t (&v)[kPerThread], uint4* __restrict__ kbuf) {
+        bool finite = true;
+#pragma unroll
+        for (int u = 0; u < kPerThread; ++u) {
+            const int id = threadIdx.x + u * kScoreThreads;
+            const int jl = id % kKeys, p = id / kKeys, c = p % NCH;
+            const uint4 x = make_uint4(v[u].x, v[u].y, v[u].z, v[u].w);
+            uint2 part[3];
+            if (__builtin_expect(all_finite(x), 1)) split_piece(x, part);
+            else { finite = false; exact_parts(x, part); }
+            uint2* dst = reinterpret_cast<uint2*>(kbuf) + 2 * (((jl >> 5) * (NCH / 2 * 3) + c / 2 * 3) * 64 + (jl & 31) + 32 * (p / NCH)) + (c & 1);
+            if ((u + 1) * kScoreThreads <= kPieces || id < kPieces) {
+#pragma unroll
+                for (int q = 0; q < 3; ++q) dst[2 * 64 * q] = part[q];
+            }
+        }
+        return finite;
     }
 };
 
@@ -216,6 +319,41 @@ __device__ __forceinline__ f32x16_t mma_chain(const uint4 (&a)[NCH], const uint4
     f32x16_t acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int c = 0; c < NCH; ++c) acc = Mma<T>::mma(a[c], b[c], acc);
+    return acc;
+}
+
+// The product of a subtile of split keys, operand c of the lane at keys[64 c], with a split row block; KEYS_FIRST: keys x queries.
+// !FINITE: some element may not be, and infinity times a part that is zero would be NaN: fp32 products.
+template <int NCH, bool FINITE, bool KEYS_FIRST>
+__device__ __forceinline__ f32x16_t split_chain(const uint4* keys, const uint4 (&q)[NCH / 2 * 3]) {
+    f32x16_t acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < NCH / 2; ++c) {
+        const uint4 k[3] = {keys[(3 * c) * 64], keys[(3 * c + 1) * 64], keys[(3 * c + 2) * 64]};
+        const uint4* x = q + 3 * c;
+        auto mma = [&](auto tag, const uint4& key, const uint4& row) {
+            acc = KEYS_FIRST ? Mma<decltype(tag)>::mma(key, row, acc) : Mma<decltype(tag)>::mma(row, key, acc);
+        };
+        if constexpr (FINITE) {
+            mma(bf16_t(), k[2], x[0]);
+            mma(bf16_t(), k[0], x[2]);
+            mma(bf16_t(), k[1], x[1]);
+            mma(bf16_t(), k[1], x[0]);
+            mma(bf16_t(), k[0], x[1]);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                mma(float(), joined_piece(k, i), joined_piece(x, i));
+                __builtin_amdgcn_sched_barrier(0);                  // one piece at a time: no registers for what is hardly ever run
+            }
+        }
+    }
+    // the products of the leading parts last: only these are rounded at the size of the sum
+    if constexpr (FINITE) {
+#pragma unroll
+        for (int c = 0; c < NCH / 2; ++c)
+            acc = KEYS_FIRST ? Mma<bf16_t>::mma(keys[3 * c * 64], q[3 * c], acc) : Mma<bf16_t>::mma(q[3 * c], keys[3 * c * 64], acc);
+    }
     return acc;
 }
 
@@ -343,6 +481,9 @@ __global__ __launch_bounds__(kScoreThreads) void row_stats_kernel(const T* __res
     const int rb0 = split * g.rbw;
     const int nrb = min(g.rbw, g.rb_total - rb0);
     __shared__ float2 shared_rows[2][64];
+    constexpr int N = kOperands<T, NCH>;
+    constexpr bool kSplit = std::is_same<T, split_t>::value;
+    __shared__ int not_finite[kSplit ? kStageBuffers : 1];          // the last stage of the buffer that held such an element
     q_text = of_video_elems(q_text, g.q_video);
     qfrag = of_video(qfrag, g.ws_video); pstat = of_video(pstat, g.ws_video); clear = of_video(clear, g.ws_video);
     const T* k_head = of_video_elems(k_all, g.k_video) + static_cast<size_t>(kvh) * g.S * g.dh;
@@ -362,16 +503,27 @@ __global__ __launch_bounds__(kScoreThreads) void row_stats_kernel(const T* __res
     u32x4_t kv[Stage::kPerThread], kv1[Stage::kPerThread];
     Stage::load(kv, k_head, kb, g.S, g.dh);
     Stage::load(kv1, k_head, kb + (n_stage > 1 ? Stage::kKeys : 0), g.S, g.dh);
-    uint4 q[RBW][NCH];
+    uint4 q[RBW][N];
+    bool finite_rows = true;
+    if (kSplit && threadIdx.x < kStageBuffers) not_finite[threadIdx.x] = -1;
     {
         QueryRows<T, NCH, RBW> rows;
+        uint4 raw[RBW][NCH];
         rows.load(q_text, g, kvh, rb0, nrb, wave, second, lane);
-        rows.to_fragments(q, lds, g, rb0, nrb, wave, second, lane);
+        rows.to_fragments(raw, lds, g, rb0, nrb, wave, second, lane);
+#pragma unroll
+        for (int i = 0; i < RBW; ++i) finite_rows = make_operands<T, NCH>(raw[i], q[i]) && finite_rows;
+        finite_rows = !__any(!finite_rows);
         __syncthreads();                                // the stages take over the waves' parts of LDS
     }
+    auto store_stage = [&](const u32x4_t (&v)[Stage::kPerThread], int s) {
+        uint4* kbuf = lds + (s % kStageBuffers) * Stage::kSlots;
+        if constexpr (kSplit) { if (!Stage::store_split(v, kbuf)) not_finite[s % kStageBuffers] = s; }
+        else Stage::store(v, kbuf);
+    };
     float m[RBW], l[RBW];
-    Stage::store(kv, lds);
-    if (n_stage > 1) Stage::store(kv1, lds + Stage::kSlots);
+    store_stage(kv, 0);
+    if (n_stage > 1) store_stage(kv1, 1);
     // Every load issued so far has to land before the loop: with query loads still pending at its head the
     // first use of a fragment inside would wait for ALL outstanding loads, the prefetch of later stages included.
     __builtin_amdgcn_s_waitcnt(0);
@@ -382,7 +534,7 @@ __global__ __launch_bounds__(kScoreThreads) void row_stats_kernel(const T* __res
         if (s + 2 < n_stage) Stage::load(kv, k_head, kb + static_cast<int64_t>(s + 2) * Stage::kKeys, g.S, g.dh);
     };
     auto publish = [&](int s) {           // registers -> LDS; that buffer was last read before the previous barrier
-        if (s + 2 < n_stage) Stage::store(kv, stage_buf(s + 2));
+        if (s + 2 < n_stage) store_stage(kv, s + 2);
         __syncthreads();
     };
 
@@ -396,14 +548,22 @@ __global__ __launch_bounds__(kScoreThreads) void row_stats_kernel(const T* __res
             for (int sub = 0; sub < SUBS; ++sub) {
                 const int64_t j0 = js + sub * 32;
                 if (j0 < ke && nrb_w > 0) {
-                    uint4 kf[NCH];
+                    const uint4* keys = kbuf + sub * N * 64 + lane;
+                    uint4 kf[kSplit ? 1 : N];
+                    bool finite = true;
+                    if constexpr (kSplit) finite = finite_rows && not_finite[s % kStageBuffers] != s;
+                    else {
 #pragma unroll
-                    for (int c = 0; c < NCH; ++c) kf[c] = kbuf[(sub * NCH + c) * 64 + lane];
+                        for (int c = 0; c < N; ++c) kf[c] = keys[c * 64];
+                    }
                     const bool full = j0 + 32 <= full_end;      // every key of the subtile is visible to every query
 #pragma unroll
                     for (int i = 0; i < RBW; ++i) {
                         if (i < nrb_w) {
-                            const f32x16_t acc = mma_chain<T, NCH>(kf, q[i]);
+                            f32x16_t acc;
+                            if constexpr (!kSplit) acc = mma_chain<T, NCH>(kf, q[i]);
+                            else if (finite) acc = split_chain<NCH, true, true>(keys, q[i]);
+                            else acc = split_chain<NCH, false, true>(keys, q[i]);
                             if (full && j0 > kb) {
                                 softmax_take(acc, g.scale_log2, m[i], l[i], softmax_sum(acc, g.scale_log2, m[i], l[i]));
                             } else if (full) {
@@ -503,7 +663,10 @@ __global__ __launch_bounds__(kScoreThreads) void row_stats_kernel(const T* __res
             if (rbl >= 0 && rbl % kScoreWaves == wave) {
                 uint4* dst = qfrag + (static_cast<size_t>(kvh) * g.rb_total + rb0 + rbl) * NCH * 64 + lane;
 #pragma unroll
-                for (int c = 0; c < NCH; ++c) dst[c * 64] = q[i][c];
+                for (int c = 0; c < NCH; ++c) {
+                    if constexpr (kSplit) dst[c * 64] = joined_piece(q[i], c);
+                    else dst[c * 64] = q[i][c];
+                }
             }
         }
     }
@@ -633,14 +796,19 @@ __global__ __launch_bounds__(256) void merge_stats_kernel(const float* __restric
 // Grids of more workgroups than CUs run two (or three) to a CU where 128 (80) registers suffice, which the merge must not exceed:
 // with eight partials a round in every kernel, 20 x 3000 tokens of 40 heads x 100 queries took 438 us for 389 with the merging kernel,
 // in bf16 with 256 elements 934 for 810, and now 381 and 793.  A thread has at most four (kMergeInPass2Bytes).
+template <typename T, int NCH, int RBW> constexpr int kColWaves = (RBW == 2 && NCH > 4) || kOperands<T, NCH> > 16 ? 2 : 4;      // per SIMD
 template <typename T, int NCH, int RBW, int SUBS>
-__global__ __launch_bounds__(kScoreThreads, RBW == 2 && NCH > 4 ? 2 : 4) void col_sums_kernel(const uint4* __restrict__ qfrag, const T* __restrict__ k_all,
+__global__ __launch_bounds__(kScoreThreads, (kColWaves<T, NCH, RBW>)) void col_sums_kernel(const uint4* __restrict__ qfrag, const T* __restrict__ k_all,
                                                                  const ScoreGeom g, int sub_per_wg, const float* __restrict__ norm,
                                                                  const float* __restrict__ pstat, int nx1, float* __restrict__ colpart) {
     using Stage = KeyStage<T, NCH, SUBS>;
     extern __shared__ uint4 lds[];                      // two stages, then the column partials [2][waves][stage keys]
     float* cs = reinterpret_cast<float*>(lds + 2 * Stage::kSlots);
     __shared__ MergeShared red;
+    constexpr int N = kOperands<T, NCH>;
+    constexpr bool kSplit = std::is_same<T, split_t>::value;
+    __shared__ int not_finite[2];                       // see pass 1
+    if (kSplit && threadIdx.x < 2) not_finite[threadIdx.x] = -1;
     __shared__ __align__(16) float own_norm[kScoreThreads];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), h = lane >> 5;
     const int kvh = blockIdx.y / g.rs, split = blockIdx.y % g.rs;
@@ -662,8 +830,8 @@ __global__ __launch_bounds__(kScoreThreads, RBW == 2 && NCH > 4 ? 2 : 4) void co
     u32x4_t kv[Stage::kPerThread];
     Stage::load(kv, k_head, static_cast<int64_t>(g.vis_start) + vb, g.S, g.dh);
 
-    uint4 q[RBW][NCH];
-    load_qfrag<NCH, RBW>(q, qfrag, g, kvh, rb0, nrb, wave, second, lane);
+    uint4 raw[RBW][NCH];
+    load_qfrag<NCH, RBW>(raw, qfrag, g, kvh, rb0, nrb, wave, second, lane);
     const float* rows_norm = norm + static_cast<size_t>(blockIdx.y) * g.rbw * 32;
     if (pstat) {                                                        // no kernel has merged the partials
         merge_rows<(RBW == 2 || NCH == 8 ? 4 : 2)>(pstat + static_cast<size_t>(blockIdx.y) * nx1 * g.rbw * 64, nx1, g.rbw * 32, rb0 * 32, g.R, red, own_norm);
@@ -680,7 +848,18 @@ __global__ __launch_bounds__(kScoreThreads, RBW == 2 && NCH > 4 ? 2 : 4) void co
             cr[i][4 * b4 + 0] = c4.x; cr[i][4 * b4 + 1] = c4.y; cr[i][4 * b4 + 2] = c4.z; cr[i][4 * b4 + 3] = c4.w;
         }
     }
-    Stage::store(kv, lds);
+    uint4 q[RBW][N];
+    bool finite_rows = true;
+#pragma unroll
+    for (int i = 0; i < RBW; ++i) finite_rows = make_operands<T, NCH>(raw[i], q[i]) && finite_rows;
+    finite_rows = !__any(!finite_rows);
+    auto store_stage = [&](int s) {
+        uint4* kbuf = lds + (s & 1) * Stage::kSlots;
+        if constexpr (kSplit) { if (!Stage::store_split(kv, kbuf)) not_finite[s & 1] = s; }
+        else Stage::store(kv, kbuf);
+    };
+    if (kSplit && !pstat) lds_barrier();        // not_finite is ready
+    store_stage(0);
     __builtin_amdgcn_s_waitcnt(0);      // queries and normalisers have landed: see row_stats_kernel
     __syncthreads();
     for (int s = 0; s < n_stage; ++s) {
@@ -693,13 +872,21 @@ __global__ __launch_bounds__(kScoreThreads, RBW == 2 && NCH > 4 ? 2 : 4) void co
             if (vs + sub * 32 < ve) {
                 float colsum = 0.f;
                 if (has_rows) {
-                    uint4 kf[NCH];
+                    const uint4* keys = kbuf + sub * N * 64 + lane;
+                    uint4 kf[kSplit ? 1 : N];
+                    bool finite = true;
+                    if constexpr (kSplit) finite = finite_rows && not_finite[s & 1] != s;
+                    else {
 #pragma unroll
-                    for (int c = 0; c < NCH; ++c) kf[c] = kbuf[(sub * NCH + c) * 64 + lane];
+                        for (int c = 0; c < N; ++c) kf[c] = keys[c * 64];
+                    }
 #pragma unroll
                     for (int i = 0; i < RBW; ++i) {
                         if (i == 0 || (second_subtiles >> sub & 1)) {
-                            const f32x16_t acc = mma_chain<T, NCH>(q[i], kf);
+                            f32x16_t acc;
+                            if constexpr (!kSplit) acc = mma_chain<T, NCH>(q[i], kf);
+                            else if (finite) acc = split_chain<NCH, true, false>(keys, q[i]);
+                            else acc = split_chain<NCH, false, false>(keys, q[i]);
 #pragma unroll
                             for (int e = 0; e < 16; ++e) colsum += fast_exp2(fmaf(acc[e], g.scale_log2, -cr[i][e]));
                         }
@@ -709,7 +896,7 @@ __global__ __launch_bounds__(kScoreThreads, RBW == 2 && NCH > 4 ? 2 : 4) void co
                 if (h == 0) csb[wave * Stage::kKeys + sub * 32 + lane] = colsum;
             }
         }
-        if (s + 1 < n_stage) Stage::store(kv, lds + ((s + 1) & 1) * Stage::kSlots);
+        if (s + 1 < n_stage) store_stage(s + 1);
         __syncthreads();
         if (threadIdx.x < Stage::kKeys) {
             const int j = vs + threadIdx.x;
@@ -1765,6 +1952,59 @@ static void launch_narrow_scores(const void* q, const void* k, const ScoreGeom& 
                        static_cast<const T*>(q), static_cast<const T*>(k), g, p.per2, pstat, p.nx1, colpart); }
 }
 
+// Whether the fp32 rows of a workgroup, at most one block per wave, are multiplied as bf16 parts.  To take a row block apart is 0.5 us
+// of each pass, so it needs keys to pay: levels by graph replay, us, fp32 MFMA / parts: 14 heads on 2 x 32 queries of 64 elements, 1500 tokens (one subtile a
+// workgroup) 26.1 / 26.8, 5000 (two) 34.2 / 32.4, 24000 65.2 / 56.4; 28 on 4 x 64 of 128, 300 (one) 29.2 / 29.3, 1500 (two) 39.8 / 36.1, 24000 233 / 154,
+// 8 x 4000 292 / 183.  Workgroups of up to four row blocks have one wave with rows to a SIMD, whose steps are a chain: 12 heads on 4 x 30 of 64,
+// 5000 (24 = subtiles x pieces of a row) 30.0 / 30.9, 24000 (96) 63.1 / 60.2; 20 on 10 x 40 of 128, 1500 (32) 30.3 / 32.2, 5000 (112) 55.7 / 52.4.
+static bool split_products(const ScoreGeom& g, const ScorePlan& p, int nch) {
+    return blocks_of_busiest_simd(g) > 1 ? p.per1 >= 2 : p.per1 * nch >= 96;
+}
+
+// Lets a kernel have more than 64 KB of LDS: an attribute of the current device's copy of it, set once.
+template <auto KERNEL>
+static bool allow_lds(size_t bytes) {
+    if (bytes <= 64 * 1024) return true;
+    static bool allowed[64] = {false};
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return false;
+    if (!allowed[dev]) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(KERNEL), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(bytes)) != hipSuccess) return false;
+        allowed[dev] = true;
+    }
+    return true;
+}
+
+// Both passes with a workgroup's rows in the waves' RBW blocks each.  false: nothing was launched.
+template <typename T, int NCH, int RBW, int SUBS>
+static bool launch_staged_scores(const void* q, const void* k, const ScoreGeom& g, const ScorePlan& p, char* ws, int batch, hipStream_t st) {
+    using Stage = KeyStage<T, NCH, SUBS>;
+    const size_t lds1 = std::max(kStageBuffers * static_cast<size_t>(Stage::kSlots) * sizeof(uint4), QueryRows<T, NCH, 1>::kLdsBytes);
+    const size_t lds2 = 2 * static_cast<size_t>(Stage::kSlots) * sizeof(uint4) + 2 * static_cast<size_t>(kScoreWaves) * Stage::kKeys * sizeof(float);
+    if (!allow_lds<&row_stats_kernel<T, NCH, RBW, SUBS>>(lds1) || !allow_lds<&col_sums_kernel<T, NCH, RBW, SUBS>>(lds2)) return false;
+    const int ny = g.Hkv * g.rs;
+    uint32_t* clear = reinterpret_cast<uint32_t*>(ws + p.off_sel + select_general_bytes(g.n_vis));
+    uint4* qfrag = reinterpret_cast<uint4*>(ws + p.off_qfrag);
+    float* pstat = reinterpret_cast<float*>(ws + p.off_pstat);
+    float* norm = reinterpret_cast<float*>(ws + p.off_norm);
+    float* colpart = reinterpret_cast<float*>(ws + p.off_colpart);
+    const unsigned nb = static_cast<unsigned>(batch);
+    {
+        TraceScope trace_scope(METOK_TRACE_ROW_STATS, st);
+        hipLaunchKernelGGL((row_stats_kernel<T, NCH, RBW, SUBS>), dim3(p.nx1, ny, nb), dim3(kScoreThreads), lds1, st, static_cast<const T*>(q),
+                           static_cast<const T*>(k), g, p.per1, pstat, qfrag, clear, kFastClearWords);
+    }
+    const float* unmerged = pstat;
+    if (partial_bytes(g, p) > kMergeInPass2Bytes) {
+        const int total_rows = ny * g.rbw * 32;
+        hipLaunchKernelGGL(merge_stats_kernel, dim3((total_rows + 15) / 16, 1, nb), dim3(256), 0, st, pstat, g, p.nx1, norm);
+        unmerged = nullptr;
+    }
+    TraceScope trace_scope(METOK_TRACE_COL_SUMS, st);
+    hipLaunchKernelGGL((col_sums_kernel<T, NCH, RBW, SUBS>), dim3(p.nx2, ny, nb), dim3(kScoreThreads), lds2, st, qfrag, static_cast<const T*>(k), g, p.per2, norm, unmerged, p.nx1, colpart);
+    return true;
+}
+
 template <typename T, int NCH>
 static void launch_scores(const void* q, const void* k, const ScoreGeom& g, const ScorePlan& p, char* ws, int batch, hipStream_t st) {
     constexpr int RBW = NCH <= 8 ? 2 : 1;
@@ -1777,39 +2017,13 @@ static void launch_scores(const void* q, const void* k, const ScoreGeom& g, cons
             case 4: launch_narrow_scores<T, NCH16, 4>(q, k, g, p, ws, batch, st); return;
         }
     }
-    using Stage = KeyStage<T, NCH, SUBS>;
-    const size_t lds1 = std::max(kStageBuffers * static_cast<size_t>(Stage::kSlots) * sizeof(uint4), QueryRows<T, NCH, 1>::kLdsBytes);
-    const size_t lds2 = 2 * static_cast<size_t>(Stage::kSlots) * sizeof(uint4) + 2 * static_cast<size_t>(kScoreWaves) * Stage::kKeys * sizeof(float);
-    const int ny = g.Hkv * g.rs;
-    uint32_t* clear = reinterpret_cast<uint32_t*>(ws + p.off_sel + select_general_bytes(g.n_vis));
-    uint4* qfrag = reinterpret_cast<uint4*>(ws + p.off_qfrag);
-    float* pstat = reinterpret_cast<float*>(ws + p.off_pstat);
-    float* norm = reinterpret_cast<float*>(ws + p.off_norm);
-    float* colpart = reinterpret_cast<float*>(ws + p.off_colpart);
-    const unsigned nb = static_cast<unsigned>(batch);
-    {
-        // With at most one row block per wave the two-block pipeline would run its second chain on zeros (32 heads on 8,
-        // 4 x 36928 keys: 159 -> 124 us; 14 heads on 2, 32 queries, 5064 keys in fp32: 10.4 -> 9.6 us).
-        TraceScope trace_scope(METOK_TRACE_ROW_STATS, st);
-        if (g.rbw <= kScoreWaves)
-            hipLaunchKernelGGL((row_stats_kernel<T, NCH, 1, SUBS>), dim3(p.nx1, ny, nb), dim3(kScoreThreads), lds1, st, static_cast<const T*>(q),
-                               static_cast<const T*>(k), g, p.per1, pstat, qfrag, clear, kFastClearWords);
-        else
-            hipLaunchKernelGGL((row_stats_kernel<T, NCH, RBW, SUBS>), dim3(p.nx1, ny, nb), dim3(kScoreThreads), lds1, st, static_cast<const T*>(q),
-                               static_cast<const T*>(k), g, p.per1, pstat, qfrag, clear, kFastClearWords);
-    }
-    const float* unmerged = pstat;
-    if (partial_bytes(g, p) > kMergeInPass2Bytes) {
-        const int total_rows = ny * g.rbw * 32;
-        hipLaunchKernelGGL(merge_stats_kernel, dim3((total_rows + 15) / 16, 1, nb), dim3(256), 0, st, pstat, g, p.nx1, norm);
-        unmerged = nullptr;
-    }
-    {
-        TraceScope trace_scope(METOK_TRACE_COL_SUMS, st);
-        if (g.rbw <= kScoreWaves)
-            hipLaunchKernelGGL((col_sums_kernel<T, NCH, 1, SUBS>), dim3(p.nx2, ny, nb), dim3(kScoreThreads), lds2, st, qfrag, static_cast<const T*>(k), g, p.per2, norm, unmerged, p.nx1, colpart);
-        else
-            hipLaunchKernelGGL((col_sums_kernel<T, NCH, RBW, SUBS>), dim3(p.nx2, ny, nb), dim3(kScoreThreads), lds2, st, qfrag, static_cast<const T*>(k), g, p.per2, norm, unmerged, p.nx1, colpart);
+    // With at most one row block per wave the two-block pipeline would run its second chain on zeros (32 heads on 8,
+    // 4 x 36928 keys: 159 -> 124 us; 14 heads on 2, 32 queries, 5064 keys in fp32: 10.4 -> 9.6 us).
+    if (g.rbw > kScoreWaves) launch_staged_scores<T, NCH, RBW, SUBS>(q, k, g, p, ws, batch, st);
+    else {
+        if constexpr (std::is_same<T, float>::value)
+            if (split_products(g, p, NCH) && launch_staged_scores<split_t, NCH, 1, SUBS>(q, k, g, p, ws, batch, st)) return;
+        launch_staged_scores<T, NCH, 1, SUBS>(q, k, g, p, ws, batch, st);
     }
 }
 

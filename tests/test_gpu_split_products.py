@@ -1,0 +1,64 @@
+"""fp32 attention scores of 65 to 256 query rows per kv head on more than a few keys, whose products are taken on three bf16 parts of
+every element: against the CPU oracle, with jumps beyond the range of float, and with elements that are not finite (fp32 products)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import metok_oracle as O
+from paper_2506_02850_amd import synth
+from tests.parity import assert_rel
+from tests.score_plan import score_plans
+from tests.test_gpu_shared_row_blocks import KV_HEADS, check_scores_of_jumps
+from tests.test_gpu_stage2 import check_prune, i32, make_layer, mk, run_prune
+
+pytestmark = pytest.mark.gpu
+
+
+def takes_parts(S, n_vis, Hq, Hkv, dh, Tq, vis_start=0, mode=0):
+    plan = score_plans(S, n_vis, Hq, Hkv, dh, Tq, dtype="f32", vis_start=vis_start, mode=mode).plan
+    return 2 < plan.rbw <= 8 and (plan.per1 >= 2 if plan.rbw > 4 else plan.per1 * dh // 8 >= 96)
+
+
+# row blocks of a workgroup: 3 (the last one ragged), 4, 5, 7, 8, and 7 + 7 split rows; the last stage of a range is ragged
+@pytest.mark.parametrize("dh,group,Tq", [(128, 3, 31), (128, 2, 64), (32, 5, 30), (64, 7, 32), (128, 4, 64), (128, 7, 64)])
+@pytest.mark.parametrize("tokens,vis_start,mode", [(1960, 7, 0), (2500, 0, 1)])
+def test_against_the_oracle(dh, group, Tq, tokens, vis_start, mode):
+    layer = make_layer(6100 + dh + group, 10, tokens // 10, 4, Tq + 3, 16, KV_HEADS * group, KV_HEADS, dh, "f32", vis_start=vis_start)
+    assert takes_parts(layer.n_vis + vis_start + Tq + 3, layer.n_vis, KV_HEADS * group, KV_HEADS, dh, Tq, vis_start, mode)
+    seg = np.zeros(layer.n_vis, dtype=np.int32)
+    quotas = [layer.n_vis // 2]
+    got, q = run_prune(layer, seg, quotas, Tq=Tq, score_mode=mode)
+    check_prune(layer, seg, quotas, got, q, score_mode=mode)
+
+
+@pytest.mark.parametrize("low", [32, 96, 224])
+def test_jumps_beyond_the_range_of_float(low):
+    S = 2048
+    check_scores_of_jumps("f32", 64, 7, 32, S, np.arange(S) % 256 >= low, 32, None)
+
+
+def test_elements_that_are_not_finite():
+    """A NaN (whose only mantissa bit is the last one) spoils its key and its kv head's rows; -inf in a key, against positive queries, is
+    probability 0; an infinite query spoils its row alone."""
+    B = mk()
+    rng = np.random.default_rng(17)
+    Hkv, group, dh, Tq, n = 4, 7, 64, 32, 5000
+    S = n + Tq
+    assert takes_parts(S, n, Hkv * group, Hkv, dh, Tq)
+    q = np.abs(rng.standard_normal((Hkv * group, Tq, dh))).astype(np.float32) + np.float32(0.1)
+    k = (0.2 * rng.standard_normal((Hkv, S, dh))).astype(np.float32)
+    bad, bad_q = k.copy(), q.copy()
+    bad[1, 50, 3] = np.array([0x7f800001], dtype=np.uint32).view(np.float32)[0]
+    bad[2, 70, 5] = bad[2, 4000, 60] = -np.inf
+    bad_q[0, 9, 2] = np.inf                                            # logits of +-inf: the row is NaN and adds nothing to finite rows
+    hidden = torch.zeros((S, 8), device="cuda")
+    run = lambda queries, keys: B.metok_prefill_prune(hidden, 0, n, i32(np.zeros(n)), [n // 2], q_text=synth.to_torch(queries, "f32", "cuda"),
+                                                      k_all=synth.to_torch(keys, "f32", "cuda"))["scores"].cpu().numpy()
+    scores = run(q, bad)
+    fixed = k.copy()
+    fixed[2, 70] = fixed[2, 4000] = np.float32(-1e5)
+    want = sum(O.text_to_visual_attention(q[h * group:(h + 1) * group], fixed[h:h + 1], 0, n, 0) for h in (0, 2, 3)) / Hkv
+    others = np.arange(n) != 50
+    assert np.isnan(scores[50])
+    assert_rel(scores[others], want[others], 1e-5, "scores")
+    assert not np.isfinite(run(bad_q, k)).all()
