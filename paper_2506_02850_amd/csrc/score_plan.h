@@ -127,19 +127,18 @@ inline void plan_grid(const ScoreGeom& g, int n_vis, int nch, int batch, size_t 
 }
 
 // Up to here every workgroup of pass 2 merges the partial statistics of its rows for itself, above a kernel in between does it
-// once.  Levels, kernels alone, us, merged in pass 2 / by the kernel: 300 tokens of 28 heads on 4, 224 rows x 12 partials (21 KB) 20.0 / 21.1; 9000,
-// 32 heads on 8, 256 x 32 (64 KB) 37.7 / 38.7.  The line was drawn where larger merges lost: with eight partials a round, 448 rows x 59
-// (206 KB) took 33.4 / 32.6 and 448 x 128 35.4 / 31.8.  With four a round (see col_sums_kernel) they no longer do: 5000 tokens in fp32, 224 x 79 (138
-// KB) 31.4 / 32.7; 18432, 448 x 58 (203 KB) 52.3 / 53.0 and with 64 elements 46.5 / 46.1.  The line stays until the rule below, which
-// reads it too, has been measured with another.
-constexpr size_t kMergeInPass2Bytes = 64 * 1024;
+// once.  Levels, kernels alone, us, by the kernel / merged in pass 2: 28 heads on 4 x 30 queries, 224 rows x 53 to 61 partials (95 to 109 KB), 5000 tokens 28.8 /
+// 27.3, 36864 64.1 / 62.5; 14 on 2 x 32 of 64 elements, 224 x 79 to 116 (138 to 203 KB), 5000 in fp32 31.6 / 30.4, 18432 36.7 / 35.4; 28 on 4 x 64, 448 x 58
+// (203 KB), 18432 54.7 / 53.4; 8 on 2 x 64 of 256, 256 x 128 (256 KB), 36864 64.4 / 62.3; beyond the line, 14 on 2 x 64 of 64, 448 x 116 (406 KB), 36864
+// 56.5 / 57.6, in fp32 123.2 / 125.4.
+constexpr size_t kMergeInPass2Bytes = 256 * 1024;
 inline size_t partial_bytes(const ScoreGeom& g, const ScorePlan& p) { return static_cast<size_t>(p.nx1) * g.rbw * 32 * 2 * sizeof(float); }
 
 // More than eight row blocks go two to a wave, which lets a key fragment feed two products and reads the keys once.  On short
 // ranges the fixed part of a workgroup (its queries, the merge of all its rows' partial statistics, the first stage) is what takes
 // the time, and half the rows in each of twice as many workgroups make it shorter: up to kSplitSubtiles subtiles a workgroup the
-// rows are split until every wave has one block, up to kSplitSubtilesMerged where the whole rows' partials would take the merging
-// kernel.  One level of 28 heads on 4 x 64 queries, us whole / split: 300 tokens 26.5 / 24.1, 2243 (2 subtiles) 32.7 / 28.9, 6000
+// rows are split until every wave has one block, up to kSplitSubtilesMerged where the whole rows' partials are more than
+// kSplitMergedBytes.  One level of 28 heads on 4 x 64 queries, us whole / split: 300 tokens 26.5 / 24.1, 2243 (2 subtiles) 32.7 / 28.9, 6000
 // 40.6 / 36.7, 9000 (5) 47.4 / 44.4, 15000 (8) 62.6 / 60.7, 18432 (10) 63.0 / 64.2; two videos of 4000 41.2 / 39.5, eight of 1000
 // (5) 45.5 / 42.6, four of 3000 (6, merged in pass 2) 49.5 / 50.1; 14 heads on 2 x 64, 8000 tokens 34.3 / 30.8.
 // Two blocks on one wave and their halves on two are the same work only where nothing is rounded: 9 to 12 blocks are three to a SIMD whole
@@ -151,6 +150,7 @@ inline size_t partial_bytes(const ScoreGeom& g, const ScorePlan& p) { return sta
 // A split needs more room for the column sums and none for the two words per token that select_bytes reserves for nobody; where
 // it does not fit the workspace of the whole rows, the rows stay whole.
 constexpr int kSplitSubtiles = 5, kSplitSubtilesMerged = 8;
+constexpr size_t kSplitMergedBytes = 64 * 1024;
 constexpr int kSplitMoreBf16 = 10, kSplitMoreF32 = 3;
 // Row blocks on the busiest SIMD of a workgroup: waves 0 and 4 share one.
 inline int blocks_of_busiest_simd(const ScoreGeom& g) {
@@ -160,7 +160,7 @@ inline int blocks_of_busiest_simd(const ScoreGeom& g) {
 inline void plan_score(ScoreGeom* g, int n_vis, int dtype, int batch, ScorePlan* p) {
     const int nch = chunk_count(g->dh, dtype);
     plan_grid(*g, n_vis, nch, batch, select_bytes(n_vis), p);
-    if (g->rbw <= kScoreWaves || p->per1 > (partial_bytes(*g, *p) > kMergeInPass2Bytes ? kSplitSubtilesMerged : kSplitSubtiles)) return;
+    if (g->rbw <= kScoreWaves || p->per1 > (partial_bytes(*g, *p) > kSplitMergedBytes ? kSplitSubtilesMerged : kSplitSubtiles)) return;
     ScoreGeom split = *g;
     split.rs = (g->rb_total + kScoreWaves - 1) / kScoreWaves;
     split.rbw = (g->rb_total + split.rs - 1) / split.rs;

@@ -795,7 +795,7 @@ __global__ __launch_bounds__(256) void merge_stats_kernel(const float* __restric
 // ---------------------------------------------------------------------------------------------
 // Grids of more workgroups than CUs run two (or three) to a CU where 128 (80) registers suffice, which the merge must not exceed:
 // with eight partials a round in every kernel, 20 x 3000 tokens of 40 heads x 100 queries took 438 us for 389 with the merging kernel,
-// in bf16 with 256 elements 934 for 810, and now 381 and 793.  A thread has at most four (kMergeInPass2Bytes).
+// in bf16 with 256 elements 934 for 810, and now, with four (two) a round, 381 and 793.
 template <typename T, int NCH, int RBW> constexpr int kColWaves = (RBW == 2 && NCH > 4) || kOperands<T, NCH> > 16 ? 2 : 4;      // per SIMD
 template <typename T, int NCH, int RBW, int SUBS>
 __global__ __launch_bounds__(kScoreThreads, (kColWaves<T, NCH, RBW>)) void col_sums_kernel(const uint4* __restrict__ qfrag, const T* __restrict__ k_all,
