@@ -964,6 +964,44 @@ __device__ __forceinline__ void load_queries(u32x4_t (&q)[NB][NCH], const T* __r
     for (int b = 0; b < NB; ++b) load_fragments<T, NCH>(q[b], q_text + static_cast<size_t>(kvh) * g.R * g.dh, b * 16, g.R - 1, g.dh);
 }
 
+// From eight fragments on the workgroup loads them once, into LDS, from where every wave takes them all.  A load in fragment order is
+// 64 bytes of 16 rows, and eight waves with 16 of them each ahead of their keys took 2.7 us of pass 1 and 2 of pass 2 for the addresses alone.  One level
+// by graph replay, us: 4507 tokens, 40 heads x 64 queries of 128 elements 49.7 -> 46.5, 839 tokens 30.5 -> 25.9, 2924 in fp32 79.8 -> 71.8; 7274, 16 heads x 64 of 64
+// 30.1 -> 28.8.  With fewer fragments, or one row block, the barrier costs more than it saves: 439 tokens, 16 x 16 of 64 17.7 / 18.1, 12587 in fp32, 32 heads on 8 x 1
+// of 128 77.3 / 79.8.
+template <int NCH, int NB> constexpr bool kShareQueries = NB >= 2 && NB * NCH >= 8;
+template <typename T, int NCH, int NB>
+struct SharedQueries {
+    static constexpr int kFragments = NB * NCH, kRounds = (kFragments * 64 + kScoreThreads - 1) / kScoreThreads;
+    u32x4_t v[kRounds];
+
+    // piece id of the fragments: (block b, chunk c, lane) = (id / 64 / NCH, id / 64 % NCH, id % 64)
+    __device__ __forceinline__ void load(const T* __restrict__ q_text, const ScoreGeom& g, int kvh) {
+        const T* rows = q_text + static_cast<size_t>(kvh) * g.R * g.dh;
+#pragma unroll
+        for (int u = 0; u < kRounds; ++u) {
+            const int id = min(static_cast<int>(threadIdx.x) + u * kScoreThreads, kFragments * 64 - 1), f = id >> 6, lane = id & 63;
+            const int row = min(f / NCH * 16 + (lane & 15), g.R - 1);
+            v[u] = *reinterpret_cast<const u32x4_t*>(rows + static_cast<size_t>(row) * g.dh + (f % NCH * 4 + (lane >> 4)) * Mma<T>::kChunkElems);
+        }
+    }
+    __device__ __forceinline__ void store(u32x4_t* lds) {
+#pragma unroll
+        for (int u = 0; u < kRounds; ++u) {
+            const int id = threadIdx.x + u * kScoreThreads;
+            if ((u + 1) * kScoreThreads <= kFragments * 64 || id < kFragments * 64) lds[id] = v[u];
+        }
+    }
+    // behind a barrier
+    static __device__ __forceinline__ void take(u32x4_t (&q)[NB][NCH], const u32x4_t* lds) {
+        const int lane = threadIdx.x & 63;
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int c = 0; c < NCH; ++c) q[b][c] = lds[(b * NCH + c) * 64 + lane];
+    }
+};
+
 template <typename T, int NCH>
 __device__ __forceinline__ f32x4_t narrow_chain(const u32x4_t (&a)[NCH], const u32x4_t (&b)[NCH]) {
     f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
@@ -1011,9 +1049,18 @@ __global__ __launch_bounds__(kScoreThreads) void narrow_row_stats_kernel(const T
     auto load = [&](u32x4_t (&dst)[NCH], int t) { load_fragments<T, NCH>(dst, k_head, first_key(t), ke - 1, g.dh); };
     // the first subtiles and the queries are requested together: one memory round trip
     u32x4_t k[DEPTH][NCH], q[NB][NCH];
-    load_queries<T, NCH, NB>(q, q_text, g, kvh);
+    constexpr bool kShare = kShareQueries<NCH, NB>;
+    __shared__ u32x4_t query_lds[kShare ? NB * NCH * 64 : 1];
+    SharedQueries<T, NCH, NB> queries;
+    if constexpr (kShare) queries.load(q_text, g, kvh);
+    else load_queries<T, NCH, NB>(q, q_text, g, kvh);
 #pragma unroll
     for (int d = 0; d < DEPTH - 1; ++d) load(k[d], d);
+    if constexpr (kShare) {
+        queries.store(query_lds);
+        lds_barrier();
+        queries.take(q, query_lds);
+    }
 
     // m is the largest logit among the lane's keys of the first subtile and stays while whole subtiles are visible: terms
     // relative to it keep their precision as long as none exceeds it by 2^127, and the running maximum with its masks is
@@ -1097,17 +1144,23 @@ __global__ __launch_bounds__(kScoreThreads) void narrow_col_sums_kernel(const T*
     const int n = subs > wave ? (subs - wave + kScoreWaves - 1) / kScoreWaves : 0;
     auto load = [&](u32x4_t (&dst)[NCH], int t) { load_fragments<T, NCH>(dst, k_head, vb + (wave + t * kScoreWaves) * kSubKeys, ve - 1, g.dh); };
     u32x4_t k[DEPTH][NCH], q[NB][NCH];
+    constexpr bool kShare = kShareQueries<NCH, NB>;
+    __shared__ u32x4_t query_lds[kShare ? NB * NCH * 64 : 1];
+    SharedQueries<T, NCH, NB> queries;
+    if constexpr (kShare) queries.load(q_text, g, kvh);
     // a wave without keys only helps with the merge: loading its queries too made short levels in fp32 slower than the merging kernel
-    // did (300 tokens, 2 heads x 64 queries of 128 elements, kernels alone: 31.5 us so, 29.9 with the merging kernel, now 26.7)
+    // did (300 tokens, 2 heads x 64 queries of 128 elements, kernels alone: 31.5 us so, 29.9 with the merging kernel, 26.7 without)
     if (n > 0) {
-        load_queries<T, NCH, NB>(q, q_text, g, kvh);
+        if constexpr (!kShare) load_queries<T, NCH, NB>(q, q_text, g, kvh);
 #pragma unroll
         for (int d = 0; d < DEPTH - 1; ++d) load(k[d], d);
     }
+    if constexpr (kShare) queries.store(query_lds);                    // the merge ends with a barrier
     const int rows = g.rbw * 32;                                       // 32 or 64; NB * 16 of them are used
     // two partials a round: with eight the kernel takes up to twice the registers, and where there is more than one workgroup per CU the
     // second one waits (fp32, 40 heads x 64 queries of 64 elements, 8 x 5000 tokens: 421 -> 407 us)
     merge_rows<2>(pstat + static_cast<size_t>(kvh) * nx1 * rows * 2, nx1, rows, 0, g.R, red, norm);
+    if (kShare && n > 0) queries.take(q, query_lds);
     float cr[NB][4];
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
