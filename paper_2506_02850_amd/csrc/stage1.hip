@@ -1506,17 +1506,20 @@ static int64_t worst_case_rows(int T, int grid_h, int grid_w, int s1, int s2, in
     return static_cast<int64_t>(T) * side(grid_h) * side(grid_w);
 }
 
-// Workgroups of the pooling pass per frame: at most 47, or 35 where frames may stay as they are, stride 1 (4 x 116 frames of 24 x 16 x 1024 at strides 1 and 2, 47
-// workgroups 165 us, 35 159; 64 and more are up to a quarter slower), fewer if
+// Workgroups of the pooling pass per frame: at most 47, or 35 where frames may stay as they are (stride 1; 4 x 116 frames of 24 x 16 x 1024 at strides 1 and 2, 47
+// workgroups 165 us, 35 159) and in fp32 (27 frames of 22 x 26 x 872 39.1, 38.6; 64 and more are up to a quarter slower), fewer if
 // a frame at its smallest stride does not hold a chunk for each of their threads (782 frames of 24 x 24 x 136: 55 -> 26 us, 2400 of 8 x 8 x 256: 110 -> 18 us).
-// An odd number: consecutive workgroups go to the chip's eight dies in turn, and in a frame of a larger stride only the first ones have
-// work.  With a multiple of 8 those of every frame meet on the same dies: 64 frames of 16 x 16 x 1024, whole calls, 32 workgroups 28.8 us, 33 24.6; 200
-// of 16 x 16 x 768 24 46.2, 25 41; 16 of 24 x 24 x 1024 36 22.8, 47 20.2; 8 x 64 of 27 x 27 x 1152 36 305, 47 296; 32 of 27 x 27 x 1152 33.0 and 32.2.
+// No multiple of 4: consecutive workgroups go to the chip's eight dies in turn, and in a frame of a larger stride only the first ones have
+// work; with a multiple of 8 (of 4) those of every frame meet on the same (two sets of) dies: 64 frames of 16 x 16 x 1024, whole calls, 32 workgroups 28.8 us, 33 24.6; 200
+// of 16 x 16 x 768 24 46.2, 25 41; 16 of 24 x 24 x 1024 36 22.8, 47 20.2; 8 x 64 of 27 x 27 x 1152 36 305, 47 296; 32 of 27 x 27 x 1152 33.0 and
+// 32.2; 8 x 106 of 16 x 16 x 1152 36 215, 37 206.
+// Fewer than 16 frames have nothing to spread: 4 of 16 x 16 x 768 24 15.6, 25 16.5; 6 of 24 x 24 x 768 at strides 1 and 2 36 21.9, 35 23.1.
 static unsigned pool_workgroups(int T, int grid_h, int grid_w, int d, int dtype, int s1, int s2, int pool_edge) {
-    const int64_t kMost = s1 > 1 && s2 > 1 ? 47 : 35;
+    const int64_t most = T < 16 ? 36 : (s1 > 1 && s2 > 1 && dtype == METOK_BF16 ? 47 : 35);
     const int64_t items = worst_case_rows(T, grid_h, grid_w, s1, s2, pool_edge) / T * (d / (dtype == METOK_BF16 ? 8 : 4));
     const int64_t n = (items + kPoolThreads - 1) / kPoolThreads;
-    return static_cast<unsigned>(n < kMost ? n | 1 : kMost);
+    if (n >= most) return static_cast<unsigned>(most);
+    return static_cast<unsigned>(n < 1 ? 1 : (T >= 16 && n % 4 == 0 ? n + 1 : n));
 }
 
 extern "C" int64_t metok_compress_encoder_tokens_capacity_rows(int T, int grid_h, int grid_w, int s1, int s2, int pool_edge) {
