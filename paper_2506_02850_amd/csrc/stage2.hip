@@ -57,11 +57,16 @@ template <> struct Mma<float> {
     }
 };
 
-// fp32 rows multiplied as bf16.  A finite x is the sum of three bf16 numbers, its leading, middle and last eight bits, without a
-// rounding; of the nine products of two such numbers the six that reach 2^-24 of the whole are taken, each with 16 times the rate of
-// an fp32 MFMA: 192 cycles of the matrix pipe per 32 x 32 x 16 products instead of 512.  28 heads on 4 x 64 queries of 128 elements, 8 x 4000 tokens: 291 ->
-// 184 us a level, 24000 tokens 233 -> 153; see split_products for where it is taken.  Against 64 bits the scores are as close as with fp32
-// products on normal data (1.64 to 1.73e-7 either way) and closer with logits three times as large (1.5e-6 -> 0.95e-6).
+// fp32 rows multiplied as bf16.  An element is the sum of three bf16 numbers, each the nearest to what the ones before leave, without a
+// rounding (the last has at most eight bits left); of the nine products of two such numbers six are taken, each with 16 times the rate
+// of an fp32 MFMA: 192 cycles of the matrix pipe per 32 x 32 x 16 products instead of 512.  The other three, middle by last and last by
+// last, are together below 2^-24 of the whole (0.9 at most) and of either sign.  (Parts that are cut off all have the sign of their
+// element: the three reach 7.8 x 2^-24 and shrink every product.)
+// Root mean square error of a sum against 64 bits, in units of its size, fp32 MFMA / parts, normal elements of which n of a row are not 0:
+// n = 1 2.54e-8 / 2.61e-8, 2 3.1e-8 / 2.6e-8, 4 4.0e-8 / 2.7e-8, 8 5.3e-8 / 2.9e-8, all 64 14.3e-8 / 4.9e-8, all 128 20.2e-8 / 6.5e-8; parts cut off 6.9e-8 up
+// to n = 8, then 7.5e-8 and 8.5e-8.
+// Whole calls by graph replay, fp32 MFMA / parts: 28 heads on 4 x 64 queries of 128 elements, 8 x 4000 tokens 353 / 243 us, 24000 tokens 287 / 206;
+// see split_products for where they are taken.
 struct split_t { float value; };
 template <> struct Mma<split_t> : Mma<float> {};
 
@@ -69,27 +74,28 @@ template <> struct Mma<split_t> : Mma<float> {};
 template <typename T, int NCH> constexpr int kOperands = std::is_same<T, split_t>::value ? NCH / 2 * 3 : NCH;
 
 __device__ __forceinline__ bool is_finite_bits(uint32_t x) { return (x & 0x7f800000u) != 0x7f800000u; }
-// x without its leading part; nothing is left of what is not finite
-__device__ __forceinline__ uint32_t below_leading(uint32_t x) { return __float_as_uint(__uint_as_float(x) - __uint_as_float(x & 0xffff0000u)); }
-// Upper halves of two words as a pair
-__device__ __forceinline__ uint32_t upper_halves(uint32_t lo, uint32_t hi) { return __builtin_amdgcn_perm(hi, lo, 0x07060302u); }
 
-// Four elements -> their leading, middle and last parts.  Where an element is not finite its parts mean nothing (a NaN with only low
-// bits would even become an infinity): the caller asks all_finite and takes exact_parts instead.
+// Four elements -> their leading, middle and last parts.  For elements beyond kPartsBelow the caller takes exact_parts instead.
 __device__ __forceinline__ void split_piece(const uint4& x, uint2 (&part)[3]) {
-    uint32_t e[4] = {x.x, x.y, x.z, x.w};
+    float e[4] = {__uint_as_float(x.x), __uint_as_float(x.y), __uint_as_float(x.z), __uint_as_float(x.w)};
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
-        part[p] = make_uint2(upper_halves(e[0], e[1]), upper_halves(e[2], e[3]));
-        if (p < 2) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) e[i] = below_leading(e[i]);
-        }
+        part[p] = make_uint2(pack_bf16x2(e[0], e[1]), pack_bf16x2(e[2], e[3]));
+        if (p < 2) { e[0] -= bf16_lo(part[p].x); e[1] -= bf16_hi(part[p].x); e[2] -= bf16_lo(part[p].y); e[3] -= bf16_hi(part[p].y); }
     }
 }
-__device__ __forceinline__ bool all_finite(const uint4& x) { return is_finite_bits(x.x) && is_finite_bits(x.y) && is_finite_bits(x.z) && is_finite_bits(x.w); }
-// The same for elements of which some may not be finite: those are their leading part alone, a NaN stays one.
+// Elements below this are multiplied in parts: no sum of 128 of their products leaves the range of float, whatever the order, and parts too
+// small for a bf16 number of full precision (below 2^-126) are less than 2^-58 of a logit together.
+constexpr float kPartsBelow = 0x1p59f;
+__device__ __forceinline__ bool all_fit(const uint4& x) {
+    auto fits = [](uint32_t e) { return fabsf(__uint_as_float(e)) < kPartsBelow; };           // not a NaN
+    return fits(x.x) && fits(x.y) && fits(x.z) && fits(x.w);
+}
+// The same for elements of which some do not fit: parts that joined_piece puts together again (short of less than 2^-133).  The leading part of
+// the largest must not round to infinity, so they are cut off; what is not finite is its leading part alone, a NaN stays one.
 __device__ __forceinline__ uint32_t quiet(uint32_t x) { return (x & 0x7fffffffu) > 0x7f800000u ? x | 0x00400000u : x; }
+__device__ __forceinline__ uint32_t below_leading(uint32_t x) { return __float_as_uint(__uint_as_float(x) - __uint_as_float(x & 0xffff0000u)); }
+__device__ __forceinline__ uint32_t upper_halves(uint32_t lo, uint32_t hi) { return __builtin_amdgcn_perm(hi, lo, 0x07060302u); }
 __device__ __forceinline__ void exact_parts(const uint4& x, uint2 (&part)[3]) {
     const uint32_t e[4] = {quiet(x.x), quiet(x.y), quiet(x.z), quiet(x.w)};
     uint32_t lead[4], mid[4], last[4];
@@ -119,17 +125,17 @@ __device__ __forceinline__ uint4 joined_piece(const uint4* f, int c) {
     };
     return make_uint4(element(0), element(1), element(2), element(3));
 }
-// Operands of a row block from its pieces; true: every element of the lane is finite.
+// Operands of a row block from its pieces; true: every element of the lane fits.
 template <typename T, int NCH>
 __device__ __forceinline__ bool make_operands(const uint4 (&raw)[NCH], uint4 (&op)[kOperands<T, NCH>]) {
-    bool finite = true;
+    bool fit = true;
     if constexpr (std::is_same<T, split_t>::value) {
 #pragma unroll
-        for (int c = 0; c < NCH; ++c) finite = finite && all_finite(raw[c]);
+        for (int c = 0; c < NCH; ++c) fit = fit && all_fit(raw[c]);
 #pragma unroll
         for (int c = 0; c < NCH; c += 2) {
             uint2 a[3], b[3];
-            if (finite) { split_piece(raw[c], a); split_piece(raw[c + 1], b); } else { exact_parts(raw[c], a); exact_parts(raw[c + 1], b); }
+            if (fit) { split_piece(raw[c], a); split_piece(raw[c + 1], b); } else { exact_parts(raw[c], a); exact_parts(raw[c + 1], b); }
 #pragma unroll
             for (int p = 0; p < 3; ++p) op[c / 2 * 3 + p] = make_uint4(a[p].x, a[p].y, b[p].x, b[p].y);
         }
@@ -137,7 +143,7 @@ __device__ __forceinline__ bool make_operands(const uint4 (&raw)[NCH], uint4 (&o
 #pragma unroll
         for (int c = 0; c < NCH; ++c) op[c] = raw[c];
     }
-    return finite;
+    return fit;
 }
 
 // Kept visual tokens of every video of a batch (the quotas of a video added up), passed by value.
@@ -186,24 +192,24 @@ struct KeyStage {
                 reinterpret_cast<u32x4_t*>(kbuf)[((jl >> 5) * NCH + (p % NCH)) * 64 + (jl & 31) + 32 * (p / NCH)] = v[u];
         }
     }
-    // Three parts of every element; false: an element of this thread is not finite.
+    // Three parts of every element; false: an element of this thread does not fit.
     static __device__ __forceinline__ bool store_split(const u32x4_t (&v)[kPerThread], uint4* __restrict__ kbuf) {
-        bool finite = true;
+        bool fit = true;
 #pragma unroll
         for (int u = 0; u < kPerThread; ++u) {
             const int id = threadIdx.x + u * kScoreThreads;
             const int jl = id % kKeys, p = id / kKeys, c = p % NCH;
             const uint4 x = make_uint4(v[u].x, v[u].y, v[u].z, v[u].w);
             uint2 part[3];
-            if (__builtin_expect(all_finite(x), 1)) split_piece(x, part);
-            else { finite = false; exact_parts(x, part); }
+            if (__builtin_expect(all_fit(x), 1)) split_piece(x, part);
+            else { fit = false; exact_parts(x, part); }
             uint2* dst = reinterpret_cast<uint2*>(kbuf) + 2 * (((jl >> 5) * (NCH / 2 * 3) + c / 2 * 3) * 64 + (jl & 31) + 32 * (p / NCH)) + (c & 1);
             if ((u + 1) * kScoreThreads <= kPieces || id < kPieces) {
 #pragma unroll
                 for (int q = 0; q < 3; ++q) dst[2 * 64 * q] = part[q];
             }
         }
-        return finite;
+        return fit;
     }
 };
 
@@ -323,36 +329,44 @@ __device__ __forceinline__ f32x16_t mma_chain(const uint4 (&a)[NCH], const uint4
 }
 
 // The product of a subtile of split keys, operand c of the lane at keys[64 c], with a split row block; KEYS_FIRST: keys x queries.
-// !FINITE: some element may not be, and infinity times a part that is zero would be NaN: fp32 products.
-template <int NCH, bool FINITE, bool KEYS_FIRST>
+// !FIT: some element may not (infinity times a part that is zero would be NaN): fp32 products.
+template <int NCH, bool FIT, bool KEYS_FIRST>
 __device__ __forceinline__ f32x16_t split_chain(const uint4* keys, const uint4 (&q)[NCH / 2 * 3]) {
-    f32x16_t acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    // The products of the leading parts have a sum of their own: a bf16 MFMA does not round to nearest what it adds to a sum, which for rows of one
+    // or two elements made a third of the error where these products went on from the sum of the others.  They run ahead of the others with 128
+    // elements (one level of 24000 tokens, 28 heads on 4 x 64: 199 us, alternating 203) and alternate with them otherwise (4 x 9000 tokens, 16 heads x 100
+    // queries of 64 elements: 203 us, alternating 188; with one sum 176).
+    constexpr bool kAhead = NCH == 16;
+    f32x16_t acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, small = acc;
+    auto mma = [&](auto tag, f32x16_t& sum, const uint4& key, const uint4& row) {
+        sum = KEYS_FIRST ? Mma<decltype(tag)>::mma(key, row, sum) : Mma<decltype(tag)>::mma(row, key, sum);
+    };
+    if constexpr (FIT && kAhead) {
+#pragma unroll
+        for (int c = 0; c < NCH / 2; ++c) mma(bf16_t(), acc, keys[3 * c * 64], q[3 * c]);
+    }
 #pragma unroll
     for (int c = 0; c < NCH / 2; ++c) {
         const uint4 k[3] = {keys[(3 * c) * 64], keys[(3 * c + 1) * 64], keys[(3 * c + 2) * 64]};
         const uint4* x = q + 3 * c;
-        auto mma = [&](auto tag, const uint4& key, const uint4& row) {
-            acc = KEYS_FIRST ? Mma<decltype(tag)>::mma(key, row, acc) : Mma<decltype(tag)>::mma(row, key, acc);
-        };
-        if constexpr (FINITE) {
-            mma(bf16_t(), k[2], x[0]);
-            mma(bf16_t(), k[0], x[2]);
-            mma(bf16_t(), k[1], x[1]);
-            mma(bf16_t(), k[1], x[0]);
-            mma(bf16_t(), k[0], x[1]);
+        if constexpr (FIT) {
+            mma(bf16_t(), small, k[2], x[0]);
+            mma(bf16_t(), small, k[0], x[2]);
+            mma(bf16_t(), small, k[1], x[1]);
+            mma(bf16_t(), small, k[1], x[0]);
+            mma(bf16_t(), small, k[0], x[1]);
+            if constexpr (!kAhead) mma(bf16_t(), acc, k[0], x[0]);
         } else {
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-                mma(float(), joined_piece(k, i), joined_piece(x, i));
+                mma(float(), acc, joined_piece(k, i), joined_piece(x, i));
                 __builtin_amdgcn_sched_barrier(0);                  // one piece at a time: no registers for what is hardly ever run
             }
         }
     }
-    // the products of the leading parts last: only these are rounded at the size of the sum
-    if constexpr (FINITE) {
+    if constexpr (FIT) {
 #pragma unroll
-        for (int c = 0; c < NCH / 2; ++c)
-            acc = KEYS_FIRST ? Mma<bf16_t>::mma(keys[3 * c * 64], q[3 * c], acc) : Mma<bf16_t>::mma(q[3 * c], keys[3 * c * 64], acc);
+        for (int e = 0; e < 16; ++e) acc[e] += small[e];
     }
     return acc;
 }
@@ -483,7 +497,7 @@ __global__ __launch_bounds__(kScoreThreads) void row_stats_kernel(const T* __res
     __shared__ float2 shared_rows[2][64];
     constexpr int N = kOperands<T, NCH>;
     constexpr bool kSplit = std::is_same<T, split_t>::value;
-    __shared__ int not_finite[kSplit ? kStageBuffers : 1];          // the last stage of the buffer that held such an element
+    __shared__ int unfit[kSplit ? kStageBuffers : 1];          // the last stage of the buffer that held an element that does not fit
     q_text = of_video_elems(q_text, g.q_video);
     qfrag = of_video(qfrag, g.ws_video); pstat = of_video(pstat, g.ws_video); clear = of_video(clear, g.ws_video);
     const T* k_head = of_video_elems(k_all, g.k_video) + static_cast<size_t>(kvh) * g.S * g.dh;
@@ -504,21 +518,21 @@ __global__ __launch_bounds__(kScoreThreads) void row_stats_kernel(const T* __res
     Stage::load(kv, k_head, kb, g.S, g.dh);
     Stage::load(kv1, k_head, kb + (n_stage > 1 ? Stage::kKeys : 0), g.S, g.dh);
     uint4 q[RBW][N];
-    bool finite_rows = true;
-    if (kSplit && threadIdx.x < kStageBuffers) not_finite[threadIdx.x] = -1;
+    bool fit_rows = true;
+    if (kSplit && threadIdx.x < kStageBuffers) unfit[threadIdx.x] = -1;
     {
         QueryRows<T, NCH, RBW> rows;
         uint4 raw[RBW][NCH];
         rows.load(q_text, g, kvh, rb0, nrb, wave, second, lane);
         rows.to_fragments(raw, lds, g, rb0, nrb, wave, second, lane);
 #pragma unroll
-        for (int i = 0; i < RBW; ++i) finite_rows = make_operands<T, NCH>(raw[i], q[i]) && finite_rows;
-        finite_rows = !__any(!finite_rows);
+        for (int i = 0; i < RBW; ++i) fit_rows = make_operands<T, NCH>(raw[i], q[i]) && fit_rows;
+        fit_rows = !__any(!fit_rows);
         __syncthreads();                                // the stages take over the waves' parts of LDS
     }
     auto store_stage = [&](const u32x4_t (&v)[Stage::kPerThread], int s) {
         uint4* kbuf = lds + (s % kStageBuffers) * Stage::kSlots;
-        if constexpr (kSplit) { if (!Stage::store_split(v, kbuf)) not_finite[s % kStageBuffers] = s; }
+        if constexpr (kSplit) { if (!Stage::store_split(v, kbuf)) unfit[s % kStageBuffers] = s; }
         else Stage::store(v, kbuf);
     };
     float m[RBW], l[RBW];
@@ -550,8 +564,8 @@ __global__ __launch_bounds__(kScoreThreads) void row_stats_kernel(const T* __res
                 if (j0 < ke && nrb_w > 0) {
                     const uint4* keys = kbuf + sub * N * 64 + lane;
                     uint4 kf[kSplit ? 1 : N];
-                    bool finite = true;
-                    if constexpr (kSplit) finite = finite_rows && not_finite[s % kStageBuffers] != s;
+                    bool fit = true;
+                    if constexpr (kSplit) fit = fit_rows && unfit[s % kStageBuffers] != s;
                     else {
 #pragma unroll
                         for (int c = 0; c < N; ++c) kf[c] = keys[c * 64];
@@ -562,7 +576,7 @@ __global__ __launch_bounds__(kScoreThreads) void row_stats_kernel(const T* __res
                         if (i < nrb_w) {
                             f32x16_t acc;
                             if constexpr (!kSplit) acc = mma_chain<T, NCH>(kf, q[i]);
-                            else if (finite) acc = split_chain<NCH, true, true>(keys, q[i]);
+                            else if (fit) acc = split_chain<NCH, true, true>(keys, q[i]);
                             else acc = split_chain<NCH, false, true>(keys, q[i]);
                             if (full && j0 > kb) {
                                 softmax_take(acc, g.scale_log2, m[i], l[i], softmax_sum(acc, g.scale_log2, m[i], l[i]));
@@ -807,8 +821,8 @@ __global__ __launch_bounds__(kScoreThreads, (kColWaves<T, NCH, RBW>)) void col_s
     __shared__ MergeShared red;
     constexpr int N = kOperands<T, NCH>;
     constexpr bool kSplit = std::is_same<T, split_t>::value;
-    __shared__ int not_finite[2];                       // see pass 1
-    if (kSplit && threadIdx.x < 2) not_finite[threadIdx.x] = -1;
+    __shared__ int unfit[2];                       // see pass 1
+    if (kSplit && threadIdx.x < 2) unfit[threadIdx.x] = -1;
     __shared__ __align__(16) float own_norm[kScoreThreads];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), h = lane >> 5;
     const int kvh = blockIdx.y / g.rs, split = blockIdx.y % g.rs;
@@ -849,16 +863,16 @@ __global__ __launch_bounds__(kScoreThreads, (kColWaves<T, NCH, RBW>)) void col_s
         }
     }
     uint4 q[RBW][N];
-    bool finite_rows = true;
+    bool fit_rows = true;
 #pragma unroll
-    for (int i = 0; i < RBW; ++i) finite_rows = make_operands<T, NCH>(raw[i], q[i]) && finite_rows;
-    finite_rows = !__any(!finite_rows);
+    for (int i = 0; i < RBW; ++i) fit_rows = make_operands<T, NCH>(raw[i], q[i]) && fit_rows;
+    fit_rows = !__any(!fit_rows);
     auto store_stage = [&](int s) {
         uint4* kbuf = lds + (s & 1) * Stage::kSlots;
-        if constexpr (kSplit) { if (!Stage::store_split(kv, kbuf)) not_finite[s & 1] = s; }
+        if constexpr (kSplit) { if (!Stage::store_split(kv, kbuf)) unfit[s & 1] = s; }
         else Stage::store(kv, kbuf);
     };
-    if (kSplit && !pstat) lds_barrier();        // not_finite is ready
+    if (kSplit && !pstat) lds_barrier();        // unfit is ready
     store_stage(0);
     __builtin_amdgcn_s_waitcnt(0);      // queries and normalisers have landed: see row_stats_kernel
     __syncthreads();
@@ -874,8 +888,8 @@ __global__ __launch_bounds__(kScoreThreads, (kColWaves<T, NCH, RBW>)) void col_s
                 if (has_rows) {
                     const uint4* keys = kbuf + sub * N * 64 + lane;
                     uint4 kf[kSplit ? 1 : N];
-                    bool finite = true;
-                    if constexpr (kSplit) finite = finite_rows && not_finite[s & 1] != s;
+                    bool fit = true;
+                    if constexpr (kSplit) fit = fit_rows && unfit[s & 1] != s;
                     else {
 #pragma unroll
                         for (int c = 0; c < N; ++c) kf[c] = keys[c * 64];
@@ -885,7 +899,7 @@ __global__ __launch_bounds__(kScoreThreads, (kColWaves<T, NCH, RBW>)) void col_s
                         if (i == 0 || (second_subtiles >> sub & 1)) {
                             f32x16_t acc;
                             if constexpr (!kSplit) acc = mma_chain<T, NCH>(q[i], kf);
-                            else if (finite) acc = split_chain<NCH, true, false>(keys, q[i]);
+                            else if (fit) acc = split_chain<NCH, true, false>(keys, q[i]);
                             else acc = split_chain<NCH, false, false>(keys, q[i]);
 #pragma unroll
                             for (int e = 0; e < 16; ++e) colsum += fast_exp2(fmaf(acc[e], g.scale_log2, -cr[i][e]));
@@ -2006,10 +2020,11 @@ static void launch_narrow_scores(const void* q, const void* k, const ScoreGeom& 
 }
 
 // Whether the fp32 rows of a workgroup, at most one block per wave, are multiplied as bf16 parts.  To take a row block apart is 0.5 us
-// of each pass, so it needs keys to pay: levels by graph replay, us, fp32 MFMA / parts: 14 heads on 2 x 32 queries of 64 elements, 1500 tokens (one subtile a
-// workgroup) 26.1 / 26.8, 5000 (two) 34.2 / 32.4, 24000 65.2 / 56.4; 28 on 4 x 64 of 128, 300 (one) 29.2 / 29.3, 1500 (two) 39.8 / 36.1, 24000 233 / 154,
-// 8 x 4000 292 / 183.  Workgroups of up to four row blocks have one wave with rows to a SIMD, whose steps are a chain: 12 heads on 4 x 30 of 64,
-// 5000 (24 = subtiles x pieces of a row) 30.0 / 30.9, 24000 (96) 63.1 / 60.2; 20 on 10 x 40 of 128, 1500 (32) 30.3 / 32.2, 5000 (112) 55.7 / 52.4.
+// of each pass, so it needs keys to pay.  Whole calls by graph replay, us, fp32 MFMA / parts: 14 heads on 2 x 32 queries of 64 elements, 5000 tokens
+// (two subtiles a workgroup) 39.1 / 36.4, 24000 80.2 / 69.9; 28 on 4 x 64 of 128, 1500 (two) 46.1 / 43.2.  Workgroups of up to four row blocks
+// have one wave with rows to a SIMD, whose steps are a chain: 12 heads on 4 x 30 of 64, 24000 (96 = subtiles x pieces of a row) 80.4 / 78.9; 20
+// on 10 x 40 of 128, 5000 (112) 61.0 / 56.4.  Below the lines, levels alone, by a chain that was a little shorter (one sum): 14 on 2 x 32 of 64, 1500 (one)
+// 26.1 / 26.8, 28 on 4 x 64 of 128, 300 (one) 29.2 / 29.3; 12 on 4 x 30 of 64, 5000 (24) 30.0 / 30.9, 20 on 10 x 40 of 128, 1500 (32) 30.3 / 32.2.
 static bool split_products(const ScoreGeom& g, const ScorePlan& p, int nch) {
     return blocks_of_busiest_simd(g) > 1 ? p.per1 >= 2 : p.per1 * nch >= 96;
 }

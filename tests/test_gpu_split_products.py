@@ -1,5 +1,6 @@
 """fp32 attention scores of 65 to 256 query rows per kv head on more than a few keys, whose products are taken on three bf16 parts of
-every element: against the CPU oracle, with jumps beyond the range of float, and with elements that are not finite (fp32 products)."""
+every element: against the CPU oracle, with jumps beyond the range of float, against the error of fp32 products, and with elements that are
+large or not finite (fp32 products)."""
 import numpy as np
 import pytest
 import torch
@@ -35,6 +36,57 @@ def test_against_the_oracle(dh, group, Tq, tokens, vis_start, mode):
 def test_jumps_beyond_the_range_of_float(low):
     S = 2048
     check_scores_of_jumps("f32", 64, 7, 32, S, np.arange(S) % 256 >= low, 32, None)
+
+
+def run_scores(q, k, n):
+    """Scores of the n keys before the text, and in 64 bits."""
+    hidden = torch.zeros((k.shape[1], 8), device="cuda")
+    out = mk().metok_prefill_prune(hidden, 0, n, i32(np.zeros(n)), [n // 2], q_text=synth.to_torch(q, "f32", "cuda"), k_all=synth.to_torch(k, "f32", "cuda"))
+    return out["scores"].cpu().numpy().astype(np.float64)
+
+
+# nonzero elements of a query row; ones: the lower halves of all words are ones, whose parts cut off are furthest from their products
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("nonzero,ones", [(1, False), (1, True), (2, False), (4, True), (8, False), (64, False), (64, True)])
+def test_error_is_that_of_fp32_products(dh, nonzero, ones):
+    """A key of probability 0 in every subtile is -1e5 for parts and -inf for fp32 products; all other scores are of the same numbers, with
+    logits of some ten to a hundred, so that the error of the logits is what a score is off."""
+    rng = np.random.default_rng(29 + nonzero)
+    Hkv, group, Tq, n = 4, 7, 32, 5000
+    assert takes_parts(n + Tq, n, Hkv * group, Hkv, dh, Tq)
+    q = np.full((Hkv * group, Tq, dh), 1e-30, dtype=np.float32)                  # not 0: -inf stays -inf
+    at = np.argsort(rng.random(q.shape), axis=2)[:, :, :nonzero]
+    np.put_along_axis(q, at, (100 / nonzero * rng.uniform(1, 4, at.shape)).astype(np.float32), axis=2)
+    k = (rng.uniform(1, 2, (Hkv, n + Tq, dh)) * np.sqrt(dh / 64)).astype(np.float32)
+    if ones:
+        q, k = (q.view(np.uint32) | 0xffff).view(np.float32), (k.view(np.uint32) | 0xffff).view(np.float32)
+    k[:, ::32] = -1e5
+    want = O.text_to_visual_attention(q, k, 0, n, 0)
+    bad = k.copy()
+    bad[:, ::32] = -np.inf
+    parts, products = run_scores(q, k, n), run_scores(q, bad, n)
+    seen = want > 1e-12 * want.max()
+    assert (parts[:n:32] == 0).all() and (products[:n:32] == 0).all() and seen.sum() > 500
+    rms = lambda got: float(np.sqrt(np.mean((got[seen] / want[seen] - 1) ** 2)))
+    # the products that are left out, 0.29 x 2^-24 rms, make one rounding (0.43 x 2^-24) 1.2 of it; parts that are cut off 1.5
+    assert rms(parts) <= 1.2 * rms(products)
+
+
+@pytest.mark.parametrize("big", [2.0 ** 59, 3.4e38])
+def test_large_elements(big):
+    """An element near the largest, whose nearest bf16 number is infinite, against queries that are tiny there."""
+    rng = np.random.default_rng(31)
+    Hkv, group, dh, Tq, n = 4, 7, 64, 32, 5000
+    q = rng.standard_normal((Hkv * group, Tq, dh)).astype(np.float32)
+    k = rng.standard_normal((Hkv, n + Tq, dh)).astype(np.float32)
+    q[:, :, 11] = np.float32(2.0 ** -120)
+    k[:, :, 11] = 0
+    k[1, 77, 11], k[1, 4001, 11], k[2, 3000, 11] = big, -big, big
+    assert_rel(run_scores(q, k, n), O.text_to_visual_attention(q, k, 0, n, 0), 1e-5, "scores")
+    big_q = q.copy()
+    big_q[3, 5, 11], big_q[8, 6, 11] = big, -big                        # against keys that are 0 there
+    k[:, :, 11] = 0
+    assert_rel(run_scores(big_q, k, n), O.text_to_visual_attention(big_q, k, 0, n, 0), 1e-5, "scores")
 
 
 def test_elements_that_are_not_finite():
