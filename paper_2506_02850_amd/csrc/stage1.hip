@@ -15,6 +15,7 @@
 // In the one-pass call a batch of videos of one shape runs as one launch of every kernel: blockIdx.z is the
 // video, every pointer advances by that video's stride.
 #include "common.h"
+#include "stage1_plan.h"
 
 namespace metok {
 
@@ -971,8 +972,6 @@ static void launch_plan(const PlanArgs1& plan, const float* frame_score, const i
 // 128 frames of 24 x 24 x 1024 36 -> 31.6 -> 26.6 us.  Four items of a thread in flight for strides 1 and 2, or eight cells
 // of a row in windows without code of their own, were 5 to 15 % slower.
 // ---------------------------------------------------------------------------------------------
-constexpr int kPoolThreads = 256;
-
 template <typename TO> struct Store;
 template <> struct Store<float> {
     // 4 or 8 fp32 values -> 16 or 32 bytes
@@ -1497,31 +1496,6 @@ extern "C" int metok_segment_events(const void* feats, int dtype, int T, int N, 
     return check_launch("segment");
 }
 
-// Pooled rows when every frame takes the smaller of the two strides (s / alpha >= s, so no frame yields more).
-static int64_t worst_case_rows(int T, int grid_h, int grid_w, int s1, int s2, int pool_edge) {
-    const int gmax = grid_h > grid_w ? grid_h : grid_w;
-    int s_min = s1 < s2 ? s1 : s2;
-    s_min = s_min < 1 ? 1 : (s_min > gmax ? gmax : s_min);
-    auto side = [&](int g) { return pool_edge == METOK_POOL_FLOOR ? (g / s_min > 1 ? g / s_min : 1) : (g + s_min - 1) / s_min; };
-    return static_cast<int64_t>(T) * side(grid_h) * side(grid_w);
-}
-
-// Workgroups of the pooling pass per frame: at most 47, or 35 where frames may stay as they are (stride 1; 4 x 116 frames of 24 x 16 x 1024 at strides 1 and 2, 47
-// workgroups 165 us, 35 159) and in fp32 (27 frames of 22 x 26 x 872 39.1, 38.6; 64 and more are up to a quarter slower), fewer if
-// a frame at its smallest stride does not hold a chunk for each of their threads (782 frames of 24 x 24 x 136: 55 -> 26 us, 2400 of 8 x 8 x 256: 110 -> 18 us).
-// No multiple of 4: consecutive workgroups go to the chip's eight dies in turn, and in a frame of a larger stride only the first ones have
-// work; with a multiple of 8 (of 4) those of every frame meet on the same (two sets of) dies: 64 frames of 16 x 16 x 1024, whole calls, 32 workgroups 28.8 us, 33 24.6; 200
-// of 16 x 16 x 768 24 46.2, 25 41; 16 of 24 x 24 x 1024 36 22.8, 47 20.2; 8 x 64 of 27 x 27 x 1152 36 305, 47 296; 32 of 27 x 27 x 1152 33.0 and
-// 32.2; 8 x 106 of 16 x 16 x 1152 36 215, 37 206.
-// Fewer than 16 frames have nothing to spread: 4 of 16 x 16 x 768 24 15.6, 25 16.5; 6 of 24 x 24 x 768 at strides 1 and 2 36 21.9, 35 23.1.
-static unsigned pool_workgroups(int T, int grid_h, int grid_w, int d, int dtype, int s1, int s2, int pool_edge) {
-    const int64_t most = T < 16 ? 36 : (s1 > 1 && s2 > 1 && dtype == METOK_BF16 ? 47 : 35);
-    const int64_t items = worst_case_rows(T, grid_h, grid_w, s1, s2, pool_edge) / T * (d / (dtype == METOK_BF16 ? 8 : 4));
-    const int64_t n = (items + kPoolThreads - 1) / kPoolThreads;
-    if (n >= most) return static_cast<unsigned>(most);
-    return static_cast<unsigned>(n < 1 ? 1 : (T >= 16 && n % 4 == 0 ? n + 1 : n));
-}
-
 extern "C" int64_t metok_compress_encoder_tokens_capacity_rows(int T, int grid_h, int grid_w, int s1, int s2, int pool_edge) {
     if (T < 1 || T > METOK_MAX_FRAMES || grid_h < 1 || grid_w < 1 || static_cast<int64_t>(grid_h) * grid_w > (1 << 24) || s1 < 1 || s2 < 1 ||
         (pool_edge != METOK_POOL_FLOOR && pool_edge != METOK_POOL_CEIL))
@@ -1610,7 +1584,7 @@ extern "C" int metok_compress_encoder_tokens(const void* feats, int dtype, int T
     { TraceScope trace_scope(METOK_TRACE_PLAN, st); launch_plan(plan, scores, event_start, T, k, st); }
     if ((rc = check_launch("plan"))) return rc;
 
-    dim3 grid(pool_workgroups(T, grid_h, grid_w, d, dtype, s1, s2, pool_edge), T);
+    dim3 grid(pool_workgroups(grid_h, grid_w, d, dtype, s1, s2, pool_edge), T);
 #define METOK_POOL_CASE(TI, TO) \
     { TraceScope trace_scope(METOK_TRACE_POOL, st); \
       hipLaunchKernelGGL((pool_kernel<TI, TO>), grid, dim3(kPoolThreads), 0, st, static_cast<const TI*>(feats), grid_h, grid_w, d, \
@@ -1780,7 +1754,7 @@ static int segment_compress_impl(int batch, const void* feats, int dtype, int T,
         if ((rc = check_launch("frame_stats"))) return rc;
         launch_segment_plan(sa, plan, nb, st);
         if ((rc = check_launch("segment and plan"))) return rc;
-        dim3 grid(pool_workgroups(T, grid_h, grid_w, d, dtype, s1, s2, pool_edge), T, nb);
+        dim3 grid(pool_workgroups(grid_h, grid_w, d, dtype, s1, s2, pool_edge), T, nb);
 #define METOK_POOL_CASE(TI, TO) \
         { TraceScope trace_scope(METOK_TRACE_POOL, st); \
           hipLaunchKernelGGL((pool_kernel<TI, TO>), grid, dim3(kPoolThreads), 0, st, static_cast<const TI*>(feats), grid_h, grid_w, d, \

@@ -1,12 +1,9 @@
 """The library's plan of the score passes (csrc/score_plan.h), built for the host: what a call's rows, keys and workspace are cut into."""
 import ctypes
-import functools
-import os
-import subprocess
-import tempfile
 from collections import namedtuple
 
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+from tests.host_plan import host_library
+
 SOURCE = r"""
 #include <initializer_list>
 #include "score_plan.h"
@@ -34,20 +31,9 @@ Plan = namedtuple("Plan", "rs rbw nx1 per1 nx2 per2 qfrag pstat norm colpart sel
 Plans = namedtuple("Plans", "plan whole rb_total general_bytes fast_bytes inplace_bytes split")
 
 
-@functools.lru_cache(None)
-def _lib():
-    with tempfile.TemporaryDirectory() as tmp:
-        src, so = os.path.join(tmp, "plan.cpp"), os.path.join(tmp, "plan.so")
-        with open(src, "w") as f:
-            f.write(SOURCE)
-        subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-shared", "-fPIC", "-I" + os.path.join(ROOT, "include"),
-                        "-I" + os.path.join(ROOT, "paper_2506_02850_amd", "csrc"), src, "-o", so], check=True)
-        return ctypes.CDLL(so)
-
-
 def score_plans(S, n_vis, Hq, Hkv, dh, Tq, dtype="bf16", batch=1, vis_start=0, mode=0):
     out = (ctypes.c_int64 * 32)()
     i, q = ctypes.c_int, ctypes.c_int64
-    assert _lib().plans(i(batch), q(S), i(Hq), i(Hkv), i(dh), i(Tq), i(vis_start), i(n_vis), i(1 if dtype == "bf16" else 0), i(mode), out) == 0
+    assert host_library(SOURCE).plans(i(batch), q(S), i(Hq), i(Hkv), i(dh), i(Tq), i(vis_start), i(n_vis), i(1 if dtype == "bf16" else 0), i(mode), out) == 0
     plan, whole = Plan(*out[:14]), Plan(*out[14:28])
     return Plans(plan, whole, *out[28:32], plan.rs != whole.rs)
