@@ -481,7 +481,10 @@ METOK_API int metok_debug_set_move_spin_limit(int polls);
  * ev_begin and ev_end (hipEvent_t passed as void*, created by the caller with timing enabled) on the
  * stream of the call, so hipEventElapsedTime(ev_begin, ev_end) after the call is the duration of that
  * kernel alone, without the small planning kernels around it.  If a call launches the kernel more than
- * once the events bracket the last launch.  kernel == METOK_TRACE_NONE (or NULL events) disarms.  Do not
+ * once the events bracket the last launch.  Names that share a launch each bracket the whole of it: besides those noted below,
+ * metok_segment_compress and its batched form do all of stage 1 of a small video (at most 32 frames, 512 tokens and 128 KB) in
+ * one launch, which FRAME_STATS, SEGMENT, PLAN and POOL (FRAME_STATS_POOL2, SEGMENT and PLAN where every stride is 2) bracket, so
+ * that their times must not be added up there.  kernel == METOK_TRACE_NONE (or NULL events) disarms.  Do not
  * arm while a stream is being captured into a graph.
  * ------------------------------------------------------------------------------------------- */
 enum {

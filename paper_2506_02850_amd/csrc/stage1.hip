@@ -1659,10 +1659,11 @@ static bool small_video(int T, int N, int d, int dtype, int64_t worst_rows, bool
     return one_pass ? stats <= 1 && pool <= 1 : stats <= 4 && pool <= 2;
 }
 static int launch_small_video(const SegmentArgs& sa, const PlanArgs1& plan, const void* feats, int dtype, const void* text, int grid_h, int grid_w, int d,
-                              int pool_edge, int64_t capacity_rows, void* out, int out_dtype, int32_t* token_event, unsigned nb, hipStream_t st) {
-    // one launch does everything: the trace hook brackets it for any name
-    TraceScope trace_stats(METOK_TRACE_FRAME_STATS, st), trace_segment(METOK_TRACE_SEGMENT, st), trace_plan(METOK_TRACE_PLAN, st), trace_pool(METOK_TRACE_POOL, st),
-               trace_pool2(METOK_TRACE_FRAME_STATS_POOL2, st);
+                              int pool_edge, int64_t capacity_rows, void* out, int out_dtype, int32_t* token_event, bool one_pass, unsigned nb,
+                              hipStream_t st) {
+    // one launch does everything: the trace hook brackets it for the name of any kernel that a larger video's call would launch
+    TraceScope trace_stats(one_pass ? METOK_TRACE_FRAME_STATS_POOL2 : METOK_TRACE_FRAME_STATS, st), trace_segment(METOK_TRACE_SEGMENT, st),
+               trace_plan(METOK_TRACE_PLAN, st), trace_pool(one_pass ? METOK_TRACE_NONE : METOK_TRACE_POOL, st);
 #define METOK_SMALL_CASE(TI, TO) \
     hipLaunchKernelGGL((small_video_kernel<TI, TO>), dim3(1, 1, nb), dim3(kSegThreads), 0, st, sa, plan, static_cast<const TI*>(feats), \
                        static_cast<const TI*>(text), grid_h, grid_w, d, pool_edge, capacity_rows, static_cast<TO*>(out), token_event);
@@ -1746,7 +1747,7 @@ static int segment_compress_impl(int batch, const void* feats, int dtype, int T,
                           0, nullptr, 0, ws_video};
         plan.set_strides({clamp_stride(s1), clamp_stride(s2), clamp_stride(s1 / alpha), clamp_stride(s2 / alpha)}, grid_h, grid_w, pool_edge);
         if (small_video(T, N, d, dtype, worst, false))
-            return launch_small_video(sa, plan, feats, dtype, text_emb, grid_h, grid_w, d, pool_edge, out_capacity_rows, out_tokens, out_dtype, token_event, nb, st);
+            return launch_small_video(sa, plan, feats, dtype, text_emb, grid_h, grid_w, d, pool_edge, out_capacity_rows, out_tokens, out_dtype, token_event, false, nb, st);
         const bool keep = keep_in_cache(batch, T, N, d, dtype);
         const bool ok = dtype == METOK_BF16 ? dispatch_stats<bf16_t>(feats, text_emb, T, N, d, p, 1, sim_mode, part, st, batch, ws_video, keep)
                                             : dispatch_stats<float>(feats, text_emb, T, N, d, p, 1, sim_mode, part, st, batch, ws_video, keep);
@@ -1828,7 +1829,7 @@ static int segment_compress_impl(int batch, const void* feats, int dtype, int T,
                             frame_offsets, frame_event_ws, nullptr, fill_here ? n_win : 0, token_event, out_capacity_rows, ws_video};
     plan.set_strides({2, 2, 2, 2}, grid_h, grid_w, pool_edge);
     if (small_video(T, N, d, dtype, rows, true))
-        return launch_small_video(sa, plan, feats, dtype, text_emb, grid_h, grid_w, d, pool_edge, out_capacity_rows, out_tokens, out_dtype, token_event, nb, st);
+        return launch_small_video(sa, plan, feats, dtype, text_emb, grid_h, grid_w, d, pool_edge, out_capacity_rows, out_tokens, out_dtype, token_event, true, nb, st);
     const int C = (n_win + kStatsWaves - 1) / kStatsWaves;          // workgroups per run of frames
     int runs = (2048 + C * kStatsWaves - 1) / (C * kStatsWaves);
     int fpr = (T + runs - 1) / runs;

@@ -65,3 +65,28 @@ def test_small_with_a_frame_that_is_not_finite(value):
     M = int(one["frame_offsets"][-1])
     assert torch.equal(one["out_tokens"][:M].isnan(), two["out_tokens"][:M].isnan())
     assert torch.equal(one["out_tokens"][:M].nan_to_num(), two["out_tokens"][:M].nan_to_num())
+
+
+@pytest.mark.parametrize("side", [4, 16])                                # one launch, and a kernel for every name
+@pytest.mark.parametrize("uniform,names", [(False, {"FRAME_STATS", "POOL", "SEGMENT", "PLAN"}), (True, {"FRAME_STATS_POOL2", "SEGMENT", "PLAN"})])
+def test_names_that_the_trace_hook_brackets(side, uniform, names):
+    B = mk()
+    ids = {"FRAME_STATS": 1, "POOL": 2, "FRAME_STATS_POOL2": 3, "SEGMENT": 4, "PLAN": 5, "ROW_STATS": 6}
+    feats, text = torch.randn((8, side * side, 64), device="cuda"), torch.randn((64,), device="cuda")
+    args = (feats, side, side, 3, text) + ((1.0, 1.0, 2, 2) if uniform else (0.5, 0.4, 2, 3))
+    B.metok_segment_compress(*args)
+    bracketed = set()
+    for name, kernel in ids.items():
+        begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        end.record()
+        torch.zeros((1,), device="cuda")
+        begin.record()                                                  # after `end` until the call records both
+        assert B.lib().metok_trace_kernel(kernel, begin.cuda_event, end.cuda_event) == 0
+        try:
+            B.metok_segment_compress(*args)
+        finally:
+            B.lib().metok_trace_kernel(0, None, None)
+        torch.cuda.synchronize()
+        if begin.elapsed_time(end) > 0:
+            bracketed.add(name)
+    assert bracketed == names
