@@ -7,6 +7,7 @@
 #include <stdio.h>
 #include <type_traits>
 
+#include "device_once.h"
 #include "metok.h"
 
 namespace metok {
@@ -37,6 +38,19 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 inline size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 inline size_t dtype_size(int dtype) { return dtype == METOK_BF16 ? 2 : 4; }
 int ceil_ratio(double x);                   // ceil(x - 1e-9)
+
+// Lets a kernel have `bytes` of dynamic LDS (the same for each of its launches): beyond 64 KB by an attribute of the current device's copy of it.
+template <auto KERNEL>
+bool allow_lds(size_t bytes) {
+    if (bytes <= 64 * 1024) return true;
+    static std::atomic<uint64_t> allowed{0};
+    int device = 0;
+    const bool ok = hipGetDevice(&device) == hipSuccess && once_per_device(allowed, device, [&] {
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(KERNEL), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(bytes)) == hipSuccess;
+    });
+    if (!ok) (void)hipGetLastError();       // the caller takes another kernel or reports the failure itself
+    return ok;
+}
 
 constexpr int kWave = 64;
 

@@ -2029,20 +2029,6 @@ static bool split_products(const ScoreGeom& g, const ScorePlan& p, int nch) {
     return blocks_of_busiest_simd(g) > 1 ? p.per1 >= 2 : p.per1 * nch >= 96;
 }
 
-// Lets a kernel have more than 64 KB of LDS: an attribute of the current device's copy of it, set once.
-template <auto KERNEL>
-static bool allow_lds(size_t bytes) {
-    if (bytes <= 64 * 1024) return true;
-    static bool allowed[64] = {false};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return false;
-    if (!allowed[dev]) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(KERNEL), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(bytes)) != hipSuccess) return false;
-        allowed[dev] = true;
-    }
-    return true;
-}
-
 // Both passes with a workgroup's rows in the waves' RBW blocks each.  false: nothing was launched.
 template <typename T, int NCH, int RBW, int SUBS>
 static bool launch_staged_scores(const void* q, const void* k, const ScoreGeom& g, const ScorePlan& p, char* ws, int batch, hipStream_t st) {
