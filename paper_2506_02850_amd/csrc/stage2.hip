@@ -2033,8 +2033,9 @@ static bool split_products(const ScoreGeom& g, const ScorePlan& p, int nch) {
 template <typename T, int NCH, int RBW, int SUBS>
 static bool launch_staged_scores(const void* q, const void* k, const ScoreGeom& g, const ScorePlan& p, char* ws, int batch, hipStream_t st) {
     using Stage = KeyStage<T, NCH, SUBS>;
-    const size_t lds1 = std::max(kStageBuffers * static_cast<size_t>(Stage::kSlots) * sizeof(uint4), QueryRows<T, NCH, 1>::kLdsBytes);
-    const size_t lds2 = 2 * static_cast<size_t>(Stage::kSlots) * sizeof(uint4) + 2 * static_cast<size_t>(kScoreWaves) * Stage::kKeys * sizeof(float);
+    constexpr size_t lds1 = std::max(kStageBuffers * static_cast<size_t>(Stage::kSlots) * sizeof(uint4), QueryRows<T, NCH, 1>::kLdsBytes);
+    constexpr size_t lds2 = 2 * static_cast<size_t>(Stage::kSlots) * sizeof(uint4) + 2 * static_cast<size_t>(kScoreWaves) * Stage::kKeys * sizeof(float);
+    static_assert(std::is_same<T, split_t>::value || std::max(lds1, lds2) <= 64 * 1024, "only the parts' kernels, which fp32 MFMA can stand in for, may not be had");
     if (!allow_lds<&row_stats_kernel<T, NCH, RBW, SUBS>>(lds1) || !allow_lds<&col_sums_kernel<T, NCH, RBW, SUBS>>(lds2)) return false;
     const int ny = g.Hkv * g.rs;
     uint32_t* clear = reinterpret_cast<uint32_t*>(ws + p.off_sel + select_general_bytes(g.n_vis));
