@@ -201,16 +201,10 @@ __global__ __launch_bounds__(kStatsThreads) void frame_stats_kernel(
 // All of it is latency: segment_short_kernel does the same for videos of at most kShortFrames frames with every comparison
 // of a ranking spread over the workgroup, see there.
 // ---------------------------------------------------------------------------------------------
-constexpr int kSegThreads = 1024;
 constexpr int kMaxReduceWgs = 64;
 // Up to here segment_short_kernel, with at least two threads per frame.  512 frames of 2 x 2 x 64, us, segment_kernel / segment_short_kernel:
 // 1 event 56.2 / 40.1, 5 46.7 / 31.9, 64 33.4 / 24.0, 256 37.1 / 25.1, 512 43.9 / 30.1; 384 frames, 1 event 44.7 / 31.1, 384 35.3 / 24.0.
 constexpr int kShortFrames = 512;
-// Up to here one workgroup adds up the partials too, two frames per wave, and nothing is handed over; but not where the frames
-// beyond one per wave bring more than kOneReducePartials partial sums, which a second workgroup would read in the meantime.  Whole
-// calls of T frames x C partials, us, one workgroup / several: 32 x 256 17.8 / 18.3 and 16.1 / 16.7, 32 x 576 22.4 / 21.6 and 29.3 / 28.3,
-// 32 x 4096 67.3 / 60.4; 24 x 1024 25.0 / 25.3, 24 x 1600 30.5 / 30.0; 17 x 4096 43.0 / 43.1.
-constexpr int kOneReduceFrames = 32, kOneReducePartials = 8192;
 constexpr int kRankLoopFrames = 2048;      // up to here every thread ranks its frames against all others
 constexpr int kFillRowsInPlan = 65536;     // up to so many uniformly pooled rows the planning workgroup writes their event ids
 
@@ -1089,10 +1083,6 @@ __global__ __launch_bounds__(kPoolThreads) void pool_kernel(
 // per-token sums meet in LDS and are added per frame; segmentation and plan are segment_short_kernel's; the pooling reads the
 // features a second time, from the caches.
 // ---------------------------------------------------------------------------------------------
-constexpr int kSmallRun = 4;                        // frames of a token that sixteen lanes take together
-constexpr int kSmallTokens = 512;                   // of all frames of the video
-constexpr int64_t kSmallBytes = 128 * 1024;
-
 template <typename TI, typename TO>
 __global__ __launch_bounds__(kSegThreads) void small_video_kernel(
     const SegmentArgs a, const PlanArgs1 plan, const TI* __restrict__ feats, const TI* __restrict__ text, int grid_h, int grid_w, int d, int pool_edge,
@@ -1639,18 +1629,6 @@ static bool launch_stats_pool2(const void* feats, const void* text, int Tf, int 
     return false;
 }
 
-// Whether small_video_kernel takes the call: the rounds of loads that its statistics and its pooling take one after the other, and
-// what it reads at one compute unit's rate.  Whole calls by graph replay, us, three launches / this one: 8 frames of 4 x 4 x 64 fp32
-// (32 KB) 12.7 / 8.3, 4 of 5 x 5 x 64 12.9 / 8.4, 4 of 4 x 4 x 1024 (128 KB) 13.8 / 10.8, 8 of 8 x 8 x 128 (128 KB) 14.3 / 12.7, 32 of 4 x 4 x 128
-// (128 KB) 15.0 / 13.5; beyond the lines, 2 of 16 x 16 x 64 (4 rounds of the statistics with half the frames missing) 11.7 / 14.3, 4 of
-// 2 x 2 x 4096 (16 rounds) 13.6 / 15.6, 32 of 4 x 4 x 128 at stride 1 (8 rounds of the pooling) 14.7 / 19.8.  Where the one-pass kernel
-// makes it two launches: 8 of 4 x 4 x 64 fp32 10.1 / 7.9, 32 of 4 x 4 x 128 12.1 / 14.4.
-static bool small_video(int T, int N, int d, int dtype, int64_t worst_rows, bool one_pass) {
-    const int64_t chunks = d / (dtype == METOK_BF16 ? 8 : 4), units = static_cast<int64_t>((T + kSmallRun - 1) / kSmallRun) * N;
-    if (T > kOneReduceFrames || units * kSmallRun > kSmallTokens || T * N * chunks * 16 > kSmallBytes) return false;
-    const int64_t stats = (units + kSegThreads / 16 - 1) / (kSegThreads / 16) * ((chunks + 31) / 32), pool = (worst_rows * chunks + kSegThreads - 1) / kSegThreads;
-    return one_pass ? stats <= 1 && pool <= 1 : stats <= 4 && pool <= 2;
-}
 static int launch_small_video(const SegmentArgs& sa, const PlanArgs1& plan, const void* feats, int dtype, const void* text, int grid_h, int grid_w, int d,
                               int pool_edge, int64_t capacity_rows, void* out, int out_dtype, int32_t* token_event, bool one_pass, unsigned nb,
                               hipStream_t st) {
