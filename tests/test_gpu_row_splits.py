@@ -17,8 +17,8 @@ KV_HEADS = 32                                                         # share th
 
 
 # Blocks of 32 rows: 9 (5 + 4), 14 (7 + 7), 16 (8 + 8), and 17 (two whole workgroups of 9 and 8, split 6 + 6 + 5, the last block partly
-# empty).  LINE: the last length of the split side, five 32-key subtiles a workgroup (so few partial statistics that pass 2 merges
-# them: with more of them the line lies at eight).
+# empty).  LINE: the last length of the split side, five 32-key subtiles a workgroup (with more than 64 KB of partial statistics
+# the line lies at eight).
 @pytest.mark.parametrize("dtype,dh,group,Tq,line", [("bf16", 64, 9, 32, 1280), ("bf16", 128, 7, 64, 1280), ("f32", 32, 16, 32, 1280), ("bf16", 32, 13, 40, 640)])
 @pytest.mark.parametrize("place,mode", [("short", 0), ("last", 0), ("past", 0), ("last", 1)])
 def test_scores_around_the_row_split(dtype, dh, group, Tq, line, place, mode):
@@ -88,7 +88,7 @@ def test_batch_around_the_row_split(keys):
 
 @pytest.mark.parametrize("keys", [8192, 8193])                        # 8 kv heads, 32 workgroups of eight subtiles along the keys
 def test_scores_around_the_row_split_with_many_partials(keys):
-    # 14 blocks x 32 partials are more than pass 2 merges for itself
+    # 14 blocks x 32 partials, 112 KB: beyond 64 KB rows are split up to eight subtiles a workgroup instead of five
     Tq, Hkv = 32, 8
     plans = score_plans(keys, keys - Tq, 14 * Hkv, Hkv, 64, Tq)
     assert plans.split == (keys == 8192) and plans.whole.partials > 65536
