@@ -91,26 +91,48 @@ def test_large_elements(big):
 
 def test_elements_that_are_not_finite():
     """A NaN (whose only mantissa bit is the last one) spoils its key and its kv head's rows; -inf in a key, against positive queries, is
-    probability 0; an infinite query spoils its row alone."""
-    B = mk()
+    probability 0."""
     rng = np.random.default_rng(17)
     Hkv, group, dh, Tq, n = 4, 7, 64, 32, 5000
     S = n + Tq
     assert takes_parts(S, n, Hkv * group, Hkv, dh, Tq)
     q = np.abs(rng.standard_normal((Hkv * group, Tq, dh))).astype(np.float32) + np.float32(0.1)
     k = (0.2 * rng.standard_normal((Hkv, S, dh))).astype(np.float32)
-    bad, bad_q = k.copy(), q.copy()
+    bad = k.copy()
     bad[1, 50, 3] = np.array([0x7f800001], dtype=np.uint32).view(np.float32)[0]
     bad[2, 70, 5] = bad[2, 4000, 60] = -np.inf
-    bad_q[0, 9, 2] = np.inf                                            # logits of +-inf: the row is NaN and adds nothing to finite rows
-    hidden = torch.zeros((S, 8), device="cuda")
-    run = lambda queries, keys: B.metok_prefill_prune(hidden, 0, n, i32(np.zeros(n)), [n // 2], q_text=synth.to_torch(queries, "f32", "cuda"),
-                                                      k_all=synth.to_torch(keys, "f32", "cuda"))["scores"].cpu().numpy()
-    scores = run(q, bad)
+    scores = run_scores(q, bad, n)
     fixed = k.copy()
     fixed[2, 70] = fixed[2, 4000] = np.float32(-1e5)
     want = sum(O.text_to_visual_attention(q[h * group:(h + 1) * group], fixed[h:h + 1], 0, n, 0) for h in (0, 2, 3)) / Hkv
     others = np.arange(n) != 50
     assert np.isnan(scores[50])
     assert_rel(scores[others], want[others], 1e-5, "scores")
-    assert not np.isfinite(run(bad_q, k)).all()
+
+
+@pytest.mark.parametrize("dh,value", [(64, np.inf), (64, -np.inf), (128, np.inf)])
+def test_an_infinite_query_element(dh, value):
+    """The logits of its row are infinite with the sign of the key's element: keys of +inf have an infinite score, for the others the
+    row adds nothing."""
+    rng = np.random.default_rng(19)
+    Hkv, group, Tq, n = 4, 7, 32, 5000
+    Hq, S = Hkv * group, n + Tq
+    assert takes_parts(S, n, Hq, Hkv, dh, Tq)
+    q, k = rng.standard_normal((Hq, Tq, dh)).astype(np.float32), rng.standard_normal((Hkv, S, dh)).astype(np.float32)
+    want = O.text_to_visual_attention(q, k, 0, n, 0) - O.text_to_visual_attention(q[:1, 9:10], k[:1, :n + 10], 0, n, 0) / (Hq * Tq)
+    q[0, 9, 2] = value
+    got = run_scores(q, k, n)
+    up = k[0, :n, 2] * np.sign(value) > 0
+    assert (got[up] == np.inf).all()
+    assert_rel(got[~up], want[~up], 1e-5, "scores")
+
+
+def test_a_query_element_that_is_no_number():
+    """A NaN whose only mantissa bit is the last one, which a bf16 number does not have, in a query: its row is NaN for every key."""
+    rng = np.random.default_rng(23)
+    Hkv, group, dh, Tq, n = 4, 7, 64, 32, 5000
+    assert takes_parts(n + Tq, n, Hkv * group, Hkv, dh, Tq)
+    q, k = rng.standard_normal((Hkv * group, Tq, dh)).astype(np.float32), rng.standard_normal((Hkv, n + Tq, dh)).astype(np.float32)
+    assert np.isfinite(run_scores(q, k, n)).all()
+    q[3, 30, 63] = np.array([0x7f800001], dtype=np.uint32).view(np.float32)[0]
+    assert np.isnan(run_scores(q, k, n)).all()
