@@ -7,8 +7,8 @@
 
 namespace metok {
 
-// Calls `act` unless an earlier call for this device has succeeded; several threads may call at once, and `act` may then run in each of them.  false: no
-// such device, or `act` failed, which the next call tries again.
+// Calls `act` unless an earlier call for this device has succeeded; several threads may call at once, and `act` may then run in each of
+// them.  false: no such device, or `act` failed, which the next call tries again.
 template <typename Act>
 bool once_per_device(std::atomic<uint64_t>& done, int device, Act act) {
     if (device < 0 || device >= 64) return false;

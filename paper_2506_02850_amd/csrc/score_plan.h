@@ -126,11 +126,11 @@ inline void plan_grid(const ScoreGeom& g, int n_vis, int nch, int batch, size_t 
     p->total = round_up_256(off);
 }
 
-// Up to here every workgroup of pass 2 merges the partial statistics of its rows for itself, above a kernel in between does it
-// once.  Levels, kernels alone, us, by the kernel / merged in pass 2: 28 heads on 4 x 30 queries, 224 rows x 53 to 61 partials (95 to 109 KB), 5000 tokens 28.8 /
-// 27.3, 36864 64.1 / 62.5; 14 on 2 x 32 of 64 elements, 224 x 79 to 116 (138 to 203 KB), 5000 in fp32 31.6 / 30.4, 18432 36.7 / 35.4; 28 on 4 x 64, 448 x 58
-// (203 KB), 18432 54.7 / 53.4; 8 on 2 x 64 of 256, 256 x 128 (256 KB), 36864 64.4 / 62.3; beyond the line, 14 on 2 x 64 of 64, 448 x 116 (406 KB), 36864
-// 56.5 / 57.6, in fp32 123.2 / 125.4.
+// Up to here every workgroup of pass 2 merges the partial statistics of its rows for itself, above a kernel in between does it once.
+// Levels, kernels alone, us, by the kernel / merged in pass 2: 28 heads on 4 x 30 queries, 224 rows x 53 to 61 partials (95 to 109 KB),
+// 5000 tokens 28.8 / 27.3, 36864 64.1 / 62.5; 14 on 2 x 32 of 64 elements, 224 x 79 to 116 (138 to 203 KB), 5000 in fp32 31.6 / 30.4,
+// 18432 36.7 / 35.4; 28 on 4 x 64, 448 x 58 (203 KB), 18432 54.7 / 53.4; 8 on 2 x 64 of 256, 256 x 128 (256 KB), 36864 64.4 / 62.3;
+// beyond the line, 14 on 2 x 64 of 64, 448 x 116 (406 KB), 36864 56.5 / 57.6, in fp32 123.2 / 125.4.
 constexpr size_t kMergeInPass2Bytes = 256 * 1024;
 inline size_t partial_bytes(const ScoreGeom& g, const ScorePlan& p) { return static_cast<size_t>(p.nx1) * g.rbw * 32 * 2 * sizeof(float); }
 
@@ -145,7 +145,7 @@ inline size_t partial_bytes(const ScoreGeom& g, const ScorePlan& p) { return sta
 // and two split, and half as many workgroups along the keys may be fewer than half.  What the split adds to the busiest SIMD, in
 // products of a row block and a subtile over both passes, must stay below what it saves.  Levels (kernels alone) with 0 to 2 products
 // more are 0.87 to 0.97 of the whole rows' time in every type; in bf16 those with 10 more are 0.96 to 0.99, with 12 0.94 to 1.05, with 16
-// 1.02 to 1.07; in fp32, where a product takes four times as long, those with 4 more are 0.97 to 1.04, with 10 1.09 to 1.16, with 24 1.26 to
+// 1.02 to 1.07; in fp32 (both sides with fp32 MFMA, four times as long a product; split rows are now multiplied in parts), those with 4 more are 0.97 to 1.04, with 10 1.09 to 1.16, with 24 1.26 to
 // 1.39 (40 heads x 352 queries, 2 x 400 tokens, 64 elements: 57.9 / 80.5 us).
 // A split needs more room for the column sums and none for the two words per token that select_bytes reserves for nobody; where
 // it does not fit the workspace of the whole rows, the rows stay whole.

@@ -1012,37 +1012,37 @@ template <typename TI, typename TO>
 __device__ __forceinline__ void pool_item(const uint4* __restrict__ frame, int grid_h, int grid_w, int d, int nchunks, int s, int ow, int orow, int chunk,
                                           int64_t out_row, int ev, TO* __restrict__ out, int32_t* __restrict__ token_event) {
     using E = Elem<TI>;
-            const int oy = orow / ow, ox = orow - oy * ow;
-            const int y0 = oy * s, y1 = min(y0 + s, grid_h);
-            const int x0 = ox * s, x1 = min(x0 + s, grid_w);
-            const uint4* corner = frame + (static_cast<size_t>(y0) * grid_w + x0) * nchunks + chunk;
-            float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-            if (y1 - y0 == s && x1 - x0 == s && s == 2) pool_window<E, 2>(corner, grid_w, nchunks, acc);
-            else if (y1 - y0 == s && x1 - x0 == s && s == 3) pool_window<E, 3>(corner, grid_w, nchunks, acc);
-            else if (y1 - y0 == s && x1 - x0 == s && s == 4) pool_window<E, 4>(corner, grid_w, nchunks, acc);
-            else if (y1 - y0 == s && x1 - x0 == s && s == 6) pool_window<E, 6>(corner, grid_w, nchunks, acc);
-            else {
-                for (int y = y0; y < y1; ++y, corner += static_cast<size_t>(grid_w) * nchunks) {
-                    const uint4* cell = corner;
-                    int xx = x0;
-                    for (; xx + 4 <= x1; xx += 4) {               // four independent loads in flight
-                        const uint4 a = load_stream(cell), b = load_stream(cell + nchunks),
-                                    c = load_stream(cell + 2 * static_cast<size_t>(nchunks)),
-                                    e = load_stream(cell + 3 * static_cast<size_t>(nchunks));
-                        E::accumulate(a, acc); E::accumulate(b, acc); E::accumulate(c, acc); E::accumulate(e, acc);
-                        cell += 4 * static_cast<size_t>(nchunks);
-                    }
-                    for (; xx < x1; ++xx) {
-                        E::accumulate(load_stream(cell), acc);
-                        cell += nchunks;
-                    }
-                }
+    const int oy = orow / ow, ox = orow - oy * ow;
+    const int y0 = oy * s, y1 = min(y0 + s, grid_h);
+    const int x0 = ox * s, x1 = min(x0 + s, grid_w);
+    const uint4* corner = frame + (static_cast<size_t>(y0) * grid_w + x0) * nchunks + chunk;
+    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (y1 - y0 == s && x1 - x0 == s && s == 2) pool_window<E, 2>(corner, grid_w, nchunks, acc);
+    else if (y1 - y0 == s && x1 - x0 == s && s == 3) pool_window<E, 3>(corner, grid_w, nchunks, acc);
+    else if (y1 - y0 == s && x1 - x0 == s && s == 4) pool_window<E, 4>(corner, grid_w, nchunks, acc);
+    else if (y1 - y0 == s && x1 - x0 == s && s == 6) pool_window<E, 6>(corner, grid_w, nchunks, acc);
+    else {
+        for (int y = y0; y < y1; ++y, corner += static_cast<size_t>(grid_w) * nchunks) {
+            const uint4* cell = corner;
+            int xx = x0;
+            for (; xx + 4 <= x1; xx += 4) {               // four independent loads in flight
+                const uint4 a = load_stream(cell), b = load_stream(cell + nchunks),
+                            c = load_stream(cell + 2 * static_cast<size_t>(nchunks)),
+                            e = load_stream(cell + 3 * static_cast<size_t>(nchunks));
+                E::accumulate(a, acc); E::accumulate(b, acc); E::accumulate(c, acc); E::accumulate(e, acc);
+                cell += 4 * static_cast<size_t>(nchunks);
             }
-            const float cnt = static_cast<float>((y1 - y0) * (x1 - x0));
-    #pragma unroll
-            for (int i = 0; i < 8; ++i) acc[i] = acc[i] / cnt;
-            Store<TO>::put(out + out_row * d, chunk, E::kVec, acc);
-            if (chunk == 0) token_event[out_row] = ev;
+            for (; xx < x1; ++xx) {
+                E::accumulate(load_stream(cell), acc);
+                cell += nchunks;
+            }
+        }
+    }
+    const float cnt = static_cast<float>((y1 - y0) * (x1 - x0));
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[i] = acc[i] / cnt;
+    Store<TO>::put(out + out_row * d, chunk, E::kVec, acc);
+    if (chunk == 0) token_event[out_row] = ev;
 }
 
 template <typename TI, typename TO>
@@ -1078,10 +1078,10 @@ __global__ __launch_bounds__(kPoolThreads) void pool_kernel(
 }
 
 // ---------------------------------------------------------------------------------------------
-// small_video_kernel: the whole of stage 1 of a video that one workgroup reads in a few round trips (see small_video).  Three
-// launches are 5.5 us on the device and 7.5 through a stream: 8 frames of 4 x 4 x 64 in a stream of calls 18.6 -> 13.3 us.  Sixteen lanes take a token of a frame together with the same token of the next frame; the
-// per-token sums meet in LDS and are added per frame; segmentation and plan are segment_short_kernel's; the pooling reads the
-// features a second time, from the caches.
+// small_video_kernel: the whole of stage 1 of a video that one workgroup reads in a few round trips (see small_video).  Three launches
+// are 5.5 us on the device and 7.5 through a stream: 8 frames of 4 x 4 x 64 in a stream of calls 18.6 -> 13.3 us.  Sixteen lanes take a
+// token of a frame together with the same token of the next frame; the per-token sums meet in LDS and are added per frame; segmentation
+// and plan are segment_short_kernel's; the pooling reads the features a second time, from the caches.
 // ---------------------------------------------------------------------------------------------
 template <typename TI, typename TO>
 __global__ __launch_bounds__(kSegThreads) void small_video_kernel(

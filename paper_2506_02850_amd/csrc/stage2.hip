@@ -58,15 +58,15 @@ template <> struct Mma<float> {
 };
 
 // fp32 rows multiplied as bf16.  An element is the sum of three bf16 numbers, each the nearest to what the ones before leave, without a
-// rounding (the last has at most eight bits left); of the nine products of two such numbers six are taken, each with 16 times the rate
-// of an fp32 MFMA: 192 cycles of the matrix pipe per 32 x 32 x 16 products instead of 512.  The other three, middle by last and last by
+// rounding (the last has at most eight bits left); of the nine products of two such numbers six are taken, each with 16 times the rate of
+// an fp32 MFMA: 192 cycles of the matrix pipe per 32 x 32 x 16 products instead of 512.  The other three, middle by last and last by
 // last, are together below 2^-24 of the whole (0.9 at most) and of either sign.  (Parts that are cut off all have the sign of their
 // element: the three reach 7.8 x 2^-24 and shrink every product.)
-// Root mean square error of a sum against 64 bits, in units of its size, fp32 MFMA / parts, normal elements of which n of a row are not 0:
-// n = 1 2.54e-8 / 2.61e-8, 2 3.1e-8 / 2.6e-8, 4 4.0e-8 / 2.7e-8, 8 5.3e-8 / 2.9e-8, all 64 14.3e-8 / 4.9e-8, all 128 20.2e-8 / 6.5e-8; parts cut off 6.9e-8 up
-// to n = 8, then 7.5e-8 and 8.5e-8.
-// Whole calls by graph replay, fp32 MFMA / parts: 28 heads on 4 x 64 queries of 128 elements, 8 x 4000 tokens 353 / 243 us, 24000 tokens 287 / 206;
-// see split_products for where they are taken.
+// Root mean square error of a sum against 64 bits, in units of its size, fp32 MFMA / parts, normal elements of which n of a row are not
+// 0: n = 1 2.54e-8 / 2.61e-8, 2 3.1e-8 / 2.6e-8, 4 4.0e-8 / 2.7e-8, 8 5.3e-8 / 2.9e-8, all 64 14.3e-8 / 4.9e-8, all 128 20.2e-8 / 6.5e-8;
+// parts cut off 6.9e-8 up to n = 8, then 7.5e-8 and 8.5e-8.
+// Whole calls by graph replay, fp32 MFMA / parts: 28 heads on 4 x 64 queries of 128 elements, 8 x 4000 tokens 353 / 243 us, 24000 tokens
+// 287 / 206; see split_products for where they are taken.
 struct split_t { float value; };
 template <> struct Mma<split_t> : Mma<float> {};
 
@@ -84,15 +84,15 @@ __device__ __forceinline__ void split_piece(const uint4& x, uint2 (&part)[3]) {
         if (p < 2) { e[0] -= bf16_lo(part[p].x); e[1] -= bf16_hi(part[p].x); e[2] -= bf16_lo(part[p].y); e[3] -= bf16_hi(part[p].y); }
     }
 }
-// Elements below this are multiplied in parts: no sum of 128 of their products leaves the range of float, whatever the order, and parts too
-// small for a bf16 number of full precision (below 2^-126) are less than 2^-58 of a logit together.
+// Elements below this are multiplied in parts: no sum of 128 of their products leaves the range of float, whatever the order, and parts
+// too small for a bf16 number of full precision (below 2^-126) are less than 2^-58 of a logit together.
 constexpr float kPartsBelow = 0x1p59f;
 __device__ __forceinline__ bool all_fit(const uint4& x) {
     auto fits = [](uint32_t e) { return fabsf(__uint_as_float(e)) < kPartsBelow; };           // not a NaN
     return fits(x.x) && fits(x.y) && fits(x.z) && fits(x.w);
 }
-// The same for elements of which some do not fit: parts that joined_piece puts together again (short of less than 2^-133).  The leading part of
-// the largest must not round to infinity, so they are cut off; what is not finite is its leading part alone, a NaN stays one.
+// The same for elements of which some do not fit: parts that joined_piece puts together again (short of less than 2^-133).  The leading
+// part of the largest must not round to infinity, so they are cut off; what is not finite is its leading part alone, a NaN stays one.
 __device__ __forceinline__ uint32_t quiet(uint32_t x) { return (x & 0x7fffffffu) > 0x7f800000u ? x | 0x00400000u : x; }
 __device__ __forceinline__ uint32_t below_leading(uint32_t x) { return __float_as_uint(__uint_as_float(x) - __uint_as_float(x & 0xffff0000u)); }
 __device__ __forceinline__ uint32_t upper_halves(uint32_t lo, uint32_t hi) { return __builtin_amdgcn_perm(hi, lo, 0x07060302u); }
@@ -332,10 +332,10 @@ __device__ __forceinline__ f32x16_t mma_chain(const uint4 (&a)[NCH], const uint4
 // !FIT: some element may not (infinity times a part that is zero would be NaN): fp32 products.
 template <int NCH, bool FIT, bool KEYS_FIRST>
 __device__ __forceinline__ f32x16_t split_chain(const uint4* keys, const uint4 (&q)[NCH / 2 * 3]) {
-    // The products of the leading parts have a sum of their own: a bf16 MFMA does not round to nearest what it adds to a sum, which for rows of one
-    // or two elements made a third of the error where these products went on from the sum of the others.  They run ahead of the others with 128
-    // elements (one level of 24000 tokens, 28 heads on 4 x 64: 199 us, alternating 203) and alternate with them otherwise (4 x 9000 tokens, 16 heads x 100
-    // queries of 64 elements: 203 us, alternating 188; with one sum 176).
+    // The products of the leading parts have a sum of their own: a bf16 MFMA does not round to nearest what it adds to a sum, which for
+    // rows of one or two elements made a third of the error where these products went on from the sum of the others.  They run ahead of
+    // the others with 128 elements (one level of 24000 tokens, 28 heads on 4 x 64: 199 us, alternating 203) and alternate with them
+    // otherwise (4 x 9000 tokens, 16 heads x 100 queries of 64 elements: 203 us, alternating 188; with one sum 176).
     constexpr bool kAhead = NCH == 16;
     f32x16_t acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, small = acc;
     auto mma = [&](auto tag, f32x16_t& sum, const uint4& key, const uint4& row) {
@@ -978,11 +978,11 @@ __device__ __forceinline__ void load_queries(u32x4_t (&q)[NB][NCH], const T* __r
     for (int b = 0; b < NB; ++b) load_fragments<T, NCH>(q[b], q_text + static_cast<size_t>(kvh) * g.R * g.dh, b * 16, g.R - 1, g.dh);
 }
 
-// From eight fragments on the workgroup loads them once, into LDS, from where every wave takes them all.  A load in fragment order is
-// 64 bytes of 16 rows, and eight waves with 16 of them each ahead of their keys took 2.7 us of pass 1 and 2 of pass 2 for the addresses alone.  One level
-// by graph replay, us: 4507 tokens, 40 heads x 64 queries of 128 elements 49.7 -> 46.5, 839 tokens 30.5 -> 25.9, 2924 in fp32 79.8 -> 71.8; 7274, 16 heads x 64 of 64
-// 30.1 -> 28.8.  With fewer fragments, or one row block, the barrier costs more than it saves: 439 tokens, 16 x 16 of 64 17.7 / 18.1, 12587 in fp32, 32 heads on 8 x 1
-// of 128 77.3 / 79.8.
+// From eight fragments on the workgroup loads them once, into LDS, from where every wave takes them all.  A load in fragment order is 64
+// bytes of 16 rows, and eight waves with 16 of them each ahead of their keys took 2.7 us of pass 1 and 2 of pass 2 for the addresses
+// alone.  One level by graph replay, us: 4507 tokens, 40 heads x 64 queries of 128 elements 49.7 -> 46.5, 839 tokens 30.5 -> 25.9, 2924
+// in fp32 79.8 -> 71.8; 7274, 16 heads x 64 of 64 30.1 -> 28.8.  With fewer fragments, or one row block, the barrier costs more than it
+// saves: 439 tokens, 16 x 16 of 64 17.7 / 18.1, 12587 in fp32, 32 heads on 8 x 1 of 128 77.3 / 79.8.
 template <int NCH, int NB> constexpr bool kShareQueries = NB >= 2 && NB * NCH >= 8;
 template <typename T, int NCH, int NB>
 struct SharedQueries {
@@ -2019,12 +2019,13 @@ static void launch_narrow_scores(const void* q, const void* k, const ScoreGeom& 
                        static_cast<const T*>(q), static_cast<const T*>(k), g, p.per2, pstat, p.nx1, colpart); }
 }
 
-// Whether the fp32 rows of a workgroup, at most one block per wave, are multiplied as bf16 parts.  To take a row block apart is 0.5 us
-// of each pass, so it needs keys to pay.  Whole calls by graph replay, us, fp32 MFMA / parts: 14 heads on 2 x 32 queries of 64 elements, 5000 tokens
-// (two subtiles a workgroup) 39.1 / 36.4, 24000 80.2 / 69.9; 28 on 4 x 64 of 128, 1500 (two) 46.1 / 43.2.  Workgroups of up to four row blocks
-// have one wave with rows to a SIMD, whose steps are a chain: 12 heads on 4 x 30 of 64, 24000 (96 = subtiles x pieces of a row) 80.4 / 78.9; 20
-// on 10 x 40 of 128, 5000 (112) 61.0 / 56.4.  Below the lines, levels alone, by a chain that was a little shorter (one sum): 14 on 2 x 32 of 64, 1500 (one)
-// 26.1 / 26.8, 28 on 4 x 64 of 128, 300 (one) 29.2 / 29.3; 12 on 4 x 30 of 64, 5000 (24) 30.0 / 30.9, 20 on 10 x 40 of 128, 1500 (32) 30.3 / 32.2.
+// Whether the fp32 rows of a workgroup, at most one block per wave, are multiplied as bf16 parts.  To take a row block apart is 0.5 us of
+// each pass, so it needs keys to pay.  Whole calls by graph replay, us, fp32 MFMA / parts: 14 heads on 2 x 32 queries of 64 elements,
+// 5000 tokens (two subtiles a workgroup) 39.1 / 36.4, 24000 80.2 / 69.9; 28 on 4 x 64 of 128, 1500 (two) 46.1 / 43.2.  Workgroups of up
+// to four row blocks have one wave with rows to a SIMD, whose steps are a chain: 12 heads on 4 x 30 of 64, 24000 (96 = subtiles x pieces
+// of a row) 80.4 / 78.9; 20 on 10 x 40 of 128, 5000 (112) 61.0 / 56.4.  Below the lines, levels alone, by a chain that was a little
+// shorter (one sum): 14 on 2 x 32 of 64, 1500 (one) 26.1 / 26.8, 28 on 4 x 64 of 128, 300 (one) 29.2 / 29.3; 12 on 4 x 30 of 64, 5000
+// (24) 30.0 / 30.9, 20 on 10 x 40 of 128, 1500 (32) 30.3 / 32.2.
 static bool split_products(const ScoreGeom& g, const ScorePlan& p, int nch) {
     return blocks_of_busiest_simd(g) > 1 ? p.per1 >= 2 : p.per1 * nch >= 96;
 }
