@@ -1574,7 +1574,7 @@ extern "C" int metok_compress_encoder_tokens(const void* feats, int dtype, int T
     { TraceScope trace_scope(METOK_TRACE_PLAN, st); launch_plan(plan, scores, event_start, T, k, st); }
     if ((rc = check_launch("plan"))) return rc;
 
-    dim3 grid(pool_workgroups(grid_h, grid_w, d, dtype, s1, s2, pool_edge), T);
+    dim3 grid(pool_workgroups(T, grid_h, grid_w, d, dtype, s1, s2, pool_edge), T);
 #define METOK_POOL_CASE(TI, TO) \
     { TraceScope trace_scope(METOK_TRACE_POOL, st); \
       hipLaunchKernelGGL((pool_kernel<TI, TO>), grid, dim3(kPoolThreads), 0, st, static_cast<const TI*>(feats), grid_h, grid_w, d, \
@@ -1726,7 +1726,7 @@ static int segment_compress_impl(int batch, const void* feats, int dtype, int T,
         if ((rc = check_launch("frame_stats"))) return rc;
         launch_segment_plan(sa, plan, nb, st);
         if ((rc = check_launch("segment and plan"))) return rc;
-        dim3 grid(pool_workgroups(grid_h, grid_w, d, dtype, s1, s2, pool_edge), T, nb);
+        dim3 grid(pool_workgroups(static_cast<int64_t>(batch) * T, grid_h, grid_w, d, dtype, s1, s2, pool_edge), T, nb);
 #define METOK_POOL_CASE(TI, TO) \
         { TraceScope trace_scope(METOK_TRACE_POOL, st); \
           hipLaunchKernelGGL((pool_kernel<TI, TO>), grid, dim3(kPoolThreads), 0, st, static_cast<const TI*>(feats), grid_h, grid_w, d, \

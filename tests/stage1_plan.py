@@ -4,8 +4,8 @@ from tests.host_plan import host_library
 SOURCE = r"""
 #include "stage1_plan.h"
 using namespace metok;
-extern "C" int workgroups(int grid_h, int grid_w, int d, int dtype, int s1, int s2, int pool_edge) {
-    return pool_workgroups(grid_h, grid_w, d, dtype, s1, s2, pool_edge);
+extern "C" int workgroups(int frames, int grid_h, int grid_w, int d, int dtype, int s1, int s2, int pool_edge) {
+    return pool_workgroups(frames, grid_h, grid_w, d, dtype, s1, s2, pool_edge);
 }
 extern "C" int small(int T, int grid_h, int grid_w, int d, int dtype, int s1, int s2, int pool_edge, int one_pass) {
     return small_video(T, grid_h * grid_w, d, dtype, worst_case_rows(T, grid_h, grid_w, s1, s2, pool_edge), one_pass);
@@ -13,8 +13,8 @@ extern "C" int small(int T, int grid_h, int grid_w, int d, int dtype, int s1, in
 """
 
 
-def pool_workgroups(grid_h, grid_w, d, dtype, s1, s2, edge=0):
-    return host_library(SOURCE).workgroups(grid_h, grid_w, d, 1 if dtype == "bf16" else 0, s1, s2, edge)
+def pool_workgroups(frames, grid_h, grid_w, d, dtype, s1, s2, edge=0):
+    return host_library(SOURCE).workgroups(frames, grid_h, grid_w, d, 1 if dtype == "bf16" else 0, s1, s2, edge)
 
 
 def small_video(T, grid, d, dtype, s1, s2, edge=0, one_pass=False):
