@@ -65,8 +65,8 @@ template <> struct Mma<float> {
 // Root mean square error of a sum against 64 bits, in units of its size, fp32 MFMA / parts, normal elements of which n of a row are not
 // 0: n = 1 2.54e-8 / 2.61e-8, 2 3.1e-8 / 2.6e-8, 4 4.0e-8 / 2.7e-8, 8 5.3e-8 / 2.9e-8, all 64 14.3e-8 / 4.9e-8, all 128 20.2e-8 / 6.5e-8;
 // parts cut off 6.9e-8 up to n = 8, then 7.5e-8 and 8.5e-8.
-// Whole calls by graph replay, fp32 MFMA / parts: 28 heads on 4 x 64 queries of 128 elements, 8 x 4000 tokens 353 / 243 us, 24000 tokens
-// 287 / 206; see split_products for where they are taken.
+// Whole calls by graph replay, fp32 MFMA / parts: 28 heads on 4 x 64 queries of 128 elements, 8 x 4000 tokens 352 / 242 us, 24000 tokens
+// 287 / 204; see split_products for where they are taken.
 struct split_t { float value; };
 template <> struct Mma<split_t> : Mma<float> {};
 
@@ -86,10 +86,12 @@ __device__ __forceinline__ void split_piece(const uint4& x, uint2 (&part)[3]) {
 }
 // Elements below this are multiplied in parts: no sum of 128 of their products leaves the range of float, whatever the order, and parts
 // too small for a bf16 number of full precision (below 2^-126) are less than 2^-58 of a logit together.
-constexpr float kPartsBelow = 0x1p59f;
+// One comparison of the largest magnitude, above which infinities and NaNs are: with four of floats the 5000 tokens at split_products took
+// 36.5 us.
+constexpr uint32_t kPartsBelow = 0x5d000000u;                      // 2^59
 __device__ __forceinline__ bool all_fit(const uint4& x) {
-    auto fits = [](uint32_t e) { return fabsf(__uint_as_float(e)) < kPartsBelow; };           // not a NaN
-    return fits(x.x) && fits(x.y) && fits(x.z) && fits(x.w);
+    auto magnitude = [](uint32_t e) { return e & 0x7fffffffu; };
+    return max(max(magnitude(x.x), magnitude(x.y)), max(magnitude(x.z), magnitude(x.w))) < kPartsBelow;
 }
 // The same for elements of which some do not fit: parts that joined_piece puts together again (short of less than 2^-133).  The leading
 // part of the largest must not round to infinity, so they are cut off; what is not finite is its leading part alone, a NaN stays one.
@@ -2021,9 +2023,9 @@ static void launch_narrow_scores(const void* q, const void* k, const ScoreGeom& 
 
 // Whether the fp32 rows of a workgroup, at most one block per wave, are multiplied as bf16 parts.  To take a row block apart is 0.5 us of
 // each pass, so it needs keys to pay.  Whole calls by graph replay, us, fp32 MFMA / parts: 14 heads on 2 x 32 queries of 64 elements,
-// 5000 tokens (two subtiles a workgroup) 39.1 / 36.4, 24000 80.2 / 69.9; 28 on 4 x 64 of 128, 1500 (two) 46.1 / 43.2.  Workgroups of up
+// 5000 tokens (two subtiles a workgroup) 39.5 / 36.0, 24000 80.4 / 69.2; 28 on 4 x 64 of 128, 1500 (two) 45.9 / 42.1.  Workgroups of up
 // to four row blocks have one wave with rows to a SIMD, whose steps are a chain: 12 heads on 4 x 30 of 64, 24000 (96 = subtiles x pieces
-// of a row) 80.4 / 78.9; 20 on 10 x 40 of 128, 5000 (112) 61.0 / 56.4.  Below the lines, levels alone, by a chain that was a little
+// of a row) 80.2 / 77.6; 20 on 10 x 40 of 128, 5000 (112) 61.0 / 55.2.  Below the lines, levels alone, by a chain that was a little
 // shorter (one sum): 14 on 2 x 32 of 64, 1500 (one) 26.1 / 26.8, 28 on 4 x 64 of 128, 300 (one) 29.2 / 29.3; 12 on 4 x 30 of 64, 5000
 // (24) 30.0 / 30.9, 20 on 10 x 40 of 128, 1500 (32) 30.3 / 32.2.
 static bool split_products(const ScoreGeom& g, const ScorePlan& p, int nch) {
