@@ -141,12 +141,13 @@ inline size_t partial_bytes(const ScoreGeom& g, const ScorePlan& p) { return sta
 // kSplitMergedBytes.  One level of 28 heads on 4 x 64 queries, us whole / split: 300 tokens 26.5 / 24.1, 2243 (2 subtiles) 32.7 / 28.9, 6000
 // 40.6 / 36.7, 9000 (5) 47.4 / 44.4, 15000 (8) 62.6 / 60.7, 18432 (10) 63.0 / 64.2; two videos of 4000 41.2 / 39.5, eight of 1000
 // (5) 45.5 / 42.6, four of 3000 (6, merged in pass 2) 49.5 / 50.1; 14 heads on 2 x 64, 8000 tokens 34.3 / 30.8.
-// Two blocks on one wave and their halves on two are the same work only where nothing is rounded: 9 to 12 blocks are three to a SIMD whole
-// and two split, and half as many workgroups along the keys may be fewer than half.  What the split adds to the busiest SIMD, in
+// Two blocks on one wave and their halves on two are the same work only where nothing is rounded: 9 to 12 blocks are three to a SIMD
+// whole and two split, and half as many workgroups along the keys may be fewer than half.  What the split adds to the busiest SIMD, in
 // products of a row block and a subtile over both passes, must stay below what it saves.  Levels (kernels alone) with 0 to 2 products
 // more are 0.87 to 0.97 of the whole rows' time in every type; in bf16 those with 10 more are 0.96 to 0.99, with 12 0.94 to 1.05, with 16
-// 1.02 to 1.07; in fp32 (both sides with fp32 MFMA, four times as long a product; split rows are now multiplied in parts), those with 4 more are 0.97 to 1.04, with 10 1.09 to 1.16, with 24 1.26 to
-// 1.39 (40 heads x 352 queries, 2 x 400 tokens, 64 elements: 57.9 / 80.5 us).
+// 1.02 to 1.07; in fp32 (both sides with fp32 MFMA, four times as long a product; split rows are now multiplied in parts), those with 4
+// more are 0.97 to 1.04, with 10 1.09 to 1.16, with 24 1.26 to 1.39 (40 heads x 352 queries, 2 x 400 tokens, 64 elements: 57.9 / 80.5
+// us).
 // A split needs more room for the column sums and none for the two words per token that select_bytes reserves for nobody; where
 // it does not fit the workspace of the whole rows, the rows stay whole.
 constexpr int kSplitSubtiles = 5, kSplitSubtilesMerged = 8;

@@ -334,10 +334,10 @@ __device__ __forceinline__ f32x16_t mma_chain(const uint4 (&a)[NCH], const uint4
 // !FIT: some element may not (infinity times a part that is zero would be NaN): fp32 products.
 template <int NCH, bool FIT, bool KEYS_FIRST>
 __device__ __forceinline__ f32x16_t split_chain(const uint4* keys, const uint4 (&q)[NCH / 2 * 3]) {
-    // The products of the leading parts have a sum of their own: a bf16 MFMA does not round to nearest what it adds to a sum, which for
-    // rows of one or two elements made a third of the error where these products went on from the sum of the others.  They run ahead of
-    // the others with 128 elements (one level of 24000 tokens, 28 heads on 4 x 64: 199 us, alternating 203) and alternate with them
-    // otherwise (4 x 9000 tokens, 16 heads x 100 queries of 64 elements: 203 us, alternating 188; with one sum 176).
+    // The products of the leading parts have a sum of their own: a bf16 MFMA does not round to nearest what it adds to a sum.  Where they
+    // went on from the sum of the others, rows of one element were 3.5e-8 off instead of 2.6e-8.  They run ahead of the others with 128
+    // elements (one level of 24000 tokens, 28 heads on 4 x 64: 199 us, alternating 203) and alternate with them otherwise (4 x 9000
+    // tokens, 16 heads x 100 queries of 64 elements: 203 us, alternating 188; with one sum 176).
     constexpr bool kAhead = NCH == 16;
     f32x16_t acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, small = acc;
     auto mma = [&](auto tag, f32x16_t& sum, const uint4& key, const uint4& row) {

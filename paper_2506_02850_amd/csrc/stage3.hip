@@ -48,7 +48,8 @@
 namespace metok {
 
 constexpr int kMoveThreads = 1024;
-constexpr int kMaxTickets = 4, kTicketStride = 16;      // counters, and words between them: two to a line of the L2, in the workspace header that there was
+// counters, and words between them: two to a line of the L2, in the workspace header that there was
+constexpr int kMaxTickets = 4, kTicketStride = 16;
 constexpr int kMoveInFlight = 8;        // 16-byte pieces per thread: 1024 x 8 x 16 B = 128 KB per tile
 
 namespace {
